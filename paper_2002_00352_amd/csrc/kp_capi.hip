@@ -31,7 +31,14 @@ hipError_t kp_launch_scd_init(KState *st, int K, const double *lam_in, const uin
 hipError_t kp_launch_scd_locate_select(KState *st, int K, const double *B, const double *R,
                                        const int *rinst, XSum *hist_sum, uint32_t *hist_cnt,
                                        const double *ev1, const double *ev2, uint32_t emit_cap,
-                                       int *pending, unsigned int *win, hipStream_t stream);
+                                       const SelWs &w, int blocks, int *pending, unsigned int *win,
+                                       hipStream_t stream);
+hipError_t kp_launch_scd_select_many(KState *st, int K, const double *B, const double *ev1, const double *ev2,
+                                     uint32_t emit_cap, const SelWs &w, int blocks, int *pending,
+                                     unsigned int *win, hipStream_t stream);
+size_t kp_sel_bytes(int K);
+size_t kp_sel_clear_bytes(int K);
+SelWs kp_sel_ws(void *mem, int K);
 hipError_t kp_launch_scd_finish(const KState *st, int K, const double *lam_in, double *lam_out,
                                 double *delta_next, hipStream_t stream);
 hipError_t kp_launch_dd_update(int K, double alpha, const double *R, const double *B, double *lam,
@@ -123,6 +130,8 @@ constexpr int kGraphLaterPasses = 5;     // later passes captured with the first
 constexpr uint32_t kEmitCapBatched = 1u << 16;   // emitted events per (instance, knapsack) per pass (at least)
 constexpr double kEmitBytesBatched = 8.0e9;        // bound on a batch's emission buffers
 constexpr size_t kBatchedLds = 40 * 1024;          // LDS per block of the batched launch (4 blocks per CU)
+constexpr int kSelBlocks = 32;                     // blocks per knapsack that bin and compact more of them
+constexpr int kSelBlocksBatched = 4;
 constexpr int kMaxInputNodes = 4096;               // local-constraint nodes accepted in a problem
 
 struct Ctx {
@@ -546,6 +555,8 @@ struct SweepWs {
                         // windows, [3] dense probe: sampled users with a line above -H
   char *stat;           // status block, followed by the histograms (SCD)
   size_t stat_bytes;    // the status block and the histograms
+  SelWs sel;            // selection among the emitted breakpoints
+  size_t sel_clear;     // bytes of its histograms
 };
 
 kp_status carve_ws(Ctx *c, const Prepared &P, bool scd, SweepWs &w) {
@@ -559,13 +570,14 @@ kp_status carve_ws(Ctx *c, const Prepared &P, bool scd, SweepWs &w) {
   // status block (cleared with the histograms in one memset): [0] pending
   // knapsacks, [8] walk-limit counter, [16] window counters, [32] list
   // counters, [48] search-mode counts
-  size_t o_st = 0, o_hs = 0, o_hc = 0, o_km = 0, o_e1 = 0, o_e2 = 0, o_stat = 0;
+  size_t o_st = 0, o_hs = 0, o_hc = 0, o_km = 0, o_e1 = 0, o_e2 = 0, o_stat = 0, o_sel = 0;
   uint32_t cap = 0;
   if (scd) o_st = cv.take((size_t)K * sizeof(KState));
   o_stat = cv.take(64);
   if (scd) {
     o_hs = cv.take((size_t)K * KP_NB * sizeof(XSum));
     o_hc = cv.take((size_t)K * KP_NB * 4);
+    o_sel = cv.take(kp_sel_bytes(K));
     o_km = cv.take((size_t)K);
     cap = kEmitCapDefault;
     o_e1 = cv.take((size_t)K * cap * 8);
@@ -604,6 +616,8 @@ kp_status carve_ws(Ctx *c, const Prepared &P, bool scd, SweepWs &w) {
   w.Ptmp = (double *)(b + o_P);
   w.stat = b + o_stat;
   w.stat_bytes = scd ? (o_hc + (size_t)K * KP_NB * 4) - o_stat : 64;
+  w.sel_clear = scd ? kp_sel_clear_bytes(K) : 0;
+  if (scd) w.sel = kp_sel_ws(b + o_sel, K);
   w.pending = (int *)(b + o_stat);
   w.err = (unsigned long long *)(b + o_stat + 8);
   w.win = (unsigned int *)(b + o_stat + 16);
@@ -1131,12 +1145,19 @@ kp_status kp_scd_sweep_masked_impl(Ctx *c, const kp_problem *prob, const double 
       }
     }
     HIP_TRY(kp_launch_scd_locate_select(w.st, K, w.B, Rd, nullptr, w.hist_sum, w.hist_cnt, w.ev1, w.ev2,
-                                        w.emit_cap, w.pending, w.win, c->stream));
+                                        w.emit_cap, w.sel, 0, w.pending, w.win, c->stream));
     // one copy of the status block: pending, walk-limit counter, window and
     // list counters
     int *st = c->pinned + 32;
     HIP_TRY(hipMemcpyAsync(st, w.stat, 48, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
+    if (st[1]) {   // more emitted breakpoints than one block selects from
+      HIP_TRY(hipMemsetAsync(w.sel.hsum, 0, w.sel_clear, c->stream));
+      HIP_TRY(kp_launch_scd_select_many(w.st, K, w.B, w.ev1, w.ev2, w.emit_cap, w.sel, kSelBlocks, w.pending,
+                                        w.win, c->stream));
+      HIP_TRY(hipMemcpyAsync(st, w.stat, 48, hipMemcpyDeviceToHost, c->stream));
+      HIP_TRY(hipStreamSynchronize(c->stream));
+    }
     if (pass == 0 && window) {
       c->win_tried += (unsigned)st[4];
       c->win_above += (unsigned)st[5];
@@ -1597,6 +1618,7 @@ struct BatchPlan {
   double *Bf = nullptr, *e1 = nullptr, *e2 = nullptr, *stats = nullptr;
   XSum *hs = nullptr;
   uint32_t *hc = nullptr;
+  SelWs sel;
   unsigned long long *err = nullptr;
   int *pinned = nullptr;     // [0] pending knapsacks, [2..3] error word, [16..] per-instance flags
   hipGraph_t graph[2] = {nullptr, nullptr};
@@ -1705,7 +1727,8 @@ kp_status plan_later_passes_dev(BatchPlan *p, int dir, hipStream_t s) {
     r.reset = j == 0 ? 1 : 0;
     HIP_TRY(kp_launch_plan_resplit(r, s));
     if (p->T > 0) HIP_TRY(kp_launch_sweep_batched(p->rd, p->rg, p->rboff, p->n, p->gfix, p->lds, s, p->ctl));
-    HIP_TRY(kp_launch_scd_locate_select(p->kst, p->Kf, p->Bf, p->stats, p->kin, p->hs, p->hc, p->e1, p->e2, p->cap, p->pend, nullptr, s));
+    HIP_TRY(kp_launch_scd_locate_select(p->kst, p->Kf, p->Bf, p->stats, p->kin, p->hs, p->hc, p->e1, p->e2, p->cap, p->sel, kSelBlocksBatched, p->pend,
+                                      nullptr, s));
     HIP_TRY(kp_launch_batched_aux(2, nullptr, p->Kf, p->kst, p->lam_tab[1 - dir], p->kin, p->klo, p->hint, nullptr,
                                   nullptr, s));
     HIP_TRY(kp_launch_inst_active(p->kst, p->koff, p->n, p->active, s));
@@ -1723,7 +1746,8 @@ kp_status plan_first_pass(BatchPlan *p, int dir, hipStream_t s) {
   if (p->T > 0) HIP_TRY(kp_launch_sweep_batched(p->d[dir][1], p->geom, p->boff, p->n, p->GB, p->lds, s));
   HIP_TRY(kp_launch_batched_aux(0, p->coltab[dir], p->ncol, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
                                 nullptr, s));
-  HIP_TRY(kp_launch_scd_locate_select(p->kst, p->Kf, p->Bf, p->stats, p->kin, p->hs, p->hc, p->e1, p->e2, p->cap, p->pend, nullptr, s));
+  HIP_TRY(kp_launch_scd_locate_select(p->kst, p->Kf, p->Bf, p->stats, p->kin, p->hs, p->hc, p->e1, p->e2, p->cap, p->sel, kSelBlocksBatched, p->pend,
+                                      nullptr, s));
   HIP_TRY(kp_launch_batched_aux(2, nullptr, p->Kf, p->kst, p->lam_tab[1 - dir], p->kin, p->klo, p->hint, nullptr,
                                 nullptr, s));
   HIP_TRY(kp_launch_inst_active(p->kst, p->koff, p->n, p->active, s));
@@ -1786,7 +1810,8 @@ kp_status plan_step(BatchPlan *p, int dir, double *stats_out, bool graph) {
       }
     }
     ++passes;
-    HIP_TRY(kp_launch_scd_locate_select(p->kst, p->Kf, p->Bf, p->stats, p->kin, p->hs, p->hc, p->e1, p->e2, p->cap, p->pend, nullptr, s));
+    HIP_TRY(kp_launch_scd_locate_select(p->kst, p->Kf, p->Bf, p->stats, p->kin, p->hs, p->hc, p->e1, p->e2, p->cap, p->sel, kSelBlocksBatched, p->pend,
+                                      nullptr, s));
     HIP_TRY(kp_launch_batched_aux(2, nullptr, p->Kf, p->kst, p->lam_tab[1 - dir], p->kin, p->klo, p->hint, nullptr,
                                 nullptr, s));
     HIP_TRY(kp_launch_inst_active(p->kst, p->koff, p->n, p->active, s));
@@ -1919,6 +1944,7 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
   const size_t o_hc = cv.take((size_t)Kf * KP_NB * 4);
   const size_t o_e1 = cv.take((size_t)ioff[n] * 8);
   const size_t o_e2 = cv.take((size_t)ioff[n] * 8);
+  const size_t o_sel = cv.take(kp_sel_bytes(Kf));
   const size_t o_eo = cv.take((size_t)Kf * 8);
   const size_t o_ec = cv.take((size_t)Kf * 4);
   // staged events per block, per instance: scaled with the block's share of
@@ -1998,6 +2024,7 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
   p->hc = (uint32_t *)(w + o_hc);
   p->e1 = (double *)(w + o_e1);
   p->e2 = (double *)(w + o_e2);
+  p->sel = kp_sel_ws(w + o_sel, Kf);
   p->err = (unsigned long long *)(w + o_err);
   p->pend = (int *)(w + o_pend);
   p->kin = (int *)(w + o_kin);
@@ -2136,6 +2163,7 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
   if (e == hipSuccess) e = hipMemsetAsync(p->ctl, 0, 16, st);
   if (e == hipSuccess) e = hipMemsetAsync(p->hs, 0, (size_t)Kf * KP_NB * sizeof(XSum), st);
   if (e == hipSuccess) e = hipMemsetAsync(p->hc, 0, (size_t)Kf * KP_NB * 4, st);
+  if (e == hipSuccess) e = hipMemsetAsync(w + o_sel, 0, kp_sel_clear_bytes(Kf), st);
   if (e == hipSuccess) e = hipMemsetAsync(p->err, 0, 8, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);   // host tables go out of scope
   if (e != hipSuccess) {

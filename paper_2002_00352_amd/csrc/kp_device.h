@@ -26,6 +26,19 @@ __device__ __forceinline__ int exp_bucket(double v, double center, double delta)
   return d < 0.0 ? -id : id;
 }
 
+// An interval that holds every breakpoint of exponential bucket id (the
+// bucket test rounds v - center, by far less than the widening here); the
+// outermost buckets are open.
+__device__ __forceinline__ void bucket_bounds(double center, double delta, int id, double &lo, double &hi) {
+  const int a = id < 0 ? -id : id;
+  const double far_ = ldexp(delta, a), near_ = a ? ldexp(delta, a - 1) : 0.0;
+  const double slack = (center + far_) * 0x1p-48;
+  if (id == 0) { lo = center - far_; hi = center + far_; }
+  else if (id > 0) { lo = center + near_; hi = a >= 31 ? INFINITY : center + far_; }
+  else { lo = a >= 31 ? 0.0 : center - far_; hi = center - near_; }
+  lo = fmax(lo - slack, 0.0);
+  hi = fmax(hi + slack, 0.0);
+}
 
 // ---- exact sums (XSum) ----
 // x = sign (hi 2^-24 + lo 2^-56) with hi = floor(|x| 2^24) and lo the rest in

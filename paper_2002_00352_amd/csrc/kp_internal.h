@@ -7,7 +7,9 @@
 #define KP_NB 64               // histogram bins per knapsack per pass
 #define KP_MAX_K_SCD 64        // per-block LDS histograms bound K for the SCD calls
 #define KP_CENTRAL_W 2         // exponential buckets |id| <= W are emitted in the first pass
-#define KP_SORT_MAX 4096       // candidates sorted in LDS by the selection kernel
+#define SEL_BITS 10            // key bins of the selection's first step over many blocks
+#define SEL_BINS (1 << SEL_BITS)
+#define SEL_COMP 8192          // events of the threshold's bin it compacts
 #define KP_PROBE_USERS 4096   // users sampled by the dense window pass's probe
 #define KP_WIN_MULT 1.25       // window half-width around lambda_k^t, in units of the last step
 #define KP_WIN_MAX_REL 0.03125 // windows wider than this fraction of lambda_k^t are not tried
@@ -85,8 +87,19 @@ struct KState {
   double hw;           // KS_WINDOW: half-width h (whi = center + h, wlo = max(center - h, 0))
   uint64_t eoff;       // batched: this knapsack's emission buffer (elements from the base), when ecap > 0
   uint32_t ecap;       // batched: its capacity (0: the uniform capacity of the call)
-  uint32_t pad2;
+  uint32_t ncomp;      // selection: events of the threshold's bin compacted (atomic)
+  uint64_t sel_lo, sel_hi;    // selection: that bin's keys
+  XSum sel_fab;        // selection: sum of increments above it
+  int sel_bin;         // selection: the bin (-1: the sum never exceeds the budget)
+  int pad3;
   XSum corr;           // KS_WINDOW: sum over users of C_ik(whi+) - v_ik(x(lambda^t))
+};
+
+// Workspace of the selection among emitted breakpoints, per knapsack.
+struct SelWs {
+  XSum *hsum;          // [K][SEL_BINS], cleared between uses
+  uint32_t *hcnt;      // [K][SEL_BINS], cleared between uses
+  double *c1, *c2;     // [K][SEL_COMP]
 };
 
 // The post-processing's per-user pass (Sec. 5.4): every candidate (a user

@@ -975,452 +975,6 @@ __global__ void __launch_bounds__(256) k_reduce_stats(const double *partials, in
   }
 }
 
-// ---------------------------------------------------------------------------
-// SCD threshold search
-// ---------------------------------------------------------------------------
-// The window a search starts with, from the multiplier's history: around
-// lambda_k^t, 1.25x the last step wide, when that step was small against
-// lambda_k^t; else, when the multiplier alternates (it returns close to
-// lambda_k^{t-1}: the drift |lambda^t - lambda^{t-2}| is under 1/8 of the
-// last step), around lambda_k^{t-1}, 1.25x the drift wide.  hw is the
-// farthest window edge from lambda_k^t (the filters bound the lines'
-// movement by it).  step, prev, drift < 0 or NaN: unknown.
-// Half-widths are at least 2^-20 of the centre: near convergence a
-// multiplier's step or its 2-cycle drift can shrink to almost nothing and
-// then move by more than that once, and a window that misses costs a full
-// pass, while a few hundred more listed users cost little.
-__device__ __forceinline__ void choose_window(KState &s, double step, double prev, double drift) {
-  double c = 0.0, h = 0.0;
-  if (step > 0.0 && KP_WIN_MULT * step <= KP_WIN_MAX_REL * s.center) {
-    c = s.center;
-    h = fmax(KP_WIN_MULT * step, s.center * 0x1p-20);
-  } else if (step > 0.0 && drift >= 0.0 && prev >= 0.0 && drift * 8.0 <= step) {
-    const double floor_ = (prev > 0x1p-20 ? prev : 0x1p-20) * 0x1p-20;
-    c = prev;
-    h = KP_WIN_MULT * (drift > floor_ ? drift : floor_);
-  } else {
-    return;
-  }
-  s.mode = KS_WINDOW;
-  s.whi = c + h;
-  s.wlo = c - h > 0.0 ? c - h : 0.0;
-  const double up = s.whi - s.center, dn = s.center - s.wlo;
-  s.hw = fmax(fabs(up), fabs(dn));
-  s.klo = dkey(s.wlo);
-  s.khi = dkey(s.whi);
-}
-
-__global__ void k_scd_init(KState *st, int K, const double *lam_in, const uint8_t *kmask,
-                           double *hist, int hinted_in, int window, int interp) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= K) return;
-  KState s;
-  s.mode = (kmask && !kmask[k]) ? KS_DONE : KS_EXP;
-  s.bstar = 0;
-  s.shift = 0;
-  s.overflow = 0;
-  s.n_emit = 0;
-  s.flags = 0;
-  s.center = lam_in[k];
-  // hist: [K] bucket widths and [K] last steps (valid when hinted_in), then
-  // [K] lambda^{t-1} and [K] lambda^{t-2} (NaN while unknown), shifted here
-  // once per iteration
-  const double *delta_hint = (hist && hinted_in) ? hist : nullptr;
-  double d = delta_hint ? delta_hint[k] : 0.0;
-  const bool hinted = d > 0.0;
-  double prev = -1.0, drift = -1.0;
-  if (hist) {
-    prev = hist[2 * K + k];
-    const double prev2 = hist[3 * K + k];
-    drift = fabs(lam_in[k] - prev2);   // NaN while unknown
-    hist[3 * K + k] = prev;
-    hist[2 * K + k] = lam_in[k];
-  }
-  if (interp) {
-    // interpolated reduce: a fixed fine central bucket, 2^-20 of the
-    // multiplier (of 2^-20 when it is smaller), a power of two
-    const double base = lam_in[k] > 0x1p-20 ? lam_in[k] : 0x1p-20;
-    d = ldexp(1.0, ilogb(base) - 20);
-  } else if (!hinted) {
-    // no history: 2^-10 of the multiplier, a power of two; at a multiplier
-    // of 0 (or below 2^-20) 2^-20, so that the base-2 buckets around 0 reach
-    // 2^11 before they are capped
-    d = lam_in[k] > 0x1p-20 ? ldexp(1.0, ilogb(lam_in[k]) - 10) : 0x1p-20;
-  }
-  s.delta = d;
-  s.fab = xs_zero();
-  s.result = lam_in[k];
-  s.klo = 0;
-  s.khi = ~0ull;
-  s.hull_lo = ~0ull;
-  s.hull_hi = 0;
-  s.wlo = 0.0;
-  s.whi = 0.0;
-  s.hw = 0.0;
-  s.corr = xs_zero();
-  s.eoff = 0;
-  s.ecap = 0;
-  s.pad2 = 0;
-  if (interp) s.flags = KS_FLAG_INTERP;
-  else if (window && hinted && s.mode == KS_EXP) choose_window(s, delta_hint[K + k], prev, drift);
-  st[k] = s;
-}
-
-__device__ __forceinline__ int bits_needed(uint64_t x) { return x ? 64 - __clzll((long long)x) : 0; }
-
-// Full search of the next pass: exponential buckets over every breakpoint.
-__device__ __forceinline__ void restart_full(KState &s) {
-  s.mode = KS_EXP;
-  s.flags = 0;
-  s.n_emit = 0;
-  s.overflow = 0;
-  s.fab = xs_zero();
-  s.klo = 0;
-  s.khi = ~0ull;
-  s.hull_lo = ~0ull;
-  s.hull_hi = 0;
-}
-
-__device__ __forceinline__ void set_refine(KState &s, uint64_t lo, uint64_t hi) {
-  s.klo = lo;
-  s.khi = hi;
-  const int nb = bits_needed(hi - lo);
-  s.shift = nb > 6 ? nb - 6 : 0;   // (hi - lo) >> shift < 64
-  s.mode = KS_REFINE;
-}
-
-// After a pass: pick the bin holding the threshold and choose the next step.
-__global__ void k_scd_locate(KState *st, int K, const double *B, const double *R, const int *rinst,
-                             XSum *hist_sum, uint32_t *hist_cnt, uint32_t emit_cap, unsigned int *win) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= K) return;
-  KState s = st[k];
-  if (s.ecap) emit_cap = s.ecap;   // batched: this knapsack's own buffer
-  const double Bk = B[k];
-  const XSum *hsum = hist_sum + (size_t)k * KP_NB;
-  const uint32_t *hcnt = hist_cnt + (size_t)k * KP_NB;
-  // sums and comparisons with B_k are exact (XSum): the bin that holds the
-  // threshold does not depend on the order of any addition
-  if (s.mode == KS_EXP) {
-    XSum total = xs_zero();
-    for (int b = 0; b < KP_NB; ++b) total = xs_plus(total, hsum[b]);
-    if (!xs_gt(total, Bk)) {
-      s.mode = KS_DONE;
-      s.result = 0.0;
-    } else {
-      XSum cum = xs_zero();
-      int bin = 1;
-      for (int b = KP_NB - 1; b >= 1; --b) {
-        if (hcnt[b] && xs_gt(xs_plus(cum, hsum[b]), Bk)) { bin = b; break; }
-        cum = xs_plus(cum, hsum[b]);
-      }
-      s.bstar = bin - 32;
-      s.fab = cum;
-      if (s.flags & KS_FLAG_INTERP) {
-        // Sec. 5.2's approximate reduce: the bucket's increments spread
-        // linearly over its interval [lo, hi] (lo clamped at 0)
-        const int id = bin - 32;
-        const double c = s.center, d = s.delta;
-        double lo, hi;
-        if (id == 0) { lo = c - d; hi = c + d; }
-        else if (id > 0) { lo = c + ldexp(d, id - 1); hi = c + ldexp(d, id); }
-        else { lo = c - ldexp(d, -id); hi = c - ldexp(d, -id - 1); }
-        lo = fmax(lo, 0.0);
-        const double frac = (Bk - xs_to_double(cum)) / xs_to_double(hsum[bin]);
-        const double width = hi - lo;
-        const double prod = frac * width;
-        const double v = hi - prod;
-        s.mode = KS_DONE;
-        s.result = fmax(v, lo);
-        st[k] = s;
-        for (int b = 0; b < KP_NB; ++b) { hist_sum[(size_t)k * KP_NB + b] = xs_zero(); hist_cnt[(size_t)k * KP_NB + b] = 0u; }
-        return;
-      }
-      const bool central = s.bstar >= -KP_CENTRAL_W && s.bstar <= KP_CENTRAL_W;
-      if (central && !s.overflow) {
-        s.mode = KS_SELECT_BUCKET;
-      } else {
-        s.mode = hcnt[bin] <= emit_cap / 2 ? KS_EMIT_BUCKET : KS_HULL_BUCKET;
-        s.n_emit = 0;
-        s.overflow = 0;
-        s.hull_lo = ~0ull;
-        s.hull_hi = 0;
-      }
-    }
-  } else if (s.mode == KS_EMIT_BUCKET || s.mode == KS_HULL_BUCKET) {
-    if (s.mode == KS_EMIT_BUCKET && !s.overflow) {
-      s.mode = KS_SELECT_BUCKET;
-    } else {
-      set_refine(s, s.hull_lo, s.hull_hi);
-    }
-  } else if (s.mode == KS_REFINE) {
-    XSum cum = s.fab;
-    int bin = -1;
-    for (int b = KP_NB - 1; b >= 0; --b) {
-      if (hcnt[b] && xs_gt(xs_plus(cum, hsum[b]), Bk)) { bin = b; break; }
-      cum = xs_plus(cum, hsum[b]);
-    }
-    if (bin < 0) {  // cannot happen with exact sums; fall back to the lowest bin
-      bin = 0;
-      cum = s.fab;
-      for (int b = KP_NB - 1; b >= 1; --b) cum = xs_plus(cum, hsum[b]);
-    }
-    s.fab = cum;
-    const uint64_t lo = s.klo + ((uint64_t)bin << s.shift);
-    const uint64_t hi0 = lo + ((((uint64_t)1) << s.shift) - 1);
-    const uint64_t hi = hi0 < s.khi ? hi0 : s.khi;
-    if (lo == hi) {
-      s.mode = KS_DONE;
-      s.result = kdbl(lo);
-    } else if (hcnt[bin] <= emit_cap / 2) {
-      s.klo = lo;
-      s.khi = hi;
-      s.mode = KS_EMIT_RANGE;
-      s.n_emit = 0;
-      s.overflow = 0;
-    } else {
-      set_refine(s, lo, hi);
-    }
-  } else if (s.mode == KS_EMIT_RANGE) {
-    if (!s.overflow) s.mode = KS_SELECT_RANGE;
-    else set_refine(s, s.klo, s.khi);
-  } else if (s.mode == KS_WINDOW) {
-    // consumption just above the window, summed over users
-    // consumption of knapsack k (batched: R of instance rinst[k] sits after
-    // the R, g, P columns of the instances before it)
-    const double Rk = rinst ? R[k + 2 * rinst[k]] : R[k];
-    const XSum above = xs_plus(xs_of(Rk), s.corr);
-    if (win) { atomicAdd(&win[0], 1u); atomicAdd(&win[3], s.n_emit); }
-    if (s.overflow || xs_gt(above, Bk)) {
-      if (win) atomicAdd(&win[1], 1u);
-      restart_full(s);                  // the threshold lies above the window
-    } else {
-      s.mode = KS_SELECT_RANGE;         // [klo, khi] is the window
-      s.fab = above;
-      s.flags |= KS_FLAG_WINDOW;
-    }
-  }
-  st[k] = s;
-  for (int b = 0; b < KP_NB; ++b) { hist_sum[(size_t)k * KP_NB + b] = xs_zero(); hist_cnt[(size_t)k * KP_NB + b] = 0u; }
-}
-
-// Exact threshold among the emitted events of one knapsack (one block per k):
-// narrow the key range with LDS histograms until at most KP_SORT_MAX events
-// remain, sort them (bitonic, descending), scan the increments and return the
-// first distinct breakpoint whose cumulative increment exceeds B_k.
-#define SEL_NT 1024
-__global__ void __launch_bounds__(SEL_NT) k_scd_select(KState *st, const double *B,
-                                                       const double *emit_v1, const double *emit_v2,
-                                                       uint32_t emit_cap, unsigned int *win) {
-  const int k = blockIdx.x;
-  __shared__ KState s;
-  __shared__ XSum hsum[256];
-  __shared__ uint32_t hcnt[256];
-  __shared__ uint64_t skey[KP_SORT_MAX];
-  __shared__ double sval[KP_SORT_MAX];
-  __shared__ uint64_t lo, hi;
-  __shared__ XSum Fab;
-  __shared__ uint32_t nsel;
-  __shared__ int done;
-  __shared__ double result;
-  const int tid = threadIdx.x;
-  if (tid == 0) s = st[k];
-  __syncthreads();
-  if (s.mode != KS_SELECT_BUCKET && s.mode != KS_SELECT_RANGE) return;
-  const size_t eo = s.ecap ? (size_t)s.eoff : (size_t)k * emit_cap;
-  if (s.ecap) emit_cap = s.ecap;
-  const uint32_t n = s.n_emit < emit_cap ? s.n_emit : emit_cap;
-  const double *V1 = emit_v1 + eo;
-  const double *V2 = emit_v2 + eo;
-  const bool bucket = s.mode == KS_SELECT_BUCKET;
-  const double Bk = B[k];
-  if (tid == 0) {
-    lo = bucket ? 0ull : s.klo;
-    hi = bucket ? ~0ull : s.khi;
-    Fab = s.fab;
-    done = 0;
-  }
-  __syncthreads();
-  if (s.flags & KS_FLAG_WINDOW) {
-    // the threshold lies in the window iff the window's increments take the
-    // running sum past B_k
-    __shared__ XSum part[SEL_NT / 64];
-    XSum v = xs_zero();
-    for (uint32_t e = tid; e < n; e += SEL_NT) xs_add(v, V2[e]);
-    for (int off = 32; off > 0; off >>= 1) {
-      v.hi = v.hi + __shfl_xor(v.hi, off, 64);
-      v.lo = v.lo + __shfl_xor(v.lo, off, 64);
-    }
-    if ((tid & 63) == 0) part[tid >> 6] = v;
-    __syncthreads();
-    if (tid == 0) {
-      XSum tot = Fab;
-      for (int w = 0; w < SEL_NT / 64; ++w) tot = xs_plus(tot, part[w]);
-      if (!xs_gt(tot, Bk)) {
-        if (s.wlo == 0.0) {             // every breakpoint is in the window
-          st[k].result = 0.0;
-          st[k].mode = KS_DONE;
-        } else {
-          KState r = s;                 // below the window: full search
-          restart_full(r);
-          st[k] = r;
-          if (win) atomicAdd(&win[2], 1u);
-        }
-        done = 2;
-      }
-    }
-    __syncthreads();
-    if (done == 2) return;
-  }
-  // narrowing loop
-  for (int it = 0; it < 80; ++it) {
-    if (tid == 0) nsel = 0;
-    if (tid < 256) { hsum[tid] = xs_zero(); hcnt[tid] = 0u; }
-    __syncthreads();
-    const uint64_t L0 = lo, H0 = hi;
-    for (uint32_t e = tid; e < n; e += SEL_NT) {
-      const double v = V1[e];
-      if (bucket && exp_bucket(v, s.center, s.delta) != s.bstar) continue;
-      const uint64_t key = dkey(v);
-      if (key < L0 || key > H0) continue;
-      atomicAdd(&nsel, 1u);
-    }
-    __syncthreads();
-    if (nsel <= KP_SORT_MAX) break;
-    const int nb = bits_needed(H0 - L0);
-    const int shift = nb > 8 ? nb - 8 : 0;
-    for (uint32_t e = tid; e < n; e += SEL_NT) {
-      const double v = V1[e];
-      if (bucket && exp_bucket(v, s.center, s.delta) != s.bstar) continue;
-      const uint64_t key = dkey(v);
-      if (key < L0 || key > H0) continue;
-      const int bin = (int)((key - L0) >> shift);
-      xs_atomic_add(&hsum[bin], V2[e]);
-      atomicAdd(&hcnt[bin], 1u);
-    }
-    __syncthreads();
-    if (tid == 0) {
-      XSum cum = Fab;
-      int bin = -1;
-      for (int b = 255; b >= 0; --b) {
-        if (hcnt[b] && xs_gt(xs_plus(cum, hsum[b]), Bk)) { bin = b; break; }
-        cum = xs_plus(cum, hsum[b]);
-      }
-      if (bin < 0) { bin = 0; }
-      Fab = cum;
-      const uint64_t nlo = L0 + ((uint64_t)bin << shift);
-      const uint64_t nhi0 = nlo + ((((uint64_t)1) << shift) - 1);
-      lo = nlo;
-      hi = nhi0 < H0 ? nhi0 : H0;
-      if (lo == hi) { done = 1; result = kdbl(lo); }
-    }
-    __syncthreads();
-    if (done) break;
-  }
-  if (!done) {
-    // gather the surviving events
-    if (tid == 0) nsel = 0;
-    __syncthreads();
-    const uint64_t L0 = lo, H0 = hi;
-    for (uint32_t e = tid; e < n; e += SEL_NT) {
-      const double v = V1[e];
-      if (bucket && exp_bucket(v, s.center, s.delta) != s.bstar) continue;
-      const uint64_t key = dkey(v);
-      if (key < L0 || key > H0) continue;
-      const uint32_t slot = atomicAdd(&nsel, 1u);
-      if (slot < KP_SORT_MAX) { skey[slot] = key; sval[slot] = V2[e]; }
-    }
-    __syncthreads();
-    const uint32_t m = nsel < KP_SORT_MAX ? nsel : KP_SORT_MAX;
-    int P2 = 1;
-    while (P2 < (int)m) P2 <<= 1;
-    for (int t = m + tid; t < P2; t += SEL_NT) { skey[t] = 0ull; sval[t] = 0.0; }
-    __syncthreads();
-    // bitonic sort, descending by key (ties: any order -- equal keys are grouped)
-    for (int size = 2; size <= P2; size <<= 1) {
-      for (int stride = size >> 1; stride > 0; stride >>= 1) {
-        for (int t = tid; t < P2; t += SEL_NT) {
-          const int pt2 = t ^ stride;
-          if (pt2 > t) {
-            const bool desc = ((t & size) == 0);
-            const uint64_t ka = skey[t], kb = skey[pt2];
-            if (desc ? (ka < kb) : (ka > kb)) {
-              skey[t] = kb; skey[pt2] = ka;
-              const double va = sval[t]; sval[t] = sval[pt2]; sval[pt2] = va;
-            }
-          }
-        }
-        __syncthreads();
-      }
-    }
-    if (tid == 0) {
-      XSum cum = Fab;
-      double ans = m ? kdbl(skey[m - 1]) : kdbl(lo);
-      uint32_t e = 0;
-      while (e < m) {
-        const uint64_t key = skey[e];
-        while (e < m && skey[e] == key) { xs_add(cum, sval[e]); ++e; }
-        if (xs_gt(cum, Bk)) { ans = kdbl(key); break; }
-      }
-      result = ans;
-    }
-    __syncthreads();
-  }
-  if (tid == 0) {
-    st[k].result = result;
-    st[k].mode = KS_DONE;
-  }
-}
-
-__global__ void k_scd_finish(const KState *st, int K, const double *lam_in, double *lam_out,
-                             double *delta_next, int *pending) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= K) return;
-  const double nl = st[k].result;
-  lam_out[k] = nl;
-  if (delta_next) {
-    // next search: the bucket width, a power of two above this step, and the
-    // step itself (bounded below) for the window
-    const double step = fabs(nl - lam_in[k]);
-    const double floor_ = (nl > 0x1p-20 ? nl : 0x1p-20) * 0x1p-30;
-    const double w = step > floor_ ? step : floor_;
-    delta_next[k] = ldexp(1.0, ilogb(w) + 1);
-    delta_next[K + k] = w;
-  }
-}
-
-// A full search (no window) centres its buckets on the threshold of a
-// sample of users (lam_hat, from the same search on the sample with its
-// budgets scaled): buckets of half-width 2^-8 of it around it, so the central
-// buckets emitted by the first pass usually hold the threshold.  With
-// windows enabled, and lambda_k^t within a quarter of lam_hat, the search
-// starts instead with a window over those central buckets (4 bucket widths
-// either side of lam_hat): the walks stop below the window and nothing is
-// binned (c3 cold iterations 95 -> 45-55 ms); from further away (a start
-// from lambda = 0) the window pass costs more than the buckets.  A miss
-// falls back to the full search around lam_hat.  Exactness does not depend
-// on either (the threshold is located by exact sums over all users).
-__global__ void k_scd_recenter(KState *st, int K, const double *lam_hat, const double *lam_in, int window) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= K) return;
-  const double c = lam_hat[k];
-  if (st[k].mode != KS_EXP || !(c > 0x1p-20)) return;
-  KState s = st[k];
-  s.center = c;
-  s.delta = ldexp(1.0, ilogb(c) - 8);
-  if (window && fabs(lam_in[k] - c) <= 0.25 * c) {
-    const double h = 4.0 * s.delta;
-    s.mode = KS_WINDOW;
-    s.whi = c + h;
-    s.wlo = c - h > 0.0 ? c - h : 0.0;
-    s.klo = dkey(s.wlo);
-    s.khi = dkey(s.whi);
-    const double l = lam_in[k];
-    s.hw = fmax(fabs(s.whi - l), fabs(l - s.wlo));
-  }
-  st[k] = s;
-}
-
 // users[s] = s * stride + off (a strided sample)
 __global__ void k_strided_users(int64_t *users, int64_t n, int64_t stride, int64_t off) {
   for (int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; s < n; s += (int64_t)gridDim.x * blockDim.x)
@@ -1431,39 +985,6 @@ __global__ void k_strided_users(int64_t *users, int64_t n, int64_t stride, int64
 __global__ void k_uniform_rowptr(int64_t *rowptr, int64_t nrows, int D) {
   for (int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; r <= nrows; r += (int64_t)gridDim.x * blockDim.x)
     rowptr[r] = r * D;
-}
-
-// Knapsacks starting with a window and those needing another search mode.
-// out[0]: knapsacks searching with a window, out[1]: with another search
-// mode, out[2]: windows that do not contain lambda_k^t (alternation windows);
-// out[3] is cleared (the dense window pass's probe counts into it)
-__global__ void k_count_modes(const KState *st, int K, int *out) {
-  __shared__ int c[3];
-  if (threadIdx.x < 3) c[threadIdx.x] = 0;
-  __syncthreads();
-  for (int k = threadIdx.x; k < K; k += blockDim.x) {
-    const KState &s = st[k];
-    if (s.mode == KS_WINDOW) {
-      atomicAdd(&c[0], 1);
-      const double cen = 0.5 * (s.wlo + s.whi);
-      if (!(fabs(cen - s.center) <= fmax(s.whi - cen, cen - s.wlo))) atomicAdd(&c[2], 1);
-    } else if (s.mode != KS_DONE) {
-      atomicAdd(&c[1], 1);
-    }
-  }
-  __syncthreads();
-  if (threadIdx.x < 3) out[threadIdx.x] = c[threadIdx.x];
-  if (threadIdx.x == 3) out[3] = 0;
-}
-
-__global__ void k_count_pending(const KState *st, int K, int *pending) {
-  __shared__ int c;
-  if (threadIdx.x == 0) c = 0;
-  __syncthreads();
-  for (int k = threadIdx.x; k < K; k += blockDim.x)
-    if (st[k].mode != KS_DONE) atomicAdd(&c, 1);
-  __syncthreads();
-  if (threadIdx.x == 0) *pending = c;
 }
 
 // ---------------------------------------------------------------------------
@@ -2265,71 +1786,9 @@ __global__ void __launch_bounds__(256) k_reduce_stats_tab(const ColDesc *tab) {
   *d.out = s;
 }
 
-__global__ void k_scd_init_flat(KState *st, int Kf, const double *const *lam_in, const int *kinst,
-                                const int *klocal, double *hint, int window, const uint64_t *eoff,
-                                const uint32_t *ecap) {
-  const int f = blockIdx.x * blockDim.x + threadIdx.x;
-  if (f >= Kf) return;
-  const double l = lam_in[kinst[f]][klocal[f]];
-  KState s;
-  s.mode = KS_EXP;
-  s.bstar = 0;
-  s.shift = 0;
-  s.overflow = 0;
-  s.n_emit = 0;
-  s.flags = 0;
-  s.center = l;
-  // bucket width: a power of two above the last step when there is one
-  s.delta = (hint && hint[f] > 0.0) ? hint[f] : (l > 0x1p-20 ? ldexp(1.0, ilogb(l) - 10) : 0x1p-20);
-  s.fab = xs_zero();
-  s.result = l;
-  s.klo = 0;
-  s.khi = ~0ull;
-  s.hull_lo = ~0ull;
-  s.hull_hi = 0;
-  s.wlo = 0.0;
-  s.whi = 0.0;
-  s.hw = 0.0;
-  s.corr = xs_zero();
-  s.eoff = eoff ? eoff[f] : 0;
-  s.ecap = ecap ? ecap[f] : 0;
-  s.pad2 = 0;
-  // a window from the multiplier's history (as the single-instance search);
-  // the history columns shift once per iteration, here
-  if (hint) {
-    const double prev = hint[2 * Kf + f];
-    const double drift = fabs(l - hint[3 * Kf + f]);
-    hint[3 * Kf + f] = prev;
-    hint[2 * Kf + f] = l;
-    if (window && hint[f] > 0.0) choose_window(s, hint[Kf + f], prev, drift);
-  }
-  st[f] = s;
-}
-
-// Batched: flags[s] = 1 if instance s has a knapsack that needs another
-// pass over its users (knapsacks koff[s] .. koff[s+1]-1 of the flat state).
-__global__ void k_inst_active(const KState *st, const int *koff, int n, int *flags) {
-  const int s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= n) return;
-  int on = 0;
-  for (int f = koff[s]; f < koff[s + 1]; ++f) on |= walk_mode(st[f].mode) ? 1 : 0;
-  flags[s] = on;
-}
-
-__global__ void k_scd_finish_flat(const KState *st, int Kf, double *const *lam_out, const int *kinst,
-                                  const int *klocal, double *hint) {
-  const int f = blockIdx.x * blockDim.x + threadIdx.x;
-  if (f >= Kf) return;
-  const double nl = st[f].result;
-  lam_out[kinst[f]][klocal[f]] = nl;
-  if (hint) {
-    // the next iteration's bucket width: the power of two above this step
-    const double step = fabs(nl - st[f].center);
-    const double floor_ = (nl > 0x1p-20 ? nl : 0x1p-20) * 0x1p-30;
-    const double w = step > floor_ ? step : floor_;
-    hint[f] = ldexp(1.0, ilogb(w) + 1);
-    hint[Kf + f] = w;
-  }
+hipError_t kp_launch_reduce_tab(const void *tab, int n, hipStream_t stream) {
+  hipLaunchKernelGGL(k_reduce_stats_tab, dim3(n), dim3(256), 0, stream, (const ColDesc *)tab);
+  return hipGetLastError();
 }
 
 hipError_t kp_launch_sweep_batched(const SweepArgs *descs, const TileGeom *geoms, const int *block_off,
@@ -2342,29 +1801,6 @@ hipError_t kp_launch_sweep_batched(const SweepArgs *descs, const TileGeom *geoms
   }
   hipLaunchKernelGGL(k_sweep_batched, dim3(total_blocks), dim3(NT), lds, stream, descs, geoms,
                      block_off, n_inst, n_dev);
-  return hipGetLastError();
-}
-
-hipError_t kp_launch_batched_aux(int which, const void *tab, int n, KState *st, const void *lam_ptrs,
-                                 const int *kinst, const int *klocal, double *hint, const uint64_t *eoff,
-                                 const uint32_t *ecap, hipStream_t stream) {
-  if (n <= 0) return hipSuccess;
-  if (which == 0) {
-    hipLaunchKernelGGL(k_reduce_stats_tab, dim3(n), dim3(256), 0, stream, (const ColDesc *)tab);
-  } else if (which == 1 || which == 3) {   // 3: with a window where the last step allows
-    hipLaunchKernelGGL(k_scd_init_flat, dim3((n + 63) / 64), dim3(64), 0, stream, st, n,
-                       (const double *const *)lam_ptrs, kinst, klocal, hint,
-                       which == 3 ? 1 : 0, eoff, ecap);
-  } else {
-    hipLaunchKernelGGL(k_scd_finish_flat, dim3((n + 63) / 64), dim3(64), 0, stream, (const KState *)st,
-                       n, (double *const *)lam_ptrs, kinst, klocal, hint);
-  }
-  return hipGetLastError();
-}
-
-hipError_t kp_launch_inst_active(const KState *st, const int *koff, int n, int *flags, hipStream_t stream) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_inst_active, dim3((n + 63) / 64), dim3(64), 0, stream, st, koff, n, flags);
   return hipGetLastError();
 }
 
@@ -2480,36 +1916,6 @@ hipError_t kp_launch_reduce_stats(const double *partials, int nblk, int K, const
   return hipGetLastError();
 }
 
-hipError_t kp_launch_scd_init(KState *st, int K, const double *lam_in, const uint8_t *kmask,
-                              double *hist, int hinted, int window, int interp, hipStream_t stream) {
-  hipLaunchKernelGGL(k_scd_init, dim3((K + 63) / 64), dim3(64), 0, stream, st, K, lam_in, kmask,
-                     hist, hinted, window, interp);
-  return hipGetLastError();
-}
-
-hipError_t kp_launch_scd_locate_select(KState *st, int K, const double *B, const double *R,
-                                       const int *rinst, XSum *hist_sum, uint32_t *hist_cnt,
-                                       const double *ev1, const double *ev2, uint32_t emit_cap,
-                                       int *pending, unsigned int *win, hipStream_t stream) {
-  hipLaunchKernelGGL(k_scd_locate, dim3((K + 63) / 64), dim3(64), 0, stream, st, K, B, R, rinst, hist_sum,
-                     hist_cnt, emit_cap, win);
-  hipLaunchKernelGGL(k_scd_select, dim3(K), dim3(SEL_NT), 0, stream, st, B, ev1, ev2, emit_cap, win);
-  hipLaunchKernelGGL(k_count_pending, dim3(1), dim3(256), 0, stream, st, K, pending);
-  return hipGetLastError();
-}
-
-hipError_t kp_launch_count_modes(const KState *st, int K, int *out, hipStream_t stream) {
-  hipLaunchKernelGGL(k_count_modes, dim3(1), dim3(256), 0, stream, st, K, out);
-  return hipGetLastError();
-}
-
-hipError_t kp_launch_scd_finish(const KState *st, int K, const double *lam_in, double *lam_out,
-                                double *delta_next, hipStream_t stream) {
-  hipLaunchKernelGGL(k_scd_finish, dim3((K + 63) / 64), dim3(64), 0, stream, st, K, lam_in,
-                     lam_out, delta_next, (int *)nullptr);
-  return hipGetLastError();
-}
-
 static unsigned gather_blocks(int64_t total) {
   int64_t b = (total + 255) / 256;
   return (unsigned)(b < 1 ? 1 : (b > 4096 ? 4096 : b));
@@ -2538,12 +1944,6 @@ hipError_t kp_launch_gather_csr(const int64_t *rowptr, const int32_t *col, const
                                 int32_t *scol, float *sval, hipStream_t stream) {
   hipLaunchKernelGGL(k_gather_csr, dim3(gather_blocks(n * M)), dim3(256), 0, stream, rowptr, col, val,
                      users, n, M, subptr, scol, sval);
-  return hipGetLastError();
-}
-
-hipError_t kp_launch_recenter(KState *st, int K, const double *lam_hat, const double *lam_in, int window,
-                              hipStream_t stream) {
-  hipLaunchKernelGGL(k_scd_recenter, dim3((K + 63) / 64), dim3(64), 0, stream, st, K, lam_hat, lam_in, window);
   return hipGetLastError();
 }
 
