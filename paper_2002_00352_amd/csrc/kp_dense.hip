@@ -47,7 +47,7 @@ __host__ __device__ inline size_t dn_lds(int M, int K, int L, bool win) {
   size_t s = dn_r16((size_t)K * 8) + dn_r16((size_t)L * 8 + 8) + dn_r16((size_t)L * 4 + 4) +
              dn_r16((size_t)TU * M * 4) + dn_r16((size_t)TU * M * K * 4);
   if (win)
-    s += dn_r16((size_t)K * sizeof(KState)) + dn_r16((size_t)K * 4) + dn_r16((size_t)(K + 1) * 8) +
+    s += dn_r16((size_t)K * sizeof(KWalk)) + dn_r16((size_t)K * 4) + dn_r16((size_t)(K + 1) * 8) +
          dn_r16((size_t)K * sizeof(XSum)) + 3 * dn_r16((size_t)K * 4) + 2 * dn_r16((size_t)K * 8) + dn_r16(16) +
          (size_t)M * 64 * 8;
   return s;
@@ -79,7 +79,7 @@ __global__ void __launch_bounds__(64) k_dense(const SweepArgs a, int x4) {
   int *tcap = (int *)carve((size_t)L * 4 + 4);
   float *sp = (float *)carve((size_t)TU * M * 4);       // [TU][M]
   float *sb = (float *)carve((size_t)TU * M * K * 4);   // [TU][M][K]
-  KState *kst = nullptr;
+  KWalk *kst = nullptr;
   int *kmode = nullptr;
   double *hwin = nullptr;
   XSum *kcorr = nullptr;
@@ -87,7 +87,7 @@ __global__ void __launch_bounds__(64) k_dense(const SweepArgs a, int x4) {
   unsigned long long *hmin = nullptr, *hmax = nullptr;
   double *ptl = nullptr;
   if (WIN) {
-    kst = (KState *)carve((size_t)K * sizeof(KState));
+    kst = (KWalk *)carve((size_t)K * sizeof(KWalk));
     kmode = (int *)carve((size_t)K * 4);
     hwin = (double *)carve((size_t)(K + 1) * 8);   // [K] window half-widths (0: none), [K] their max
     kcorr = (XSum *)carve((size_t)K * sizeof(XSum));

@@ -123,10 +123,10 @@ __device__ __forceinline__ int fx_bin_of(const uint64_t *split, int nb, uint64_t
 // Breakpoint arithmetic of the walks.  For lines z_a = c_a - lambda b_a and
 // z_b = c_b - lambda b_b with b_a > b_b, the crossing is
 // fl(fl(c_a - c_b) / fl(b_a - b_b)) and line a ranks above line b for lambda
-// below it; a line's zero crossing is fl(c_a / b_a).  cr_gt / cr_ge decide
-// fl(num / den) > t and >= t for den > 0 from exact fma residual signs and
-// divide only when the quotient lies within one ulp of t, so that the
-// decisions agree with the divided crossings bit for bit.
+// below it; a line's zero crossing is fl(c_a / b_a).  cr_gt decides
+// fl(num / den) > t for den > 0 from exact fma residual signs and divides
+// only when the quotient lies within one ulp of t, so that the decisions
+// agree with the divided crossings bit for bit.
 __device__ __forceinline__ bool cr_gt(double num, double den, double t) {   // t >= 0
   const double r = fma(-t, den, num);            // sign of num - t*den, exact
   if (!(r > 0.0)) return false;                  // quotient <= t
@@ -135,33 +135,6 @@ __device__ __forceinline__ bool cr_gt(double num, double den, double t) {   // t
   if (r2 >= 0.0) return true;                    // quotient >= up
   return num / den > t;
 }
-__device__ __forceinline__ bool cr_ge(double num, double den, double t) {   // t > 0
-  const double r = fma(-t, den, num);
-  if (r >= 0.0) return true;                     // quotient >= t
-  const double dn = kdbl(dkey(t) - 1);           // next double below t
-  const double r2 = fma(-dn, den, num);
-  if (!(r2 > 0.0)) return false;                 // quotient <= dn
-  return num / den >= t;
-}
-// Is the line (c, b), b >= 0, positive just above t (side > 0) or just below
-// t (side < 0, t > 0)?
-__device__ __forceinline__ bool line_pos(double c, double b, double t, int side) {
-  if (b == 0.0) return c > 0.0;
-  return side > 0 ? cr_gt(c, b, t) : cr_ge(c, b, t);
-}
-// Does line o rank above line s just above / below t?  Parallel lines keep
-// the order (c desc, index asc).
-__device__ __forceinline__ bool line_beats(double co, double bo, int o, double cs, double bs, int s,
-                                           double t, int side) {
-  if (bo == bs) return co > cs || (co == cs && o < s);
-  if (bo > bs) {
-    const double num = co - cs, den = bo - bs;
-    return side > 0 ? cr_gt(num, den, t) : cr_ge(num, den, t);
-  }
-  const double num = cs - co, den = bs - bo;
-  return side > 0 ? !cr_gt(num, den, t) : !cr_ge(num, den, t);
-}
-
 // Laminar-matroid greedy over the ranked items: accept an eligible item when
 // no node containing it is full.  Equivalent to Alg.1 (both return the unique
 // maximum-weight independent set under the strict order (p~ desc, j asc)).
@@ -188,7 +161,7 @@ __device__ __forceinline__ uint64_t greedy_mask(const uint8_t *perm, int M, uint
 // lambda_k^t and emits the central ones; later passes emit one bucket or key
 // range, record a bucket's key hull, or bin a key range linearly.  Emitted
 // events go to the block's staging region (published by publish_block).
-__device__ __forceinline__ void record_event(const SweepArgs &a, const KState &ks, int k, double best,
+__device__ __forceinline__ void record_event(const SweepArgs &a, const KWalk &ks, int k, double best,
                                              double v2, int mode, XSum *hs, uint32_t *hc,
                                              unsigned long long *hmin, unsigned long long *hmax,
                                              uint32_t *kcnt, uint32_t *kovf, uint32_t *nstage,
@@ -274,58 +247,181 @@ __device__ __forceinline__ void publish_block(const SweepArgs &a, int K, XSum *h
   }
 }
 
-// Is S, the greedy set at lambda^t, still the greedy solution of the lines
-// z_j = c_j - lambda_k b_jk just above t (side > 0) or just below t
-// (side < 0)?  Only relations that involve an item moving with k (A) can
-// differ from those at lambda^t.  S is the greedy solution iff its members
-// stay positive and every positive non-member closes a circuit with S (the
-// members of the innermost full set containing it) and ranks below every
-// member of it.  line(j, c, b) gives item j's line (b = 0 outside A); Bpos:
-// the items with p~ > 0 outside S.
-template <class LINE>
-__device__ __forceinline__ bool window_keeps(uint64_t S, uint64_t A, uint64_t Bpos, LINE line,
-                                             const uint64_t *tmask, const int *tcap, int L, double t,
-                                             int side) {
-  auto circuit = [&](int o) -> uint64_t {
+// Relative tolerance of the decisions taken from moved lines: values computed
+// as z - d b differ from the lines that the breakpoint arithmetic uses by a
+// few 2^-53 of |z| + (lambda_k + t) b, so what is farther apart than 2^-44 of
+// those magnitudes is decided the same way by both.
+#define KP_LINE_TOL 0x1p-44
+
+// One (user, knapsack) pair of a breakpoint phase: its breakpoints in
+// [ks.tlo, ks.thi], from the top.
+//
+// The state of the walk is the greedy set S; the next breakpoint below is the
+// highest crossing of an item outside S with zero (a free item) or with a
+// member of the innermost full set that holds it (Alg.1's exchange);
+// fma-residual comparisons decide which is highest.  Above every breakpoint S
+// is the greedy set T of the items that do not move with k: S0, the one at
+// lambda^t, without its moving members and with the best fixed items that
+// come in for them.  Where the range has an upper end the walk starts there:
+// each moving item, positive at thi, is added to T or exchanged for the
+// lowest member of its circuit (the matroid greedy does not depend on the
+// order of insertion), and a set that is still the greedy one at tlo has no
+// breakpoint in between -- for most pairs these two looks at the moving items
+// are all.  Decisions within rounding of a tie are not taken from moved
+// lines: such a pair is walked from the top.  (Walking every pair from the
+// top in every pass cost 3-4.5 ms a pass of 3e5 users with M = 23, K = 12.)
+//
+// A: the items moving with k, zv(j): p~_j, bv(j): item j's cost in k (0
+// outside A), rk(r): the item of rank r by (p~ desc, index asc), pos: the
+// items with p~ > 0; emit(v1, v2) takes a breakpoint in the range.  *above:
+// a window's consumption just above thi.  Returns false when the walk runs
+// past its event limit.
+template <class ZV, class BV, class RK, class EM>
+__device__ __forceinline__ bool walk_pair(int M, int L, const uint64_t *tmask, const int *tcap, uint64_t A,
+                                          uint64_t S0, uint64_t pos, ZV zv, BV bv, RK rk, double lk,
+                                          const KWalk &ks, EM emit, double *above_out) {
+  const bool window = ks.mode == KS_WINDOW;
+  const double tlo = ks.tlo, thi = ks.thi;
+  // the members of S in the innermost full set that holds o (0: none is full)
+  auto circuit = [&](uint64_t S, int o) -> uint64_t {
     for (int l = 0; l < L; ++l) {
       const uint64_t m = tmask[l];
       if ((m >> o & 1) && popc64(S & m) >= tcap[l]) return S & m;
     }
     return 0;
   };
-  for (uint64_t m = S & A; m; m &= m - 1) {
-    const int s = __ffsll((long long)m) - 1;
-    double c, b;
-    line(s, c, b);
-    if (!line_pos(c, b, t, side)) return false;
-  }
-  for (uint64_t m = A & ~S; m; m &= m - 1) {
-    const int o = __ffsll((long long)m) - 1;
-    double co, bo;
-    line(o, co, bo);
-    if (!line_pos(co, bo, t, side)) continue;
-    uint64_t circ = circuit(o);
-    if (!circ) return false;
-    for (; circ; circ &= circ - 1) {
-      const int s = __ffsll((long long)circ) - 1;
-      double cs, bs;
-      line(s, cs, bs);
-      if (line_beats(co, bo, o, cs, bs, s, t, side)) return false;
+  uint64_t T = S0 & ~A;
+  {
+    // every moving member gone lets at most one fixed item in
+    int left = popc64(S0 & A);
+    uint64_t cand = pos & ~A & ~S0;
+    for (int r = 0; left > 0 && cand; ++r) {
+      const int j = rk(r);
+      if (!(cand >> j & 1)) continue;
+      cand &= ~(1ull << j);
+      if (!circuit(T, j)) { T |= 1ull << j; --left; }
     }
   }
-  for (uint64_t m = Bpos & ~A; m; m &= m - 1) {
-    const int o = __ffsll((long long)m) - 1;
-    uint64_t circ = circuit(o) & A;
-    if (!circ) continue;
-    double co, bo;
-    line(o, co, bo);
-    for (; circ; circ &= circ - 1) {
-      const int s = __ffsll((long long)circ) - 1;
-      double cs, bs;
-      line(s, cs, bs);
-      if (line_beats(co, bo, o, cs, bs, s, t, side)) return false;
+  uint64_t S = T;
+  bool at = thi < INFINITY;   // S is the greedy set at thi
+  if (at) {
+    const double d = thi - lk, mt = lk + thi;
+    uint64_t cc = 0;           // the circuit that the lowest member below belongs to
+    int s1 = -1;
+    double v1 = 0.0, z1 = 0.0, b1 = 0.0, t1 = 0.0;
+    bool amb = false;          // another, different line within rounding of it
+    for (uint64_t m = A; m; m &= m - 1) {
+      const int o = __ffsll((long long)m) - 1;
+      const double zo = zv(o), bo = bv(o), so = d * bo;
+      const double vo = zo - so, to = KP_LINE_TOL * (fabs(zo) + mt * bo);
+      if (vo < -to) continue;
+      if (!(vo > to)) { at = false; break; }
+      const uint64_t circ = circuit(S, o);
+      if (!circ) { S |= 1ull << o; continue; }
+      if (circ != cc) {
+        cc = circ;
+        s1 = -1;
+        amb = false;
+        for (uint64_t c = circ; c; c &= c - 1) {
+          const int s = __ffsll((long long)c) - 1;
+          const double zs = zv(s), bs = bv(s), ss = d * bs;
+          const double vs = zs - ss, ts = KP_LINE_TOL * (fabs(zs) + mt * bs);
+          if (s1 >= 0 && zs == z1 && bs == b1) { s1 = s; continue; }   // one line: the higher index is lower
+          if (s1 < 0 || vs < v1) {
+            amb = s1 >= 0 && v1 - vs <= t1 + ts;
+            s1 = s; v1 = vs; z1 = zs; b1 = bs; t1 = ts;
+          } else if (vs - v1 <= t1 + ts) {
+            amb = true;
+          }
+        }
+      }
+      if (zo == z1 && bo == b1) {
+        if (o > s1) continue;
+      } else {
+        const double diff = vo - v1;
+        if (fabs(diff) <= to + t1) { at = false; break; }
+        if (diff < 0.0) continue;
+      }
+      if (amb) { at = false; break; }
+      S = (S | (1ull << o)) & ~(1ull << s1);
+      cc = 0;
     }
+    if (!at) S = T;
   }
+  double above = 0.0;
+  if (at) {
+    if (window)
+      for (uint64_t m = S & A; m; m &= m - 1) above = above + bv(__ffsll((long long)m) - 1);
+    // does any moving item outside S come in at or above tlo?
+    const double d = tlo - lk, mt = lk + tlo;
+    bool quiet = true;
+    uint64_t cc = 0;
+    double vmin = 0.0, tmax = 0.0;   // lowest value at tlo over that circuit, largest tolerance
+    for (uint64_t m = A & ~S; quiet && m; m &= m - 1) {
+      const int o = __ffsll((long long)m) - 1;
+      const double zo = zv(o), bo = bv(o), so = d * bo;
+      const double vo = zo - so, to = KP_LINE_TOL * (fabs(zo) + mt * bo);
+      if (vo < -to) continue;
+      const uint64_t circ = circuit(S, o);
+      if (!circ) { quiet = false; break; }
+      if (circ != cc) {
+        cc = circ;
+        vmin = INFINITY;
+        tmax = 0.0;
+        for (uint64_t c = circ; c; c &= c - 1) {
+          const int s = __ffsll((long long)c) - 1;
+          const double zs = zv(s), bs = bv(s), ss = d * bs;
+          vmin = fmin(vmin, zs - ss);
+          tmax = fmax(tmax, KP_LINE_TOL * (fabs(zs) + mt * bs));
+        }
+      }
+      if (vmin - vo > to + tmax) continue;
+      for (uint64_t c = circ; c; c &= c - 1) {
+        const int s = __ffsll((long long)c) - 1;
+        const double bs = bv(s);
+        if (bs >= bo) continue;   // stays above o all the way down
+        const double zs = zv(s), ss = d * bs;
+        if (!(zs - ss - vo > to + KP_LINE_TOL * (fabs(zs) + mt * bs))) { quiet = false; break; }
+      }
+    }
+    if (quiet) { *above_out = above; return true; }
+  }
+  const int maxev = M * M + M + 8;
+  for (int ev = 0;; ++ev) {
+    if (ev >= maxev) return false;
+    double best = 0.0;
+    int bo = -1, bs = -1;
+    for (uint64_t cand = A & ~S; cand; cand &= cand - 1) {
+      const int o = __ffsll((long long)cand) - 1;
+      const double bo_d = bv(o);
+      const double add_o = lk * bo_d;
+      const double co = zv(o) + add_o;
+      uint64_t circ = circuit(S, o);
+      // compared with the running maximum through cr_gt: a division only
+      // for a crossing that beats it
+      if (!circ) {
+        if (co > 0.0 && cr_gt(co, bo_d, best)) { best = co / bo_d; bo = o; bs = -1; }
+      } else {
+        for (; circ; circ &= circ - 1) {
+          const int s = __ffsll((long long)circ) - 1;
+          const double bs_d = bv(s);
+          if (bs_d < bo_d) {
+            const double add_s = lk * bs_d;
+            const double cs = zv(s) + add_s;
+            const double num = co - cs;
+            const double den = bo_d - bs_d;
+            if (cr_gt(num, den, best)) { best = num / den; bo = o; bs = s; }
+          }
+        }
+      }
+    }
+    if (bo < 0 || best < tlo) break;   // every later breakpoint is lower
+    const double v2 = bs >= 0 ? bv(bo) - bv(bs) : bv(bo);
+    S = (S | (1ull << bo)) & ~(bs >= 0 ? (1ull << bs) : 0ull);
+    if (window && best > thi) above = above + v2;
+    else emit(best, v2);
+  }
+  *above_out = above;
   return true;
 }
 

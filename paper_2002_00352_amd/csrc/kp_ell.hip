@@ -26,7 +26,7 @@ static size_t ell_lds(int M, int K, int D, int L, int mode, int waves, int *regi
   if (mode != KM_EVAL && mode != KM_FIX) s += r16((size_t)K * 4) + r16((size_t)K * 8 + 16);
   if (mode == KM_WMAIN) s += r16((size_t)(K + 1) * sizeof(LamW));
   if (brk)   // (the listed users' pass of a window pass bins nothing: no histograms)
-    s += r16((size_t)K * sizeof(XSum)) + r16((size_t)K * sizeof(KState)) +
+    s += r16((size_t)K * sizeof(XSum)) + r16((size_t)K * sizeof(KWalk)) +
          (mode == KM_SCD ? r16((size_t)K * KP_NB * sizeof(XSum)) + r16((size_t)K * KP_NB * 4) : 0) +
          3 * r16((size_t)K * 4) + 2 * r16((size_t)K * 8) + r16(16);
   s += (size_t)ew * region;

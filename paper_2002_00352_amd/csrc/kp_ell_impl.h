@@ -104,108 +104,31 @@ struct EllGeom {
 };
 
 // One (user, knapsack) pair of a lane-per-user breakpoint phase, run by
-// any lane of the wave for the user of lane col.  In a window pass the
-// user's greedy set at lambda^t is kept when it stays optimal at both edges
-// of the window; otherwise the pair is walked exactly from above every
-// breakpoint: the next breakpoint below is the highest crossing of an item
-// outside the current set with zero (a free item) or with a member of the
-// innermost full set holding it (Alg.1's exchange), fma-residual comparisons
-// deciding which is highest.  Breakpoints inside the window are emitted
-// (other search modes: binned or emitted by record_event), those above it
-// add up to C_ik(whi+), and C_ik(whi+) - v_ik goes into the window
+// any lane of the wave for the user of lane col (walk_pair).  Breakpoints in
+// the pass's range are emitted (other search modes: binned or emitted by
+// record_event), and in a window pass C_ik(whi+) - v_ik goes into the window
 // correction.  A: the items moving with k; bkc(j, c): the cost in k of item
 // j of lane c's user (j in A); ptl: the lanes' p~ columns [M][64]; Sc, posc,
 // permc: the user's greedy set, positive items and rank order.
 template <class BKC>
 __device__ __forceinline__ void lane_walk_pair(const SweepArgs &a, int M, int L, int col, int k, uint64_t A,
                                                uint64_t Sc, uint64_t posc, uint64_t permc, BKC bkc,
-                                               const double *ptl, const double *lam, const KState *kst,
+                                               const double *ptl, const double *lam, const KWalk *kst,
                                                const int *kmode, const uint64_t *tmask, const int *tcap,
                                                XSum *kcorr, XSum *hs, uint32_t *hc, unsigned long long *hmin,
                                                unsigned long long *hmax, uint32_t *kcnt, uint32_t *kovf,
                                                uint32_t *nstage) {
   const int mode = kmode[k];
-  const double lk = lam[k];
-  if (mode == KS_WINDOW) {
-    const double whi = kst[k].whi, wlo = kst[k].wlo;
-    auto line = [&](int j, double &c, double &b) {
-      b = (A >> j & 1) ? bkc(j, col) : 0.0;
-      const double add = lk * b;
-      c = ptl[j * 64 + col] + add;
-    };
-    if (window_keeps(Sc, A, posc & ~Sc, line, tmask, tcap, L, whi, 1) &&
-        window_keeps(Sc, A, posc & ~Sc, line, tmask, tcap, L, wlo, wlo > 0.0 ? -1 : 1))
-      return;
-  }
-  // start: only horizontal positive lines, in p~ order
-  uint64_t Sw = 0;
-  {
-    uint64_t blocked = 0;
-    const uint64_t elig = posc & ~A;
-    for (int r = 0; r < M; ++r) {
-      const int j = (int)((permc >> (4 * r)) & 15);
-      const uint64_t bit = 1ull << j;
-      if ((elig & bit) && !(blocked & bit)) {
-        Sw |= bit;
-        for (int l = 0; l < L; ++l) {
-          const uint64_t m = tmask[l];
-          if ((m & bit) && popc64(Sw & m) >= tcap[l]) blocked |= m;
-        }
-      }
-    }
-  }
   double above = 0.0;
-  const int maxev = M * M + M + 8;
-  for (int ev = 0;; ++ev) {
-    if (ev >= maxev) { atomicAdd(a.err, 1ull); break; }
-    double best = 0.0;
-    int bo = -1, bs = -1;
-    uint64_t cand = A & ~Sw;
-    while (cand) {
-      const int o = __ffsll((long long)cand) - 1;
-      cand &= cand - 1;
-      const double bo_d = bkc(o, col);
-      const double add_o = lk * bo_d;
-      const double co = ptl[o * 64 + col] + add_o;
-      uint64_t circ = 0;
-      bool tight = false;
-      for (int l = 0; l < L; ++l) {
-        const uint64_t m = tmask[l];
-        if ((m >> o & 1) && popc64(Sw & m) >= tcap[l]) { circ = Sw & m; tight = true; break; }
-      }
-      // compared with the running maximum through cr_gt: a division only
-      // for a crossing that beats it
-      if (!tight) {
-        if (co > 0.0 && cr_gt(co, bo_d, best)) { best = co / bo_d; bo = o; bs = -1; }
-      } else {
-        while (circ) {
-          const int s2 = __ffsll((long long)circ) - 1;
-          circ &= circ - 1;
-          const double bs_d = (A >> s2 & 1) ? bkc(s2, col) : 0.0;
-          if (bs_d < bo_d) {
-            const double add_s = lk * bs_d;
-            const double cs = ptl[s2 * 64 + col] + add_s;
-            const double num = co - cs;
-            const double den = bo_d - bs_d;
-            if (cr_gt(num, den, best)) { best = num / den; bo = o; bs = s2; }
-          }
-        }
-      }
-    }
-    if (bo < 0) break;
-    const double bo_d = bkc(bo, col);
-    const double bsv = (bs >= 0 && (A >> bs & 1)) ? bkc(bs, col) : 0.0;
-    const double v2 = bs >= 0 ? bo_d - bsv : bo_d;
-    if (mode == KS_WINDOW) {
-      const uint64_t key = dkey(best);
-      if (key < kst[k].klo) break;          // every later breakpoint is lower
-      if (key > kst[k].khi) above = above + v2;
-      else record_event(a, kst[k], k, best, v2, mode, hs, hc, hmin, hmax, kcnt, kovf, nstage, blockIdx.x);
-    } else {
-      record_event(a, kst[k], k, best, v2, mode, hs, hc, hmin, hmax, kcnt, kovf, nstage, blockIdx.x);
-    }
-    Sw = (Sw | (1ull << bo)) & ~(bs >= 0 ? (1ull << bs) : 0ull);
-  }
+  const bool ok = walk_pair(
+      M, L, tmask, tcap, A, Sc, posc, [&](int j) -> double { return ptl[j * 64 + col]; },
+      [&](int j) -> double { return (A >> j & 1) ? bkc(j, col) : 0.0; },
+      [&](int r) -> int { return (int)((permc >> (4 * r)) & 15); }, lam[k], kst[k],
+      [&](double v1, double v2) {
+        record_event(a, kst[k], k, v1, v2, mode, hs, hc, hmin, hmax, kcnt, kovf, nstage, blockIdx.x);
+      },
+      &above);
+  if (!ok) atomicAdd(a.err, 1ull);
   if (mode == KS_WINDOW) {
     double now = 0.0;
     for (uint64_t m = Sc & A; m; m &= m - 1) now = now + bkc(__ffsll((long long)m) - 1, col);
@@ -264,7 +187,7 @@ __device__ __forceinline__ void scd_user(const SweepArgs &a, int M, int K, int L
                                          uint64_t S, uint64_t pos, uint64_t perm, double bmax,
                                          const double *ptl, const float *btl, const uint8_t *ktl,
                                          const uint16_t *mskl, const double *lam, const uint64_t *tmask,
-                                         const int *tcap, const KState *kst, const int *kmode,
+                                         const int *tcap, const KWalk *kst, const int *kmode,
                                          const double *hwin, XSum *kcorr, XSum *hs, uint32_t *hc,
                                          unsigned long long *hmin, unsigned long long *hmax,
                                          uint32_t *kcnt, uint32_t *kovf, uint32_t *nstage) {
@@ -384,10 +307,10 @@ __device__ __forceinline__ void scd_user(const SweepArgs &a, int M, int K, int L
       if (!walk_mode(mode)) continue;
       const uint32_t A = mskl[k * 64 + lane];
       if (A != (1u << j)) {
-        if (j == __ffs((int)A) - 1 && !(mode == KS_WINDOW && calm(k, A))) pending |= 1ull << k;
+        if (j == __ffs((int)A) - 1 && !(hwin[k] > 0.0 && calm(k, A))) pending |= 1ull << k;
         continue;
       }
-      if (mode == KS_WINDOW && calm(k, A)) continue;
+      if (hwin[k] > 0.0 && calm(k, A)) continue;
       const double lk = lam[k];
       const double bo_d = (double)btl[(j * D + t) * 64 + lane];
       const double add_o = lk * bo_d;
@@ -401,19 +324,18 @@ __device__ __forceinline__ void scd_user(const SweepArgs &a, int M, int K, int L
           const double num = pk - pbar;
           best = num / bo_d;
         }
-      } else if (zlev >> j & 1) {
-        if (co > 0.0) best = co / bo_d;
       } else {
-        const int th = (int)((tau >> (4 * j)) & 15);
-        const double bs_d = 0.0;
-        const double add_s = lk * bs_d;
-        const double cs = ptl[th * 64 + lane] + add_s;
-        const double num = co - cs;
-        const double den = bo_d - bs_d;
-        const double val = num / den;
-        if (val > 0.0) best = val;
+        // the threshold element is a fixed line (or zero): (co - cs) / bo_d
+        double num = co;
+        if (!(zlev >> j & 1)) num = co - ptl[(int)((tau >> (4 * j)) & 15) * 64 + lane];
+        // divided only where the quotient can lie in the pass's range: below
+        // it nothing is emitted, above it a window counts it as above
+        if (num > 0.0 && num >= kst[k].tlo * bo_d * (1.0 - 0x1p-40)) {
+          if (mode == KS_WINDOW && num > kst[k].thi * bo_d * (1.0 + 0x1p-40)) best = INFINITY;
+          else best = num / bo_d;
+        }
       }
-      if (best > 0.0)
+      if (best > 0.0 && best < INFINITY)
         record_event(a, kst[k], k, best, bo_d, mode, hs, hc, hmin, hmax, kcnt, kovf, nstage, blockIdx.x);
       if (mode == KS_WINDOW) {
         // consumption just above the window against the one at lambda^t
@@ -488,7 +410,7 @@ k_ell(const SweepArgs a, const EllGeom g) {
   uint64_t *tmask = (uint64_t *)carve((size_t)a.tree.L * 8 + 8);
   int *tcap = (int *)carve((size_t)a.tree.L * 4 + 4);
   double *wacc = (double *)carve((size_t)EWM * (K + 2) * 8);
-  KState *kst = BREAK ? (KState *)carve((size_t)K * sizeof(KState)) : nullptr;
+  KWalk *kst = BREAK ? (KWalk *)carve((size_t)K * sizeof(KWalk)) : nullptr;
   XSum *hs = nullptr;
   uint32_t *hc = nullptr, *kcnt = nullptr, *kpos = nullptr, *kovf = nullptr, *nstage = nullptr;
   int *kmode = nullptr;
@@ -539,7 +461,9 @@ k_ell(const SweepArgs a, const EllGeom g) {
   if (!EV) {
     for (int t = tid; t < K; t += ENT) {
       kmode[t] = a.st[t].mode;
-      hwin[t] = a.st[t].mode == KS_WINDOW ? a.st[t].hw : 0.0;
+      // (breakpoint phases: only windows that contain lambda_k^t take the gap
+      // tests; a window away from it moves the lines past each other)
+      hwin[t] = a.st[t].mode == KS_WINDOW && !(BREAK && a.st[t].far) ? a.st[t].hw : 0.0;
       if (MODE == KM_WMAIN) {
         const double h = hwin[t];
         // wA_k, widened by 2^-20 before rounding to fp32 so that the fp32

@@ -70,29 +70,34 @@ enum {
 #define KS_FLAG_WINDOW 1u  // the key range of KS_SELECT_RANGE is a window: the threshold may lie outside
 #define KS_FLAG_INTERP 2u  // approximate reduce: interpolate inside the bucket that holds the threshold
 
-struct KState {
+// What a sweep pass needs of a knapsack's search state (its LDS copy).
+struct KWalk {
   int mode;
   int bstar;           // exponential bucket id (-31..31) for the bucket modes
   int shift;           // key-bin shift for KS_REFINE
+  int far;             // KS_WINDOW: the window does not contain lambda_k^t
+  double center;       // lambda_k^t (or a sample's threshold)
+  double delta;        // central bucket half-width (a power of two)
+  uint64_t klo, khi;   // inclusive key range
+  double wlo, whi;     // KS_WINDOW: breakpoints with wlo <= v1 <= whi are emitted (wlo may be 0)
+  double hw;           // KS_WINDOW: the distance from lambda_k^t to the window's far edge
+  double tlo, thi;     // every breakpoint the pass looks for lies in [tlo, thi] (thi may be infinite)
+};
+
+struct KState : KWalk {
   int overflow;        // emission exceeded the buffer
   uint32_t n_emit;     // emitted events (atomic)
   uint32_t flags;      // KS_FLAG_*
-  double center;       // lambda_k^t
-  double delta;        // central bucket half-width (a power of two)
+  uint32_t ecap;       // batched: this knapsack's emission capacity (0: the uniform capacity of the call)
+  uint64_t eoff;       // batched: its emission buffer (elements from the base), when ecap > 0
   XSum fab;            // sum of increments strictly above the current target
   double result;       // lambda_k^{t+1} once mode == KS_DONE
-  uint64_t klo, khi;   // inclusive key range
   uint64_t hull_lo, hull_hi;  // atomics: key hull of the bucket's events
-  double wlo, whi;     // KS_WINDOW: breakpoints with wlo <= v1 <= whi are emitted (wlo may be 0)
-  double hw;           // KS_WINDOW: half-width h (whi = center + h, wlo = max(center - h, 0))
-  uint64_t eoff;       // batched: this knapsack's emission buffer (elements from the base), when ecap > 0
-  uint32_t ecap;       // batched: its capacity (0: the uniform capacity of the call)
-  uint32_t ncomp;      // selection: events of the threshold's bin compacted (atomic)
-  uint64_t sel_lo, sel_hi;    // selection: that bin's keys
+  XSum corr;           // KS_WINDOW: sum over users of C_ik(whi+) - v_ik(x(lambda^t))
+  uint64_t sel_lo, sel_hi;    // selection: keys of the bin that holds the threshold
   XSum sel_fab;        // selection: sum of increments above it
   int sel_bin;         // selection: the bin (-1: the sum never exceeds the budget)
-  int pad3;
-  XSum corr;           // KS_WINDOW: sum over users of C_ik(whi+) - v_ik(x(lambda^t))
+  uint32_t ncomp;      // selection: events of that bin compacted (atomic)
 };
 
 // Workspace of the selection among emitted breakpoints, per knapsack.

@@ -85,8 +85,12 @@ __device__ __forceinline__ void issue_entries(Prefetch &f, const ProbDev &pr, in
   }
 }
 
-// The far-window test for at most one binding set (far_window_single) in
-// two parts.  First pass: zmax, the selection outside the set (whose moving
+// A window that does not contain lambda_k^t, dense costs, at most one binding
+// set (mask m1, cap c1): the lines moved to the window's centre c,
+// z'_j = p~_j - (c - lambda_k^t) b_jk.  Over the window (radius r around c) a
+// line moves by at most r b_jk, so the selection at c stays the same when
+// the selected lines stay farther than r bmax (plus a rounding margin) from
+// the others of the set and from zero.  In two parts.  First pass: zmax, the selection outside the set (whose moving
 // members must keep their sign: the smallest |z'| among those that may be
 // positive is checked against the bound), and the set's positive members
 // with their smallest z' and the best other members (all of them; moving
@@ -196,100 +200,6 @@ __device__ __forceinline__ bool far_finish(const FarPass &f, const double *zu, c
   return true;
 }
 
-// The same test for at most one binding set (top-Q and the like: set mask
-// m1 with cap c1, or no set), for any M, in O(M c1) with no per-item
-// state: items outside the set are selected when positive, so a moving one
-// must keep its sign over the window; inside the set the selection at c is
-// the c1 best positive members T (picked by repeated maxima, two per pass
-// over the set, ties to the lower index), and it stays the same when T
-// stays positive and the best other member stays below T (one gap: every
-// pair across it moves against each other by at most r bmax), or, when
-// fewer than c1 members are positive, when no moving member outside T can
-// turn positive.  Returns false when the test does not apply or fails; else
-// true with *cw = the selection's consumption of k.
-__device__ __forceinline__ bool far_window_single(const double *zu, const float *bu, int M, int K, int k,
-                                                  uint64_t A, double lk, double wlo, double whi, double bmk,
-                                                  uint64_t m1, int c1, double *cw) {
-  const double c = 0.5 * (wlo + whi);
-  const double r = fmax(whi - c, c - wlo);
-  const double dl = c - lk;
-  if (!(fabs(dl) > r)) return false;
-  const double Hs = r * bmk * (1.0 + 0x1p-30) + 0x1p-36 * (1.0 + (lk + fabs(dl) + r) * bmk);
-  FarPass f;
-  #pragma unroll 4
-  for (int j = 0; j < M; ++j) {
-    const double b = (A >> j & 1) ? (double)bu[j * K + k] : 0.0;
-    const double s = dl * b;
-    far_item(f, zu[j] - s, j, (A >> j & 1) != 0, (m1 >> j & 1) != 0, Hs);
-  }
-  return far_finish(f, zu, bu, M, K, k, A, lk, dl, r, bmk, Hs, m1, c1, cw);
-}
-
-// A window that does not contain lambda_k^t (an alternation window around
-// lambda_k^{t-1}): move the user's lines to the window's centre c,
-// z'_j = p~_j - (c - lambda_k^t) b_jk.  Over the window (radius r around c)
-// a moving line moves by at most r b_jk, so no two lines cross in it (nor a
-// moving line and zero) when every such gap between lines that can turn
-// positive there exceeds r bmax plus a rounding margin; then the greedy set
-// is the same over the whole window, and it is Alg.1 on the moved lines (in
-// rank space, as a mask of ranks).  Returns false when the test does not
-// apply or fails; else true with *cw = the set's consumption of k, in item
-// order.  zu: p~ of the user's items, bu: its costs [M][K]; A: the items
-// moving with k.  M <= 16.
-__device__ __forceinline__ bool far_window_set(const double *zu, const float *bu, int M, int K, int k,
-                                               uint64_t A, double lk, double wlo, double whi, double bmk,
-                                               const TreeDev &T, double *cw) {
-  const double c = 0.5 * (wlo + whi);
-  const double r = fmax(whi - c, c - wlo);
-  const double dl = c - lk;
-  if (M > 16 || !(fabs(dl) > r)) return false;
-  const double Hs = r * bmk * (1.0 + 0x1p-30) + 0x1p-36 * (1.0 + (lk + fabs(dl) + r) * bmk);
-  auto moved = [&](int j) -> double {
-    const double b = (A >> j & 1) ? (double)bu[j * K + k] : 0.0;
-    const double s = dl * b;
-    return zu[j] - s;
-  };
-  uint64_t rk = 0;   // rank of every item by (z' desc, index asc), 4 bits each
-  for (int j = 0; j < M; ++j) rk |= (uint64_t)j << (4 * j);
-  uint64_t posc = 0;
-  double gmin = 1e300, zmax = 0.0;
-  for (int x = 0; x < M; ++x) {
-    const double zx = moved(x);
-    const bool mx = A >> x & 1, rx = zx > -Hs;
-    if (zx > 0.0) posc |= 1ull << x;
-    if (rx) zmax = fmax(zmax, fabs(zx));
-    if (rx && mx) gmin = fmin(gmin, fabs(zx));
-    for (int y = x + 1; y < M; ++y) {
-      const double zy = moved(y);
-      if (zy > zx) { rk += 1ull << (4 * x); rk -= 1ull << (4 * y); }
-      // pairs that can cross: at least one moves, and not two equal lines
-      // with equal costs in k (they coincide over the whole window)
-      const bool my = A >> y & 1;
-      if (rx && zy > -Hs && (mx || my) && !(zx == zy && bu[x * K + k] == bu[y * K + k]))
-        gmin = fmin(gmin, fabs(zx - zy));
-    }
-  }
-  const double need = r * bmk * (1.0 + 0x1p-30) + 0x1p-36 * (1.0 + zmax + Hs + (lk + fabs(dl) + r) * bmk);
-  if (!(gmin > need)) return false;
-  uint32_t alive = 0;
-  for (int j = 0; j < M; ++j)
-    if (posc >> j & 1) alive |= 1u << ((rk >> (4 * j)) & 15);
-  for (int l = 0; l < T.L; ++l) {
-    const uint64_t m = T.mask[l];
-    uint32_t mr = 0;
-    for (int j = 0; j < M; ++j)
-      if (m >> j & 1) mr |= 1u << ((rk >> (4 * j)) & 15);
-    uint32_t x = alive & mr;
-    for (int q = 0; q < T.cap[l]; ++q) x &= x - 1u;
-    alive &= ~x;
-  }
-  double sum = 0.0;
-  for (int j = 0; j < M; ++j)
-    if ((A >> j & 1) && (alive >> ((rk >> (4 * j)) & 15) & 1)) sum = sum + (double)bu[j * K + k];
-  *cw = sum;
-  return true;
-}
-
 // MX, KX: the item and knapsack counts when they are fixed at compile time
 // (dense costs with M = K = 10, or M = 20 and K = 50), else 0: the loops
 // over the items and the knapsacks then have constant trip counts (c2 SCD
@@ -309,7 +219,8 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a, const TileGeom &g
   uint8_t *perm = (uint8_t *)carve((size_t)R);            // [U][M] rank -> item
   uint64_t *Sm = (uint64_t *)carve((size_t)U * 8);        // greedy set at lambda^t
   uint64_t *Pm = (uint64_t *)carve((size_t)U * 8);        // items with p~ > 0
-  int8_t *tau = (int8_t *)carve(SCD ? (size_t)R : 0);     // per item: threshold element (-1 = zero level)
+  int8_t *tau = (int8_t *)carve(SCD ? (size_t)U * 2 : 0); // per user: the threshold elements (at most one set)
+  uint64_t *Am = (uint64_t *)carve(SCD && FMT == 1 ? (size_t)Q * 8 : 0);  // CSR: items with an entry, per (user, knapsack)
   double *vk = (double *)carve((size_t)Q * 8);            // per (user,k) consumption
   double *uPG = (double *)carve((size_t)U * 16);          // per user P_i, G_i
   double *acc = (double *)carve((size_t)(K + 2) * 8);     // block running sums
@@ -319,7 +230,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a, const TileGeom &g
   int32_t *ecl = (int32_t *)carve(FMT == 1 ? (size_t)NT * ECH * 4 : 0);  // CSR: staged entries
   float *evl = (float *)carve(FMT == 1 ? (size_t)NT * ECH * 4 : 0);
   int64_t *ebase = (int64_t *)carve(16);                  // CSR: first entry of the next tile
-  KState *kst = SCD ? (KState *)carve((size_t)K * sizeof(KState)) : nullptr;
+  KWalk *kst = SCD ? (KWalk *)carve((size_t)K * sizeof(KWalk)) : nullptr;
   XSum *hs = nullptr;
   uint32_t *hc = nullptr;
   const bool hist = !a.no_hist;   // histograms (exponential buckets, refinement bins) in LDS
@@ -439,6 +350,8 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a, const TileGeom &g
         if (t < n_ent && t < NT * ECH) { ecl[t] = f.ec[i]; evl[t] = f.ev[i]; }
       }
       for (int t = tid; t < R * K; t += NT) bt[t] = 0.0f;
+      if (SCD)
+        for (int t = tid; t < Q; t += NT) Am[t] = 0ull;
     }
     // ---- issue the next tile's loads (they land during this tile's compute) ----
     const int64_t ntile = tile + nblk;
@@ -456,8 +369,8 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a, const TileGeom &g
     // with at most one set the threshold elements follow from two items per
     // user, found by the rank phase: [0] the set's lowest selected member
     // (set full) and [1] its best positive member left out
-    const bool fastau = SCD && fastsel && M >= 2;
-    if (fastau && tid < nu) { tau[tid * M] = -1; tau[tid * M + 1] = -1; }
+    const bool fastau = SCD && fastsel;
+    if (fastau && tid < nu) { tau[2 * tid] = -1; tau[2 * tid + 1] = -1; }
     // window filter, per user: [0] the smallest gap (a minimum over the
     // rows, taken on the bits of non-negative doubles), [1] the largest cost
     // (a maximum over the rows, on the bits of a non-negative float)
@@ -492,6 +405,10 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a, const TileGeom &g
           else { k = a.pr.col[e_first + e]; v = a.pr.val[e_first + e]; }   // tile beyond the staging
           if ((unsigned)k >= (unsigned)K) continue;   // malformed column: ignored (kp_validate_inputs reports it)
           bt[(size_t)r * K + k] = v;
+          if (SCD && v > 0.0f) {
+            const int u = r / M;
+            atomicOr((unsigned long long *)&Am[u * K + k], 1ull << (r - u * M));
+          }
           const double prod = lam[k] * (double)v;
           accp = accp - prod;
         }
@@ -530,8 +447,8 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a, const TileGeom &g
       if (fastsel && zj > 0.0 && (!(m1 >> j & 1) || rank1 < c1))
         atomicOr((unsigned long long *)&Sm[u], 1ull << j);
       if (fastau && zj > 0.0 && (m1 >> j & 1)) {
-        if (rank1 == c1 - 1) tau[u * M] = (int8_t)j;
-        else if (rank1 == c1) tau[u * M + 1] = (int8_t)j;
+        if (rank1 == c1 - 1) tau[2 * u] = (int8_t)j;
+        else if (rank1 == c1) tau[2 * u + 1] = (int8_t)j;
       }
     }
     // CSR: the next tile's entry range is known now that its row offsets have
@@ -551,67 +468,6 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a, const TileGeom &g
       const uint64_t S = fastsel ? Sm[u] : greedy_mask(perm + u * M, M, pos, a.tree);
       Sm[u] = S;
       Pm[u] = pos;
-      if (SCD && !fastau) {
-        // Threshold element of every item o against the greedy solution G_o of
-        // the other items (their order does not depend on lambda_k when o is
-        // the only item that moves with it): o is selected exactly when its
-        // line beats that element (or is positive, for the zero level -1).
-        //   o not in S: G_o = S; the lowest-ranked member of S in the smallest
-        //     full set containing o, or the zero level if no set containing o
-        //     is full.
-        //   o in S: G_o = S - o + r(o) with r(o) the best positive item outside
-        //     S whose smallest full set contains o; the threshold is r(o), or
-        //     the zero level when there is none.
-        const uint8_t *pu = perm + u * M;
-        int8_t *tu = tau + u * M;
-        uint64_t assigned = S;   // items outside S get their value below
-        for (int l = 0; l < a.tree.L; ++l) {
-          const uint64_t m = a.tree.mask[l];
-          if (popc64(S & m) < a.tree.cap[l]) continue;
-          uint64_t pend = m & ~assigned;
-          if (!pend) continue;
-          int low = -1;
-          for (int r = M - 1; r >= 0; --r) {
-            const int j = pu[r];
-            if ((S & m) >> j & 1) { low = j; break; }
-          }
-          assigned |= pend;
-          while (pend) {
-            const int o = __ffsll((long long)pend) - 1;
-            pend &= pend - 1;
-            tu[o] = (int8_t)low;
-          }
-        }
-        uint64_t rest = ~assigned & ((M == 64) ? ~0ull : ((1ull << M) - 1));
-        while (rest) {
-          const int o = __ffsll((long long)rest) - 1;
-          rest &= rest - 1;
-          tu[o] = -1;
-        }
-        uint64_t resolved = 0;
-        for (int r = 0; r < M && resolved != S; ++r) {
-          const int e = pu[r];
-          if ((S >> e & 1) || !(pos >> e & 1)) continue;
-          uint64_t lm = 0;
-          for (int l = 0; l < a.tree.L; ++l) {
-            const uint64_t m = a.tree.mask[l];
-            if ((m >> e & 1) && popc64(S & m) >= a.tree.cap[l]) { lm = m; break; }
-          }
-          uint64_t nw = S & lm & ~resolved;
-          resolved |= nw;
-          while (nw) {
-            const int o = __ffsll((long long)nw) - 1;
-            nw &= nw - 1;
-            tu[o] = (int8_t)e;
-          }
-        }
-        uint64_t left = S & ~resolved;
-        while (left) {
-          const int o = __ffsll((long long)left) - 1;
-          left &= left - 1;
-          tu[o] = -1;
-        }
-      }
       // sums over the selected items in ascending index order
       double Pi = 0.0, Gi = 0.0;
       const float *pp = pl + u * M;
@@ -678,7 +534,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a, const TileGeom &g
         for (uint64_t m = S0; m; m &= m - 1) v = v + (double)bu[(__ffsll((long long)m) - 1) * K + k];
       } else if (SCD) {
         double fr = 0.0, fdl = 0.0;
-        if (kmode[k] == KS_WINDOW && a.tree.L <= 1 && kwide[0] > 0.0) {
+        if (FMT == 0 && kmode[k] == KS_WINDOW && kst[k].far && a.tree.L <= 1 && kwide[0] > 0.0) {
           const double wlo = kst[k].wlo, whi = kst[k].whi;
           const double c = 0.5 * (wlo + whi);
           fr = fmax(whi - c, c - wlo);
@@ -706,6 +562,15 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a, const TileGeom &g
           const double Hs = fr * (double)bmk * (1.0 + 0x1p-30) + 0x1p-36 * (1.0 + (lk + fabs(fdl) + fr) * (double)bmk);
           fused_ok = far_finish(f, zu, bu, M, K, k, A, lk, fdl, fr, (double)bmk, Hs, m1,
                                 a.tree.L == 1 ? a.tree.cap[0] : 0, &fused_cw);
+        } else if (FMT == 1) {
+          // the stored entries only, in ascending item order
+          A = Am[q];
+          for (uint64_t m = A; m; m &= m - 1) {
+            const int j = __ffsll((long long)m) - 1;
+            const float bj = bu[j * K + k];
+            if (S0 >> j & 1) v = v + (double)bj;
+            bmk = bj > bmk ? bj : bmk;
+          }
         } else {
           #pragma unroll 4
           for (int j = 0; j < M; ++j) {
@@ -742,119 +607,46 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a, const TileGeom &g
             const double gscale = fabs(zu[perm[u * M]]) + Hu;
             if (window_calm(ugap[2 * u], gscale, kst[k].hw, (double)bmk, lk)) {
               walk = false;
-            } else if (fused ? fused_ok
-                             : a.tree.L <= 1
-                                 ? far_window_single(zu, bu, M, K, k, A, lk, kst[k].wlo, kst[k].whi, (double)bmk,
-                                                     a.tree.L == 1 ? a.tree.mask[0] : 0ull,
-                                                     a.tree.L == 1 ? a.tree.cap[0] : 0, &cw)
-                                 : far_window_set(zu, bu, M, K, k, A, lk, kst[k].wlo, kst[k].whi, (double)bmk,
-                                                  a.tree, &cw)) {
+            } else if (fused && fused_ok) {
               // no breakpoint inside the window: its consumption just above
               // the window is the window's set's
               walk = false;
               if (cw != v) {
                 xs_atomic_add_sum(&kxs[k], xs_minus(xs_of(cw), xs_of(v)));
               }
-            } else {
-              auto line = [&](int j, double &c, double &b) {
-                b = (A >> j & 1) ? (double)bu[j * K + k] : 0.0;
-                const double add = lk * b;
-                c = zu[j] + add;
-              };
-              const double whi = kst[k].whi, wlo = kst[k].wlo;
-              if (window_keeps(S0, A, Pm[u] & ~S0, line, a.tree.mask, a.tree.cap, a.tree.L, whi, 1) &&
-                  window_keeps(S0, A, Pm[u] & ~S0, line, a.tree.mask, a.tree.cap, a.tree.L, wlo,
-                               wlo > 0.0 ? -1 : 1))
-                walk = false;
             }
           }
           if (walk) {
-            double above = 0.0;   // window: increments of the breakpoints above it
-            const KState &ks = kst[k];
-            const double center = ks.center, delta = ks.delta;
-            const int bstar = ks.bstar;
-            const uint64_t klo = ks.klo, khi = ks.khi;
-            const int shift = ks.shift;
-            const int maxev = M * M + M + 8;
-            const bool single = (A & (A - 1)) == 0;
-            // start above every breakpoint: only horizontal positive lines,
-            // ranked by p~ (their lines are c_j = p~_j exactly)
-            uint64_t S = single ? 0ull : greedy_mask(perm + u * M, M, Pm[u] & ~A, a.tree);
-            for (int ev = 0; ; ++ev) {
-              if (ev >= maxev) { atomicAdd(a.err, 1ull); break; }
-              if (single && ev > 0) break;
-              double best = 0.0;
-              int bo = -1, bs = -1;
-              uint64_t cand = single ? 0ull : (A & ~S);
-              if (single) {
-                // one moving line: its only breakpoint is where it crosses its
-                // threshold element (a horizontal line) or the zero level
-                const int o = __ffsll((long long)A) - 1;
-                // with one set: the lowest selected member when o is out,
-                // the best member left out when o is in (set full), else zero
-                const int th = !fastau ? (int)tau[u * M + o]
-                               : (!(m1 >> o & 1) || tau[u * M] < 0) ? -1
-                               : (int)tau[u * M + ((S0 >> o & 1) ? 1 : 0)];
-                const double bo_d = (double)bu[o * K + k];
-                const double add_o = lk * bo_d;
-                const double co = zu[o] + add_o;
-                if (th < 0) {
-                  if (co > 0.0) { best = co / bo_d; bo = o; bs = -1; }
-                } else {
-                  const double bs_d = 0.0;
-                  const double add_s = lk * bs_d;
-                  const double cs = zu[th] + add_s;
-                  const double num = co - cs;
-                  const double den = bo_d - bs_d;
-                  const double val = num / den;
-                  if (val > 0.0) { best = val; bo = o; bs = th; }
-                }
+            const KWalk &ks = kst[k];
+            double above = 0.0;   // window: the consumption just above it
+            if (fastau && (A & (A - 1)) == 0) {
+              // one moving line: its only breakpoint is where it crosses its
+              // threshold element (a horizontal line) or the zero level: the
+              // lowest selected member when it is out, the best member left
+              // out when it is in (set full), else zero
+              const int o = __ffsll((long long)A) - 1;
+              const int th = (!(m1 >> o & 1) || tau[2 * u] < 0) ? -1 : (int)tau[2 * u + ((S0 >> o & 1) ? 1 : 0)];
+              const double bo_d = (double)bu[o * K + k];
+              const double add_o = lk * bo_d;
+              const double co = zu[o] + add_o;
+              const double num = th < 0 ? co : co - zu[th];
+              // divided only where the quotient can lie in the pass's range
+              if (num > 0.0 && num >= ks.tlo * bo_d * (1.0 - 0x1p-40)) {
+                const bool over = mode == KS_WINDOW && num > ks.thi * bo_d * (1.0 + 0x1p-40);
+                const double best = over ? INFINITY : num / bo_d;
+                if (mode == KS_WINDOW && best > ks.thi) above = bo_d;
+                else if (best >= ks.tlo) record_event(a, ks, k, best, bo_d, mode, hs, hc, hmin, hmax, kcnt, kovf, nstage, bid);
               }
-              while (cand) {
-                const int o = __ffsll((long long)cand) - 1;
-                cand &= cand - 1;
-                const double bo_d = (double)bu[o * K + k];
-                const double add_o = lk * bo_d;
-                const double co = zu[o] + add_o;
-                // lowest full node containing o (nodes are ordered subsets first)
-                uint64_t circ = 0;
-                bool tight = false;
-                for (int l = 0; l < a.tree.L; ++l) {
-                  const uint64_t m = a.tree.mask[l];
-                  if ((m >> o & 1) && popc64(S & m) >= a.tree.cap[l]) { circ = S & m; tight = true; break; }
-                }
-                // candidates are compared with the running maximum through
-                // cr_gt (fma residuals), so a division is only taken for a
-                // crossing that beats it: the same decisions as comparing
-                // the divided crossings
-                if (!tight) {
-                  if (co > 0.0 && cr_gt(co, bo_d, best)) { best = co / bo_d; bo = o; bs = -1; }
-                } else {
-                  while (circ) {
-                    const int s = __ffsll((long long)circ) - 1;
-                    circ &= circ - 1;
-                    const float bsf = bu[s * K + k];
-                    if ((double)bsf < bo_d) {
-                      const double bs_d = (double)bsf;
-                      const double add_s = lk * bs_d;
-                      const double cs = zu[s] + add_s;
-                      const double num = co - cs;
-                      const double den = bo_d - bs_d;
-                      if (cr_gt(num, den, best)) { best = num / den; bo = o; bs = s; }
-                    }
-                  }
-                }
-              }
-              if (bo < 0) break;
-              const double bo_d = (double)bu[bo * K + k];
-              const double v2 = bs >= 0 ? bo_d - (double)bu[bs * K + k] : bo_d;
-              S = (S | (1ull << bo)) & ~(bs >= 0 ? (1ull << bs) : 0ull);
-              if (mode == KS_WINDOW) {
-                const uint64_t key = dkey(best);
-                if (key < klo) break;                 // every later breakpoint is lower
-                if (key > khi) { above = above + v2; continue; }
-              }
-              record_event(a, ks, k, best, v2, mode, hs, hc, hmin, hmax, kcnt, kovf, nstage, bid);
+            } else {
+              const bool ok = walk_pair(
+                  M, a.tree.L, a.tree.mask, a.tree.cap, A, S0, Pm[u], [&](int j) -> double { return zu[j]; },
+                  [&](int j) -> double { return (A >> j & 1) ? (double)bu[j * K + k] : 0.0; },
+                  [&](int r) -> int { return (int)perm[u * M + r]; }, lk, ks,
+                  [&](double v1, double v2) {
+                    record_event(a, ks, k, v1, v2, mode, hs, hc, hmin, hmax, kcnt, kovf, nstage, bid);
+                  },
+                  &above);
+              if (!ok) atomicAdd(a.err, 1ull);
             }
             if (mode == KS_WINDOW && above != v) {
               xs_atomic_add_sum(&kxs[k], xs_minus(xs_of(above), xs_of(v)));
@@ -1832,10 +1624,11 @@ size_t kp_sweep_lds_bytes(int U, int M, int K, bool scd, int fmt, bool hist = tr
              r16((size_t)U * 16) + r16((size_t)(K + 2) * 8);
   s += r16((size_t)K * 8);   // lambda
   s += r16(R * 4) + r16((R + 1) * 4) + r16(16);   // staged profits, row offsets, entry base
-  if (scd) s += r16(R);                            // per-item threshold elements
+  if (scd) s += r16((size_t)U * 2);                // threshold elements
+  if (scd && fmt == 1) s += r16(Q * 8);            // moving items of every (user, knapsack)
   if (fmt == 1) s += 2 * r16((size_t)NT * ECH * 4);  // staged CSR entries
   if (scd)
-    s += r16((size_t)K * sizeof(KState)) + (hist ? r16((size_t)K * KP_NB * sizeof(XSum)) + r16((size_t)K * KP_NB * 4) : 0) +
+    s += r16((size_t)K * sizeof(KWalk)) + (hist ? r16((size_t)K * KP_NB * sizeof(XSum)) + r16((size_t)K * KP_NB * 4) : 0) +
          4 * r16((size_t)K * 4) + 2 * r16((size_t)K * 8) + r16(16) +
          r16(16) + r16((size_t)K * sizeof(XSum)) + r16((size_t)U * 16);   // widest window, corrections, per-user filter
   return s;

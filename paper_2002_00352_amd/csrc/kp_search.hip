@@ -11,6 +11,18 @@ hipError_t kp_launch_reduce_tab(const void *tab, int n, hipStream_t stream);   /
 // ---------------------------------------------------------------------------
 // SCD threshold search
 // ---------------------------------------------------------------------------
+// The rest of a window state from its edges (l: lambda_k^t).
+__device__ __forceinline__ void set_window(KState &s, double l) {
+  s.mode = KS_WINDOW;
+  s.klo = dkey(s.wlo);
+  s.khi = dkey(s.whi);
+  s.tlo = s.wlo;
+  s.thi = s.whi;
+  const double up = s.whi - l, dn = l - s.wlo;
+  s.hw = fmax(fabs(up), fabs(dn));
+  s.far = l < s.wlo || l > s.whi;
+}
+
 // The window a search starts with, from the multiplier's history: around
 // lambda_k^t, 1.25x the last step wide, when that step was small against
 // lambda_k^t; else, when the multiplier alternates (it returns close to
@@ -34,13 +46,9 @@ __device__ __forceinline__ void choose_window(KState &s, double step, double pre
   } else {
     return;
   }
-  s.mode = KS_WINDOW;
   s.whi = c + h;
   s.wlo = c - h > 0.0 ? c - h : 0.0;
-  const double up = s.whi - s.center, dn = s.center - s.wlo;
-  s.hw = fmax(fabs(up), fabs(dn));
-  s.klo = dkey(s.wlo);
-  s.khi = dkey(s.whi);
+  set_window(s, s.center);
 }
 
 __global__ void k_scd_init(KState *st, int K, const double *lam_in, const uint8_t *kmask,
@@ -98,7 +106,9 @@ __global__ void k_scd_init(KState *st, int K, const double *lam_in, const uint8_
   s.sel_hi = 0;
   s.sel_fab = xs_zero();
   s.sel_bin = -1;
-  s.pad3 = 0;
+  s.far = 0;
+  s.tlo = 0.0;
+  s.thi = INFINITY;
   if (interp) s.flags = KS_FLAG_INTERP;
   else if (window && hinted && s.mode == KS_EXP) choose_window(s, delta_hint[K + k], prev, drift);
   st[k] = s;
@@ -109,6 +119,9 @@ __device__ __forceinline__ int bits_needed(uint64_t x) { return x ? 64 - __clzll
 // Full search of the next pass: exponential buckets over every breakpoint.
 __device__ __forceinline__ void restart_full(KState &s) {
   s.mode = KS_EXP;
+  s.far = 0;
+  s.tlo = 0.0;
+  s.thi = INFINITY;
   s.flags = 0;
   s.n_emit = 0;
   s.overflow = 0;
@@ -254,6 +267,13 @@ __global__ void __launch_bounds__(64) k_scd_locate(KState *st, int K, const doub
       s.fab = above;
       s.flags |= KS_FLAG_WINDOW;
     }
+  }
+  // where the breakpoints that the next pass looks for lie
+  if (s.mode == KS_EMIT_BUCKET || s.mode == KS_HULL_BUCKET) {
+    bucket_bounds(s.center, s.delta, s.bstar, s.tlo, s.thi);
+  } else if (s.mode == KS_REFINE || s.mode == KS_EMIT_RANGE) {
+    s.tlo = kdbl(s.klo);
+    s.thi = s.khi < 0x7FF0000000000000ull ? kdbl(s.khi) : INFINITY;
   }
   s.ncomp = 0;
   if (lane == 0) st[k] = s;
@@ -628,13 +648,9 @@ __global__ void k_scd_recenter(KState *st, int K, const double *lam_hat, const d
   s.delta = ldexp(1.0, ilogb(c) - 8);
   if (window && fabs(lam_in[k] - c) <= 0.25 * c) {
     const double h = 4.0 * s.delta;
-    s.mode = KS_WINDOW;
     s.whi = c + h;
     s.wlo = c - h > 0.0 ? c - h : 0.0;
-    s.klo = dkey(s.wlo);
-    s.khi = dkey(s.whi);
-    const double l = lam_in[k];
-    s.hw = fmax(fabs(s.whi - l), fabs(l - s.wlo));
+    set_window(s, lam_in[k]);
   }
   st[k] = s;
 }
@@ -651,8 +667,7 @@ __global__ void k_count_modes(const KState *st, int K, int *out) {
     const KState &s = st[k];
     if (s.mode == KS_WINDOW) {
       atomicAdd(&c[0], 1);
-      const double cen = 0.5 * (s.wlo + s.whi);
-      if (!(fabs(cen - s.center) <= fmax(s.whi - cen, cen - s.wlo))) atomicAdd(&c[2], 1);
+      if (s.far) atomicAdd(&c[2], 1);
     } else if (s.mode != KS_DONE) {
       atomicAdd(&c[1], 1);
     }
@@ -695,7 +710,9 @@ __global__ void k_scd_init_flat(KState *st, int Kf, const double *const *lam_in,
   s.sel_hi = 0;
   s.sel_fab = xs_zero();
   s.sel_bin = -1;
-  s.pad3 = 0;
+  s.far = 0;
+  s.tlo = 0.0;
+  s.thi = INFINITY;
   // a window from the multiplier's history (as the single-instance search);
   // the history columns shift once per iteration, here
   if (hint) {
