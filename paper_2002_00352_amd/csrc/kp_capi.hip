@@ -27,7 +27,8 @@ hipError_t kp_launch_reduce_stats(const double *partials, int nblk, int K, const
                                   const double *B, double *R, double *g, double *P,
                                   hipStream_t stream);
 hipError_t kp_launch_scd_init(KState *st, int K, const double *lam_in, const uint8_t *kmask,
-                              double *hist, int hinted, int window, int interp, hipStream_t stream);
+                              double *hist, int hinted, int window, int interp, double frac,
+                              hipStream_t stream);
 hipError_t kp_launch_scd_locate_select(KState *st, int K, const double *B, const double *R,
                                        const int *rinst, XSum *hist_sum, uint32_t *hist_cnt,
                                        const double *ev1, const double *ev2, uint32_t emit_cap,
@@ -79,7 +80,7 @@ size_t kp_resplit_lds(int n);
 hipError_t kp_launch_plan_resplit(const ResplitArgs &r, hipStream_t stream);
 hipError_t kp_launch_batched_aux(int which, const void *tab, int n, KState *st, const void *lam_ptrs,
                                  const int *kinst, const int *klocal, double *hint, const uint64_t *eoff,
-                                 const uint32_t *ecap, hipStream_t stream);
+                                 const uint32_t *ecap, const double *frac, hipStream_t stream);
 TileGeom kp_tile_geom(const SweepArgs &a, int U);
 size_t kp_coldesc_size();
 void kp_coldesc_fill(void *dst, const double *partials, const double *lam, const double *B,
@@ -88,10 +89,8 @@ void kp_coldesc_fill(void *dst, const double *partials, const double *lam, const
 hipError_t kp_launch_validate_csr(const int64_t *rowptr, const int32_t *col, int64_t nrows, int K,
                                   unsigned int *flags, hipStream_t stream);
 hipError_t kp_launch_fill_f64(double *dst, int64_t n, double v, hipStream_t stream);
-hipError_t kp_launch_recenter(KState *st, int K, const double *lam_hat, const double *lam_in, int window,
-                              hipStream_t stream);
-hipError_t kp_launch_strided_users(int64_t *users, int64_t n, int64_t stride, int64_t off, hipStream_t stream);
-hipError_t kp_launch_uniform_rowptr(int64_t *rowptr, int64_t nrows, int D, hipStream_t stream);
+hipError_t kp_launch_sample_window(KState *st, int K, const double *B, const double *ev1, const double *ev2,
+                                   uint32_t emit_cap, const SelWs &w, int blocks, hipStream_t stream);
 hipError_t kp_launch_stream_read(const void *src, int64_t n16, unsigned long long *out, int grid,
                                  hipStream_t stream);
 
@@ -122,10 +121,17 @@ constexpr int kTileBudget = 24 * 1024;   // bytes of staged costs per tile
 constexpr int kTileRowsMin = 160;        // item rows per tile at least, when the rows are long
 constexpr size_t kMaxLds = 160 * 1024;   // LDS per workgroup on gfx950
 constexpr int kMaxGrid = 2048;
-constexpr uint32_t kEmitCapDefault = 1u << 20;
+// A search without a window on an instance of at least kSampleMin users starts
+// from a sample of the users, 1/16 of them between these bounds (c3's recipe,
+// 5e6 users from lambda = 0: 11 full passes of exponential buckets and
+// refinements in four iterations, 45.7 ms; one sampled and one window pass an
+// iteration, SAMPLED_MS ms); smaller instances emit every breakpoint at once.
+constexpr int64_t kSampleMin = 32768;
+constexpr int64_t kSampleUsersMin = 12288, kSampleUsersMax = 1 << 18;
 constexpr int kMaxPasses = 96;
 constexpr uint32_t kStageCap = 4096;    // staged events per block per pass (at least)
 constexpr uint32_t kStageCapMax = 65536;
+constexpr uint32_t kEmitCapMin = 1u << 16, kEmitCapMax = 1u << 23;   // emitted events per knapsack
 constexpr int kGraphLaterPasses = 5;     // later passes captured with the first in a batched iteration's graph
 constexpr uint32_t kEmitCapBatched = 1u << 16;   // emitted events per (instance, knapsack) per pass (at least)
 constexpr double kEmitBytesBatched = 8.0e9;        // bound on a batch's emission buffers
@@ -158,13 +164,9 @@ struct Ctx {
   bool window_enabled = true;
   bool alg5 = false;      // Alg.5 map for the users in its setting
   bool interp = false;    // approximate reduce: interpolation inside the threshold's bucket
-  // full searches of problems with at least this many users start from the
-  // threshold of a strided sample (0: never); the sample's search runs on a
-  // child context (no windows, no sampling) in a buffer of this context
-  int64_t sample_min = (int64_t)1 << 22;
-  struct Ctx *child = nullptr;
-  void *sbuf = nullptr;
-  size_t sbuf_cap = 0;
+  // searches without a window of problems with at least this many users
+  // start from a sample of them (0: never)
+  int64_t sample_min = kSampleMin;
   int stats_grid = 0;     // blocks of the last sweep launch (slots of the per-block partials)
   // shape of the last sweep launch: kernel (0 general, 1 uniform-row), users
   // per tile, blocks
@@ -274,6 +276,11 @@ struct Prepared {
   // its SCD window pass (0 = not used)
   int dwin_grid = 0;
   double ell_bytes = 0.0;
+  // search without a window: the share of the users sampled, or 0 (every
+  // breakpoint is emitted) or -1 (exponential buckets), and the sample's tiles
+  double frac = -1.0;
+  int64_t samp_tiles = 0, samp_stride = 1, samp_off = 0;
+  int64_t samp_users = 0;
   int stage_grid() const {
     return std::max(std::max(std::max(grid, grid_nh), std::max(ell_grid, dense_grid)), dwin_grid);
   }
@@ -537,6 +544,34 @@ kp_status check_rows(Ctx *c, const int64_t *rowptr, int64_t nrows, unsigned int 
   return KP_OK;
 }
 
+// How a search without a window starts (window: windows are on), over tiles of
+// U users: every (ntiles / samp_tiles)-th full tile is a sample.
+void choose_start(Prepared &P, int64_t sample_min, bool window, int U) {
+  const int64_t N = P.pr.N;
+  P.frac = -1.0;
+  const int64_t full = N / U;
+  if (sample_min > 0 && N >= sample_min) {
+    if (!window) return;
+    const int64_t want = std::min(std::max(N / 16, kSampleUsersMin), std::min(N / 2, kSampleUsersMax));
+    P.samp_tiles = std::min(full / 2, std::max<int64_t>(1, want / U));
+    if (P.samp_tiles >= 1) {
+      P.samp_stride = full / P.samp_tiles;
+      P.samp_off = (P.samp_stride - 1) / 2;
+      P.samp_users = P.samp_tiles * U;
+      P.frac = (double)P.samp_users / (double)N;
+      return;
+    }
+  }
+  if (N <= kSampleMin) P.frac = 0.0;
+}
+
+// Breakpoints of a (user, knapsack) pair, roughly: every item that moves with
+// the knapsack enters, and a few leave and enter again.
+double pair_events(const Prepared &P) {
+  if (P.pr.fmt == KP_B_DENSE) return P.pr.M + 4.0;
+  return P.row_nnz ? 2.0 + 2.0 * P.pr.M * P.row_nnz / P.pr.K : 8.0;
+}
+
 struct SweepWs {
   double *partials, *B, *ev1, *ev2, *Rtmp, *gtmp, *Ptmp, *sv1, *sv2;
   XSum *hist_sum;
@@ -579,19 +614,39 @@ kp_status carve_ws(Ctx *c, const Prepared &P, bool scd, SweepWs &w) {
     o_hc = cv.take((size_t)K * KP_NB * 4);
     o_sel = cv.take(kp_sel_bytes(K));
     o_km = cv.take((size_t)K);
-    cap = kEmitCapDefault;
-    o_e1 = cv.take((size_t)K * cap * 8);
-    o_e2 = cv.take((size_t)K * cap * 8);
   }
   size_t o_s1 = 0, o_s2 = 0, o_sk = 0;
   // staged events per block: scale with the block's share of (user, knapsack)
   // pairs so that large window passes do not overflow
   uint32_t scap = 0;
   if (scd) {
-    // (sized for the general kernel's smaller grid, the one with histograms)
-    const int blocks = P.ell_D ? P.ell_brk_grid : P.grid;
-    const double share = (double)P.pr.N * K / std::max(1, blocks) / 64.0;
+    // (sized for the general kernel's smaller grid, the one with histograms);
+    // a sample's pass, or a small instance's, emits every breakpoint
+    const int64_t blocks = std::max(1, P.ell_D ? P.ell_brk_grid : P.grid);
+    const double every = pair_events(P);
+    double share = (double)P.pr.N * K / (double)blocks / 64.0;
+    const int64_t all = P.frac > 0.0 ? P.samp_users : P.frac == 0.0 ? P.pr.N : 0;
+    const int64_t per = (int64_t)(P.ell_D ? 512 : P.U_nh);   // users a block takes at a time
+    const int64_t run = std::min<int64_t>(blocks, std::max<int64_t>(1, all / per));
+    share = std::max(share, every * K * (double)((all + run - 1) / run));
     scap = (uint32_t)std::min<double>(kStageCapMax, std::max<double>(kStageCap, share));
+    // emitted events per knapsack: every breakpoint of a sample or a small
+    // instance, and what windows hold of a large one
+    const int64_t want = std::max<int64_t>((int64_t)(every * (double)all), P.pr.N / 16);
+    cap = (uint32_t)std::min<int64_t>(kEmitCapMax, std::max<int64_t>(kEmitCapMin, want));
+    if (c->max_ws) {
+      // a capped workspace: what is left of it after the rest (events that do
+      // not fit cost further passes, no more)
+      const size_t rest = cv.off + (size_t)P.stage_grid() * kStageCap * 18 + (size_t)P.pr.N * 4 +
+                          (size_t)KP_LIST_CHUNK * P.ell_grid * 16 + (1u << 16);
+      if (rest + (size_t)K * cap * 16 + (size_t)P.stage_grid() * (scap - kStageCap) * 18 > c->max_ws) {
+        scap = kStageCap;
+        const size_t left = c->max_ws > rest ? (c->max_ws - rest) / ((size_t)K * 16) : 0;
+        cap = (uint32_t)std::min<size_t>(cap, std::max<size_t>(4096, left));
+      }
+    }
+    o_e1 = cv.take((size_t)K * cap * 8);
+    o_e2 = cv.take((size_t)K * cap * 8);
   }
   if (scd) {
     o_s1 = cv.take((size_t)P.stage_grid() * scap * 8);
@@ -705,7 +760,7 @@ hipError_t timed_sweep(Ctx *c, const SweepArgs &a, const Prepared &P, bool scd, 
     }
   } else if (P.ell_D) {
     SweepArgs ae = a;
-    ae.ntiles = P.ell_ntiles;
+    if (!a.sampled) ae.ntiles = P.ell_ntiles;
     err = kp_launch_ell(ae, P.ell_D, P.ell_grid, scd ? 1 : 0, c->stream, &c->stats_grid);
   } else if (P.dense_grid && !scd) {
     SweepArgs ae = a;
@@ -716,7 +771,7 @@ hipError_t timed_sweep(Ctx *c, const SweepArgs &a, const Prepared &P, bool scd, 
     ae.ntiles = P.dense_ntiles;
     err = kp_launch_dense(ae, P.dwin_grid, c->stream, &c->stats_grid, true);
   } else {
-    err = a.no_hist ? kp_launch_sweep(a, P.U_nh, P.grid_nh, scd, c->stream, &c->stats_grid)
+    err = a.no_hist ? kp_launch_sweep(a, P.U_nh, (int)std::min<int64_t>(P.grid_nh, a.ntiles), scd, c->stream, &c->stats_grid)
                     : kp_launch_sweep(a, P.U, P.grid, scd, c->stream, &c->stats_grid);
   }
   if (c->timing && e0 && e1) {
@@ -755,6 +810,7 @@ SweepArgs make_args(const Prepared &P, const double *lam, const SweepWs &w, uint
   a.tree = P.tree;
   a.lam = lam;
   a.ntiles = P.ntiles;
+  a.tstride = 1;
   a.want_stats = stats ? 1 : 0;
   a.partials = w.partials;
   a.x_out = x;
@@ -775,125 +831,20 @@ SweepArgs make_args(const Prepared &P, const double *lam, const SweepWs &w, uint
   return a;
 }
 
-kp_status kp_scd_sweep_masked_impl(Ctx *c, const kp_problem *prob, const double *lambda_in, double *lambda_out,
-                                   const uint8_t *kmask, double *R, double *g, double *primal);
-
-// Start the full searches of this sweep from a sample's thresholds: every
-// stride-th user (n = max(N/64, min(N/2, 2^20)) of them) is gathered into
-// the context's sample buffer, the same SCD search runs on that sample with
-// every budget scaled by n/N on the child context, and each knapsack in full
-// search mode centres its buckets on the sample's threshold.
-kp_status sample_center(Ctx *c, const kp_problem *prob, const Prepared &P, const SweepWs &w,
-                        const double *lambda_in, const uint8_t *kmask) {
-  const int64_t N = P.pr.N;
-  const int M = P.pr.M, K = P.pr.K;
-  const int64_t n = std::max<int64_t>(N / 64, std::min<int64_t>(N / 2, (int64_t)1 << 20));
-  if (n < 1 || n >= N) return KP_OK;
-  const int64_t stride = N / n;
-  const bool csr = P.pr.fmt == KP_B_CSR;
-  const int D = P.row_nnz;
-  Carve cv;
-  const size_t o_u = cv.take((size_t)n * 8);
-  const size_t o_p = cv.take((size_t)n * M * 4);
-  const size_t o_b = csr ? 0 : cv.take((size_t)n * M * K * 4);
-  const size_t o_len = (csr && !D) ? cv.take((size_t)n * M * 8) : 0;
-  const size_t o_rp = csr ? cv.take((size_t)(n * M + 1) * 8) : 0;
-  const size_t o_col = (csr && D) ? cv.take((size_t)n * M * D * 4) : 0;
-  const size_t o_val = (csr && D) ? cv.take((size_t)n * M * D * 4) : 0;
-  const size_t o_lam = cv.take((size_t)K * 8);
-  int64_t nnz = n * M * (int64_t)D;
-  size_t o_ent = 0;
-  if (csr && !D) {
-    // the sampled rows' lengths and offsets first, to size the entries
-    if (cv.off > c->sbuf_cap) {
-      if (c->sbuf) HIP_TRY(hipFree(c->sbuf));
-      c->sbuf = nullptr;
-      c->sbuf_cap = 0;
-      if (hipMalloc(&c->sbuf, cv.off) != hipSuccess) { c->sbuf = nullptr; return fail(KP_ERR_NOMEM, "hipMalloc failed"); }
-      c->sbuf_cap = cv.off;
-    }
-    char *b = (char *)c->sbuf;
-    HIP_TRY(kp_launch_strided_users((int64_t *)(b + o_u), n, stride, stride / 2, c->stream));
-    HIP_TRY(kp_launch_gather_csr_ptr(P.pr.rowptr, (int64_t *)(b + o_u), n, M, (int64_t *)(b + o_len),
-                                     (int64_t *)(b + o_rp), c->stream));
-    int64_t *h = (int64_t *)(c->pinned + 8);
-    HIP_TRY(hipMemcpyAsync(h, (int64_t *)(b + o_rp) + n * M, 8, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
-    nnz = *h;
-    o_ent = cv.take((size_t)std::max<int64_t>(nnz, 1) * 8);
-  }
-  if (cv.off > c->sbuf_cap) {
-    // (a grown buffer keeps nothing: the general-CSR offsets are rebuilt below)
-    if (c->sbuf) {
-      HIP_TRY(hipStreamSynchronize(c->stream));
-      HIP_TRY(hipFree(c->sbuf));
-    }
-    c->sbuf = nullptr;
-    c->sbuf_cap = 0;
-    if (hipMalloc(&c->sbuf, cv.off) != hipSuccess) { c->sbuf = nullptr; return fail(KP_ERR_NOMEM, "hipMalloc failed"); }
-    c->sbuf_cap = cv.off;
-  }
-  char *b = (char *)c->sbuf;
-  int64_t *users = (int64_t *)(b + o_u);
-  HIP_TRY(kp_launch_strided_users(users, n, stride, stride / 2, c->stream));
-  kp_problem sub = *prob;
-  sub.N = n;
-  sub.p = (const float *)(b + o_p);
-  if (!csr) {
-    sub.b = (const float *)(b + o_b);
-    HIP_TRY(kp_launch_gather_dense(P.pr.p, P.pr.b, users, n, M, K, (float *)(b + o_p), (float *)(b + o_b),
-                                   c->stream));
-  } else if (D) {
-    HIP_TRY(kp_launch_gather_dense(P.pr.p, nullptr, users, n, M, K, (float *)(b + o_p), nullptr, c->stream));
-    // a user's entries are M * D consecutive values of col and val
-    HIP_TRY(kp_launch_gather_dense((const float *)P.pr.col, nullptr, users, n, M * D, 1, (float *)(b + o_col),
-                                   nullptr, c->stream));
-    HIP_TRY(kp_launch_gather_dense(P.pr.val, nullptr, users, n, M * D, 1, (float *)(b + o_val), nullptr,
-                                   c->stream));
-    HIP_TRY(kp_launch_uniform_rowptr((int64_t *)(b + o_rp), n * M, D, c->stream));
-    sub.b_rowptr = (const int64_t *)(b + o_rp);
-    sub.b_col = (const int32_t *)(b + o_col);
-    sub.b_val = (const float *)(b + o_val);
-  } else {
-    HIP_TRY(kp_launch_gather_dense(P.pr.p, nullptr, users, n, M, K, (float *)(b + o_p), nullptr, c->stream));
-    int64_t *subptr = (int64_t *)(b + o_rp);
-    HIP_TRY(kp_launch_gather_csr_ptr(P.pr.rowptr, users, n, M, (int64_t *)(b + o_len), subptr, c->stream));
-    int32_t *scol = (int32_t *)(b + o_ent);
-    float *sval = (float *)(b + o_ent + (size_t)std::max<int64_t>(nnz, 1) * 4);
-    HIP_TRY(kp_launch_gather_csr(P.pr.rowptr, P.pr.col, P.pr.val, users, n, M, subptr, scol, sval, c->stream));
-    sub.b_rowptr = subptr;
-    sub.b_col = scol;
-    sub.b_val = sval;
-  }
-  std::vector<double> Bs(K);
-  const double scale = (double)n / (double)N;
-  for (int k = 0; k < K; ++k) Bs[k] = P.B[k] * scale;
-  sub.B = Bs.data();
-  if (!c->child) {
-    void *ch = nullptr;
-    kp_status st = kp_create(&ch, c->stream, c->max_ws);
-    if (st != KP_OK) return st;
-    c->child = (Ctx *)ch;
-  }
-  Ctx *ch = c->child;
-  ch->stream = c->stream;
-  ch->window_enabled = false;
-  ch->sample_min = 0;
-  ch->ell_enabled = c->ell_enabled;
-  ch->alg5 = c->alg5;
-  ch->delta_valid = false;
-  ch->B_host.clear();
-  double *lam_hat = (double *)(b + o_lam);
-  kp_status st = kp_scd_sweep_masked_impl(ch, &sub, lambda_in, lam_hat, kmask, nullptr, nullptr, nullptr);
-  if (st != KP_OK) {
-    char m[sizeof g_err];
-    memcpy(m, g_err, sizeof m);
-    return fail(st, "sample search: %s", m);
-  }
-  // with windows on, the full searches start with a window around the
-  // sample's threshold
-  HIP_TRY(kp_launch_recenter(w.st, K, lam_hat, lambda_in, (c->window_enabled && !c->interp) ? 1 : 0,
-                             c->stream));
+// The sampled searches of this sweep: one pass over the sample's tiles that
+// emits every breakpoint of theirs, and the windows made of them.  No
+// synchronisation; knapsacks that search otherwise are left alone, and with
+// no sampled search the launches do nothing.
+kp_status sample_phase(Ctx *c, const Prepared &P, const SweepWs &w, const double *lambda_in) {
+  SweepArgs a = make_args(P, lambda_in, w, nullptr, false);
+  a.alg5_q = alg5_q(c, P);
+  a.no_hist = 1;
+  a.sampled = 1;
+  a.ntiles = P.samp_tiles;
+  a.tstride = P.samp_stride;
+  a.toff = P.samp_off;
+  HIP_TRY(timed_sweep(c, a, P, true, P.bytes * P.frac));
+  HIP_TRY(kp_launch_sample_window(w.st, P.pr.K, w.B, w.ev1, w.ev2, w.emit_cap, w.sel, kSelBlocks, c->stream));
   return KP_OK;
 }
 
@@ -974,8 +925,6 @@ kp_status kp_destroy(void *ctx) {
   if (c->delta_dev) (void)hipFree(c->delta_dev);
   if (c->B_dev) (void)hipFree(c->B_dev);
   if (c->pinned) (void)hipHostFree(c->pinned);
-  if (c->sbuf) (void)hipFree(c->sbuf);
-  if (c->child) (void)kp_destroy(c->child);
   delete c;
   return KP_OK;
 }
@@ -1046,20 +995,13 @@ kp_status kp_scd_sweep_masked(void *ctx, const kp_problem *prob, const double *l
                               double *lambda_out, const uint8_t *kmask, double *R, double *g,
                               double *primal) {
   if (!ctx) return fail(KP_ERR_INVALID, "ctx is NULL");
-  return kp_scd_sweep_masked_impl((Ctx *)ctx, prob, lambda_in, lambda_out, kmask, R, g, primal);
-}
-
-}  // extern "C"
-
-namespace {
-kp_status kp_scd_sweep_masked_impl(Ctx *c, const kp_problem *prob, const double *lambda_in,
-                                   double *lambda_out, const uint8_t *kmask, double *R, double *g,
-                                   double *primal) {
+  Ctx *c = (Ctx *)ctx;
   if (!lambda_in || !lambda_out) return fail(KP_ERR_INVALID, "lambda is NULL");
   Prepared P;
   kp_status s = prepare(prob, true, P, c);
   if (s != KP_OK) return s;
   if ((s = choose_kernel(c, P, true)) != KP_OK) return s;
+  if (!c->interp) choose_start(P, c->sample_min, c->window_enabled, P.ell_D ? 64 : P.U_nh);
   SweepWs w;
   if ((s = carve_ws(c, P, true, w)) != KP_OK) return s;
   const int K = P.pr.K;
@@ -1068,8 +1010,9 @@ kp_status kp_scd_sweep_masked_impl(Ctx *c, const kp_problem *prob, const double 
   // window hint from the previous call with the same K (performance only)
   if (!c->delta_dev || c->delta_K != K) {
     if (c->delta_dev) HIP_TRY(hipFree(c->delta_dev));
-    // [K] bucket widths, [K] last steps, [K] lambda^{t-1}, [K] lambda^{t-2}
-    HIP_TRY(hipMalloc(&c->delta_dev, (size_t)K * 32));
+    // [K] bucket widths, [K] last steps, [K] lambda^{t-1}, [K] lambda^{t-2},
+    // [K] the multipliers last returned
+    HIP_TRY(hipMalloc(&c->delta_dev, (size_t)K * 40));
     c->delta_K = K;
     c->delta_valid = false;
   }
@@ -1078,47 +1021,41 @@ kp_status kp_scd_sweep_masked_impl(Ctx *c, const kp_problem *prob, const double 
   // the window pass needs the statistics of the same pass (R at lambda_in)
   const int window = (c->window_enabled && P.pr.N > 0 && !c->interp) ? 1 : 0;
   HIP_TRY(kp_launch_scd_init(w.st, K, lambda_in, kmask ? w.kmask : nullptr, c->delta_dev,
-                             c->delta_valid ? 1 : 0, window, c->interp ? 1 : 0, c->stream));
+                             c->delta_valid ? 1 : 0, window, c->interp ? 1 : 0, P.frac, c->stream));
   // the first pass runs split (all users, then the listed ones) when every
   // knapsack still searching starts with a window
   // (uniform-row kernel); the general kernel runs such a pass without the
   // histograms of the other search modes
-  bool split = false, nohist = false, dwin = false;
-  const bool nh_gain = !P.ell_D && (P.U_nh != P.U || P.grid_nh != P.grid);
-  const bool sample = c->sample_min > 0 && P.pr.N >= c->sample_min && !c->interp;
-  const bool counts = window && c->delta_valid && (w.fcap || nh_gain || P.dwin_grid);
+  // (a search that emits every breakpoint bins none either)
+  const bool sample = P.frac > 0.0;
+  bool split = false, dwin = false;
   // the search-mode counts, and for dense costs the probe of the users'
-  // lines (read back together), decide the first pass's kernel
-  auto count_and_choose = [&]() -> kp_status {
+  // lines (read back together), decide the first pass's kernel; without
+  // history there is nothing to choose
+  const bool counts = window && c->delta_valid && (w.fcap || P.dwin_grid || P.frac != 0.0);
+  bool searching = sample && !counts;   // some knapsack starts from the sample
+  if (counts) {
     HIP_TRY(kp_launch_count_modes(w.st, K, w.modes, c->stream));
-    const bool probe = counts && P.dwin_grid;
+    const bool probe = P.dwin_grid != 0;
     if (probe) HIP_TRY(kp_launch_dense_probe(make_args(P, lambda_in, w, nullptr, true), w.modes + 3, c->stream));
     HIP_TRY(hipMemcpyAsync(c->pinned + 20, w.modes, 16, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
-    if (counts) {
-      split = w.fcap && c->pinned[20] > 0 && c->pinned[21] == 0;
-      nohist = nh_gain && c->pinned[21] == 0;
-      // dense costs: the lane-per-user window pass when every window is
-      // centred on lambda^t, or when almost no sampled user has a line that
-      // can turn positive in any window (its gap test then settles every
-      // pair, whatever the windows); alternation windows otherwise go to the
-      // general kernel, whose per-(user, knapsack) tests stop early
-      dwin = probe && c->pinned[21] == 0 &&
-             (c->pinned[22] == 0 || c->pinned[23] * 64 <= KP_PROBE_USERS);
-    }
-    return KP_OK;
-  };
-  if (counts || sample) {
-    if ((s = count_and_choose()) != KP_OK) return s;
-    // full searches (knapsacks without a window) start from a sample
-    if (sample && c->pinned[21] > 0) {
-      if ((s = sample_center(c, prob, P, w, lambda_in, kmask)) != KP_OK) return s;
-      // the sample's threshold may have opened windows for all of them:
-      // choose the first pass's kernel again
-      if (counts && window && (s = count_and_choose()) != KP_OK) return s;
-    }
+    searching = sample && c->pinned[21] > 0;
+    // the uniform-row kernel's split pass takes windows that contain lambda^t
+    // (its gap filter lists almost every user for one far away)
+    split = w.fcap && c->pinned[20] > 0 && c->pinned[21] == 0 && c->pinned[22] == 0;
+    // dense costs: the lane-per-user window pass when every window is
+    // centred on lambda^t, or when almost no sampled user has a line that
+    // can turn positive in any window (its gap test then settles every
+    // pair, whatever the windows); alternation windows otherwise go to the
+    // general kernel, whose per-(user, knapsack) tests stop early
+    dwin = probe && c->pinned[21] == 0 &&
+           (c->pinned[22] == 0 || c->pinned[23] * 64 <= KP_PROBE_USERS);
   }
+  const bool nohist = !P.ell_D && !c->interp && P.pr.N > 0 && (P.frac >= 0.0 || (counts && c->pinned[21] == 0));
   HIP_TRY(hipMemsetAsync(w.stat, 0, w.stat_bytes, c->stream));   // status, histograms
+  if (sample) HIP_TRY(hipMemsetAsync(w.sel.hsum, 0, w.sel_clear, c->stream));
+  if (searching && (s = sample_phase(c, P, w, lambda_in)) != KP_OK) return s;
   double *Rd = R ? R : w.Rtmp;
   double *gd = g ? g : w.gtmp;
   double *Pd = primal ? primal : w.Ptmp;
@@ -1168,14 +1105,13 @@ kp_status kp_scd_sweep_masked_impl(Ctx *c, const kp_problem *prob, const double 
     if (*(unsigned long long *)(st + 2))
       return fail(KP_ERR_INTERNAL, "breakpoint walk exceeded its event limit");
     if (st[0] == 0) break;
+    // a window that missed: the sample opens another one
+    if (pass == 0 && sample && (s = sample_phase(c, P, w, lambda_in)) != KP_OK) return s;
   }
   HIP_TRY(kp_launch_scd_finish(w.st, K, lambda_in, lambda_out, c->delta_dev, c->stream));
   c->delta_valid = true;
   return KP_OK;
 }
-}  // namespace
-
-extern "C" {
 
 kp_status kp_scd_sweep(void *ctx, const kp_problem *prob, const double *lambda_in,
                        double *lambda_out, double *R, double *g, double *primal) {
@@ -1612,6 +1548,10 @@ struct BatchPlan {
   void *coltab[2] = {nullptr, nullptr};    // [dir]: statistics column table (reads lambda_in)
   KState *kst = nullptr;
   double *hint = nullptr;   // [2 Kf] bucket widths and last steps carried between iterations
+  double *frac = nullptr;   // [Kf] how a search without a window starts
+  SweepArgs *sd[2] = {nullptr, nullptr};   // [dir] descriptors of the sampled pass
+  int *sboff = nullptr;     // [n+1] its blocks
+  int SB = 0;               // blocks of the sampled pass (0: no instance samples)
   uint64_t *eoff = nullptr; // [Kf] start of each knapsack's emission buffer
   uint32_t *ecap = nullptr; // [Kf] its capacity
   bool window = true;       // iterations start with a window where the last step allows
@@ -1700,10 +1640,22 @@ int plan_resplit(BatchPlan *p, int dir, int *blocks, size_t *lds) {
   return na;
 }
 
+// The sampled searches of a batch: a pass over the sampled tiles of the
+// instances with one, and their windows (nothing to do: the blocks exit).
+kp_status plan_sample_phase(BatchPlan *p, int dir, hipStream_t s) {
+  if (p->SB == 0) return KP_OK;
+  HIP_TRY(kp_launch_sweep_batched(p->sd[dir], p->geom, p->sboff, p->n, p->SB, p->lds, s));
+  HIP_TRY(kp_launch_sample_window(p->kst, p->Kf, p->Bf, p->e1, p->e2, p->cap, p->sel, kSelBlocksBatched, s));
+  return KP_OK;
+}
+
 // The later passes of a whole-iteration graph: each splits the open
 // instances' blocks on the device, sweeps them (blocks past the split exit),
 // and runs the threshold search; a pass with nothing open does no work.
 kp_status plan_later_passes_dev(BatchPlan *p, int dir, hipStream_t s) {
+  // (windows of the first pass that missed)
+  const kp_status st0 = plan_sample_phase(p, dir, s);
+  if (st0 != KP_OK) return st0;
   for (int j = 0; j < p->glater; ++j) {
     ResplitArgs r;
     r.order = p->dord;
@@ -1730,7 +1682,7 @@ kp_status plan_later_passes_dev(BatchPlan *p, int dir, hipStream_t s) {
     HIP_TRY(kp_launch_scd_locate_select(p->kst, p->Kf, p->Bf, p->stats, p->kin, p->hs, p->hc, p->e1, p->e2, p->cap, p->sel, kSelBlocksBatched, p->pend,
                                       nullptr, s));
     HIP_TRY(kp_launch_batched_aux(2, nullptr, p->Kf, p->kst, p->lam_tab[1 - dir], p->kin, p->klo, p->hint, nullptr,
-                                  nullptr, s));
+                                  nullptr, nullptr, s));
     HIP_TRY(kp_launch_inst_active(p->kst, p->koff, p->n, p->active, s));
   }
   HIP_TRY(hipMemcpyAsync(p->pinned, p->pend, sizeof(int), hipMemcpyDeviceToHost, s));
@@ -1742,14 +1694,16 @@ kp_status plan_later_passes_dev(BatchPlan *p, int dir, hipStream_t s) {
 
 kp_status plan_first_pass(BatchPlan *p, int dir, hipStream_t s) {
   HIP_TRY(kp_launch_batched_aux(p->window ? 3 : 1, nullptr, p->Kf, p->kst, p->lam_tab[dir], p->kin, p->klo, p->hint,
-                                p->eoff, p->ecap, s));
+                                p->eoff, p->ecap, p->frac, s));
+  kp_status st0 = plan_sample_phase(p, dir, s);
+  if (st0 != KP_OK) return st0;
   if (p->T > 0) HIP_TRY(kp_launch_sweep_batched(p->d[dir][1], p->geom, p->boff, p->n, p->GB, p->lds, s));
   HIP_TRY(kp_launch_batched_aux(0, p->coltab[dir], p->ncol, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
-                                nullptr, s));
+                                nullptr, nullptr, s));
   HIP_TRY(kp_launch_scd_locate_select(p->kst, p->Kf, p->Bf, p->stats, p->kin, p->hs, p->hc, p->e1, p->e2, p->cap, p->sel, kSelBlocksBatched, p->pend,
                                       nullptr, s));
   HIP_TRY(kp_launch_batched_aux(2, nullptr, p->Kf, p->kst, p->lam_tab[1 - dir], p->kin, p->klo, p->hint, nullptr,
-                                nullptr, s));
+                                nullptr, nullptr, s));
   HIP_TRY(kp_launch_inst_active(p->kst, p->koff, p->n, p->active, s));
   HIP_TRY(hipMemcpyAsync(p->pinned, p->pend, sizeof(int), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipMemcpyAsync(p->pinned + 2, p->err, 8, hipMemcpyDeviceToHost, s));
@@ -1796,6 +1750,10 @@ kp_status plan_step(BatchPlan *p, int dir, double *stats_out, bool graph) {
       return fail(KP_ERR_INTERNAL, "breakpoint walk exceeded its event limit");
     if (p->pinned[0] == 0) break;
     if (pass >= kMaxPasses) return fail(KP_ERR_INTERNAL, "SCD threshold search exceeded %d passes", kMaxPasses);
+    if (pass == 1) {
+      const kp_status st = plan_sample_phase(p, dir, s);
+      if (st != KP_OK) return st;
+    }
     if (p->T > 0) {
       int blocks = 0;
       size_t lds = 0;
@@ -1813,7 +1771,7 @@ kp_status plan_step(BatchPlan *p, int dir, double *stats_out, bool graph) {
     HIP_TRY(kp_launch_scd_locate_select(p->kst, p->Kf, p->Bf, p->stats, p->kin, p->hs, p->hc, p->e1, p->e2, p->cap, p->sel, kSelBlocksBatched, p->pend,
                                       nullptr, s));
     HIP_TRY(kp_launch_batched_aux(2, nullptr, p->Kf, p->kst, p->lam_tab[1 - dir], p->kin, p->klo, p->hint, nullptr,
-                                nullptr, s));
+                                nullptr, nullptr, s));
     HIP_TRY(kp_launch_inst_active(p->kst, p->koff, p->n, p->active, s));
     HIP_TRY(hipMemcpyAsync(p->pinned, p->pend, sizeof(int), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipMemcpyAsync(p->pinned + 2, p->err, 8, hipMemcpyDeviceToHost, s));
@@ -1848,8 +1806,20 @@ void plan_free(BatchPlan *p) {
   delete p;
 }
 
+// (user, knapsack) pairs of an instance as the staging counts them: one event
+// staged for 64 of them, and all of each where a pass emits every breakpoint
+double stage_pairs(const Prepared &P) {
+  return (double)P.pr.N * P.pr.K * (P.frac == 0.0 ? 64.0 * pair_events(P) : 1.0);
+}
+
+uint32_t samp_stage(const Prepared &P) {
+  return (uint32_t)std::min(65536.0, (double)P.U * P.pr.K * pair_events(P));
+}
+
+// lean: the smaller buffers of a plan whose context's workspace is capped (no
+// sampled starts, fewer emitted events: those that do not fit cost passes)
 kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *const *lam_a,
-                      double *const *lam_b, BatchPlan **out) {
+                      double *const *lam_b, BatchPlan **out, bool lean = false) {
   if (n < 1 || !probs || !lam_a || !lam_b) return fail(KP_ERR_INVALID, "bad batch arguments");
   std::vector<Prepared> P(n);
   for (int s = 0; s < n; ++s) {
@@ -1877,6 +1847,8 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
       q.ntiles = (q.pr.N + U - 1) / U;
     }
   }
+  if (!lean)
+    for (auto &q : P) choose_start(q, c->sample_min, c->window_enabled, q.U);
   int64_t T = 0;
   int Kf = 0;
   for (auto &q : P) { T += q.ntiles; Kf += q.pr.K; }
@@ -1916,18 +1888,21 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
   for (auto &q : P) { p->Umin = std::min(p->Umin, q.U); p->Umax = std::max(p->Umax, q.U); }
   p->bytes = bytes;
   const uint32_t cap = p->cap;
-  // emission buffers per instance: room for two breakpoints per user and
-  // knapsack (at least the uniform capacity, at most 2^20), scaled down when
+  // emission buffers per instance: every breakpoint of a small instance or a
+  // sample (at least the uniform capacity, at most 2^20), scaled down when
   // the whole batch would exceed kEmitBytesBatched
   std::vector<uint32_t> icap(n);
   double ebytes = 0.0;
   for (int s = 0; s < n; ++s) {
-    icap[s] = (uint32_t)std::min<int64_t>(1 << 20, std::max<int64_t>(cap, 2 * P[s].pr.N));
+    const double all = P[s].frac > 0.0 ? (double)P[s].samp_users : P[s].frac == 0.0 ? (double)P[s].pr.N : 0.0;
+    const int64_t want = std::max<int64_t>((int64_t)(pair_events(P[s]) * all), P[s].pr.N / 4);
+    icap[s] = (uint32_t)std::min<int64_t>(1 << 20, std::max<int64_t>(cap, want));
+    if (lean) icap[s] = (uint32_t)std::min<int64_t>(1 << 20, std::max<int64_t>(cap, 2 * P[s].pr.N)) - 24 * 1024;
     ebytes += (double)P[s].pr.K * icap[s] * 16.0;
   }
   if (ebytes > kEmitBytesBatched)
     for (int s = 0; s < n; ++s)
-      icap[s] = std::max<uint32_t>(cap, (uint32_t)(icap[s] * (kEmitBytesBatched / ebytes)));
+      icap[s] = std::max<uint32_t>(lean ? icap[s] / 4 : cap, (uint32_t)(icap[s] * (kEmitBytesBatched / ebytes)));
   std::vector<uint64_t> ioff(n + 1, 0);
   for (int s = 0; s < n; ++s) ioff[s + 1] = ioff[s] + (uint64_t)P[s].pr.K * icap[s];
   const int ncol = Kf + 2 * n;
@@ -1954,13 +1929,23 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
   std::vector<size_t> soff(n + 1, 0);
   for (int s = 0; s < n; ++s) {
     const int nb = boff[s + 1] - boff[s];
-    const double share = (double)P[s].pr.N * P[s].pr.K / std::max(1, nb) / 64.0;
+    const double share = stage_pairs(P[s]) / std::max(1, nb) / 64.0;
     scap[s] = (uint32_t)std::min<double>(kStageCapMax, std::max<double>(kStageCap, share));
     soff[s + 1] = soff[s] + (size_t)nb * scap[s];
   }
-  const size_t o_s1 = cv.take(soff[n] * 8);
-  const size_t o_s2 = cv.take(soff[n] * 8);
-  const size_t o_sk = cv.take(soff[n] * 2);
+  // the sampled pass: a block per sampled tile, its staging every event
+  // of the tile, over the same area
+  std::vector<int> sboff(n + 1, 0);
+  size_t sstage = 0;
+  for (int s = 0; s < n; ++s) sstage += P[s].frac > 0.0 ? (size_t)P[s].samp_tiles * samp_stage(P[s]) : 0;
+  const size_t stage_all = std::max(soff[n], sstage);
+  const size_t o_s1 = cv.take(stage_all * 8);
+  const size_t o_s2 = cv.take(stage_all * 8);
+  const size_t o_sk = cv.take(stage_all * 2);
+  const size_t o_frac = cv.take((size_t)Kf * 8);
+  const size_t o_sd0 = cv.take((size_t)n * sizeof(SweepArgs));
+  const size_t o_sd1 = cv.take((size_t)n * sizeof(SweepArgs));
+  const size_t o_sbo = cv.take((size_t)(n + 1) * 4);
   const size_t o_err = cv.take(8);
   const size_t o_pend = cv.take(8);
   const size_t o_kin = cv.take((size_t)Kf * 4);
@@ -1970,7 +1955,7 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
   const size_t o_tab0 = cv.take((size_t)ncol * kp_coldesc_size());
   const size_t o_tab1 = cv.take((size_t)ncol * kp_coldesc_size());
   const size_t o_stat = cv.take((size_t)ncol * 8);
-  const size_t o_hint = cv.take((size_t)Kf * 32);  // per knapsack: bucket width, last step, two past multipliers
+  const size_t o_hint = cv.take((size_t)Kf * 40);  // per knapsack: bucket width, last step, two past multipliers, the last result
   const size_t o_koff = cv.take((size_t)(n + 1) * 4);
   const size_t o_act = cv.take((size_t)n * 4);
   const size_t o_rd = cv.take((size_t)n * sizeof(SweepArgs));
@@ -1986,6 +1971,7 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
   const size_t o_ctl = cv.take(16);
   if (c->max_ws && cv.off > c->max_ws) {
     plan_free(p);
+    if (!lean) return plan_create(c, probs, n, lam_a, lam_b, out, true);
     return fail(KP_ERR_NOMEM, "batched plan needs %zu bytes, above the context cap", cv.off);
   }
   if (hipMalloc(&p->ws, cv.off) != hipSuccess) {
@@ -2015,7 +2001,7 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
   p->ecap = (uint32_t *)(w + o_ec);
   p->window = c->window_enabled;
   if (hipMemset(p->hint, 0, (size_t)Kf * 16) != hipSuccess ||
-      hipMemset(p->hint + 2 * (size_t)Kf, 0xFF, (size_t)Kf * 16) != hipSuccess) {
+      hipMemset(p->hint + 2 * (size_t)Kf, 0xFF, (size_t)Kf * 24) != hipSuccess) {
     plan_free(p);
     return fail(KP_ERR_HIP, "hipMemset failed");
   }
@@ -2025,6 +2011,10 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
   p->e1 = (double *)(w + o_e1);
   p->e2 = (double *)(w + o_e2);
   p->sel = kp_sel_ws(w + o_sel, Kf);
+  p->frac = (double *)(w + o_frac);
+  p->sd[0] = (SweepArgs *)(w + o_sd0);
+  p->sd[1] = (SweepArgs *)(w + o_sd1);
+  p->sboff = (int *)(w + o_sbo);
   p->err = (unsigned long long *)(w + o_err);
   p->pend = (int *)(w + o_pend);
   p->kin = (int *)(w + o_kin);
@@ -2049,17 +2039,20 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
   p->s1 = (double *)(w + o_s1);
   p->s2 = (double *)(w + o_s2);
   p->sk = (uint16_t *)(w + o_sk);
-  p->stage_total = soff[n];
+  p->stage_total = stage_all;
   p->gmax = gmax;
   p->ntiles.resize(n);
   p->pairs.resize(n);
   p->ilds.resize(n);
   for (int s = 0; s < n; ++s) {
     p->ntiles[s] = P[s].ntiles;
-    p->pairs[s] = (double)P[s].pr.N * P[s].pr.K;
+    p->pairs[s] = stage_pairs(P[s]);
     p->ilds[s] = kp_sweep_lds_bytes(P[s].U, P[s].pr.M, P[s].pr.K, true, P[s].pr.fmt);
   }
-  std::vector<SweepArgs> hd[2][2];
+  std::vector<SweepArgs> hd[2][2], hsd[2];
+  for (int d = 0; d < 2; ++d) hsd[d].resize(n);
+  std::vector<double> hfrac(Kf);
+  size_t sso = 0;
   for (int d = 0; d < 2; ++d) for (int f = 0; f < 2; ++f) hd[d][f].resize(n);
   std::vector<TileGeom> hg(n);
   std::vector<double> hB(Kf);
@@ -2077,6 +2070,7 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
     a.pr = P[s].pr;
     a.tree = P[s].tree;
     a.ntiles = P[s].ntiles;
+    a.tstride = 1;
     a.partials = (double *)(w + o_part) + poff[s];
     a.st = p->kst + koff[s];
     a.hist_sum = p->hs + (size_t)koff[s] * KP_NB;
@@ -2095,7 +2089,18 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
       hd[d][1][s] = a;
       a.want_stats = 0;
       hd[d][0][s] = a;
+      SweepArgs q = a;
+      q.sampled = 1;
+      q.ntiles = P[s].frac > 0.0 ? P[s].samp_tiles : 0;
+      q.tstride = P[s].samp_stride;
+      q.toff = P[s].samp_off;
+      q.stage_cap = samp_stage(P[s]);
+      q.stage_v1 = p->s1 + sso;
+      q.stage_v2 = p->s2 + sso;
+      q.stage_k = p->sk + sso;
+      hsd[d][s] = q;
     }
+    sso += (size_t)hsd[0][s].ntiles * hsd[0][s].stage_cap;
     hg[s] = kp_tile_geom(hd[0][1][s], P[s].U);
     for (int k = 0; k < K; ++k) {
       hB[koff[s] + k] = P[s].B[k];
@@ -2103,6 +2108,7 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
       klo[koff[s] + k] = k;
       heo[koff[s] + k] = ioff[s] + (uint64_t)k * icap[s];
       hec[koff[s] + k] = icap[s];
+      hfrac[koff[s] + k] = P[s].frac;
     }
     lt0[s] = lam_a[s];
     lt1[s] = lam_b[s];
@@ -2133,15 +2139,23 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
   std::vector<int> bpos(n + 1, 0);
   std::vector<SweepArgs> pd[2][2];
   std::vector<TileGeom> pg(n);
+  std::vector<SweepArgs> psd[2];
+  for (int d = 0; d < 2; ++d) psd[d].resize(n);
   for (int d = 0; d < 2; ++d) for (int f = 0; f < 2; ++f) pd[d][f].resize(n);
   for (int i = 0; i < n; ++i) {
     const int si = ord[i];
     bpos[i + 1] = bpos[i] + (boff[si + 1] - boff[si]);
     for (int d = 0; d < 2; ++d) for (int f = 0; f < 2; ++f) pd[d][f][i] = hd[d][f][si];
     pg[i] = hg[si];
+    for (int d = 0; d < 2; ++d) psd[d][i] = hsd[d][si];
+    sboff[i + 1] = sboff[i] + (int)hsd[0][si].ntiles;
   }
+  p->SB = sboff[n];
   for (int d = 0; d < 2 && e == hipSuccess; ++d)
     for (int f = 0; f < 2 && e == hipSuccess; ++f) e = up(p->d[d][f], pd[d][f].data(), (size_t)n * sizeof(SweepArgs));
+  for (int d = 0; d < 2 && e == hipSuccess; ++d) e = up(p->sd[d], psd[d].data(), (size_t)n * sizeof(SweepArgs));
+  if (e == hipSuccess) e = up(p->sboff, sboff.data(), (size_t)(n + 1) * 4);
+  if (e == hipSuccess) e = up(p->frac, hfrac.data(), (size_t)Kf * 8);
   if (e == hipSuccess) e = up(p->geom, pg.data(), (size_t)n * sizeof(TileGeom));
   if (e == hipSuccess) e = up(p->boff, bpos.data(), (size_t)(n + 1) * 4);
   if (e == hipSuccess) e = up(p->koff, koff.data(), (size_t)(n + 1) * 4);
@@ -2243,6 +2257,7 @@ kp_status kp_eval_dual_noalloc(void *hip_stream, const kp_problem *prob, const d
   a.pr = P.pr;
   a.tree = P.tree;
   a.lam = lambda;
+  a.tstride = 1;
   a.want_stats = 1;
   a.partials = partials;
   a.x_out = x;

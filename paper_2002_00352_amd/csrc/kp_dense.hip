@@ -104,8 +104,8 @@ __global__ void __launch_bounds__(64) k_dense(const SweepArgs a, int x4) {
   if (WIN) {
     for (int t = lane; t < K; t += 64) {
       kst[t] = a.st[t];
-      kmode[t] = a.st[t].mode;
-      hwin[t] = a.st[t].mode == KS_WINDOW ? a.st[t].hw : 0.0;
+      kmode[t] = pass_mode(a, t);
+      hwin[t] = kmode[t] == KS_WINDOW ? a.st[t].hw : 0.0;
       kcorr[t] = xs_zero();
       kcnt[t] = 0u; kpos[t] = 0u; kovf[t] = 0u;
       hmin[t] = ~0ull; hmax[t] = 0ull;

@@ -185,8 +185,12 @@ __device__ __forceinline__ void record_event(const SweepArgs &a, const KWalk &ks
       xs_atomic_add(&hs[k * KP_NB + bin], v2);
       atomicAdd(&hc[k * KP_NB + bin], 1u);
     }
-  } else {  // KS_EMIT_RANGE
+  } else {  // KS_EMIT_RANGE, KS_WINDOW
     emit = (key >= ks.klo && key <= ks.khi);
+    if (emit && mode == KS_EMIT_RANGE) {
+      atomicMin(&hmin[k], (unsigned long long)key);
+      atomicMax(&hmax[k], (unsigned long long)key);
+    }
   }
   if (emit) {
     const uint32_t slot = atomicAdd(nstage, 1u);
@@ -206,6 +210,13 @@ __device__ __forceinline__ void record_event(const SweepArgs &a, const KWalk &ks
 __device__ __forceinline__ bool walk_mode(int m) {
   return m == KS_EXP || m == KS_EMIT_BUCKET || m == KS_HULL_BUCKET || m == KS_REFINE ||
          m == KS_EMIT_RANGE || m == KS_WINDOW;
+}
+
+// A knapsack's search state in this pass: sampled passes take the knapsacks
+// that search a sample, the others the rest.
+__device__ __forceinline__ int pass_mode(const SweepArgs &a, int k) {
+  const KState &s = a.st[k];
+  return ((s.flags & KS_FLAG_SAMPLE) != 0) == (a.sampled != 0) ? s.mode : (int)KS_DONE;
 }
 
 // End of a sweep block: add its histograms to the global ones, reserve space

@@ -460,10 +460,10 @@ k_ell(const SweepArgs a, const EllGeom g) {
   for (int t = tid; t < EWM * (K + 2); t += ENT) wacc[t] = 0.0;
   if (!EV) {
     for (int t = tid; t < K; t += ENT) {
-      kmode[t] = a.st[t].mode;
+      kmode[t] = pass_mode(a, t);
       // (breakpoint phases: only windows that contain lambda_k^t take the gap
       // tests; a window away from it moves the lines past each other)
-      hwin[t] = a.st[t].mode == KS_WINDOW && !(BREAK && a.st[t].far) ? a.st[t].hw : 0.0;
+      hwin[t] = kmode[t] == KS_WINDOW && !(BREAK && a.st[t].far) ? a.st[t].hw : 0.0;
       if (MODE == KM_WMAIN) {
         const double h = hwin[t];
         // wA_k, widened by 2^-20 before rounding to fp32 so that the fp32
@@ -493,6 +493,12 @@ k_ell(const SweepArgs a, const EllGeom g) {
     hwin[K] = m;
     hwin[K + 1] = l;
   }
+  if (MODE == KM_SCD && !a.want_stats) {
+    // nothing to search in this pass
+    bool busy = false;
+    for (int k = 0; k < K; ++k) busy = busy || walk_mode(kmode[k]);
+    if (!busy) return;
+  }
   uint32_t nlisted = 0;
   if (MODE == KM_WFAIL) {
     const uint32_t cnt = *a.fcount;
@@ -517,7 +523,7 @@ k_ell(const SweepArgs a, const EllGeom g) {
   uint32_t nlist = 0;                 // users the wave listed
   // tile indices fit 32 bits (the launcher rejects more than 2^31 - 1 tiles)
   for (int tile = (int)blockIdx.x * EWM + wv; tile < (int)ntiles; tile += (int)W) {
-    const int64_t u0 = (int64_t)tile * 64;
+    const int64_t u0 = (MODE == KM_SCD ? (int64_t)tile * a.tstride + a.toff : (int64_t)tile) * 64;
     float pv[EM];
     int cl[EM * D];
     float vl[EM * D];

@@ -7,9 +7,9 @@
 #define KP_NB 64               // histogram bins per knapsack per pass
 #define KP_MAX_K_SCD 64        // per-block LDS histograms bound K for the SCD calls
 #define KP_CENTRAL_W 2         // exponential buckets |id| <= W are emitted in the first pass
-#define SEL_BITS 10            // key bins of the selection's first step over many blocks
+#define SEL_BITS 11            // key bins of the selection's first step over many blocks
 #define SEL_BINS (1 << SEL_BITS)
-#define SEL_COMP 8192          // events of the threshold's bin it compacts
+#define SEL_COMP 16384         // events of the threshold's bin it compacts
 #define KP_PROBE_USERS 4096   // users sampled by the dense window pass's probe
 #define KP_WIN_MULT 1.25       // window half-width around lambda_k^t, in units of the last step
 #define KP_WIN_MAX_REL 0.03125 // windows wider than this fraction of lambda_k^t are not tried
@@ -68,6 +68,8 @@ enum {
 };
 
 #define KS_FLAG_WINDOW 1u  // the key range of KS_SELECT_RANGE is a window: the threshold may lie outside
+#define KS_FLAG_SAMPLE 4u  // searching a sample of the users: the others' passes leave this knapsack out
+#define KS_FLAG_TRIED 8u   // the sample's window (or the pass that emits everything) was tried in this search
 #define KS_FLAG_INTERP 2u  // approximate reduce: interpolate inside the bucket that holds the threshold
 
 // What a sweep pass needs of a knapsack's search state (its LDS copy).
@@ -92,6 +94,8 @@ struct KState : KWalk {
   uint64_t eoff;       // batched: its emission buffer (elements from the base), when ecap > 0
   XSum fab;            // sum of increments strictly above the current target
   double result;       // lambda_k^{t+1} once mode == KS_DONE
+  double frac;         // > 0: a search without a window starts from this share of the users; 0: it emits every
+                       // breakpoint; < 0: exponential buckets
   uint64_t hull_lo, hull_hi;  // atomics: key hull of the bucket's events
   XSum corr;           // KS_WINDOW: sum over users of C_ik(whi+) - v_ik(x(lambda^t))
   uint64_t sel_lo, sel_hi;    // selection: keys of the bin that holds the threshold
@@ -124,7 +128,9 @@ struct SweepArgs {
   ProbDev pr;
   TreeDev tree;
   const double *lam;       // [K]
-  int64_t ntiles;
+  int64_t ntiles;          // tiles of the pass: tile t of it is tile t * tstride + toff of the instance
+  int64_t tstride, toff;
+  int sampled;             // the pass of the knapsacks searching a sample of the users (a subset of the tiles)
   // statistics (first pass only)
   int want_stats;
   int no_hist;             // SCD: no knapsack bins events (no EXP / REFINE mode): no histograms in LDS

@@ -262,7 +262,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a, const TileGeom &g
     if (hist)
       for (int t = tid; t < K * KP_NB; t += NT) { hs[t] = xs_zero(); hc[t] = 0u; }
     for (int t = tid; t < K; t += NT) {
-      kmode[t] = a.st[t].mode;
+      kmode[t] = pass_mode(a, t);
       kcnt[t] = 0u;
       kpos[t] = 0u;
       kovf[t] = 0u;
@@ -274,7 +274,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a, const TileGeom &g
       *nstage = 0u;
       double m = 0.0;
       for (int k = 0; k < K; ++k)
-        if (a.st[k].mode == KS_WINDOW) m = a.st[k].hw > m ? a.st[k].hw : m;
+        if (pass_mode(a, k) == KS_WINDOW) m = a.st[k].hw > m ? a.st[k].hw : m;
       kwide[0] = m;
     }
   }
@@ -294,7 +294,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a, const TileGeom &g
   Prefetch f;
   int64_t tile = bid;
   if (tile < a.ntiles) {
-    const int64_t u0 = tile * (int64_t)U;
+    const int64_t u0 = SCD ? (tile * a.tstride + a.toff) * U : tile * (int64_t)U;
     const int nu = (int)((N - u0) < U ? (N - u0) : U);
     issue_rows<FMT>(f, a.pr, u0, nu * M, K, tid, g.aligned);
     if (FMT == 1) {
@@ -305,7 +305,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a, const TileGeom &g
   }
 
   for (; tile < a.ntiles; tile += nblk) {
-    const int64_t u0 = tile * (int64_t)U;
+    const int64_t u0 = SCD ? (tile * a.tstride + a.toff) * U : tile * (int64_t)U;
     const int nu = (int)((N - u0) < U ? (N - u0) : U);     // users in this tile
     const int nr = nu * M;
     __syncthreads();   // previous tile's readers are done with the LDS tile
@@ -358,7 +358,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a, const TileGeom &g
     int64_t nu0 = 0;
     int nnr = 0;
     if (ntile < a.ntiles) {
-      nu0 = ntile * (int64_t)U;
+      nu0 = SCD ? (ntile * a.tstride + a.toff) * U : ntile * (int64_t)U;
       nnr = (int)((N - nu0) < U ? (N - nu0) : U) * M;
       issue_rows<FMT>(f, a.pr, nu0, nnr, K, tid, g.aligned);
     }
@@ -765,18 +765,6 @@ __global__ void __launch_bounds__(256) k_reduce_stats(const double *partials, in
   } else {
     if (P) *P = s;
   }
-}
-
-// users[s] = s * stride + off (a strided sample)
-__global__ void k_strided_users(int64_t *users, int64_t n, int64_t stride, int64_t off) {
-  for (int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; s < n; s += (int64_t)gridDim.x * blockDim.x)
-    users[s] = s * stride + off;
-}
-
-// rowptr of a sample whose rows all hold D entries: r * D
-__global__ void k_uniform_rowptr(int64_t *rowptr, int64_t nrows, int D) {
-  for (int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; r <= nrows; r += (int64_t)gridDim.x * blockDim.x)
-    rowptr[r] = r * D;
 }
 
 // ---------------------------------------------------------------------------
@@ -1737,16 +1725,6 @@ hipError_t kp_launch_gather_csr(const int64_t *rowptr, const int32_t *col, const
                                 int32_t *scol, float *sval, hipStream_t stream) {
   hipLaunchKernelGGL(k_gather_csr, dim3(gather_blocks(n * M)), dim3(256), 0, stream, rowptr, col, val,
                      users, n, M, subptr, scol, sval);
-  return hipGetLastError();
-}
-
-hipError_t kp_launch_strided_users(int64_t *users, int64_t n, int64_t stride, int64_t off, hipStream_t stream) {
-  hipLaunchKernelGGL(k_strided_users, dim3(gather_blocks(n)), dim3(256), 0, stream, users, n, stride, off);
-  return hipGetLastError();
-}
-
-hipError_t kp_launch_uniform_rowptr(int64_t *rowptr, int64_t nrows, int D, hipStream_t stream) {
-  hipLaunchKernelGGL(k_uniform_rowptr, dim3(gather_blocks(nrows + 1)), dim3(256), 0, stream, rowptr, nrows, D);
   return hipGetLastError();
 }
 

@@ -51,8 +51,39 @@ __device__ __forceinline__ void choose_window(KState &s, double step, double pre
   set_window(s, s.center);
 }
 
+// The start of a search without a window.  frac > 0: the search runs on that
+// share of the users first and turns into a window around the sample's
+// threshold (k_sample_window).  frac == 0: the instance is small, its pass
+// emits every breakpoint and the threshold is selected among them (one pass;
+// the exponential buckets took two or three).  frac < 0, or the other starts
+// failed: exponential buckets over every breakpoint.
+__device__ __forceinline__ void search_start(KState &s) {
+  s.far = 0;
+  s.tlo = 0.0;
+  s.thi = INFINITY;
+  s.klo = 0;
+  s.khi = ~0ull;
+  s.n_emit = 0;
+  s.overflow = 0;
+  s.fab = xs_zero();
+  s.hull_lo = ~0ull;
+  s.hull_hi = 0;
+  s.corr = xs_zero();
+  const uint32_t tried = s.flags & KS_FLAG_TRIED;
+  if (tried || s.frac < 0.0) {
+    s.mode = KS_EXP;
+    s.flags = tried;
+  } else {
+    s.mode = KS_EMIT_RANGE;
+    s.wlo = 0.0;
+    // (KS_FLAG_WINDOW: the threshold is 0 when the increments do not exceed
+    // the budget)
+    s.flags = s.frac > 0.0 ? KS_FLAG_SAMPLE : (KS_FLAG_TRIED | KS_FLAG_WINDOW);
+  }
+}
+
 __global__ void k_scd_init(KState *st, int K, const double *lam_in, const uint8_t *kmask,
-                           double *hist, int hinted_in, int window, int interp) {
+                           double *hist, int hinted_in, int window, int interp, double frac) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= K) return;
   KState s;
@@ -65,8 +96,10 @@ __global__ void k_scd_init(KState *st, int K, const double *lam_in, const uint8_
   s.center = lam_in[k];
   // hist: [K] bucket widths and [K] last steps (valid when hinted_in), then
   // [K] lambda^{t-1} and [K] lambda^{t-2} (NaN while unknown), shifted here
-  // once per iteration
-  const double *delta_hint = (hist && hinted_in) ? hist : nullptr;
+  // once per iteration, and [K] the multipliers last returned
+  // A multiplier that the last call did not return (by more than its last
+  // step) starts a new trajectory: its windows would be stale.
+  const double *delta_hint = (hist && hinted_in && fabs(lam_in[k] - hist[4 * K + k]) <= hist[K + k]) ? hist : nullptr;
   double d = delta_hint ? delta_hint[k] : 0.0;
   const bool hinted = d > 0.0;
   double prev = -1.0, drift = -1.0;
@@ -109,28 +142,17 @@ __global__ void k_scd_init(KState *st, int K, const double *lam_in, const uint8_
   s.far = 0;
   s.tlo = 0.0;
   s.thi = INFINITY;
-  if (interp) s.flags = KS_FLAG_INTERP;
-  else if (window && hinted && s.mode == KS_EXP) choose_window(s, delta_hint[K + k], prev, drift);
+  s.frac = frac;
+  if (interp) {
+    s.flags = KS_FLAG_INTERP;
+  } else if (s.mode == KS_EXP) {
+    if (window && hinted) choose_window(s, delta_hint[K + k], prev, drift);
+    if (s.mode == KS_EXP) search_start(s);
+  }
   st[k] = s;
 }
 
 __device__ __forceinline__ int bits_needed(uint64_t x) { return x ? 64 - __clzll((long long)x) : 0; }
-
-// Full search of the next pass: exponential buckets over every breakpoint.
-__device__ __forceinline__ void restart_full(KState &s) {
-  s.mode = KS_EXP;
-  s.far = 0;
-  s.tlo = 0.0;
-  s.thi = INFINITY;
-  s.flags = 0;
-  s.n_emit = 0;
-  s.overflow = 0;
-  s.fab = xs_zero();
-  s.klo = 0;
-  s.khi = ~0ull;
-  s.hull_lo = ~0ull;
-  s.hull_hi = 0;
-}
 
 __device__ __forceinline__ void set_refine(KState &s, uint64_t lo, uint64_t hi) {
   s.klo = lo;
@@ -250,8 +272,18 @@ __global__ void __launch_bounds__(64) k_scd_locate(KState *st, int K, const doub
       set_refine(s, lo, hi);
     }
   } else if (s.mode == KS_EMIT_RANGE) {
-    if (!s.overflow) s.mode = KS_SELECT_RANGE;
-    else set_refine(s, s.klo, s.khi);
+    if (s.flags & KS_FLAG_SAMPLE) {   // (a sample's search waits for its own pass)
+    } else if (!s.overflow) {
+      s.mode = KS_SELECT_RANGE;
+      if (s.flags & KS_FLAG_WINDOW) {   // every breakpoint was emitted: their keys
+        s.klo = s.hull_lo;
+        s.khi = s.hull_hi;
+      }
+    } else if (s.flags & KS_FLAG_WINDOW) {
+      search_start(s);                  // too many to emit: buckets
+    } else {
+      set_refine(s, s.klo, s.khi);
+    }
   } else if (s.mode == KS_WINDOW) {
     // consumption just above the window, summed over users
     // consumption of knapsack k (batched: R of instance rinst[k] sits after
@@ -261,7 +293,7 @@ __global__ void __launch_bounds__(64) k_scd_locate(KState *st, int K, const doub
     if (win && lane == 0) { atomicAdd(&win[0], 1u); atomicAdd(&win[3], s.n_emit); }
     if (s.overflow || xs_gt(above, Bk)) {
       if (win && lane == 0) atomicAdd(&win[1], 1u);
-      restart_full(s);                  // the threshold lies above the window
+      search_start(s);                  // the threshold lies above the window
     } else {
       s.mode = KS_SELECT_RANGE;         // [klo, khi] is the window
       s.fab = above;
@@ -296,6 +328,11 @@ __device__ __forceinline__ bool sel_mode(int m) { return m == KS_SELECT_BUCKET |
 // breakpoint of exponential bucket bstar (widened by more than the rounding
 // of the bucket test).
 __device__ __forceinline__ void sel_keys(const KState &s, uint64_t &lo, uint64_t &hi) {
+  if (s.flags & KS_FLAG_SAMPLE) {
+    lo = s.hull_lo;
+    hi = s.hull_hi;
+    return;
+  }
   if (s.mode == KS_SELECT_RANGE) {
     lo = s.klo;
     hi = s.khi;
@@ -349,10 +386,13 @@ __device__ __forceinline__ void sel_pick(const XSum *hsum, const uint32_t *hcnt,
 
 #define SH_NT 512
 __global__ void __launch_bounds__(SH_NT) k_sel_hist(const KState *st, const double *V1, const double *V2,
-                                                    uint32_t emit_cap, SelWs w) {
+                                                    uint32_t emit_cap, SelWs w, int sample) {
   const int k = blockIdx.x, tid = threadIdx.x;
   const int mode = st[k].mode;
-  if (!sel_mode(mode) || st[k].n_emit <= SEL_SMALL) return;
+  // (sample: the sampled searches' emitted breakpoints, whatever their count)
+  if (sample ? !(st[k].flags & KS_FLAG_SAMPLE) || mode != KS_EMIT_RANGE || st[k].n_emit == 0
+             : !sel_mode(mode) || st[k].n_emit <= SEL_SMALL)
+    return;
   __shared__ KState s;
   __shared__ XSum hs[SEL_BINS];
   __shared__ uint32_t hc[SEL_BINS];
@@ -506,8 +546,8 @@ __global__ void __launch_bounds__(SEL_NT) k_sel_final(KState *st, const double *
         st[k].result = 0.0;
         st[k].mode = KS_DONE;
       } else {
-        KState r = s;                   // below the window: full search
-        restart_full(r);
+        KState r = s;                   // below the window: search again
+        search_start(r);
         st[k] = r;
         if (win) atomicAdd(&win[2], 1u);
         atomicAdd(pending, 1);
@@ -624,35 +664,94 @@ __global__ void k_scd_finish(const KState *st, int K, const double *lam_in, doub
     const double w = step > floor_ ? step : floor_;
     delta_next[k] = ldexp(1.0, ilogb(w) + 1);
     delta_next[K + k] = w;
+    delta_next[4 * K + k] = nl;
   }
 }
 
-// A full search (no window) centres its buckets on the threshold of a
-// sample of users (lam_hat, from the same search on the sample with its
-// budgets scaled): buckets of half-width 2^-8 of it around it, so the central
-// buckets emitted by the first pass usually hold the threshold.  With
-// windows enabled, and lambda_k^t within a quarter of lam_hat, the search
-// starts instead with a window over those central buckets (4 bucket widths
-// either side of lam_hat): the walks stop below the window and nothing is
-// binned (c3 cold iterations 95 -> 45-55 ms); from further away (a start
-// from lambda = 0) the window pass costs more than the buckets.  A miss
-// falls back to the full search around lam_hat.  Exactness does not depend
-// on either (the threshold is located by exact sums over all users).
-__global__ void k_scd_recenter(KState *st, int K, const double *lam_hat, const double *lam_in, int window) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= K) return;
-  const double c = lam_hat[k];
-  if (st[k].mode != KS_EXP || !(c > 0x1p-20)) return;
-  KState s = st[k];
-  s.center = c;
-  s.delta = ldexp(1.0, ilogb(c) - 8);
-  if (window && fabs(lam_in[k] - c) <= 0.25 * c) {
-    const double h = 4.0 * s.delta;
-    s.whi = c + h;
-    s.wlo = c - h > 0.0 ? c - h : 0.0;
-    set_window(s, lam_in[k]);
+// The window a sampled search turns into: every breakpoint of the sample was
+// emitted and binned by key (2048 bins of about 2 % each over the keys'
+// span), and the window runs from the bin where the sample's running sum
+// exceeds its budget by KP_SAMPLE_DEV deviations down -- to where it falls
+// short of it by as much.  The sum of n increments from a sample deviates by
+// about 1.3 / sqrt(n) of itself (increments of a spread like the uniform's);
+// at 3.5 deviations a window misses once in thousands.  A sample with too
+// few breakpoints above the threshold, or one that overflowed its buffer,
+// opens the window over everything.  Exactness does not depend on any of it:
+// the window's search compares exact sums over all users, and a miss falls
+// back to the buckets.
+#define KP_SAMPLE_DEV 4.5
+#define SW_NT 256
+__global__ void __launch_bounds__(SW_NT) k_sample_window(KState *st, const double *B, SelWs w) {
+  const int k = blockIdx.x, tid = threadIdx.x;
+  if (!(st[k].flags & KS_FLAG_SAMPLE) || st[k].mode != KS_EMIT_RANGE) return;
+  __shared__ KState s;
+  __shared__ XSum hs[SEL_BINS];
+  __shared__ uint32_t hc[SEL_BINS];
+  __shared__ XSum part[SW_NT / 64 + 1];
+  __shared__ int bin, b0;
+  __shared__ XSum cum;
+  __shared__ uint32_t above;
+  if (tid == 0) { s = st[k]; above = 0; }
+  __syncthreads();
+  const bool any = s.n_emit != 0;
+  for (int t = tid; any && t < SEL_BINS; t += SW_NT) {
+    hs[t] = w.hsum[(size_t)k * SEL_BINS + t];
+    hc[t] = w.hcnt[(size_t)k * SEL_BINS + t];
+    w.hsum[(size_t)k * SEL_BINS + t] = xs_zero();
+    w.hcnt[(size_t)k * SEL_BINS + t] = 0u;
   }
-  st[k] = s;
+  __syncthreads();
+  double wlo = 0.0, whi = INFINITY;
+  if (any && !s.overflow) {
+    const double Bs = B[k] * s.frac;
+    const int shift = sel_shift(s.hull_lo, s.hull_hi, SEL_BITS);
+    sel_pick<SEL_BINS, SW_NT>(hs, hc, xs_zero(), Bs, part, &bin, &cum);
+    if (tid == 0) b0 = bin;
+    __syncthreads();
+    uint32_t c = 0;
+    for (int t = tid; t < SEL_BINS; t += SW_NT)
+      if (t >= b0) c += hc[t];
+    if (c) atomicAdd(&above, c);
+    __syncthreads();
+    if (above >= 16u) {
+      const double dev = fmin(0.5, KP_SAMPLE_DEV / sqrt((double)above));
+      sel_pick<SEL_BINS, SW_NT>(hs, hc, xs_zero(), Bs * (1.0 - dev), part, &bin, &cum);
+      // the top of that bin; nothing exceeds it: no threshold above the lowest breakpoint
+      const int bh = bin;
+      __syncthreads();
+      sel_pick<SEL_BINS, SW_NT>(hs, hc, xs_zero(), Bs * (1.0 + dev), part, &bin, &cum);
+      const int bl = bin;
+      const uint64_t one = 1;
+      if (bh < 0) {
+        whi = kdbl(s.hull_lo);
+      } else {
+        const uint64_t key = s.hull_lo + ((uint64_t)(bh + 1) << shift);
+        whi = kdbl(key < s.hull_hi ? key : s.hull_hi);
+      }
+      if (bl >= 0) {
+        const uint64_t key = s.hull_lo + ((uint64_t)bl << shift);
+        wlo = kdbl(key - one);
+      }
+    }
+  }
+  if (tid == 0) {
+    const double l = s.center;   // lambda_k^t
+    s.flags = KS_FLAG_TRIED;
+    s.n_emit = 0;
+    s.overflow = 0;
+    s.fab = xs_zero();
+    s.hull_lo = ~0ull;
+    s.hull_hi = 0;
+    s.corr = xs_zero();
+    s.wlo = wlo;
+    s.whi = whi;
+    set_window(s, l);
+    if (whi < INFINITY) {   // a miss continues with buckets around it
+      s.center = 0.5 * (wlo + whi);
+      s.delta = ldexp(1.0, ilogb(fmax(whi - wlo, whi * 0x1p-20)));
+    }
+    st[k] = s;
+  }
 }
 
 // Knapsacks starting with a window and those needing another search mode.
@@ -679,7 +778,7 @@ __global__ void k_count_modes(const KState *st, int K, int *out) {
 
 __global__ void k_scd_init_flat(KState *st, int Kf, const double *const *lam_in, const int *kinst,
                                 const int *klocal, double *hint, int window, const uint64_t *eoff,
-                                const uint32_t *ecap) {
+                                const uint32_t *ecap, const double *frac) {
   const int f = blockIdx.x * blockDim.x + threadIdx.x;
   if (f >= Kf) return;
   const double l = lam_in[kinst[f]][klocal[f]];
@@ -720,8 +819,12 @@ __global__ void k_scd_init_flat(KState *st, int Kf, const double *const *lam_in,
     const double drift = fabs(l - hint[3 * Kf + f]);
     hint[3 * Kf + f] = prev;
     hint[2 * Kf + f] = l;
-    if (window && hint[f] > 0.0) choose_window(s, hint[Kf + f], prev, drift);
+    // (a multiplier that the last step did not return: no window)
+    if (window && hint[f] > 0.0 && fabs(l - hint[4 * Kf + f]) <= hint[Kf + f])
+      choose_window(s, hint[Kf + f], prev, drift);
   }
+  s.frac = frac[f];
+  if (s.mode == KS_EXP) search_start(s);
   st[f] = s;
 }
 
@@ -743,24 +846,25 @@ __global__ void k_scd_finish_flat(const KState *st, int Kf, double *const *lam_o
   lam_out[kinst[f]][klocal[f]] = nl;
   if (hint) {
     // the next iteration's bucket width: the power of two above this step
-    const double step = fabs(nl - st[f].center);
+    const double step = fabs(nl - hint[2 * Kf + f]);   // (that column holds this iteration's lambda_in)
     const double floor_ = (nl > 0x1p-20 ? nl : 0x1p-20) * 0x1p-30;
     const double w = step > floor_ ? step : floor_;
     hint[f] = ldexp(1.0, ilogb(w) + 1);
     hint[Kf + f] = w;
+    hint[4 * Kf + f] = nl;
   }
 }
 
 
 hipError_t kp_launch_batched_aux(int which, const void *tab, int n, KState *st, const void *lam_ptrs,
                                  const int *kinst, const int *klocal, double *hint, const uint64_t *eoff,
-                                 const uint32_t *ecap, hipStream_t stream) {
+                                 const uint32_t *ecap, const double *frac, hipStream_t stream) {
   if (n <= 0) return hipSuccess;
   if (which == 0) return kp_launch_reduce_tab(tab, n, stream);
   if (which == 1 || which == 3) {   // 3: with a window where the last step allows
     hipLaunchKernelGGL(k_scd_init_flat, dim3((n + 63) / 64), dim3(64), 0, stream, st, n,
                        (const double *const *)lam_ptrs, kinst, klocal, hint,
-                       which == 3 ? 1 : 0, eoff, ecap);
+                       which == 3 ? 1 : 0, eoff, ecap, frac);
   } else {
     hipLaunchKernelGGL(k_scd_finish_flat, dim3((n + 63) / 64), dim3(64), 0, stream, (const KState *)st,
                        n, (double *const *)lam_ptrs, kinst, klocal, hint);
@@ -775,9 +879,10 @@ hipError_t kp_launch_inst_active(const KState *st, const int *koff, int n, int *
 }
 
 hipError_t kp_launch_scd_init(KState *st, int K, const double *lam_in, const uint8_t *kmask,
-                              double *hist, int hinted, int window, int interp, hipStream_t stream) {
+                              double *hist, int hinted, int window, int interp, double frac,
+                              hipStream_t stream) {
   hipLaunchKernelGGL(k_scd_init, dim3((K + 63) / 64), dim3(64), 0, stream, st, K, lam_in, kmask,
-                     hist, hinted, window, interp);
+                     hist, hinted, window, interp, frac);
   return hipGetLastError();
 }
 
@@ -816,7 +921,7 @@ hipError_t kp_launch_scd_locate_select(KState *st, int K, const double *B, const
   hipLaunchKernelGGL(k_scd_locate, dim3(K), dim3(64), 0, stream, st, K, B, R, rinst, hist_sum,
                      hist_cnt, emit_cap, pending, win);
   if (blocks > 0) {
-    hipLaunchKernelGGL(k_sel_hist, dim3(K, blocks), dim3(SH_NT), 0, stream, st, ev1, ev2, emit_cap, w);
+    hipLaunchKernelGGL(k_sel_hist, dim3(K, blocks), dim3(SH_NT), 0, stream, st, ev1, ev2, emit_cap, w, 0);
     hipLaunchKernelGGL(k_sel_compact, dim3(K, blocks), dim3(SH_NT), 0, stream, st, B, ev1, ev2, emit_cap, w);
   }
   hipLaunchKernelGGL(k_sel_final, dim3(K), dim3(SEL_NT), 0, stream, st, B, ev1, ev2, emit_cap, w,
@@ -829,7 +934,7 @@ hipError_t kp_launch_scd_select_many(KState *st, int K, const double *B, const d
                                      unsigned int *win, hipStream_t stream) {
   hipError_t e = kp_launch_fill_i32(pending, 2, 0, stream);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_sel_hist, dim3(K, blocks), dim3(SH_NT), 0, stream, st, ev1, ev2, emit_cap, w);
+  hipLaunchKernelGGL(k_sel_hist, dim3(K, blocks), dim3(SH_NT), 0, stream, st, ev1, ev2, emit_cap, w, 0);
   hipLaunchKernelGGL(k_sel_compact, dim3(K, blocks), dim3(SH_NT), 0, stream, st, B, ev1, ev2, emit_cap, w);
   hipLaunchKernelGGL(k_sel_final, dim3(K), dim3(SEL_NT), 0, stream, st, B, ev1, ev2, emit_cap, w, 1, pending, win);
   return hipGetLastError();
@@ -847,8 +952,11 @@ hipError_t kp_launch_scd_finish(const KState *st, int K, const double *lam_in, d
   return hipGetLastError();
 }
 
-hipError_t kp_launch_recenter(KState *st, int K, const double *lam_hat, const double *lam_in, int window,
-                              hipStream_t stream) {
-  hipLaunchKernelGGL(k_scd_recenter, dim3((K + 63) / 64), dim3(64), 0, stream, st, K, lam_hat, lam_in, window);
+// The sampled searches' emitted breakpoints to windows (the sample's sweep
+// ran): blocks per knapsack that bin them.
+hipError_t kp_launch_sample_window(KState *st, int K, const double *B, const double *ev1, const double *ev2,
+                                   uint32_t emit_cap, const SelWs &w, int blocks, hipStream_t stream) {
+  hipLaunchKernelGGL(k_sel_hist, dim3(K, blocks), dim3(SH_NT), 0, stream, st, ev1, ev2, emit_cap, w, 1);
+  hipLaunchKernelGGL(k_sample_window, dim3(K), dim3(SW_NT), 0, stream, st, B, w);
   return hipGetLastError();
 }
