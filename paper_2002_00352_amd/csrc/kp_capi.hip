@@ -18,10 +18,10 @@
 #include "kp_internal.h"
 
 // launchers (kp_kernels.hip)
-size_t kp_sweep_lds_bytes(int U, int M, int K, bool scd, int fmt, bool hist = true);
+size_t kp_sweep_lds_bytes(int U, int M, int K, int L, bool scd, int fmt, bool hist = true);
 hipError_t kp_launch_sweep(const SweepArgs &a, int U, int grid, bool scd, hipStream_t stream,
                            int *used);
-int kp_sweep_resident_grid(int U, int M, int K, bool scd, int fmt, bool hist = true);
+int kp_sweep_resident_grid(int U, int M, int K, int L, bool scd, int fmt, bool hist = true);
 int kp_sweep_batched_resident(size_t lds);
 hipError_t kp_launch_reduce_stats(const double *partials, int nblk, int K, const double *lam,
                                   const double *B, double *R, double *g, double *P,
@@ -373,6 +373,14 @@ kp_status prepare(const kp_problem *p, bool scd, Prepared &out, const Ctx *ctx =
   for (int t = 0; t < nn; ++t) {
     out.tree.mask[t] = nmask[t];
     out.tree.cap[t] = ncap[t];
+    out.tree.up[t] = -1;
+    for (int q = t + 1; q < nn && out.tree.up[t] < 0; ++q)
+      if ((nmask[t] & ~nmask[q]) == 0) out.tree.up[t] = (int16_t)q;
+  }
+  for (int j = 0; j < M; ++j) {
+    out.tree.first[j] = -1;
+    for (int t = 0; t < nn && out.tree.first[j] < 0; ++t)
+      if (nmask[t] >> j & 1) out.tree.first[j] = (int16_t)t;
   }
   ProbDev &pr = out.pr;
   memset(&pr, 0, sizeof(pr));
@@ -402,8 +410,8 @@ kp_status prepare(const kp_problem *p, bool scd, Prepared &out, const Ctx *ctx =
     }
   }
   const int U0 = U;
-  while (U > 1 && kp_sweep_lds_bytes(U, M, p->K, scd, p->b_format) > 64 * 1024) --U;
-  if (kp_sweep_lds_bytes(U, M, p->K, scd, p->b_format) > kMaxLds)
+  while (U > 1 && kp_sweep_lds_bytes(U, M, p->K, nn, scd, p->b_format) > 64 * 1024) --U;
+  if (kp_sweep_lds_bytes(U, M, p->K, nn, scd, p->b_format) > kMaxLds)
     return fail(KP_ERR_UNSUPPORTED, "M*K = %d too large for one tile", M * p->K);
   out.U = U;
   out.ntiles = (p->N + U - 1) / U;
@@ -420,7 +428,7 @@ kp_status prepare(const kp_problem *p, bool scd, Prepared &out, const Ctx *ctx =
   out.grid = (int)std::max<int64_t>(1, std::min<int64_t>(out.ntiles, grid_override > 0 ? grid_override : kMaxGrid));
   // persistent launch: no more blocks than can be resident at once
   if (p->N > 0) {
-    const int res = kp_sweep_resident_grid(U, M, p->K, scd, p->b_format);
+    const int res = kp_sweep_resident_grid(U, M, p->K, nn, scd, p->b_format);
     if (res > 0) out.grid = std::min(out.grid, res);
   }
   out.U_nh = out.U;
@@ -430,10 +438,10 @@ kp_status prepare(const kp_problem *p, bool scd, Prepared &out, const Ctx *ctx =
     // without the K x 64 histogram bins a tile can hold more users, and more
     // blocks fit on a compute unit
     int Un = U0;
-    while (Un > 1 && kp_sweep_lds_bytes(Un, M, p->K, true, p->b_format, false) > 64 * 1024) --Un;
+    while (Un > 1 && kp_sweep_lds_bytes(Un, M, p->K, nn, true, p->b_format, false) > 64 * 1024) --Un;
     const int64_t nt = (p->N + Un - 1) / Un;
     int g = (int)std::max<int64_t>(1, std::min<int64_t>(nt, grid_override > 0 ? grid_override : kMaxGrid));
-    const int res = kp_sweep_resident_grid(Un, M, p->K, true, p->b_format, false);
+    const int res = kp_sweep_resident_grid(Un, M, p->K, nn, true, p->b_format, false);
     if (res > 0) g = std::min(g, res);
     out.U_nh = Un;
     out.ntiles_nh = nt;
@@ -1840,7 +1848,7 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
   const size_t lds_budget = c->bt_lds > 0 ? (size_t)c->bt_lds : kBatchedLds;
   for (auto &q : P) {
     int U = q.U;
-    while (U > 1 && kp_sweep_lds_bytes(U, q.pr.M, q.pr.K, true, q.pr.fmt) > lds_budget) --U;
+    while (U > 1 && kp_sweep_lds_bytes(U, q.pr.M, q.pr.K, q.tree.L, true, q.pr.fmt) > lds_budget) --U;
     while (U > 1 && q.pr.fmt == KP_B_DENSE && ((int64_t)U * q.pr.M * q.pr.K) % 4 != 0) --U;
     if (U != q.U) {
       q.U = U;
@@ -1854,7 +1862,7 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
   for (auto &q : P) { T += q.ntiles; Kf += q.pr.K; }
   size_t lds = 0;
   for (int s = 0; s < n; ++s)
-    lds = std::max(lds, kp_sweep_lds_bytes(P[s].U, P[s].pr.M, P[s].pr.K, true, P[s].pr.fmt));
+    lds = std::max(lds, kp_sweep_lds_bytes(P[s].U, P[s].pr.M, P[s].pr.K, P[s].tree.L, true, P[s].pr.fmt));
   // blocks are split among the instances in proportion to their tiles; many
   // more blocks than can be resident at once keep the split fine-grained, and
   // the hardware dispatcher balances them (every instance gets at least one)
@@ -2047,7 +2055,7 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
   for (int s = 0; s < n; ++s) {
     p->ntiles[s] = P[s].ntiles;
     p->pairs[s] = stage_pairs(P[s]);
-    p->ilds[s] = kp_sweep_lds_bytes(P[s].U, P[s].pr.M, P[s].pr.K, true, P[s].pr.fmt);
+    p->ilds[s] = kp_sweep_lds_bytes(P[s].U, P[s].pr.M, P[s].pr.K, P[s].tree.L, true, P[s].pr.fmt);
   }
   std::vector<SweepArgs> hd[2][2], hsd[2];
   for (int d = 0; d < 2; ++d) hsd[d].resize(n);

@@ -47,7 +47,7 @@ __host__ __device__ inline size_t dn_lds(int M, int K, int L, bool win) {
   size_t s = dn_r16((size_t)K * 8) + dn_r16((size_t)L * 8 + 8) + dn_r16((size_t)L * 4 + 4) +
              dn_r16((size_t)TU * M * 4) + dn_r16((size_t)TU * M * K * 4);
   if (win)
-    s += dn_r16((size_t)K * sizeof(KWalk)) + dn_r16((size_t)K * 4) + dn_r16((size_t)(K + 1) * 8) +
+    s += set_tree_bytes(L, M) + dn_r16((size_t)K * sizeof(KWalk)) + dn_r16((size_t)K * 4) + dn_r16((size_t)(K + 1) * 8) +
          dn_r16((size_t)K * sizeof(XSum)) + 3 * dn_r16((size_t)K * 4) + 2 * dn_r16((size_t)K * 8) + dn_r16(16) +
          (size_t)M * 64 * 8;
   return s;
@@ -86,6 +86,7 @@ __global__ void __launch_bounds__(64) k_dense(const SweepArgs a, int x4) {
   uint32_t *kcnt = nullptr, *kpos = nullptr, *kovf = nullptr, *nstage = nullptr;
   unsigned long long *hmin = nullptr, *hmax = nullptr;
   double *ptl = nullptr;
+  SetTree tr;
   if (WIN) {
     kst = (KWalk *)carve((size_t)K * sizeof(KWalk));
     kmode = (int *)carve((size_t)K * 4);
@@ -97,6 +98,7 @@ __global__ void __launch_bounds__(64) k_dense(const SweepArgs a, int x4) {
     hmin = (unsigned long long *)carve((size_t)K * 8);
     hmax = (unsigned long long *)carve((size_t)K * 8);
     nstage = (uint32_t *)carve(16);
+    tr = set_tree_load(carve(set_tree_bytes(L, M)), a.tree, M, lane, 64);
     ptl = (double *)carve((size_t)M * 64 * 8);
   }
   for (int t = lane; t < K; t += 64) lam[t] = a.lam[t];
@@ -307,9 +309,9 @@ __global__ void __launch_bounds__(64) k_dense(const SweepArgs a, int x4) {
         uint64_t A = 0;
         for (int j = 0; j < M; ++j)
           if (bc[j * K] > 0.0f) A |= 1ull << j;
-        lane_walk_pair(a, M, L, col, k, A, So, poso, permo,
+        lane_walk_pair(a, M, col, k, A, So, poso, permo,
                        [&](int j, int cc) { return (double)sb[((size_t)cc * M + j) * K + k]; }, ptl, lam, kst,
-                       kmode, tmask, tcap, kcorr, nullptr, nullptr, hmin, hmax, kcnt, kovf, nstage);
+                       kmode, tr, kcorr, nullptr, nullptr, hmin, hmax, kcnt, kovf, nstage);
       });
     }
   }

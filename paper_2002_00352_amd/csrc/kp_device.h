@@ -135,9 +135,72 @@ __device__ __forceinline__ bool cr_gt(double num, double den, double t) {   // t
   if (r2 >= 0.0) return true;                    // quotient >= up
   return num / den > t;
 }
+// The laminar sets in LDS, as chains from an item's smallest set up: the
+// breakpoint phases look for the innermost full set that holds an item all
+// the time, in code where lanes diverge; read from the kernel's arguments
+// (scalar loads, each waited for, over all the sets) those looks were most of
+// a walk's time.  One set or none (top-Q) stays in registers.
+struct SetNode {
+  uint64_t mask;
+  int cap, up;
+};
+struct SetTree {
+  const SetNode *node;
+  const int16_t *first;
+  int L, c1;
+  uint64_t m1;
+  // the members of S in the innermost full set that holds o (0: none is full)
+  __device__ __forceinline__ uint64_t circuit(uint64_t S, int o) const {
+    if (L <= 1) return (m1 >> o & 1) && popc64(S & m1) >= c1 ? S & m1 : 0ull;
+    for (int l = first[o]; l >= 0;) {
+      const SetNode n = node[l];
+      if (popc64(S & n.mask) >= n.cap) return S & n.mask;
+      l = n.up;
+    }
+    return 0;
+  }
+};
+__host__ __device__ __forceinline__ size_t set_tree_bytes(int L, int M) {
+  return (((size_t)L * sizeof(SetNode) + 15) & ~(size_t)15) + (((size_t)M * 2 + 15) & ~(size_t)15);
+}
+// Copy T into mem (set_tree_bytes of LDS); the block synchronises afterwards.
+__device__ __forceinline__ SetTree set_tree_load(void *mem, const TreeDev &T, int M, int tid, int nthreads) {
+  SetNode *n = (SetNode *)mem;
+  int16_t *f = (int16_t *)((unsigned char *)mem + (((size_t)T.L * sizeof(SetNode) + 15) & ~(size_t)15));
+  for (int l = tid; l < T.L; l += nthreads) { n[l].mask = T.mask[l]; n[l].cap = T.cap[l]; n[l].up = T.up[l]; }
+  for (int j = tid; j < M; j += nthreads) f[j] = T.first[j];
+  SetTree t;
+  t.node = n;
+  t.first = f;
+  t.L = T.L;
+  t.c1 = T.L == 1 ? T.cap[0] : 0;
+  t.m1 = T.L == 1 ? T.mask[0] : 0ull;
+  return t;
+}
+
 // Laminar-matroid greedy over the ranked items: accept an eligible item when
 // no node containing it is full.  Equivalent to Alg.1 (both return the unique
 // maximum-weight independent set under the strict order (p~ desc, j asc)).
+__device__ __forceinline__ uint64_t greedy_mask(const uint8_t *perm, int M, uint64_t eligible,
+                                                const SetTree &T) {
+  uint64_t S = 0, blocked = 0;
+  for (int r = 0; r < M && (eligible & ~blocked); ++r) {
+    const int j = perm[r];
+    const uint64_t bit = 1ull << j;
+    if ((eligible & ~blocked) & bit) {
+      S |= bit;
+      eligible &= ~bit;
+      for (int l = T.first[j]; l >= 0;) {
+        const SetNode n = T.node[l];
+        if (popc64(S & n.mask) >= n.cap) blocked |= n.mask;
+        l = n.up;
+      }
+    }
+  }
+  return S;
+}
+
+// The same from the kernel's arguments (evaluations: no chains in LDS).
 __device__ __forceinline__ uint64_t greedy_mask(const uint8_t *perm, int M, uint64_t eligible,
                                                 const TreeDev &T) {
   uint64_t S = 0, blocked = 0;
@@ -154,7 +217,6 @@ __device__ __forceinline__ uint64_t greedy_mask(const uint8_t *perm, int M, uint
   }
   return S;
 }
-
 
 // Bin or emit one breakpoint (v1, v2) of knapsack k according to its search
 // mode: the first pass bins every breakpoint into exponential buckets around
@@ -264,6 +326,28 @@ __device__ __forceinline__ void publish_block(const SweepArgs &a, int K, XSum *h
 // those magnitudes is decided the same way by both.
 #define KP_LINE_TOL 0x1p-44
 
+// No moving item of a (user, knapsack) pair is selected at lambda^t (S0 & A
+// empty): does none come in at or above tlo?  Items only rise as lambda_k
+// falls, so one that is below zero, or below the lowest member of its circuit
+// (all of them fixed lines), at tlo has no breakpoint above it.
+template <class ZV, class BV>
+__device__ __forceinline__ bool pair_idle(const SetTree &T, uint64_t A, uint64_t S0, ZV zv, BV bv, double lk, double tlo) {
+  const double d = tlo - lk, mt = lk + tlo;
+  for (uint64_t m = A; m; m &= m - 1) {
+    const int o = __ffsll((long long)m) - 1;
+    const double zo = zv(o), bo = bv(o), so = d * bo;
+    const double vo = zo - so, to = KP_LINE_TOL * (fabs(zo) + mt * bo);
+    if (vo < -to) continue;
+    uint64_t circ = T.circuit(S0, o);
+    if (!circ) return false;
+    for (; circ; circ &= circ - 1) {
+      const double zs = zv(__ffsll((long long)circ) - 1);
+      if (!(zs - vo > to + KP_LINE_TOL * fabs(zs))) return false;
+    }
+  }
+  return true;
+}
+
 // One (user, knapsack) pair of a breakpoint phase: its breakpoints in
 // [ks.tlo, ks.thi], from the top.
 //
@@ -282,25 +366,20 @@ __device__ __forceinline__ void publish_block(const SweepArgs &a, int K, XSum *h
 // lines: such a pair is walked from the top.  (Walking every pair from the
 // top in every pass cost 3-4.5 ms a pass of 3e5 users with M = 23, K = 12.)
 //
+// The two parts are separate functions because most pairs end with the first:
+// a wave whose lanes all take the second costs a fraction of one where a few
+// lanes do.
+//
 // A: the items moving with k, zv(j): p~_j, bv(j): item j's cost in k (0
 // outside A), rk(r): the item of rank r by (p~ desc, index asc), pos: the
-// items with p~ > 0; emit(v1, v2) takes a breakpoint in the range.  *above:
-// a window's consumption just above thi.  Returns false when the walk runs
-// past its event limit.
-template <class ZV, class BV, class RK, class EM>
-__device__ __forceinline__ bool walk_pair(int M, int L, const uint64_t *tmask, const int *tcap, uint64_t A,
-                                          uint64_t S0, uint64_t pos, ZV zv, BV bv, RK rk, double lk,
-                                          const KWalk &ks, EM emit, double *above_out) {
+// items with p~ > 0.  Returns 0 when no breakpoint lies in the range (*above:
+// a window's consumption just above thi), else the start of the walk: 1 with
+// *So the greedy set at thi, 2 with *So the set T above every breakpoint.
+template <class ZV, class BV, class RK>
+__device__ __forceinline__ int pair_start(const SetTree &tr, uint64_t A, uint64_t S0, uint64_t pos, ZV zv, BV bv, RK rk, double lk,
+                                          const KWalk &ks, uint64_t *So, double *above_out) {
   const bool window = ks.mode == KS_WINDOW;
   const double tlo = ks.tlo, thi = ks.thi;
-  // the members of S in the innermost full set that holds o (0: none is full)
-  auto circuit = [&](uint64_t S, int o) -> uint64_t {
-    for (int l = 0; l < L; ++l) {
-      const uint64_t m = tmask[l];
-      if ((m >> o & 1) && popc64(S & m) >= tcap[l]) return S & m;
-    }
-    return 0;
-  };
   uint64_t T = S0 & ~A;
   {
     // every moving member gone lets at most one fixed item in
@@ -310,7 +389,7 @@ __device__ __forceinline__ bool walk_pair(int M, int L, const uint64_t *tmask, c
       const int j = rk(r);
       if (!(cand >> j & 1)) continue;
       cand &= ~(1ull << j);
-      if (!circuit(T, j)) { T |= 1ull << j; --left; }
+      if (!tr.circuit(T, j)) { T |= 1ull << j; --left; }
     }
   }
   uint64_t S = T;
@@ -327,7 +406,7 @@ __device__ __forceinline__ bool walk_pair(int M, int L, const uint64_t *tmask, c
       const double vo = zo - so, to = KP_LINE_TOL * (fabs(zo) + mt * bo);
       if (vo < -to) continue;
       if (!(vo > to)) { at = false; break; }
-      const uint64_t circ = circuit(S, o);
+      const uint64_t circ = tr.circuit(S, o);
       if (!circ) { S |= 1ull << o; continue; }
       if (circ != cc) {
         cc = circ;
@@ -359,8 +438,8 @@ __device__ __forceinline__ bool walk_pair(int M, int L, const uint64_t *tmask, c
     }
     if (!at) S = T;
   }
-  double above = 0.0;
   if (at) {
+    double above = 0.0;
     if (window)
       for (uint64_t m = S & A; m; m &= m - 1) above = above + bv(__ffsll((long long)m) - 1);
     // does any moving item outside S come in at or above tlo?
@@ -373,7 +452,7 @@ __device__ __forceinline__ bool walk_pair(int M, int L, const uint64_t *tmask, c
       const double zo = zv(o), bo = bv(o), so = d * bo;
       const double vo = zo - so, to = KP_LINE_TOL * (fabs(zo) + mt * bo);
       if (vo < -to) continue;
-      const uint64_t circ = circuit(S, o);
+      const uint64_t circ = tr.circuit(S, o);
       if (!circ) { quiet = false; break; }
       if (circ != cc) {
         cc = circ;
@@ -395,8 +474,24 @@ __device__ __forceinline__ bool walk_pair(int M, int L, const uint64_t *tmask, c
         if (!(zs - ss - vo > to + KP_LINE_TOL * (fabs(zs) + mt * bs))) { quiet = false; break; }
       }
     }
-    if (quiet) { *above_out = above; return true; }
+    if (quiet) { *above_out = above; return 0; }
   }
+  *So = S;
+  return at ? 1 : 2;
+}
+
+// The walk of a pair from the set S (at: the greedy set at thi, else the one
+// above every breakpoint) down to tlo; emit(v1, v2) takes a breakpoint in the
+// range.  *above: a window's consumption just above thi.  Returns false when
+// the walk runs past its event limit.
+template <class ZV, class BV, class EM>
+__device__ __forceinline__ bool pair_walk(int M, const SetTree &tr, uint64_t A, uint64_t S, bool at, ZV zv, BV bv, double lk, const KWalk &ks, EM emit,
+                                          double *above_out) {
+  const bool window = ks.mode == KS_WINDOW;
+  const double tlo = ks.tlo, thi = ks.thi;
+  double above = 0.0;
+  if (at && window)
+    for (uint64_t m = S & A; m; m &= m - 1) above = above + bv(__ffsll((long long)m) - 1);
   const int maxev = M * M + M + 8;
   for (int ev = 0;; ++ev) {
     if (ev >= maxev) return false;
@@ -407,7 +502,7 @@ __device__ __forceinline__ bool walk_pair(int M, int L, const uint64_t *tmask, c
       const double bo_d = bv(o);
       const double add_o = lk * bo_d;
       const double co = zv(o) + add_o;
-      uint64_t circ = circuit(S, o);
+      uint64_t circ = tr.circuit(S, o);
       // compared with the running maximum through cr_gt: a division only
       // for a crossing that beats it
       if (!circ) {

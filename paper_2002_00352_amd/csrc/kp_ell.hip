@@ -21,7 +21,7 @@ static size_t ell_lds(int M, int K, int D, int L, int mode, int waves, int *regi
   }
   region = r16(region);
   const int ew = waves;
-  size_t s = r16((size_t)(K + 1) * 8) + r16((size_t)L * 8 + 8) + r16((size_t)L * 4 + 4) +
+  size_t s = r16((size_t)(K + 1) * 8) + (brk ? r16(set_tree_bytes(L, M)) : 0) +
              r16((size_t)ew * (K + 2) * 8);
   if (mode != KM_EVAL && mode != KM_FIX) s += r16((size_t)K * 4) + r16((size_t)K * 8 + 16);
   if (mode == KM_WMAIN) s += r16((size_t)(K + 1) * sizeof(LamW));

@@ -104,31 +104,36 @@ struct EllGeom {
 };
 
 // One (user, knapsack) pair of a lane-per-user breakpoint phase, run by
-// any lane of the wave for the user of lane col (walk_pair).  Breakpoints in
+// any lane of the wave for the user of lane col (pair_start, pair_walk).  Breakpoints in
 // the pass's range are emitted (other search modes: binned or emitted by
 // record_event), and in a window pass C_ik(whi+) - v_ik goes into the window
 // correction.  A: the items moving with k; bkc(j, c): the cost in k of item
 // j of lane c's user (j in A); ptl: the lanes' p~ columns [M][64]; Sc, posc,
 // permc: the user's greedy set, positive items and rank order.
 template <class BKC>
-__device__ __forceinline__ void lane_walk_pair(const SweepArgs &a, int M, int L, int col, int k, uint64_t A,
+__device__ __forceinline__ void lane_walk_pair(const SweepArgs &a, int M, int col, int k, uint64_t A,
                                                uint64_t Sc, uint64_t posc, uint64_t permc, BKC bkc,
                                                const double *ptl, const double *lam, const KWalk *kst,
-                                               const int *kmode, const uint64_t *tmask, const int *tcap,
+                                               const int *kmode, const SetTree &tr,
                                                XSum *kcorr, XSum *hs, uint32_t *hc, unsigned long long *hmin,
                                                unsigned long long *hmax, uint32_t *kcnt, uint32_t *kovf,
                                                uint32_t *nstage) {
   const int mode = kmode[k];
   double above = 0.0;
-  const bool ok = walk_pair(
-      M, L, tmask, tcap, A, Sc, posc, [&](int j) -> double { return ptl[j * 64 + col]; },
-      [&](int j) -> double { return (A >> j & 1) ? bkc(j, col) : 0.0; },
-      [&](int r) -> int { return (int)((permc >> (4 * r)) & 15); }, lam[k], kst[k],
-      [&](double v1, double v2) {
-        record_event(a, kst[k], k, v1, v2, mode, hs, hc, hmin, hmax, kcnt, kovf, nstage, blockIdx.x);
-      },
-      &above);
-  if (!ok) atomicAdd(a.err, 1ull);
+  uint64_t Sw = 0;
+  auto zv = [&](int j) -> double { return ptl[j * 64 + col]; };
+  auto bv = [&](int j) -> double { return (A >> j & 1) ? bkc(j, col) : 0.0; };
+  const int st = pair_start(tr, A, Sc, posc, zv, bv,
+                            [&](int r) -> int { return (int)((permc >> (4 * r)) & 15); }, lam[k], kst[k], &Sw, &above);
+  if (st) {
+    const bool ok = pair_walk(M, tr, A, Sw, st == 1, zv, bv, lam[k], kst[k],
+                              [&](double v1, double v2) {
+                                record_event(a, kst[k], k, v1, v2, mode, hs, hc, hmin, hmax, kcnt, kovf, nstage,
+                                             blockIdx.x);
+                              },
+                              &above);
+    if (!ok) atomicAdd(a.err, 1ull);
+  }
   if (mode == KS_WINDOW) {
     double now = 0.0;
     for (uint64_t m = Sc & A; m; m &= m - 1) now = now + bkc(__ffsll((long long)m) - 1, col);
@@ -179,15 +184,16 @@ __device__ __forceinline__ void lane_deal_pairs(int lane, uint64_t pending, uint
 
 // Breakpoint phase of one user (one lane) from its per-lane LDS scratch:
 // p~ (ptl), stored costs (btl) and their knapsacks (ktl), and the items
-// moving with each knapsack (mskl).  S is the greedy set at lambda^t, pos the
+// moving with each knapsack (mskl).  pend: the knapsacks that may have a
+// breakpoint of this user in the pass's range.  S is the greedy set at lambda^t, pos the
 // items with p~ > 0, perm the items ranked by (p~ desc, index asc).
 template <int D>
-__device__ __forceinline__ void scd_user(const SweepArgs &a, int M, int K, int L, int lane, bool act,
-                                         int alg5q, int64_t uidx,
+__device__ __forceinline__ void scd_user(const SweepArgs &a, int M, int K, int lane, bool act,
+                                         int alg5q, int64_t uidx, uint64_t pend,
                                          uint64_t S, uint64_t pos, uint64_t perm, double bmax,
                                          const double *ptl, const float *btl, const uint8_t *ktl,
-                                         const uint16_t *mskl, const double *lam, const uint64_t *tmask,
-                                         const int *tcap, const KWalk *kst, const int *kmode,
+                                         const uint16_t *mskl, const double *lam, const SetTree &tr,
+                                         const KWalk *kst, const int *kmode,
                                          const double *hwin, XSum *kcorr, XSum *hs, uint32_t *hc,
                                          unsigned long long *hmin, unsigned long long *hmax,
                                          uint32_t *kcnt, uint32_t *kovf, uint32_t *nstage) {
@@ -240,52 +246,6 @@ __device__ __forceinline__ void scd_user(const SweepArgs &a, int M, int K, int L
     }
     return true;
   };
-  // threshold element of every item against the greedy solution of the other
-  // items (valid when it is the only item that moves with lambda_k): the
-  // lowest member of the innermost full set holding a non-member, or for a
-  // member the best positive non-member whose innermost full set holds it;
-  // zlev marks items whose only competitor is zero
-  uint64_t tau = 0, zlev = 0;
-  {
-    uint64_t assigned = S;
-    for (int l = 0; l < L; ++l) {
-      const uint64_t m = tmask[l];
-      if (popc64(S & m) < tcap[l]) continue;
-      uint64_t pend = m & ~assigned;
-      if (!pend) continue;
-      int low = 0;
-      for (int r = M - 1; r >= 0; --r) {
-        const int j = (int)((perm >> (4 * r)) & 15);
-        if ((S & m) >> j & 1) { low = j; break; }
-      }
-      assigned |= pend;
-      while (pend) {
-        const int o = __ffsll((long long)pend) - 1;
-        pend &= pend - 1;
-        tau |= (uint64_t)low << (4 * o);
-      }
-    }
-    const uint64_t all = (M == 64) ? ~0ull : ((1ull << M) - 1);
-    zlev |= ~assigned & all;
-    uint64_t resolved = 0;
-    for (int r = 0; r < M && resolved != S; ++r) {
-      const int e = (int)((perm >> (4 * r)) & 15);
-      if ((S >> e & 1) || !(pos >> e & 1)) continue;
-      uint64_t lm = 0;
-      for (int l = 0; l < L; ++l) {
-        const uint64_t m = tmask[l];
-        if ((m >> e & 1) && popc64(S & m) >= tcap[l]) { lm = m; break; }
-      }
-      uint64_t nw = S & lm & ~resolved;
-      resolved |= nw;
-      while (nw) {
-        const int o = __ffsll((long long)nw) - 1;
-        nw &= nw - 1;
-        tau |= (uint64_t)e << (4 * o);
-      }
-    }
-    zlev |= S & ~resolved;
-  }
   // Alg.5 (Sec. 5.1; a user whose item j consumes only knapsack j, M = K,
   // one top-Q set): the Q-th and (Q+1)-th largest adjusted profits
   // max(p~, 0) are read off the rank order Alg.1 already holds (0 past the
@@ -297,45 +257,24 @@ __device__ __forceinline__ void scd_user(const SweepArgs &a, int M, int K, int L
     if (alg5q <= M) qth = fmax(ptl[(int)((perm >> (4 * (alg5q - 1))) & 15) * 64 + lane], 0.0);
     if (alg5q + 1 <= M) q1th = fmax(ptl[(int)((perm >> (4 * alg5q)) & 15) * 64 + lane], 0.0);
   }
-  // one breakpoint per (item, knapsack) that moves alone; queue the others
-  uint64_t pending = 0;
-  for (int j = 0; act && j < M; ++j) {
-    for (int t = 0; t < D; ++t) {
-      const int k = ktl[(j * D + t) * 64 + lane];
-      if (k >= K) continue;
+  // Alg.5: one breakpoint per item and its knapsack
+  uint64_t pending = act ? pend : 0;
+  if (alg5q > 0) {
+    for (int j = 0; act && j < M; ++j) {
+      const int k = j;
       const int mode = kmode[k];
-      if (!walk_mode(mode)) continue;
-      const uint32_t A = mskl[k * 64 + lane];
-      if (A != (1u << j)) {
-        if (j == __ffs((int)A) - 1 && !(hwin[k] > 0.0 && calm(k, A))) pending |= 1ull << k;
-        continue;
-      }
-      if (hwin[k] > 0.0 && calm(k, A)) continue;
-      const double lk = lam[k];
-      const double bo_d = (double)btl[(j * D + t) * 64 + lane];
-      const double add_o = lk * bo_d;
-      const double co = ptl[j * 64 + lane] + add_o;
+      const double bo_d = (double)btl[j * 64 + lane];
+      if (!walk_mode(mode) || !(bo_d > 0.0)) continue;
+      if (hwin[k] > 0.0 && calm(k, 1u << j)) continue;
       double best = 0.0;
-      if (alg5q > 0) {
-        const double pk = (double)a.pr.p[uidx * M + j];
-        const double adj = fmax(ptl[j * 64 + lane], 0.0);
-        const double pbar = adj >= qth ? q1th : qth;
-        if (pk > pbar && bo_d > 0.0) {
-          const double num = pk - pbar;
-          best = num / bo_d;
-        }
-      } else {
-        // the threshold element is a fixed line (or zero): (co - cs) / bo_d
-        double num = co;
-        if (!(zlev >> j & 1)) num = co - ptl[(int)((tau >> (4 * j)) & 15) * 64 + lane];
-        // divided only where the quotient can lie in the pass's range: below
-        // it nothing is emitted, above it a window counts it as above
-        if (num > 0.0 && num >= kst[k].tlo * bo_d * (1.0 - 0x1p-40)) {
-          if (mode == KS_WINDOW && num > kst[k].thi * bo_d * (1.0 + 0x1p-40)) best = INFINITY;
-          else best = num / bo_d;
-        }
+      const double pk = (double)a.pr.p[uidx * M + j];
+      const double adj = fmax(ptl[j * 64 + lane], 0.0);
+      const double pbar = adj >= qth ? q1th : qth;
+      if (pk > pbar) {
+        const double num = pk - pbar;
+        best = num / bo_d;
       }
-      if (best > 0.0 && best < INFINITY)
+      if (best > 0.0)
         record_event(a, kst[k], k, best, bo_d, mode, hs, hc, hmin, hmax, kcnt, kovf, nstage, blockIdx.x);
       if (mode == KS_WINDOW) {
         // consumption just above the window against the one at lambda^t
@@ -344,15 +283,21 @@ __device__ __forceinline__ void scd_user(const SweepArgs &a, int M, int K, int L
         if (above != now) xs_atomic_add(&kcorr[k], above - now);
       }
     }
+    pending = 0;
   }
-  // Knapsacks moving several items of a user: dealt over the wave (see
+  // pairs that are calm in their window need no walk
+  for (uint64_t m = pending; m; m &= m - 1) {
+    const int k = __ffsll((long long)m) - 1;
+    if (hwin[k] > 0.0 && calm(k, (uint32_t)mskl[k * 64 + lane])) pending &= ~(1ull << k);
+  }
+  // The other pairs that may have a breakpoint: dealt over the wave (see
   // lane_deal_pairs) and walked through the owner's LDS column
   __builtin_amdgcn_s_waitcnt(0);   // every lane's scratch column is written before any lane reads another's
   __builtin_amdgcn_wave_barrier();
   __asm__ volatile("" ::: "memory");
   lane_deal_pairs(lane, pending, S, pos, perm, [&](int col, int k, uint64_t So, uint64_t poso, uint64_t permo) {
-    lane_walk_pair(a, M, L, col, k, (uint64_t)mskl[k * 64 + col], So, poso, permo,
-                   [&](int j, int c) { return bkc(j, k, c); }, ptl, lam, kst, kmode, tmask, tcap, kcorr, hs, hc,
+    lane_walk_pair(a, M, col, k, (uint64_t)mskl[k * 64 + col], So, poso, permo,
+                   [&](int j, int c) { return bkc(j, k, c); }, ptl, lam, kst, kmode, tr, kcorr, hs, hc,
                    hmin, hmax, kcnt, kovf, nstage);
   });
 }
@@ -407,8 +352,8 @@ k_ell(const SweepArgs a, const EllGeom g) {
   size_t off = 0;
   auto carve = [&](size_t bytes) { unsigned char *p = smem + off; off += (bytes + 15) & ~(size_t)15; return p; };
   double *lam = (double *)carve((size_t)(K + 1) * 8);   // [K] = 0 for the clamped reads
-  uint64_t *tmask = (uint64_t *)carve((size_t)a.tree.L * 8 + 8);
-  int *tcap = (int *)carve((size_t)a.tree.L * 4 + 4);
+  SetTree tr;
+  if (BREAK) tr = set_tree_load(carve(set_tree_bytes(a.tree.L, M)), a.tree, M, tid, ENT);
   double *wacc = (double *)carve((size_t)EWM * (K + 2) * 8);
   KWalk *kst = BREAK ? (KWalk *)carve((size_t)K * sizeof(KWalk)) : nullptr;
   XSum *hs = nullptr;
@@ -456,7 +401,6 @@ k_ell(const SweepArgs a, const EllGeom g) {
   unsigned char *wreg = smem + off + (size_t)wv * g.region;   // this wave's region
   for (int t = tid; t <= K; t += ENT) lam[t] = t < K ? a.lam[t] : 0.0;
   if (MODE == KM_WMAIN && tid == 0) lw[K] = LamW{0.0, 0.0f, 0.0f};
-  for (int t = tid; t < a.tree.L; t += ENT) { tmask[t] = a.tree.mask[t]; tcap[t] = a.tree.cap[t]; }
   for (int t = tid; t < EWM * (K + 2); t += ENT) wacc[t] = 0.0;
   if (!EV) {
     for (int t = tid; t < K; t += ENT) {
@@ -675,6 +619,7 @@ k_ell(const SweepArgs a, const EllGeom g) {
     // from the kernel arguments into scalar registers.
     uint64_t S = 0;
     uint32_t rbit[EM];   // 1 << rank (the rank itself is its lowest set bit)
+    double thr[BREAK ? EM : 1];
     {
       uint32_t alive = 0;
       #pragma unroll
@@ -699,6 +644,31 @@ k_ell(const SweepArgs a, const EllGeom g) {
       for (int j = 0; j < EM; ++j)
         if (alive & rbit[j]) S32 |= 1u << j;
       S = S32;
+      if (BREAK) {
+        // per item outside S: the value it has to pass to come in while the
+        // selected items stay (the lowest member of the innermost full set
+        // that holds it, or zero)
+        uint32_t set = 0;
+        #pragma unroll
+        for (int j = 0; j < EM; ++j) thr[j] = 0.0;
+        for (int l = 0; l < L; ++l) {
+          const uint32_t m = (uint32_t)a.tree.mask[l];
+          uint32_t mr = 0;
+          #pragma unroll
+          for (int j = 0; j < EM; ++j)
+            if (m >> j & 1u) mr |= rbit[j];
+          const uint32_t x = alive & mr;
+          if (__popc(x) < a.tree.cap[l]) continue;
+          const uint32_t low = 1u << (31 - __clz((int)x));
+          double zl = 0.0;
+          #pragma unroll
+          for (int j = 0; j < EM; ++j) zl = rbit[j] == low ? pt[j] : zl;
+          #pragma unroll
+          for (int j = 0; j < EM; ++j)
+            if ((m & ~set) >> j & 1u) thr[j] = zl;
+          set |= m;
+        }
+      }
     }
     double bmax = 0.0;
     if (!EV) {
@@ -939,6 +909,7 @@ k_ell(const SweepArgs a, const EllGeom g) {
       uint8_t *ktl = (uint8_t *)(wreg + sl.kt);
       uint16_t *mskl = (uint16_t *)(wreg + sl.msk);
       for (int k = 0; k < K; ++k) mskl[k * 64 + lane] = 0;
+      uint64_t pend = 0;
       #pragma unroll
       for (int j = 0; j < EM; ++j) {
         if (j < M) {
@@ -947,9 +918,18 @@ k_ell(const SweepArgs a, const EllGeom g) {
           for (int t = 0; t < D; ++t) {
             const int k = cl[j * D + t];
             const bool ok = (unsigned)k < (unsigned)K;
-            btl[(j * D + t) * 64 + lane] = vl[j * D + t];
+            const float v = vl[j * D + t];
+            btl[(j * D + t) * 64 + lane] = v;
             ktl[(j * D + t) * 64 + lane] = (uint8_t)(ok ? k : 255);
-            if (ok) mskl[k * 64 + lane] = (uint16_t)(mskl[k * 64 + lane] | (1u << j));
+            // a knapsack may have a breakpoint in the pass's range when one of
+            // its moving items is selected, or passes its threshold element
+            // at the range's lower end (items only rise as lambda_k falls)
+            if (ok && v > 0.0f && walk_mode(kmode[k])) {
+              const double d = kst[k].tlo - lam[k], b = (double)v, sh = d * b;
+              const double tol = KP_LINE_TOL * (fabs(pt[j]) + fabs(thr[j]) + (lam[k] + kst[k].tlo) * b);
+              if ((S >> j & 1) || !(pt[j] - sh < thr[j] - tol)) pend |= 1ull << k;
+            }
+            if (ok && v > 0.0f) mskl[k * 64 + lane] = (uint16_t)(mskl[k * 64 + lane] | (1u << j));
           }
         }
       }
@@ -959,8 +939,8 @@ k_ell(const SweepArgs a, const EllGeom g) {
       for (int j = 0; j < EM; ++j)
         if (j < M) diag = diag && cl[j * D] == j;
       const int64_t uidx = STAGED ? u0 + lane : (act ? (int64_t)a.flist[u0 + lane] : 0);
-      scd_user<D>(a, M, K, L, lane, act, diag ? a.alg5_q : 0, uidx, S, pos, perm, bmax, ptl, btl, ktl, mskl,
-                  lam, tmask, tcap, kst,
+      scd_user<D>(a, M, K, lane, act, diag ? a.alg5_q : 0, uidx, pend, S, pos, perm, bmax, ptl, btl, ktl, mskl,
+                  lam, tr, kst,
                   kmode, hwin, kcorr, hs, hc, hmin, hmax, kcnt, kovf, nstage);
       __builtin_amdgcn_s_waitcnt(0);
       __builtin_amdgcn_wave_barrier();

@@ -34,6 +34,8 @@ struct TreeDev {
   int pad;
   uint64_t mask[KP_MAX_NODES];
   int cap[KP_MAX_NODES];
+  int16_t up[KP_MAX_NODES];     // the smallest set that holds this one, or -1
+  int16_t first[KP_MAX_M];      // the smallest set that holds the item, or -1
 };
 
 struct TileGeom {

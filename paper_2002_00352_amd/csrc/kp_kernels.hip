@@ -222,6 +222,10 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a, const TileGeom &g
   int8_t *tau = (int8_t *)carve(SCD ? (size_t)U * 2 : 0); // per user: the threshold elements (at most one set)
   uint64_t *Am = (uint64_t *)carve(SCD && FMT == 1 ? (size_t)Q * 8 : 0);  // CSR: items with an entry, per (user, knapsack)
   double *vk = (double *)carve((size_t)Q * 8);            // per (user,k) consumption
+  uint16_t *wq = (uint16_t *)carve(SCD ? (size_t)Q * 2 : 0);  // (user,k) pairs left to walk
+  uint32_t *nwq = (uint32_t *)carve(SCD ? 16 : 0);            // [0] of them, [1] of those below
+  uint16_t *wq2 = (uint16_t *)carve(SCD ? (size_t)Q * 2 : 0); // ... with a breakpoint to find (bit 15: from the top)
+  uint64_t *wS = (uint64_t *)carve(SCD ? (size_t)Q * 8 : 0);  // ... and the set their walk starts with
   double *uPG = (double *)carve((size_t)U * 16);          // per user P_i, G_i
   double *acc = (double *)carve((size_t)(K + 2) * 8);     // block running sums
   double *lam = (double *)carve((size_t)K * 8);           // lambda^t staged once per block
@@ -255,6 +259,8 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a, const TileGeom &g
     hmax = (unsigned long long *)carve((size_t)K * 8);
     nstage = (uint32_t *)carve(16);
   }
+  SetTree tr;
+  if (SCD) tr = set_tree_load(carve(set_tree_bytes(a.tree.L, M)), a.tree, M, tid, NT);
   for (int t = tid; t < K + 2; t += NT) acc[t] = 0.0;
   for (int t = tid; t < K; t += NT) lam[t] = a.lam[t];
   if (SCD) {
@@ -371,6 +377,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a, const TileGeom &g
     // (set full) and [1] its best positive member left out
     const bool fastau = SCD && fastsel;
     if (fastau && tid < nu) { tau[2 * tid] = -1; tau[2 * tid + 1] = -1; }
+    if (SCD && tid == 0) { nwq[0] = 0u; nwq[1] = 0u; }
     // window filter, per user: [0] the smallest gap (a minimum over the
     // rows, taken on the bits of non-negative doubles), [1] the largest cost
     // (a maximum over the rows, on the bits of a non-negative float)
@@ -465,7 +472,10 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a, const TileGeom &g
       uint64_t pos = 0;
       #pragma unroll 4
       for (int j = 0; j < M; ++j) if (z[j] > 0.0) pos |= 1ull << j;
-      const uint64_t S = fastsel ? Sm[u] : greedy_mask(perm + u * M, M, pos, a.tree);
+      uint64_t S;
+      if (fastsel) S = Sm[u];
+      else if (SCD) S = greedy_mask(perm + u * M, M, pos, tr);
+      else S = greedy_mask(perm + u * M, M, pos, a.tree);
       Sm[u] = S;
       Pm[u] = pos;
       // sums over the selected items in ascending index order
@@ -512,7 +522,11 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a, const TileGeom &g
       }
     }
     __syncthreads();
-    // ---- phase B2: one thread per (user, knapsack) ----
+    // ---- phase B2: one thread per (user, knapsack): its consumption, and
+    // whether it can have a breakpoint in the pass's range.  The pairs left
+    // are queued and walked by as many threads as there are pairs: without the
+    // queue every wave took the walk's time for the few of its lanes that
+    // needed one (pairs looked at: 11-26 % of them, walked: 3-12 %) ----
     for (int q = tid; q < nu * K; q += NT) {
       const int u = q / K, k = q - u * K;
       const uint64_t S0 = Sm[u];
@@ -616,46 +630,105 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a, const TileGeom &g
               }
             }
           }
-          if (walk) {
-            const KWalk &ks = kst[k];
-            double above = 0.0;   // window: the consumption just above it
-            if (fastau && (A & (A - 1)) == 0) {
-              // one moving line: its only breakpoint is where it crosses its
-              // threshold element (a horizontal line) or the zero level: the
-              // lowest selected member when it is out, the best member left
-              // out when it is in (set full), else zero
-              const int o = __ffsll((long long)A) - 1;
-              const int th = (!(m1 >> o & 1) || tau[2 * u] < 0) ? -1 : (int)tau[2 * u + ((S0 >> o & 1) ? 1 : 0)];
-              const double bo_d = (double)bu[o * K + k];
-              const double add_o = lk * bo_d;
-              const double co = zu[o] + add_o;
-              const double num = th < 0 ? co : co - zu[th];
-              // divided only where the quotient can lie in the pass's range
-              if (num > 0.0 && num >= ks.tlo * bo_d * (1.0 - 0x1p-40)) {
-                const bool over = mode == KS_WINDOW && num > ks.thi * bo_d * (1.0 + 0x1p-40);
-                const double best = over ? INFINITY : num / bo_d;
-                if (mode == KS_WINDOW && best > ks.thi) above = bo_d;
-                else if (best >= ks.tlo) record_event(a, ks, k, best, bo_d, mode, hs, hc, hmin, hmax, kcnt, kovf, nstage, bid);
-              }
-            } else {
-              const bool ok = walk_pair(
-                  M, a.tree.L, a.tree.mask, a.tree.cap, A, S0, Pm[u], [&](int j) -> double { return zu[j]; },
-                  [&](int j) -> double { return (A >> j & 1) ? (double)bu[j * K + k] : 0.0; },
-                  [&](int r) -> int { return (int)perm[u * M + r]; }, lk, ks,
-                  [&](double v1, double v2) {
-                    record_event(a, ks, k, v1, v2, mode, hs, hc, hmin, hmax, kcnt, kovf, nstage, bid);
-                  },
-                  &above);
-              if (!ok) atomicAdd(a.err, 1ull);
-            }
-            if (mode == KS_WINDOW && above != v) {
-              xs_atomic_add_sum(&kxs[k], xs_minus(xs_of(above), xs_of(v)));
-            }
+          if (walk && (S0 & A) == 0 &&
+              pair_idle(tr, A, S0, [&](int j) -> double { return zu[j]; },
+                        [&](int j) -> double { return (double)bu[j * K + k]; }, lk, kst[k].tlo)) {
+            walk = false;   // (in a window its consumption stays 0)
           }
+          if (walk) wq[atomicAdd(nwq, 1u)] = (uint16_t)q;
         }
       }
     }
     __syncthreads();
+    if (SCD) {
+      const int nw = (int)nwq[0];
+      // (dealt over the waves in turn: a wave's time is its slowest lane's)
+      for (int i = (tid & 63) * (NT / 64) + (tid >> 6); i < nw; i += NT) {
+        const int q = wq[i];
+        const int u = q / K, k = q - u * K;
+        const int mode = kmode[k];
+        const KWalk &ks = kst[k];
+        const double lk = lam[k], v = vk[q];
+        const double *zu = pt + u * M;
+        const float *bu = bt + (size_t)u * M * K;
+        const uint64_t S0 = Sm[u];
+        uint64_t A = 0;
+        if (FMT == 1) {
+          A = Am[q];
+        } else {
+          #pragma unroll 4
+          for (int j = 0; j < M; ++j)
+            if (bu[j * K + k] > 0.0f) A |= 1ull << j;
+        }
+        double above = 0.0;   // window: the consumption just above it
+        if (fastau && (A & (A - 1)) == 0) {
+          // one moving line: its only breakpoint is where it crosses its
+          // threshold element (a horizontal line) or the zero level: the
+          // lowest selected member when it is out, the best member left
+          // out when it is in (set full), else zero
+          const int o = __ffsll((long long)A) - 1;
+          const int th = (!(m1 >> o & 1) || tau[2 * u] < 0) ? -1 : (int)tau[2 * u + ((S0 >> o & 1) ? 1 : 0)];
+          const double bo_d = (double)bu[o * K + k];
+          const double add_o = lk * bo_d;
+          const double co = zu[o] + add_o;
+          const double num = th < 0 ? co : co - zu[th];
+          // divided only where the quotient can lie in the pass's range
+          if (num > 0.0 && num >= ks.tlo * bo_d * (1.0 - 0x1p-40)) {
+            const bool over = mode == KS_WINDOW && num > ks.thi * bo_d * (1.0 + 0x1p-40);
+            const double best = over ? INFINITY : num / bo_d;
+            if (mode == KS_WINDOW && best > ks.thi) above = bo_d;
+            else if (best >= ks.tlo) record_event(a, ks, k, best, bo_d, mode, hs, hc, hmin, hmax, kcnt, kovf, nstage, bid);
+          }
+        } else {
+          uint64_t Sw = 0;
+          const int st = pair_start(
+              tr, A, S0, Pm[u], [&](int j) -> double { return zu[j]; },
+              [&](int j) -> double { return (A >> j & 1) ? (double)bu[j * K + k] : 0.0; },
+              [&](int r) -> int { return (int)perm[u * M + r]; }, lk, ks, &Sw, &above);
+          if (st) {
+            const uint32_t w = atomicAdd(&nwq[1], 1u);
+            wq2[w] = (uint16_t)(q | (st == 2 ? 0x8000 : 0));
+            wS[w] = Sw;
+            continue;
+          }
+        }
+        if (mode == KS_WINDOW && above != v) {
+          xs_atomic_add_sum(&kxs[k], xs_minus(xs_of(above), xs_of(v)));
+        }
+      }
+      __syncthreads();
+      const int nw2 = (int)nwq[1];
+      for (int i = (tid & 63) * (NT / 64) + (tid >> 6); i < nw2; i += NT) {
+        const int q = wq2[i] & 0x7FFF;
+        const int u = q / K, k = q - u * K;
+        const int mode = kmode[k];
+        const KWalk &ks = kst[k];
+        const double *zu = pt + u * M;
+        const float *bu = bt + (size_t)u * M * K;
+        uint64_t A = 0;
+        if (FMT == 1) {
+          A = Am[q];
+        } else {
+          #pragma unroll 4
+          for (int j = 0; j < M; ++j)
+            if (bu[j * K + k] > 0.0f) A |= 1ull << j;
+        }
+        double above = 0.0;
+        const bool ok = pair_walk(
+            M, tr, A, wS[i], !(wq2[i] & 0x8000),
+            [&](int j) -> double { return zu[j]; },
+            [&](int j) -> double { return (A >> j & 1) ? (double)bu[j * K + k] : 0.0; }, lam[k], ks,
+            [&](double v1, double v2) {
+              record_event(a, ks, k, v1, v2, mode, hs, hc, hmin, hmax, kcnt, kovf, nstage, bid);
+            },
+            &above);
+        if (!ok) atomicAdd(a.err, 1ull);
+        if (mode == KS_WINDOW && above != vk[q]) {
+          xs_atomic_add_sum(&kxs[k], xs_minus(xs_of(above), xs_of(vk[q])));
+        }
+      }
+      __syncthreads();
+    }
     // ---- fixed-order sums of the tile into the block accumulators ----
     if (a.want_stats) {
       for (int k = tid; k < K; k += NT) {
@@ -1605,14 +1678,16 @@ void kp_coldesc_fill(void *dst, const double *partials, const double *lam, const
 // ---------------------------------------------------------------------------
 // host-side launch helpers (called from the C ABI)
 // ---------------------------------------------------------------------------
-size_t kp_sweep_lds_bytes(int U, int M, int K, bool scd, int fmt, bool hist = true) {
+size_t kp_sweep_lds_bytes(int U, int M, int K, int L, bool scd, int fmt, bool hist = true) {
   auto r16 = [](size_t b) { return (b + 15) & ~(size_t)15; };
   const size_t R = (size_t)U * M, Q = (size_t)U * K;
   size_t s = r16(R * K * 4) + r16(R * 8) + r16(R) + r16((size_t)U * 8) * 2 + r16(Q * 8) +
              r16((size_t)U * 16) + r16((size_t)(K + 2) * 8);
   s += r16((size_t)K * 8);   // lambda
   s += r16(R * 4) + r16((R + 1) * 4) + r16(16);   // staged profits, row offsets, entry base
+  if (scd) s += set_tree_bytes(L, M);
   if (scd) s += r16((size_t)U * 2);                // threshold elements
+  if (scd) s += 2 * r16(Q * 2) + r16(16) + r16(Q * 8);  // pairs left to look at and to walk
   if (scd && fmt == 1) s += r16(Q * 8);            // moving items of every (user, knapsack)
   if (fmt == 1) s += 2 * r16((size_t)NT * ECH * 4);  // staged CSR entries
   if (scd)
@@ -1636,8 +1711,8 @@ int kp_sweep_batched_resident(size_t lds) {
 }
 
 // Blocks of the general sweep kernel that can be resident at once (0 if unknown).
-int kp_sweep_resident_grid(int U, int M, int K, bool scd, int fmt, bool hist = true) {
-  const size_t lds = kp_sweep_lds_bytes(U, M, K, scd, fmt, hist);
+int kp_sweep_resident_grid(int U, int M, int K, int L, bool scd, int fmt, bool hist = true) {
+  const size_t lds = kp_sweep_lds_bytes(U, M, K, L, scd, fmt, hist);
   const void *fn = sweep_fn(fmt, scd, M, K);
   if (lds > 64 * 1024 && hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
     return 0;
@@ -1657,7 +1732,7 @@ hipError_t kp_launch_sweep(const SweepArgs &a, int U, int grid, bool scd, hipStr
   g.K = a.pr.K;
   g.aligned = a.pr.fmt == 0 && ((uintptr_t)a.pr.b & 15) == 0 &&
               (((int64_t)U * g.M * g.K) & 3) == 0;
-  const size_t lds = kp_sweep_lds_bytes(U, g.M, g.K, scd, a.pr.fmt, !(scd && a.no_hist));
+  const size_t lds = kp_sweep_lds_bytes(U, g.M, g.K, a.tree.L, scd, a.pr.fmt, !(scd && a.no_hist));
   const void *fn = sweep_fn(a.pr.fmt, scd, g.M, g.K);
   if (lds > 64 * 1024) {
     // shapes with many knapsacks need more than the default 64 KB of LDS
