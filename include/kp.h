@@ -165,7 +165,7 @@ kp_status kp_dual_backward(void *ctx, const kp_problem *prob, const double *R,
    that are multiples of 2^-56 with totals below 2^38).  R_out = R(x(lambda))
    minus the removed consumption; primal_out likewise.  N < 2^32.
    Outputs (DEV): x_out [N*M] (may be NULL), primal_out [1], R_out [K],
-   n_reset_out [1] (int64).  Synchronises the context stream (three times). */
+   n_reset_out [1] (int64).  Synchronises the context stream (at least twice). */
 kp_status kp_primal_fixup(void *ctx, const kp_problem *prob, const double *lambda,
                           uint8_t *x_out, double *primal_out, double *R_out,
                           int64_t *n_reset_out);

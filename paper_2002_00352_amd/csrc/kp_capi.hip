@@ -1515,15 +1515,15 @@ kp_status kp_primal_fixup(void *ctx, const kp_problem *prob, const double *lambd
   HIP_TRY(hipMemcpyAsync(vkd, vk.data(), (size_t)nv * 4, hipMemcpyHostToDevice, c->stream));
   HIP_TRY(hipMemcpyAsync(Bvd, bv.data(), (size_t)nv * 8, hipMemcpyHostToDevice, c->stream));
   // blocks of the passes over users: a few per compute unit
-  const int64_t nch = (N + 4095) / 4096;
-  const int persist = (int)std::max<int64_t>(1, std::min<int64_t>(nch, 1024));
+  const int persist = 1024;
   // the per-user bin pass: the uniform-row kernel's evaluation with the bins
   // (LDS for the sums kept to 24 KB, next to its staged tiles) when it
   // applies, else a thread per user
   std::function<hipError_t(const FixBins &)> lean;
   int nb = kp_fixup_bins(nv, 40 * 1024);
-  if (P.ell_D) {
-    nb = kp_fixup_bins(nv, 24 * 1024);
+  const int nbl = kp_fixup_bins(nv, 24 * 1024);
+  if (P.ell_D && (size_t)nbl * nv * sizeof(XSum) <= 24 * 1024) {
+    nb = nbl;
     lean = [&](const FixBins &fb) -> hipError_t {
       SweepArgs a = make_args(P, lambda, w, nullptr, false);
       a.ntiles = P.ell_ntiles;

@@ -1391,3 +1391,43 @@ def test_stream_read_checksum(nbytes):
     acc = np.bitwise_xor.reduce(words, axis=0).astype(np.uint64)
     want = int(((acc[0] ^ acc[2]) << np.uint64(32)) | (acc[1] ^ acc[3]))
     assert got == want
+
+
+def _fixup_instance(kind):
+    """Instances whose post-processing takes the different ways to its
+    boundary: a list of at most 1024 users, lists cut again over several
+    levels, keys that are all equal (ordered by index), a heavy value among
+    distinct ones, and more violated knapsacks than the bins' sums fit."""
+    from util import make
+    rng = np.random.default_rng(len(kind))
+    N, M, K, Q = {"small": (700, 5, 3, 2), "levels": (140_001, 4, 2, 2), "equal": (5000, 4, 3, 2),
+                  "heavy": (9000, 4, 2, 1), "many-knapsacks": (600, 3, 900, 2)}[kind]
+    p = 0.5 + rng.integers(0, 1 << 20, (N, M)) / float(1 << 20)
+    b = rng.integers(1, 1 << 20, (N, M, K)) / float(1 << 20)
+    if kind == "equal":
+        p[:], b[:] = p[0], b[0]
+    if kind == "heavy":
+        p[N // 5:], b[N // 5:] = p[0], b[0]
+    B = 0.3 * b.sum(axis=(0, 1)) * Q / M
+    return make(p, b, B, kpgen.tree_topq(M, Q), name=kind)
+
+
+@gpu
+@pytest.mark.parametrize("kind", ["small", "levels", "equal", "heavy", "many-knapsacks"])
+def test_fixup_boundary_search(kind):
+    """The post-processing's search for the boundary of the reset prefix (bins,
+    lists cut again, the last users sorted): the reset set, the decisions and
+    the consumption equal the oracle's; the profit within 1e-9 (a sum of
+    at most 3e5 FP64 terms against an exact one)."""
+    kp, torch = _kp()
+    print("case fixup", kind, flush=True)
+    inst = _fixup_instance(kind)
+    prob = kp.Problem.from_host(inst)
+    lam = np.full(inst.K, 1e-4 / inst.K)
+    got = kp.kp_primal_fixup(prob, _lamd(torch, lam), want_x=True)
+    ref = oracle.fixup(inst, lam)
+    x = got["x"].cpu().numpy()
+    assert np.array_equal(x, ref["x"])
+    assert int(got["n_reset"].item()) == ref["n_reset"] > 0
+    assert np.allclose(got["R"].cpu().numpy(), ref["R"], rtol=1e-12, atol=0)
+    assert abs(got["P"].item() - ref["P"]) <= REL * abs(ref["P"])
