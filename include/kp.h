@@ -186,7 +186,7 @@ kp_status kp_scd_sweep_batched(void *ctx, const kp_problem *probs, int32_t n,
    lam_a into lam_b (dir 0) or from lam_b into lam_a (dir 1); stats as in
    kp_scd_sweep_batched (DEV, may be NULL).  With use_graph != 0 the
    iteration (init, sweep, statistics, threshold search, update) is captured
-   once per direction as a HIP graph and replayed: the first pass and five
+   once per direction as a HIP graph and replayed: the first pass and two
    later passes, each later pass splitting the blocks among the instances
    whose threshold is still open on the device (a pass with none open does
    no work; plans of more than 1706 instances capture the first pass

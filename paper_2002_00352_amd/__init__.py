@@ -394,7 +394,7 @@ def kp_scd_sweep_batched(probs: Sequence[Problem], lams_in, lams_out=None,
 
 class BatchedSCD:
     """Repeated SCD iterations over a batch of instances: device tables built
-    once, each iteration (its first pass and up to five later passes, split
+    once, each iteration (its first pass and up to two later passes, split
     among the open instances on the device) replayed from a captured HIP
     graph; a search still open after them continues from the host."""
 

@@ -32,8 +32,8 @@ hipError_t kp_launch_scd_init(KState *st, int K, const double *lam_in, const uin
 hipError_t kp_launch_scd_locate_select(KState *st, int K, const double *B, const double *R,
                                        const int *rinst, XSum *hist_sum, uint32_t *hist_cnt,
                                        const double *ev1, const double *ev2, uint32_t emit_cap,
-                                       const SelWs &w, int blocks, int *pending, unsigned int *win,
-                                       hipStream_t stream);
+                                       const SelWs &w, int blocks, int nohist, int *pending,
+                                       unsigned int *win, hipStream_t stream);
 hipError_t kp_launch_scd_select_many(KState *st, int K, const double *B, const double *ev1, const double *ev2,
                                      uint32_t emit_cap, const SelWs &w, int blocks, int *pending,
                                      unsigned int *win, hipStream_t stream);
@@ -132,10 +132,10 @@ constexpr int kMaxPasses = 96;
 constexpr uint32_t kStageCap = 4096;    // staged events per block per pass (at least)
 constexpr uint32_t kStageCapMax = 65536;
 constexpr uint32_t kEmitCapMin = 1u << 16, kEmitCapMax = 1u << 23;   // emitted events per knapsack
-constexpr int kGraphLaterPasses = 5;     // later passes captured with the first in a batched iteration's graph
+constexpr int kGraphLaterPasses = 2;     // later passes captured with the first in a batched iteration's graph
 constexpr uint32_t kEmitCapBatched = 1u << 16;   // emitted events per (instance, knapsack) per pass (at least)
 constexpr double kEmitBytesBatched = 8.0e9;        // bound on a batch's emission buffers
-constexpr size_t kBatchedLds = 40 * 1024;          // LDS per block of the batched launch (4 blocks per CU)
+constexpr size_t kBatchedLds = 48 * 1024;          // LDS per block of the batched launch (three per CU; 40 KB 14.1, 24 KB 19.2, 48 KB 13.6 ms for 32 instances)
 constexpr int kSelBlocks = 32;                     // blocks per knapsack that bin and compact more of them
 constexpr int kSelBlocksBatched = 4;
 constexpr int kMaxInputNodes = 4096;               // local-constraint nodes accepted in a problem
@@ -851,6 +851,7 @@ kp_status sample_phase(Ctx *c, const Prepared &P, const SweepWs &w, const double
   a.ntiles = P.samp_tiles;
   a.tstride = P.samp_stride;
   a.toff = P.samp_off;
+  HIP_TRY(hipMemsetAsync(w.sel.hsum, 0, w.sel_clear, c->stream));
   HIP_TRY(timed_sweep(c, a, P, true, P.bytes * P.frac));
   HIP_TRY(kp_launch_sample_window(w.st, P.pr.K, w.B, w.ev1, w.ev2, w.emit_cap, w.sel, kSelBlocks, c->stream));
   return KP_OK;
@@ -1062,7 +1063,6 @@ kp_status kp_scd_sweep_masked(void *ctx, const kp_problem *prob, const double *l
   }
   const bool nohist = !P.ell_D && !c->interp && P.pr.N > 0 && (P.frac >= 0.0 || (counts && c->pinned[21] == 0));
   HIP_TRY(hipMemsetAsync(w.stat, 0, w.stat_bytes, c->stream));   // status, histograms
-  if (sample) HIP_TRY(hipMemsetAsync(w.sel.hsum, 0, w.sel_clear, c->stream));
   if (searching && (s = sample_phase(c, P, w, lambda_in)) != KP_OK) return s;
   double *Rd = R ? R : w.Rtmp;
   double *gd = g ? g : w.gtmp;
@@ -1090,7 +1090,7 @@ kp_status kp_scd_sweep_masked(void *ctx, const kp_problem *prob, const double *l
       }
     }
     HIP_TRY(kp_launch_scd_locate_select(w.st, K, w.B, Rd, nullptr, w.hist_sum, w.hist_cnt, w.ev1, w.ev2,
-                                        w.emit_cap, w.sel, 0, w.pending, w.win, c->stream));
+                                        w.emit_cap, w.sel, 0, nohist && pass == 0 ? 1 : 0, w.pending, w.win, c->stream));
     // one copy of the status block: pending, walk-limit counter, window and
     // list counters
     int *st = c->pinned + 32;
@@ -1560,6 +1560,7 @@ struct BatchPlan {
   SweepArgs *sd[2] = {nullptr, nullptr};   // [dir] descriptors of the sampled pass
   int *sboff = nullptr;     // [n+1] its blocks
   int SB = 0;               // blocks of the sampled pass (0: no instance samples)
+  int nohist = 0;           // the passes on the device run without histograms
   uint64_t *eoff = nullptr; // [Kf] start of each knapsack's emission buffer
   uint32_t *ecap = nullptr; // [Kf] its capacity
   bool window = true;       // iterations start with a window where the last step allows
@@ -1687,7 +1688,7 @@ kp_status plan_later_passes_dev(BatchPlan *p, int dir, hipStream_t s) {
     r.reset = j == 0 ? 1 : 0;
     HIP_TRY(kp_launch_plan_resplit(r, s));
     if (p->T > 0) HIP_TRY(kp_launch_sweep_batched(p->rd, p->rg, p->rboff, p->n, p->gfix, p->lds, s, p->ctl));
-    HIP_TRY(kp_launch_scd_locate_select(p->kst, p->Kf, p->Bf, p->stats, p->kin, p->hs, p->hc, p->e1, p->e2, p->cap, p->sel, kSelBlocksBatched, p->pend,
+    HIP_TRY(kp_launch_scd_locate_select(p->kst, p->Kf, p->Bf, p->stats, p->kin, p->hs, p->hc, p->e1, p->e2, p->cap, p->sel, kSelBlocksBatched, p->nohist, p->pend,
                                       nullptr, s));
     HIP_TRY(kp_launch_batched_aux(2, nullptr, p->Kf, p->kst, p->lam_tab[1 - dir], p->kin, p->klo, p->hint, nullptr,
                                   nullptr, nullptr, s));
@@ -1708,7 +1709,7 @@ kp_status plan_first_pass(BatchPlan *p, int dir, hipStream_t s) {
   if (p->T > 0) HIP_TRY(kp_launch_sweep_batched(p->d[dir][1], p->geom, p->boff, p->n, p->GB, p->lds, s));
   HIP_TRY(kp_launch_batched_aux(0, p->coltab[dir], p->ncol, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
                                 nullptr, nullptr, s));
-  HIP_TRY(kp_launch_scd_locate_select(p->kst, p->Kf, p->Bf, p->stats, p->kin, p->hs, p->hc, p->e1, p->e2, p->cap, p->sel, kSelBlocksBatched, p->pend,
+  HIP_TRY(kp_launch_scd_locate_select(p->kst, p->Kf, p->Bf, p->stats, p->kin, p->hs, p->hc, p->e1, p->e2, p->cap, p->sel, kSelBlocksBatched, p->nohist, p->pend,
                                       nullptr, s));
   HIP_TRY(kp_launch_batched_aux(2, nullptr, p->Kf, p->kst, p->lam_tab[1 - dir], p->kin, p->klo, p->hint, nullptr,
                                 nullptr, nullptr, s));
@@ -1776,7 +1777,7 @@ kp_status plan_step(BatchPlan *p, int dir, double *stats_out, bool graph) {
       }
     }
     ++passes;
-    HIP_TRY(kp_launch_scd_locate_select(p->kst, p->Kf, p->Bf, p->stats, p->kin, p->hs, p->hc, p->e1, p->e2, p->cap, p->sel, kSelBlocksBatched, p->pend,
+    HIP_TRY(kp_launch_scd_locate_select(p->kst, p->Kf, p->Bf, p->stats, p->kin, p->hs, p->hc, p->e1, p->e2, p->cap, p->sel, kSelBlocksBatched, 0, p->pend,
                                       nullptr, s));
     HIP_TRY(kp_launch_batched_aux(2, nullptr, p->Kf, p->kst, p->lam_tab[1 - dir], p->kin, p->klo, p->hint, nullptr,
                                 nullptr, nullptr, s));
@@ -1846,29 +1847,42 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
   // needs, so instances with long rows take smaller tiles: the launch keeps
   // kBatchedBlocksPerCu blocks per compute unit for everyone
   const size_t lds_budget = c->bt_lds > 0 ? (size_t)c->bt_lds : kBatchedLds;
-  for (auto &q : P) {
-    int U = q.U;
-    while (U > 1 && kp_sweep_lds_bytes(U, q.pr.M, q.pr.K, q.tree.L, true, q.pr.fmt) > lds_budget) --U;
+  auto tile_users = [&](const Prepared &q, int U, bool hist) {
+    auto need = [&](int u) { return kp_sweep_lds_bytes(u, q.pr.M, q.pr.K, q.tree.L, true, q.pr.fmt, hist); };
+    while (U > 1 && need(U) > lds_budget) --U;
     while (U > 1 && q.pr.fmt == KP_B_DENSE && ((int64_t)U * q.pr.M * q.pr.K) % 4 != 0) --U;
-    if (U != q.U) {
-      q.U = U;
-      q.ntiles = (q.pr.N + U - 1) / U;
-    }
+    return U;
+  };
+  // Searches that start from a sample or emit everything bin nothing, so the
+  // passes on the device run without the histograms (20 of 40 KB at K = 16)
+  // and on larger tiles; a search that does fall back to the buckets waits
+  // for a pass from the host, on the tiles that leave room for them.
+  bool nohist = !lean;
+  for (auto &q : P) {
+    if (!lean) choose_start(q, c->sample_min, c->window_enabled, tile_users(q, q.U_nh, false));
+    nohist = nohist && q.frac >= 0.0;
   }
-  if (!lean)
-    for (auto &q : P) choose_start(q, c->sample_min, c->window_enabled, q.U);
+  std::vector<int> Uh(n);
+  for (int s = 0; s < n; ++s) {
+    Prepared &q = P[s];
+    Uh[s] = tile_users(q, q.U, true);
+    q.U = nohist ? tile_users(q, q.U_nh, false) : Uh[s];
+    if (!lean && !nohist) choose_start(q, c->sample_min, c->window_enabled, q.U);
+    q.ntiles = (q.pr.N + q.U - 1) / q.U;
+  }
+  auto hist_lds = [&](int s) { return kp_sweep_lds_bytes(Uh[s], P[s].pr.M, P[s].pr.K, P[s].tree.L, true, P[s].pr.fmt); };
   int64_t T = 0;
   int Kf = 0;
   for (auto &q : P) { T += q.ntiles; Kf += q.pr.K; }
   size_t lds = 0;
   for (int s = 0; s < n; ++s)
-    lds = std::max(lds, kp_sweep_lds_bytes(P[s].U, P[s].pr.M, P[s].pr.K, P[s].tree.L, true, P[s].pr.fmt));
+    lds = std::max(lds, kp_sweep_lds_bytes(P[s].U, P[s].pr.M, P[s].pr.K, P[s].tree.L, true, P[s].pr.fmt, !nohist));
   // blocks are split among the instances in proportion to their tiles; many
   // more blocks than can be resident at once keep the split fine-grained, and
   // the hardware dispatcher balances them (every instance gets at least one)
   int gmax = 32768;
   const int res = kp_sweep_batched_resident(lds);
-  if (res > 0) gmax = std::min(gmax, (c->bt_mult > 0 ? c->bt_mult : 64) * res);
+  if (res > 0) gmax = std::min(gmax, (c->bt_mult > 0 ? c->bt_mult : 16) * res);
   const int G = (int)std::max<int64_t>(n, std::min<int64_t>(T, gmax));
   // algorithmic bytes of one pass over every instance
   double bytes = 0.0;
@@ -1890,6 +1904,7 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
     poff[s + 1] = poff[s] + (size_t)b * (P[s].pr.K + 2);
   }
   if (lds > kMaxLds) { plan_free(p); return fail(KP_ERR_UNSUPPORTED, "an instance needs too much LDS"); }
+  p->nohist = nohist ? 1 : 0;
   p->T = T; p->Kf = Kf; p->GB = boff[n]; p->lds = lds; p->cap = kEmitCapBatched;
   p->Umin = P[0].U;
   p->Umax = P[0].U;
@@ -2050,12 +2065,14 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
   p->stage_total = stage_all;
   p->gmax = gmax;
   p->ntiles.resize(n);
+  std::vector<int64_t> dnt(n);
   p->pairs.resize(n);
   p->ilds.resize(n);
   for (int s = 0; s < n; ++s) {
-    p->ntiles[s] = P[s].ntiles;
+    p->ntiles[s] = (P[s].pr.N + Uh[s] - 1) / Uh[s];
+    dnt[s] = P[s].ntiles;
     p->pairs[s] = stage_pairs(P[s]);
-    p->ilds[s] = kp_sweep_lds_bytes(P[s].U, P[s].pr.M, P[s].pr.K, P[s].tree.L, true, P[s].pr.fmt);
+    p->ilds[s] = hist_lds(s);
   }
   std::vector<SweepArgs> hd[2][2], hsd[2];
   for (int d = 0; d < 2; ++d) hsd[d].resize(n);
@@ -2078,6 +2095,7 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
     a.pr = P[s].pr;
     a.tree = P[s].tree;
     a.ntiles = P[s].ntiles;
+    a.no_hist = nohist ? 1 : 0;
     a.tstride = 1;
     a.partials = (double *)(w + o_part) + poff[s];
     a.st = p->kst + koff[s];
@@ -2180,7 +2198,7 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
   if (e == hipSuccess) e = up(p->dhd[1], hd[1][0].data(), (size_t)n * sizeof(SweepArgs));
   if (e == hipSuccess) e = up(p->dhg, hg.data(), (size_t)n * sizeof(TileGeom));
   if (e == hipSuccess) e = up(p->dord, ord.data(), (size_t)n * 4);
-  if (e == hipSuccess) e = up(p->dnt, p->ntiles.data(), (size_t)n * 8);
+  if (e == hipSuccess) e = up(p->dnt, dnt.data(), (size_t)n * 8);
   if (e == hipSuccess) e = up(p->dpairs, p->pairs.data(), (size_t)n * 8);
   if (e == hipSuccess) e = hipMemsetAsync(p->ctl, 0, 16, st);
   if (e == hipSuccess) e = hipMemsetAsync(p->hs, 0, (size_t)Kf * KP_NB * sizeof(XSum), st);
@@ -2191,6 +2209,14 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
   if (e != hipSuccess) {
     plan_free(p);
     return fail(KP_ERR_HIP, "plan upload failed: %s", hipGetErrorString(e));
+  }
+  // (the host's later passes: the tiles with histograms)
+  for (int s = 0; s < n; ++s) {
+    for (int d = 0; d < 2; ++d) {
+      hd[d][0][s].no_hist = 0;
+      hd[d][0][s].ntiles = p->ntiles[s];
+    }
+    hg[s] = kp_tile_geom(hd[0][0][s], Uh[s]);
   }
   for (int d = 0; d < 2; ++d) p->hd[d] = hd[d][0];
   p->hg = hg;

@@ -392,34 +392,51 @@ auto dispatch_dense(int M, int K, F f) {
 // largest cost).  A user without one is settled by the window pass's gap
 // test whatever its windows (no line can turn positive in any of them); the
 // host runs the lane-per-user pass when almost every sampled user is such.
-__global__ void __launch_bounds__(64) k_dense_probe(const float *p, const float *b, const double *lam,
-                                                    const KState *st, int64_t N, int M, int K, int *out) {
-  const int64_t i = (int64_t)blockIdx.x * 64 + threadIdx.x;
-  if (i >= KP_PROBE_USERS) return;
+//
+// 16 lanes per user, one item each (M <= 16); the loads of a row do not
+// wait for each other (one thread per user took 25 us, its 110 loads in a
+// chain).
+__global__ void __launch_bounds__(256) k_dense_probe(const float *p, const float *b, const double *lam,
+                                                     const KState *st, int64_t N, int M, int K, int *out) {
+  __shared__ double hmax, sl[16];
+  const int t = threadIdx.x;
+  if (t < 64) {
+    double hm = t < K && st[t].mode == KS_WINDOW ? st[t].hw : 0.0;
+    for (int d = 8; d > 0; d >>= 1) hm = fmax(hm, __shfl_xor(hm, d, 64));
+    if (t == 0) hmax = hm;
+    if (t < K) sl[t] = lam[t];
+  }
+  __syncthreads();
+  const int64_t i = (int64_t)blockIdx.x * 16 + (t >> 4);
+  const int j = t & 15;
   const int64_t u = i * N / KP_PROBE_USERS;
-  double hm = 0.0;
-  for (int k = 0; k < K; ++k)
-    if (st[k].mode == KS_WINDOW) hm = fmax(hm, st[k].hw);
-  const float *pu = p + u * M;
-  const float *bu = b + u * M * K;
+  float c[16];
   float bm = 0.0f;
-  for (int e = 0; e < M * K; ++e) bm = fmaxf(bm, bu[e]);
-  const double H = hm * (double)bm * (1.0 + 0x1p-30) + 0x1p-36 * (1.0 + (double)bm * hm);
-  bool up = false;
-  for (int j = 0; j < M; ++j) {
-    double acc = (double)pu[j];
-    for (int k = 0; k < K; ++k) {
-      const double prod = lam[k] * (double)bu[j * K + k];
+  const int jj = j < M ? j : 0;
+  const float *br = b + (u * M + jj) * K;
+  #pragma unroll
+  for (int k = 0; k < 16; ++k) c[k] = br[k < K ? k : 0];
+  double acc = (double)p[u * M + jj];
+  #pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    if (k < K) {
+      bm = fmaxf(bm, c[k]);
+      const double prod = sl[k] * (double)c[k];
       acc = acc - prod;
     }
-    up = up || acc > -H;
   }
-  if (up) atomicAdd(out, 1);
+  for (int d = 8; d > 0; d >>= 1) bm = fmaxf(bm, __shfl_xor(bm, d, 64));   // over the user's 16 lanes
+  const double hm = hmax;
+  const double H = hm * (double)bm * (1.0 + 0x1p-30) + 0x1p-36 * (1.0 + (double)bm * hm);
+  const uint64_t up = __ballot(j < M && acc > -H);
+  const int mine = j == 0 && (up >> (t & 48) & 0xFFFFull) ? 1 : 0;
+  const int cnt = __syncthreads_count(mine);
+  if (t == 0 && cnt) atomicAdd(out, cnt);
 }
 
 hipError_t kp_launch_dense_probe(const SweepArgs &a, int *out, hipStream_t stream) {
   if (a.pr.fmt != 0 || a.pr.N <= 0 || !a.st) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_dense_probe, dim3(KP_PROBE_USERS / 64), dim3(64), 0, stream, a.pr.p, a.pr.b, a.lam, a.st,
+  hipLaunchKernelGGL(k_dense_probe, dim3(KP_PROBE_USERS / 16), dim3(256), 0, stream, a.pr.p, a.pr.b, a.lam, a.st,
                      (int64_t)a.pr.N, a.pr.M, a.pr.K, out);
   return hipGetLastError();
 }

@@ -278,7 +278,9 @@ __device__ __forceinline__ bool walk_mode(int m) {
 // that search a sample, the others the rest.
 __device__ __forceinline__ int pass_mode(const SweepArgs &a, int k) {
   const KState &s = a.st[k];
-  return ((s.flags & KS_FLAG_SAMPLE) != 0) == (a.sampled != 0) ? s.mode : (int)KS_DONE;
+  if (((s.flags & KS_FLAG_SAMPLE) != 0) != (a.sampled != 0)) return KS_DONE;
+  // (a pass without histograms leaves the searches that bin to another one)
+  return a.no_hist && (s.mode == KS_EXP || s.mode == KS_REFINE) ? (int)KS_DONE : s.mode;
 }
 
 // End of a sweep block: add its histograms to the global ones, reserve space

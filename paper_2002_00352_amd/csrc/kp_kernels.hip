@@ -222,17 +222,31 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a, const TileGeom &g
   int8_t *tau = (int8_t *)carve(SCD ? (size_t)U * 2 : 0); // per user: the threshold elements (at most one set)
   uint64_t *Am = (uint64_t *)carve(SCD && FMT == 1 ? (size_t)Q * 8 : 0);  // CSR: items with an entry, per (user, knapsack)
   double *vk = (double *)carve((size_t)Q * 8);            // per (user,k) consumption
-  uint16_t *wq = (uint16_t *)carve(SCD ? (size_t)Q * 2 : 0);  // (user,k) pairs left to walk
-  uint32_t *nwq = (uint32_t *)carve(SCD ? 16 : 0);            // [0] of them, [1] of those below
-  uint16_t *wq2 = (uint16_t *)carve(SCD ? (size_t)Q * 2 : 0); // ... with a breakpoint to find (bit 15: from the top)
-  uint64_t *wS = (uint64_t *)carve(SCD ? (size_t)Q * 8 : 0);  // ... and the set their walk starts with
+  uint32_t *nwq = (uint32_t *)carve(SCD ? 16 : 0);            // pairs left to look at, to walk
   double *uPG = (double *)carve((size_t)U * 16);          // per user P_i, G_i
   double *acc = (double *)carve((size_t)(K + 2) * 8);     // block running sums
   double *lam = (double *)carve((size_t)K * 8);           // lambda^t staged once per block
   float *pl = (float *)carve((size_t)R * 4);              // staged profits
   int32_t *rpl = (int32_t *)carve((size_t)(R + 1) * 4);   // CSR: row offsets relative to the tile
-  int32_t *ecl = (int32_t *)carve(FMT == 1 ? (size_t)NT * ECH * 4 : 0);  // CSR: staged entries
+  // CSR: staged entries (SCD: at most 64 knapsacks, a byte each; 255: malformed)
+  void *eclv = carve(FMT == 1 ? (size_t)NT * ECH * (SCD ? 1 : 4) : 0);
+  int32_t *ecl = (int32_t *)eclv;
+  uint8_t *ecb = (uint8_t *)eclv;
   float *evl = (float *)carve(FMT == 1 ? (size_t)NT * ECH * 4 : 0);
+  // the (user, knapsack) pairs left to look at, those with a breakpoint to
+  // find (bit 15: from the top) and the sets their walks start with; CSR: over
+  // the staged entries, which the scores have consumed by then
+  auto qcarve = [&](size_t bytes, size_t &at) {
+    if (FMT == 0) return carve(bytes);
+    unsigned char *p = (unsigned char *)evl + at;
+    at += (bytes + 15) & ~(size_t)15;
+    return p;
+  };
+  size_t qat = 0;
+  uint64_t *wS = (uint64_t *)qcarve(SCD ? (size_t)Q * 8 : 0, qat);
+  uint16_t *wq = (uint16_t *)qcarve(SCD ? (size_t)Q * 2 : 0, qat);
+  uint16_t *wq2 = (uint16_t *)qcarve(SCD ? (size_t)Q * 2 : 0, qat);
+  if (FMT == 1 && qat > (size_t)NT * ECH * 4) carve(qat - (size_t)NT * ECH * 4);   // (beyond them)
   int64_t *ebase = (int64_t *)carve(16);                  // CSR: first entry of the next tile
   KWalk *kst = SCD ? (KWalk *)carve((size_t)K * sizeof(KWalk)) : nullptr;
   XSum *hs = nullptr;
@@ -353,7 +367,11 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a, const TileGeom &g
       #pragma unroll
       for (int i = 0; i < ECH; ++i) {
         const int t = tid + i * NT;
-        if (t < n_ent && t < NT * ECH) { ecl[t] = f.ec[i]; evl[t] = f.ev[i]; }
+        if (t < n_ent && t < NT * ECH) {
+          if (SCD) ecb[t] = (uint8_t)((unsigned)f.ec[i] < 255u ? f.ec[i] : 255);
+          else ecl[t] = f.ec[i];
+          evl[t] = f.ev[i];
+        }
       }
       for (int t = tid; t < R * K; t += NT) bt[t] = 0.0f;
       if (SCD)
@@ -408,7 +426,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a, const TileGeom &g
         for (int e = e0; e < e1; ++e) {
           int k;
           float v;
-          if (e < NT * ECH) { k = ecl[e]; v = evl[e]; }
+          if (e < NT * ECH) { k = SCD ? (int)ecb[e] : ecl[e]; v = evl[e]; }
           else { k = a.pr.col[e_first + e]; v = a.pr.val[e_first + e]; }   // tile beyond the staging
           if ((unsigned)k >= (unsigned)K) continue;   // malformed column: ignored (kp_validate_inputs reports it)
           bt[(size_t)r * K + k] = v;
@@ -605,10 +623,6 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a, const TileGeom &g
           const double lk = lam[k];
           const double *zu = pt + u * M;
           bool walk = A != 0;
-          if (walk && !hist && (mode == KS_EXP || mode == KS_REFINE)) {
-            atomicAdd(a.err, 1ull);   // launched without the histograms these modes need
-            walk = false;
-          }
           if (walk && mode == KS_WINDOW) {
             // no breakpoint of this user inside the window: nothing to emit
             // and its consumption just above the window is v_ik (no correction)
@@ -1039,9 +1053,13 @@ size_t kp_sweep_lds_bytes(int U, int M, int K, int L, bool scd, int fmt, bool hi
   s += r16(R * 4) + r16((R + 1) * 4) + r16(16);   // staged profits, row offsets, entry base
   if (scd) s += set_tree_bytes(L, M);
   if (scd) s += r16((size_t)U * 2);                // threshold elements
-  if (scd) s += 2 * r16(Q * 2) + r16(16) + r16(Q * 8);  // pairs left to look at and to walk
+  if (scd) {
+    // pairs left to look at and to walk (CSR: over the staged entries)
+    const size_t q = 2 * r16(Q * 2) + r16(Q * 8), e = fmt == 1 ? (size_t)NT * ECH * 4 : 0;
+    s += r16(16) + (fmt == 0 ? q : q > e ? r16(q - e) : 0);
+  }
   if (scd && fmt == 1) s += r16(Q * 8);            // moving items of every (user, knapsack)
-  if (fmt == 1) s += 2 * r16((size_t)NT * ECH * 4);  // staged CSR entries
+  if (fmt == 1) s += r16((size_t)NT * ECH * (scd ? 1 : 4)) + r16((size_t)NT * ECH * 4);  // staged CSR entries
   if (scd)
     s += r16((size_t)K * sizeof(KWalk)) + (hist ? r16((size_t)K * KP_NB * sizeof(XSum)) + r16((size_t)K * KP_NB * 4) : 0) +
          4 * r16((size_t)K * 4) + 2 * r16((size_t)K * 8) + r16(16) +

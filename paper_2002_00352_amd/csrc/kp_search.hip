@@ -97,15 +97,17 @@ __global__ void k_scd_init(KState *st, int K, const double *lam_in, const uint8_
   // hist: [K] bucket widths and [K] last steps (valid when hinted_in), then
   // [K] lambda^{t-1} and [K] lambda^{t-2} (NaN while unknown), shifted here
   // once per iteration, and [K] the multipliers last returned
-  // A multiplier that the last call did not return (by more than its last
-  // step) starts a new trajectory: its windows would be stale.
-  const double *delta_hint = (hist && hinted_in && fabs(lam_in[k] - hist[4 * K + k]) <= hist[K + k]) ? hist : nullptr;
+  // A multiplier that the last call did not return (by more than 1/16 of
+  // its last step) starts a new trajectory: its windows and its past multipliers would
+  // be stale.
+  const bool same = hist && hinted_in && fabs(lam_in[k] - hist[4 * K + k]) <= 0.0625 * hist[K + k];
+  const double *delta_hint = same ? hist : nullptr;
   double d = delta_hint ? delta_hint[k] : 0.0;
   const bool hinted = d > 0.0;
   double prev = -1.0, drift = -1.0;
   if (hist) {
-    prev = hist[2 * K + k];
-    const double prev2 = hist[3 * K + k];
+    prev = same ? hist[2 * K + k] : NAN;
+    const double prev2 = same ? hist[3 * K + k] : NAN;
     drift = fabs(lam_in[k] - prev2);   // NaN while unknown
     hist[3 * K + k] = prev;
     hist[2 * K + k] = lam_in[k];
@@ -185,9 +187,12 @@ __device__ __forceinline__ XSum shfl_xs(const XSum &v, int src) {
 // bins through global memory took 5-16 us a pass, this 3-4.
 __global__ void __launch_bounds__(64) k_scd_locate(KState *st, int K, const double *B, const double *R,
                                                    const int *rinst, XSum *hist_sum, uint32_t *hist_cnt,
-                                                   uint32_t emit_cap, int *pending, unsigned int *win) {
+                                                   uint32_t emit_cap, int nohist, int *pending, unsigned int *win) {
   const int k = blockIdx.x, lane = threadIdx.x;
   if (k == 0 && lane == 0) { pending[0] = 0; pending[1] = 0; }   // counted again by the selection
+  if (st[k].mode == KS_DONE) return;
+  // (a pass without histograms left these searches out)
+  if (nohist && (st[k].mode == KS_EXP || st[k].mode == KS_REFINE)) return;
   KState s = st[k];
   if (s.ecap) emit_cap = s.ecap;   // batched: this knapsack's own buffer
   const double Bk = B[k];
@@ -815,13 +820,13 @@ __global__ void k_scd_init_flat(KState *st, int Kf, const double *const *lam_in,
   // a window from the multiplier's history (as the single-instance search);
   // the history columns shift once per iteration, here
   if (hint) {
-    const double prev = hint[2 * Kf + f];
-    const double drift = fabs(l - hint[3 * Kf + f]);
+    // (a multiplier that the last step did not return: no window, no past)
+    const bool same = hint[f] > 0.0 && fabs(l - hint[4 * Kf + f]) <= 0.0625 * hint[Kf + f];
+    const double prev = same ? hint[2 * Kf + f] : NAN;
+    const double drift = same ? fabs(l - hint[3 * Kf + f]) : NAN;
     hint[3 * Kf + f] = prev;
     hint[2 * Kf + f] = l;
-    // (a multiplier that the last step did not return: no window)
-    if (window && hint[f] > 0.0 && fabs(l - hint[4 * Kf + f]) <= hint[Kf + f])
-      choose_window(s, hint[Kf + f], prev, drift);
+    if (window && same) choose_window(s, hint[Kf + f], prev, drift);
   }
   s.frac = frac[f];
   if (s.mode == KS_EXP) search_start(s);
@@ -916,10 +921,10 @@ SelWs kp_sel_ws(void *mem, int K) {
 hipError_t kp_launch_scd_locate_select(KState *st, int K, const double *B, const double *R,
                                        const int *rinst, XSum *hist_sum, uint32_t *hist_cnt,
                                        const double *ev1, const double *ev2, uint32_t emit_cap,
-                                       const SelWs &w, int blocks, int *pending, unsigned int *win,
-                                       hipStream_t stream) {
+                                       const SelWs &w, int blocks, int nohist, int *pending,
+                                       unsigned int *win, hipStream_t stream) {
   hipLaunchKernelGGL(k_scd_locate, dim3(K), dim3(64), 0, stream, st, K, B, R, rinst, hist_sum,
-                     hist_cnt, emit_cap, pending, win);
+                     hist_cnt, emit_cap, nohist, pending, win);
   if (blocks > 0) {
     hipLaunchKernelGGL(k_sel_hist, dim3(K, blocks), dim3(SH_NT), 0, stream, st, ev1, ev2, emit_cap, w, 0);
     hipLaunchKernelGGL(k_sel_compact, dim3(K, blocks), dim3(SH_NT), 0, stream, st, B, ev1, ev2, emit_cap, w);
