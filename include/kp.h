@@ -74,7 +74,7 @@ typedef struct {
   const int32_t *leaf_of_item;/* HOST [M], innermost node containing item j, or -1 */
   int32_t b_row_nnz;          /* CSR only: 0 = general rows; D in {1, 2} = the caller declares that
                                  every item row holds exactly D stored entries, row r's at
-                                 [r*D, r*D + D) (rowptr[r] == r*D).  With M <= 16 the library then
+                                 [r*D, r*D + D) (rowptr[r] == r*D).  With M <= 20 (D = 2) or 24 (D = 1) the library then
                                  runs a lean per-user kernel that never reads b_rowptr.
                                  kp_csr_row_nnz finds D; kp_validate_inputs checks a declared D.
                                  A false declaration is undefined behaviour, like an unsorted row.
@@ -285,7 +285,7 @@ kp_status kp_get_launch_shape(void *ctx, int32_t *kernel, int32_t *users_per_til
 kp_status kp_set_batched_tuning(void *ctx, int32_t lds_bytes, int32_t block_mult);
 
 /* Kernel choice for CSR costs: a problem that declares b_row_nnz = D (every
-   item row holds D in {1, 2} entries at r*D) with M <= 16 runs the lean
+   item row holds D in {1, 2} entries at r*D) with M <= 20 (D = 2) or 24 (D = 1) runs the lean
    per-user kernel, which never reads b_rowptr; any other CSR problem runs
    the general kernel.  Evaluations (kp_eval_dual, kp_dd_step, the first
    pass of kp_primal_fixup) of dense costs with M <= 16 and K <= 16 run a

@@ -64,6 +64,7 @@ int kp_fixup_bins(int nv, size_t budget);
 size_t kp_fixup_scratch_bytes(int64_t N, int nv, int K);
 size_t kp_ell_lds_bytes(int M, int K, int D, int L, int mode, int *region_out);
 hipError_t kp_launch_ell(const SweepArgs &a, int D, int grid, int mode, hipStream_t stream, int *used);
+int kp_ell_max_items(int D);
 int kp_ell_resident_grid(int D, int mode, int M, int K, int L);
 hipError_t kp_launch_dense(const SweepArgs &a, int grid, hipStream_t stream, int *used, bool win);
 int kp_dense_tile_users();
@@ -174,7 +175,7 @@ struct Ctx {
   // batched plans created later: LDS per block and blocks per resident block
   // (0: built-in)
   int bt_lds = 0, bt_mult = 0;
-  std::map<std::tuple<int, int, int, int>, std::pair<int, int>> ell_grids;  // (D, M, K, L) -> resident grids
+  std::map<std::tuple<int, int, int, int>, std::pair<int, int>> ell_grids;  // (D, 2 M + SCD, K, L) -> resident grids
   std::map<std::tuple<int, int, int>, int> dense_grids;                     // (M, K, L) -> resident grid
   int64_t win_tried = 0, win_above = 0, win_below = 0;   // window searches since creation
   int64_t win_emitted = 0;                                 // breakpoints emitted inside windows
@@ -453,7 +454,7 @@ kp_status prepare(const kp_problem *p, bool scd, Prepared &out, const Ctx *ctx =
 constexpr int kEllGrid = 1024;
 
 // Decide whether the uniform-row CSR kernel applies: CSR declared with D in
-// {1, 2} entries per item row at r*D (b_row_nnz), M <= 16, and its LDS fits.
+// {1, 2} entries per item row at r*D (b_row_nnz), its item count and its LDS fit.
 kp_status choose_kernel(Ctx *c, Prepared &P, bool scd) {
   P.ell_D = 0;
   P.ell_grid = 0;
@@ -486,7 +487,9 @@ kp_status choose_kernel(Ctx *c, Prepared &P, bool scd) {
     }
     return KP_OK;
   }
-  if (!c->ell_enabled || P.pr.fmt != KP_B_CSR || P.pr.M > 16 || P.pr.N == 0 || P.row_nnz == 0) return KP_OK;
+  if (!c->ell_enabled || P.pr.fmt != KP_B_CSR || P.pr.N == 0 || P.row_nnz == 0 ||
+      P.pr.M > kp_ell_max_items(P.row_nnz))
+    return KP_OK;
   const int D = P.row_nnz;
   const int64_t nnz = P.pr.N * P.pr.M * (int64_t)D;
   if (kp_ell_lds_bytes(P.pr.M, P.pr.K, D, P.tree.L, scd ? 1 : 0, nullptr) > kMaxLds) return KP_OK;
@@ -496,13 +499,13 @@ kp_status choose_kernel(Ctx *c, Prepared &P, bool scd) {
   // modes; the staging of emitted events is sized for the smallest grid of
   // its breakpoint modes (those blocks each take a larger share of the users)
   int gmax = 0, gbrk = 0;
-  const auto gkey = std::make_tuple(D, (int)P.pr.M, (int)P.pr.K, (int)P.tree.L);
+  const auto gkey = std::make_tuple(D, (int)P.pr.M * 2 + (scd ? 1 : 0), (int)P.pr.K, (int)P.tree.L);
   auto git = c->ell_grids.find(gkey);
   if (git != c->ell_grids.end()) {
     gmax = git->second.first;
     gbrk = git->second.second;
   } else {
-    for (int mode = 0; mode < 4; ++mode) {
+    for (int mode = 0; mode < (scd ? 4 : 1); ++mode) {
       const int r = kp_ell_resident_grid(D, mode, P.pr.M, P.pr.K, P.tree.L);
       if (r <= 0) return fail(KP_ERR_HIP, "occupancy query failed");
       gmax = std::max(gmax, r);
@@ -510,7 +513,8 @@ kp_status choose_kernel(Ctx *c, Prepared &P, bool scd) {
     }
     c->ell_grids[gkey] = std::make_pair(gmax, gbrk);
   }
-  P.ell_grid = (int)std::max<int64_t>(1, std::min<int64_t>((P.ell_ntiles + 3) / 4, std::min(gmax, kEllGrid)));
+  const int tpb = P.pr.M > 16 ? 2 : 4;   // waves of most modes' blocks
+  P.ell_grid = (int)std::max<int64_t>(1, std::min<int64_t>((P.ell_ntiles + tpb - 1) / tpb, std::min(gmax, kEllGrid)));
   // a tuned grid for this shape (the kernel's users per tile are fixed: one
   // lane per user, 64 per wave); never above what can be resident
   auto tit = c->tuning.find(std::make_tuple((int)P.pr.M, (int)P.pr.K, (int)KP_B_CSR));
@@ -634,7 +638,7 @@ kp_status carve_ws(Ctx *c, const Prepared &P, bool scd, SweepWs &w) {
     const double every = pair_events(P);
     double share = (double)P.pr.N * K / (double)blocks / 64.0;
     const int64_t all = P.frac > 0.0 ? P.samp_users : P.frac == 0.0 ? P.pr.N : 0;
-    const int64_t per = (int64_t)(P.ell_D ? 512 : P.U_nh);   // users a block takes at a time
+    const int64_t per = (int64_t)(P.ell_D ? (P.pr.M > 16 ? 256 : 512) : P.U_nh);   // users a block takes at a time
     const int64_t run = std::min<int64_t>(blocks, std::max<int64_t>(1, all / per));
     share = std::max(share, every * K * (double)((all + run - 1) / run));
     scap = (uint32_t)std::min<double>(kStageCapMax, std::max<double>(kStageCap, share));
@@ -2296,7 +2300,7 @@ kp_status kp_eval_dual_noalloc(void *hip_stream, const kp_problem *prob, const d
   a.partials = partials;
   a.x_out = x;
   int used = 0;
-  const bool ell = P.row_nnz && P.pr.M <= 16 &&
+  const bool ell = P.row_nnz && P.pr.M <= kp_ell_max_items(P.row_nnz) &&
                    kp_ell_lds_bytes(P.pr.M, K, P.row_nnz, P.tree.L, 0, nullptr) <= kMaxLds;
   if (ell) {
     a.ntiles = (P.pr.N + 63) / 64;

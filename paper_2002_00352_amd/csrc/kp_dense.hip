@@ -305,11 +305,12 @@ __global__ void __launch_bounds__(64) k_dense(const SweepArgs a, int x4) {
       __asm__ volatile("" ::: "memory");
       lane_deal_pairs(lane, pending, (uint64_t)S, pos, perm,
                       [&](int col, int k, uint64_t So, uint64_t poso, uint64_t permo) {
+        auto rk = [&](int r) -> int { return (int)((permo >> (4 * r)) & 15); };
         const float *bc = sb + (size_t)col * M * K + k;   // lane col's costs in k, stride K
         uint64_t A = 0;
         for (int j = 0; j < M; ++j)
           if (bc[j * K] > 0.0f) A |= 1ull << j;
-        lane_walk_pair(a, M, col, k, A, So, poso, permo,
+        lane_walk_pair(a, M, col, k, A, So, poso, rk,
                        [&](int j, int cc) { return (double)sb[((size_t)cc * M + j) * K + k]; }, ptl, lam, kst,
                        kmode, tr, kcorr, nullptr, nullptr, hmin, hmax, kcnt, kovf, nstage);
       });

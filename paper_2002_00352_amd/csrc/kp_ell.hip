@@ -9,9 +9,9 @@ static size_t ell_lds(int M, int K, int D, int L, int mode, int waves, int *regi
   const bool brk = mode == KM_SCD || mode == KM_WFAIL;
   size_t region = 0;
   if (mode != KM_WFAIL) {
-    // staged tile, plus slack for the reads of up to 16 items per lane past
-    // the last lane's row
-    region = (size_t)64 * M * 4 + (size_t)64 * M * D * 8 + (size_t)16 * D * 4;
+    // staged tile, plus slack for the reads of up to 16 (24) items per lane
+    // past the last lane's row
+    region = (size_t)64 * M * 4 + (size_t)64 * M * D * 8 + (size_t)(M > 16 ? 24 : 16) * D * 4;
     region = region > (size_t)8 * 65 * 8 ? region : (size_t)8 * 65 * 8;      // statistics rows
     if (mode == KM_WMAIN && region < (size_t)64 * M * 12) region = (size_t)64 * M * 12;  // filter: p~ and bounds by rank
   }
@@ -34,11 +34,15 @@ static size_t ell_lds(int M, int K, int D, int L, int mode, int waves, int *regi
   return s;
 }
 
+// The most items per user that the kernel takes.
+int kp_ell_max_items(int D) { return D == 1 ? 24 : 20; }
+
 // Waves per block of a mode: 8 for the full-search pass of the kernels
 // instantiated for the exact item count when its LDS fits, else 4 (with 8
 // waves a block may hold 256 registers per lane, and the kernels for a
-// class of item counts would spill).
+// class of item counts would spill); above 16 items see launch_ell_big.
 int kp_ell_waves(int M, int K, int D, int L, int mode) {
+  if (M > 16) return mode == KM_SCD && ell_lds(M, K, D, L, mode, EW, nullptr) <= (size_t)160 * 1024 ? EW : 2;
   const bool exact = M == 8 || M == 10 || M == 12 || M == 16;
   if (mode == KM_SCD && exact && ell_lds(M, K, D, L, mode, 8, nullptr) <= (size_t)160 * 1024) return 8;
   return EW;
@@ -82,7 +86,7 @@ hipError_t kp_launch_ell(const SweepArgs &a, int D, int grid, int mode, hipStrea
   EllGeom g;
   g.M = a.pr.M;
   g.K = a.pr.K;
-  if (g.M < 1 || g.M > 16 || (D != 1 && D != 2) || mode < 0 || mode > 4) return hipErrorInvalidValue;
+  if (g.M < 1 || g.M > kp_ell_max_items(D) || (D != 1 && D != 2) || mode < 0 || mode > 4) return hipErrorInvalidValue;
   if (a.ntiles > 0x7fffffffLL) return hipErrorInvalidValue;  // the kernel's tile indices are 32-bit
   if ((mode == KM_FIX) != (a.fx.bin != nullptr)) return hipErrorInvalidValue;
   size_t lds = kp_ell_lds_bytes(g.M, g.K, D, a.tree.L, mode, &g.region);
@@ -109,7 +113,7 @@ hipError_t kp_launch_ell(const SweepArgs &a, int D, int grid, int mode, hipStrea
 // Blocks of the given mode that can be resident on the device at once (the
 // grid kp_launch_ell launches at most); 0 when the query fails.
 int kp_ell_resident_grid(int D, int mode, int M, int K, int L) {
-  if (M < 1 || M > 16 || (D != 1 && D != 2) || mode < 0 || mode > 3) return 0;
+  if (M < 1 || M > kp_ell_max_items(D) || (D != 1 && D != 2) || mode < 0 || mode > 3) return 0;
   const size_t lds = kp_ell_lds_bytes(M, K, D, L, mode, nullptr);
   const int w = kp_ell_waves(M, K, D, L, mode);
   switch (mode) {

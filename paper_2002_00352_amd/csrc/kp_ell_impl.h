@@ -1,5 +1,5 @@
 // Lean sweep kernel for per-item CSR costs whose item rows all hold the same
-// number D of stored entries (row r's entries at [r*D, r*D + D)), M <= 16.
+// number D of stored entries (row r's entries at [r*D, r*D + D)), M <= 20 (D = 2) or 24 (D = 1).
 //
 // One wave owns a tile of 64 users, one lane per user; waves never wait for
 // each other inside the tile loop.  The tile's profits and entries are staged
@@ -19,6 +19,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <string.h>
+#include <type_traits>
 #include "kp_device.h"
 
 #define EW 4                 // waves per block (the full-search pass: 8 when its LDS allows)
@@ -81,8 +82,10 @@ struct LamW {
 };
 
 // Per-wave scratch of the breakpoint phase (byte offsets in the wave's region).
+// Above 16 items the moving-item masks take 32 bits and the rank order a byte
+// per item (prm) instead of the nibbles of a register.
 struct EllScratch {
-  int pt, bt, kt, msk, end;
+  int pt, bt, kt, msk, prm, end;
 };
 __host__ __device__ inline EllScratch ell_scratch(int M, int D, int K) {
   auto r16 = [](int b) { return (b + 15) & ~15; };
@@ -91,7 +94,8 @@ __host__ __device__ inline EllScratch ell_scratch(int M, int D, int K) {
   x.bt = x.pt + r16(M * 64 * 8);
   x.kt = x.bt + r16(M * D * 64 * 4);
   x.msk = x.kt + r16(M * D * 64);
-  x.end = x.msk + r16(K * 64 * 2);
+  x.prm = x.msk + r16(K * 64 * (M > 16 ? 4 : 2));
+  x.end = x.prm + (M > 16 ? r16(M * 64) : 0);
   return x;
 }
 
@@ -108,11 +112,11 @@ struct EllGeom {
 // the pass's range are emitted (other search modes: binned or emitted by
 // record_event), and in a window pass C_ik(whi+) - v_ik goes into the window
 // correction.  A: the items moving with k; bkc(j, c): the cost in k of item
-// j of lane c's user (j in A); ptl: the lanes' p~ columns [M][64]; Sc, posc,
-// permc: the user's greedy set, positive items and rank order.
-template <class BKC>
+// j of lane c's user (j in A); ptl: the lanes' p~ columns [M][64]; Sc, posc:
+// the user's greedy set and positive items, rk(r) its item of rank r.
+template <class RK, class BKC>
 __device__ __forceinline__ void lane_walk_pair(const SweepArgs &a, int M, int col, int k, uint64_t A,
-                                               uint64_t Sc, uint64_t posc, uint64_t permc, BKC bkc,
+                                               uint64_t Sc, uint64_t posc, RK rk, BKC bkc,
                                                const double *ptl, const double *lam, const KWalk *kst,
                                                const int *kmode, const SetTree &tr,
                                                XSum *kcorr, XSum *hs, uint32_t *hc, unsigned long long *hmin,
@@ -123,8 +127,7 @@ __device__ __forceinline__ void lane_walk_pair(const SweepArgs &a, int M, int co
   uint64_t Sw = 0;
   auto zv = [&](int j) -> double { return ptl[j * 64 + col]; };
   auto bv = [&](int j) -> double { return (A >> j & 1) ? bkc(j, col) : 0.0; };
-  const int st = pair_start(tr, A, Sc, posc, zv, bv,
-                            [&](int r) -> int { return (int)((permc >> (4 * r)) & 15); }, lam[k], kst[k], &Sw, &above);
+  const int st = pair_start(tr, A, Sc, posc, zv, bv, rk, lam[k], kst[k], &Sw, &above);
   if (st) {
     const bool ok = pair_walk(M, tr, A, Sw, st == 1, zv, bv, lam[k], kst[k],
                               [&](double v1, double v2) {
@@ -187,12 +190,12 @@ __device__ __forceinline__ void lane_deal_pairs(int lane, uint64_t pending, uint
 // moving with each knapsack (mskl).  pend: the knapsacks that may have a
 // breakpoint of this user in the pass's range.  S is the greedy set at lambda^t, pos the
 // items with p~ > 0, perm the items ranked by (p~ desc, index asc).
-template <int D>
+template <int D, bool BIG, class MSK>
 __device__ __forceinline__ void scd_user(const SweepArgs &a, int M, int K, int lane, bool act,
                                          int alg5q, int64_t uidx, uint64_t pend,
                                          uint64_t S, uint64_t pos, uint64_t perm, double bmax,
                                          const double *ptl, const float *btl, const uint8_t *ktl,
-                                         const uint16_t *mskl, const double *lam, const SetTree &tr,
+                                         const MSK *mskl, const uint8_t *prml, const double *lam, const SetTree &tr,
                                          const KWalk *kst, const int *kmode,
                                          const double *hwin, XSum *kcorr, XSum *hs, uint32_t *hc,
                                          unsigned long long *hmin, unsigned long long *hmax,
@@ -216,7 +219,7 @@ __device__ __forceinline__ void scd_user(const SweepArgs &a, int M, int K, int l
   // largest cost) never turn positive in any window and never matter.
   double H = 0.0, gscale = 0.0;
   uint64_t rinv = 0;   // rank of every item, 4 bits each
-  if (hwin[K] > 0.0) {
+  if (!BIG && hwin[K] > 0.0) {
     H = hwin[K] * bmax * (1.0 + 0x1p-30) + 0x1p-36 * (1.0 + bmax * hwin[K]);
     for (int r = 0; r < M; ++r) rinv |= (uint64_t)r << (4 * ((perm >> (4 * r)) & 15));
     gscale = fabs(ptl[(int)(perm & 15) * 64 + lane]) + H;
@@ -254,8 +257,9 @@ __device__ __forceinline__ void scd_user(const SweepArgs &a, int M, int K, int l
   // in it), else the Q-th
   double qth = 0.0, q1th = 0.0;
   if (alg5q > 0) {
-    if (alg5q <= M) qth = fmax(ptl[(int)((perm >> (4 * (alg5q - 1))) & 15) * 64 + lane], 0.0);
-    if (alg5q + 1 <= M) q1th = fmax(ptl[(int)((perm >> (4 * alg5q)) & 15) * 64 + lane], 0.0);
+    auto item = [&](int r) -> int { return BIG ? (int)prml[r * 64 + lane] : (int)((perm >> (4 * r)) & 15); };
+    if (alg5q <= M) qth = fmax(ptl[item(alg5q - 1) * 64 + lane], 0.0);
+    if (alg5q + 1 <= M) q1th = fmax(ptl[item(alg5q) * 64 + lane], 0.0);
   }
   // Alg.5: one breakpoint per item and its knapsack
   uint64_t pending = act ? pend : 0;
@@ -265,7 +269,7 @@ __device__ __forceinline__ void scd_user(const SweepArgs &a, int M, int K, int l
       const int mode = kmode[k];
       const double bo_d = (double)btl[j * 64 + lane];
       if (!walk_mode(mode) || !(bo_d > 0.0)) continue;
-      if (hwin[k] > 0.0 && calm(k, 1u << j)) continue;
+      if (!BIG && hwin[k] > 0.0 && calm(k, 1u << j)) continue;
       double best = 0.0;
       const double pk = (double)a.pr.p[uidx * M + j];
       const double adj = fmax(ptl[j * 64 + lane], 0.0);
@@ -285,8 +289,9 @@ __device__ __forceinline__ void scd_user(const SweepArgs &a, int M, int K, int l
     }
     pending = 0;
   }
-  // pairs that are calm in their window need no walk
-  for (uint64_t m = pending; m; m &= m - 1) {
+  // pairs that are calm in their window need no walk (above 16 items the
+  // walk's own first look settles them)
+  for (uint64_t m = BIG ? 0ull : pending; m; m &= m - 1) {
     const int k = __ffsll((long long)m) - 1;
     if (hwin[k] > 0.0 && calm(k, (uint32_t)mskl[k * 64 + lane])) pending &= ~(1ull << k);
   }
@@ -296,7 +301,8 @@ __device__ __forceinline__ void scd_user(const SweepArgs &a, int M, int K, int l
   __builtin_amdgcn_wave_barrier();
   __asm__ volatile("" ::: "memory");
   lane_deal_pairs(lane, pending, S, pos, perm, [&](int col, int k, uint64_t So, uint64_t poso, uint64_t permo) {
-    lane_walk_pair(a, M, col, k, (uint64_t)mskl[k * 64 + col], So, poso, permo,
+    lane_walk_pair(a, M, col, k, (uint64_t)mskl[k * 64 + col], So, poso,
+                   [&](int r) -> int { return BIG ? (int)prml[r * 64 + col] : (int)((permo >> (4 * r)) & 15); },
                    [&](int j, int c) { return bkc(j, k, c); }, ptl, lam, kst, kmode, tr, kcorr, hs, hc,
                    hmin, hmax, kcnt, kovf, nstage);
   });
@@ -320,14 +326,12 @@ enum { KM_EVAL = 0, KM_SCD = 1, KM_WMAIN = 2, KM_WFAIL = 3, KM_FIX = 4 };
 // The window main pass of the exact kernels up to 10 items is held to 3
 // waves per SIMD, the occupancy its LDS allows (without the hint it compiles
 // just above the register limit).  The larger ones would spill registers
-// under that limit; a build of one of them that spilled gave wrong
-// multipliers after a window pass where the same source without the limit
-// did not, so they keep every register they need.
+// under that limit, so they keep every register they need.
 template <int MODE, int EM, bool EXACT> struct EllWaves {
   static constexpr int value = (MODE == 2 && EXACT && EM <= 10) ? 3 : 1;
 };
 
-// EM: the item-count class (8, 10, 12, 16); EXACT: M equals EM, so every
+// EM: the item-count class (8, 10, 12, 16, 20, 24); EXACT: M equals EM, so every
 // test of an item index against M folds away.  KX: the knapsack count when
 // it is fixed at compile time (10 or 20 with M = 10, and every statistics
 // row in one chunk), else 0: the loops over the knapsacks and the rows then
@@ -343,7 +347,14 @@ k_ell(const SweepArgs a, const EllGeom g) {
   constexpr bool STAGED = (MODE != KM_WFAIL);                    // contiguous tiles
   constexpr bool EV = (MODE == KM_EVAL || MODE == KM_FIX);       // evaluation only
   extern __shared__ __align__(16) unsigned char smem[];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  // the wave's index in a scalar register: tile indices and what depends on
+  // them are then uniform to the compiler too, and a branch on the tile (full
+  // or partial) is a scalar branch.  As a per-lane value it became a masked
+  // branch, and register spills that the compiler placed at its end, before
+  // the lane mask was restored, ran with no lane active: the window kernels
+  // that spill read stale multipliers and list slots after a partial tile.
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int M = EXACT ? EM : g.M, K = KX ? KX : g.K;
   const int grows = KX ? KX + 2 : g.rows;   // statistics rows per chunk
   // g.compact, fixed at compile time for the kernels instantiated for one
@@ -607,12 +618,12 @@ k_ell(const SweepArgs a, const EllGeom g) {
     #pragma unroll
     for (int j = 0; j < EM; ++j) {
       if (j < M) {
-        perm |= (uint64_t)j << (4 * rk[j]);
+        if (EM <= 16) perm |= (uint64_t)j << (4 * rk[j]);
         if (pt[j] > 0.0) pos |= 1ull << j;
       }
     }
     if (!act) pos = 0;
-    // ---- Alg.1's cap pass, in rank space (M <= 16: 32-bit masks) ----
+    // ---- Alg.1's cap pass, in rank space (at most 24 items: 32-bit masks) ----
     // Bit r of `alive` stands for the item of rank r; starting from the
     // items with p~ > 0, every laminar set (subsets first) keeps its cap
     // best live members.  The sets are uniform: their masks and caps come
@@ -907,13 +918,16 @@ k_ell(const SweepArgs a, const EllGeom g) {
       double *ptl = (double *)(wreg + sl.pt);
       float *btl = (float *)(wreg + sl.bt);
       uint8_t *ktl = (uint8_t *)(wreg + sl.kt);
-      uint16_t *mskl = (uint16_t *)(wreg + sl.msk);
+      using Msk = typename std::conditional<(EM > 16), uint32_t, uint16_t>::type;
+      Msk *mskl = (Msk *)(wreg + sl.msk);
+      uint8_t *prml = (uint8_t *)(wreg + sl.prm);
       for (int k = 0; k < K; ++k) mskl[k * 64 + lane] = 0;
       uint64_t pend = 0;
       #pragma unroll
       for (int j = 0; j < EM; ++j) {
         if (j < M) {
           ptl[j * 64 + lane] = pt[j];
+          if (EM > 16) prml[__builtin_ctz(rbit[j]) * 64 + lane] = (uint8_t)j;
           #pragma unroll
           for (int t = 0; t < D; ++t) {
             const int k = cl[j * D + t];
@@ -929,7 +943,7 @@ k_ell(const SweepArgs a, const EllGeom g) {
               const double tol = KP_LINE_TOL * (fabs(pt[j]) + fabs(thr[j]) + (lam[k] + kst[k].tlo) * b);
               if ((S >> j & 1) || !(pt[j] - sh < thr[j] - tol)) pend |= 1ull << k;
             }
-            if (ok && v > 0.0f) mskl[k * 64 + lane] = (uint16_t)(mskl[k * 64 + lane] | (1u << j));
+            if (ok && v > 0.0f) mskl[k * 64 + lane] = (Msk)(mskl[k * 64 + lane] | (1u << j));
           }
         }
       }
@@ -939,7 +953,7 @@ k_ell(const SweepArgs a, const EllGeom g) {
       for (int j = 0; j < EM; ++j)
         if (j < M) diag = diag && cl[j * D] == j;
       const int64_t uidx = STAGED ? u0 + lane : (act ? (int64_t)a.flist[u0 + lane] : 0);
-      scd_user<D>(a, M, K, lane, act, diag ? a.alg5_q : 0, uidx, pend, S, pos, perm, bmax, ptl, btl, ktl, mskl,
+      scd_user<D, (EM > 16), Msk>(a, M, K, lane, act, diag ? a.alg5_q : 0, uidx, pend, S, pos, perm, bmax, ptl, btl, ktl, mskl, prml,
                   lam, tr, kst,
                   kmode, hwin, kcorr, hs, hc, hmin, hmax, kcnt, kovf, nstage);
       __builtin_amdgcn_s_waitcnt(0);
@@ -1044,15 +1058,6 @@ static hipError_t launch_ell_mw(const SweepArgs &a, const EllGeom &g, size_t lds
   }
 }
 
-template <int D, int MODE>
-static hipError_t launch_ell_m(const SweepArgs &a, const EllGeom &g, size_t lds, int grid,
-                               hipStream_t stream, int *used) {
-  if constexpr (MODE == KM_SCD) {
-    if (g.waves == 8) return launch_ell_mw<D, MODE, 8>(a, g, lds, grid, stream, used);
-  }
-  return launch_ell_mw<D, MODE, EW>(a, g, lds, grid, stream, used);
-}
-
 template <int D, int MODE, int EM, bool EXACT, int WPB, bool CMP = false, int KX = 0>
 static int resident_blocks_t(size_t lds) {
   const void *fn = (const void *)k_ell<D, MODE, EM, EXACT, WPB, CMP, KX>;
@@ -1078,6 +1083,47 @@ static int resident_blocks_c(size_t lds) {
   }
   return r;
 }
+// Above 16 items a wave's scratch is 20-30 KB: blocks of two waves pack a
+// compute unit's LDS best, except where the histograms take a share per block
+// (the full-search pass: four waves when they fit).  At two stored entries per
+// item the classes end at 20 items and at one at 24: above, the breakpoint
+// phase needs more than the 512 registers that a lane can have (348-1032
+// bytes a lane spilled).
+template <int D, int MODE, int WPB>
+static hipError_t launch_ell_big(const SweepArgs &a, const EllGeom &g, size_t lds, int grid,
+                                 hipStream_t stream, int *used) {
+  if (g.M == 20) return launch_ell_c<D, MODE, 20, WPB, 0>(a, g, lds, grid, stream, used);
+  if (g.M < 20) return launch_ell_t<D, MODE, 20, false, WPB>(a, g, lds, grid, stream, used);
+  if constexpr (D == 1) {
+    if (g.M <= 24) return launch_ell_t<D, MODE, 24, false, WPB>(a, g, lds, grid, stream, used);
+  }
+  return hipErrorInvalidValue;
+}
+template <int D, int MODE, int WPB>
+static int resident_blocks_big(int M, size_t lds) {
+  if (M == 20) return resident_blocks_c<D, MODE, 20, WPB, 0>(lds);
+  if (M < 20) return resident_blocks_t<D, MODE, 20, false, WPB>(lds);
+  if constexpr (D == 1) {
+    if (M <= 24) return resident_blocks_t<D, MODE, 24, false, WPB>(lds);
+  }
+  return 0;
+}
+
+template <int D, int MODE>
+static hipError_t launch_ell_m(const SweepArgs &a, const EllGeom &g, size_t lds, int grid,
+                               hipStream_t stream, int *used) {
+  if (g.M > 16) {
+    if constexpr (MODE == KM_SCD) {
+      if (g.waves == EW) return launch_ell_big<D, MODE, EW>(a, g, lds, grid, stream, used);
+    }
+    return launch_ell_big<D, MODE, 2>(a, g, lds, grid, stream, used);
+  }
+  if constexpr (MODE == KM_SCD) {
+    if (g.waves == 8) return launch_ell_mw<D, MODE, 8>(a, g, lds, grid, stream, used);
+  }
+  return launch_ell_mw<D, MODE, EW>(a, g, lds, grid, stream, used);
+}
+
 template <int D, int MODE, int EM, int WPB>
 static int resident_blocks_x(size_t lds) {
   int r = resident_blocks_c<D, MODE, EM, WPB, 0>(lds);
@@ -1111,6 +1157,12 @@ static int resident_blocks_mw(int M, size_t lds) {
 
 template <int D, int MODE>
 static int resident_blocks_m(int M, size_t lds, int waves) {
+  if (M > 16) {
+    if constexpr (MODE == KM_SCD) {
+      if (waves == EW) return resident_blocks_big<D, MODE, EW>(M, lds);
+    }
+    return resident_blocks_big<D, MODE, 2>(M, lds);
+  }
   if constexpr (MODE == KM_SCD) {
     if (waves == 8) return resident_blocks_mw<D, MODE, 8>(M, lds);
   }

@@ -1431,3 +1431,38 @@ def test_fixup_boundary_search(kind):
     assert int(got["n_reset"].item()) == ref["n_reset"] > 0
     assert np.allclose(got["R"].cpu().numpy(), ref["R"], rtol=1e-12, atol=0)
     assert abs(got["P"].item() - ref["P"]) <= REL * abs(ref["P"])
+
+
+@gpu
+@pytest.mark.parametrize("M,K,D,Q", [(17, 5, 1, 3), (18, 4, 2, None), (20, 20, 2, 3), (20, 7, 1, 6), (19, 9, 2, 5),
+                                     (22, 6, 1, None), (24, 30, 1, 2), (21, 5, 2, 3), (25, 5, 1, 3)])
+def test_uniform_row_kernel_above_16_items(M, K, D, Q):
+    """The uniform-row kernel's classes above 16 items (20 with two entries per
+    item, 20 and 24 with one: 32-bit item masks, ranks in LDS) and the first
+    sizes past them (the general kernel), with one top-Q set or laminar sets
+    (Q None): decisions, statistics and SCD updates, with and without windows,
+    equal the oracle's bit for bit; so do the post-processed decisions."""
+    kp, torch = _kp()
+    print("case", M, K, D, Q, flush=True)
+    tree = random_laminar(M, np.random.default_rng(M)) if Q is None else None
+    inst = kpgen.make_instance(3001, M, K, seed=M + K, Q=Q or 3, csr_d=D, budget_frac=0.08, tree=tree)
+    prob = kp.Problem.from_host(inst)
+    ctxs = [kp.Context(), kp.Context()]
+    ctxs[1].set_window(False)
+    lam = np.zeros(K)
+    for t in range(10):
+        ref = oracle.eval_dual(inst, lam)
+        want = oracle.scd_sweep(inst, lam)
+        for ctx in ctxs:
+            ev = kp.kp_eval_dual(prob, _lamd(torch, lam), want_x=True, ctx=ctx)
+            assert ctx.launch_shape()[0] == (1 if M <= (24 if D == 1 else 20) else 0)
+            assert np.array_equal(ev["x"].cpu().numpy(), ref["x"])
+            assert np.array_equal(ev["R"].cpu().numpy(), ref["R"])
+            for key in ("g", "P"):
+                assert abs(ev[key].item() - ref[key]) <= REL * max(1.0, abs(ref[key]))
+            got = kp.kp_scd_sweep(prob, _lamd(torch, lam), ctx=ctx)["lam"].cpu().numpy()
+            assert np.array_equal(got, want), (t, got, want)
+        lam = want
+    print("window searches", ctxs[0].window_stats(), "listed", ctxs[0].window_listed(), flush=True)
+    fixed = kp.kp_primal_fixup(prob, _lamd(torch, lam * 0.5), want_x=True)
+    assert np.array_equal(fixed["x"].cpu().numpy(), oracle.fixup(inst, lam * 0.5)["x"])
