@@ -139,19 +139,33 @@ __device__ __forceinline__ bool cr_gt(double num, double den, double t) {   // t
 // breakpoint phases look for the innermost full set that holds an item all
 // the time, in code where lanes diverge; read from the kernel's arguments
 // (scalar loads, each waited for, over all the sets) those looks were most of
-// a walk's time.  One set or none (top-Q) stays in registers.
+// a walk's time.  Up to three sets (top-Q; two groups and a total) are held in
+// scalar registers instead: three tests cost less than a chain of dependent
+// LDS reads (N = 5e6, M = 10, K = 20, three sets: 9.4 -> 8.4 ms for four
+// iterations), and more of them would push the scalar registers out.
 struct SetNode {
   uint64_t mask;
   int cap, up;
 };
-struct SetTree {
+// FEW: how many sets are held in registers.  3 in the lean kernel up to 16
+// items; 1 in the others, whose scalar registers already spill (M = 20 with
+// 11 sets lost 4 %, batches 1 %; ragged CSR costs gained nothing).
+template <int FEW>
+struct SetTreeN {
   const SetNode *node;
   const int16_t *first;
-  int L, c1;
-  uint64_t m1;
+  int L;
+  int cap[FEW];         // up to that many sets: in registers (scalar ones, the same for every lane)
+  uint64_t m[FEW];
   // the members of S in the innermost full set that holds o (0: none is full)
   __device__ __forceinline__ uint64_t circuit(uint64_t S, int o) const {
-    if (L <= 1) return (m1 >> o & 1) && popc64(S & m1) >= c1 ? S & m1 : 0ull;
+    if (L <= FEW) {
+      uint64_t c = 0;
+      #pragma unroll
+      for (int l = FEW - 1; l >= 0; --l)   // (subsets come first: the innermost one last)
+        if ((m[l] >> o & 1) && popc64(S & m[l]) >= cap[l]) c = S & m[l];
+      return c;
+    }
     for (int l = first[o]; l >= 0;) {
       const SetNode n = node[l];
       if (popc64(S & n.mask) >= n.cap) return S & n.mask;
@@ -160,21 +174,26 @@ struct SetTree {
     return 0;
   }
 };
+using SetTree = SetTreeN<1>;
 __host__ __device__ __forceinline__ size_t set_tree_bytes(int L, int M) {
   return (((size_t)L * sizeof(SetNode) + 15) & ~(size_t)15) + (((size_t)M * 2 + 15) & ~(size_t)15);
 }
 // Copy T into mem (set_tree_bytes of LDS); the block synchronises afterwards.
-__device__ __forceinline__ SetTree set_tree_load(void *mem, const TreeDev &T, int M, int tid, int nthreads) {
+template <int FEW = 1>
+__device__ __forceinline__ SetTreeN<FEW> set_tree_load(void *mem, const TreeDev &T, int M, int tid, int nthreads) {
   SetNode *n = (SetNode *)mem;
   int16_t *f = (int16_t *)((unsigned char *)mem + (((size_t)T.L * sizeof(SetNode) + 15) & ~(size_t)15));
   for (int l = tid; l < T.L; l += nthreads) { n[l].mask = T.mask[l]; n[l].cap = T.cap[l]; n[l].up = T.up[l]; }
   for (int j = tid; j < M; j += nthreads) f[j] = T.first[j];
-  SetTree t;
+  SetTreeN<FEW> t;
   t.node = n;
   t.first = f;
   t.L = T.L;
-  t.c1 = T.L == 1 ? T.cap[0] : 0;
-  t.m1 = T.L == 1 ? T.mask[0] : 0ull;
+  #pragma unroll
+  for (int l = 0; l < FEW; ++l) {
+    t.m[l] = l < T.L ? T.mask[l] : 0ull;
+    t.cap[l] = l < T.L ? T.cap[l] : 0;
+  }
   return t;
 }
 
@@ -332,8 +351,8 @@ __device__ __forceinline__ void publish_block(const SweepArgs &a, int K, XSum *h
 // empty): does none come in at or above tlo?  Items only rise as lambda_k
 // falls, so one that is below zero, or below the lowest member of its circuit
 // (all of them fixed lines), at tlo has no breakpoint above it.
-template <class ZV, class BV>
-__device__ __forceinline__ bool pair_idle(const SetTree &T, uint64_t A, uint64_t S0, ZV zv, BV bv, double lk, double tlo) {
+template <class TR, class ZV, class BV>
+__device__ __forceinline__ bool pair_idle(const TR &T, uint64_t A, uint64_t S0, ZV zv, BV bv, double lk, double tlo) {
   const double d = tlo - lk, mt = lk + tlo;
   for (uint64_t m = A; m; m &= m - 1) {
     const int o = __ffsll((long long)m) - 1;
@@ -377,8 +396,8 @@ __device__ __forceinline__ bool pair_idle(const SetTree &T, uint64_t A, uint64_t
 // items with p~ > 0.  Returns 0 when no breakpoint lies in the range (*above:
 // a window's consumption just above thi), else the start of the walk: 1 with
 // *So the greedy set at thi, 2 with *So the set T above every breakpoint.
-template <class ZV, class BV, class RK>
-__device__ __forceinline__ int pair_start(const SetTree &tr, uint64_t A, uint64_t S0, uint64_t pos, ZV zv, BV bv, RK rk, double lk,
+template <class TR, class ZV, class BV, class RK>
+__device__ __forceinline__ int pair_start(const TR &tr, uint64_t A, uint64_t S0, uint64_t pos, ZV zv, BV bv, RK rk, double lk,
                                           const KWalk &ks, uint64_t *So, double *above_out) {
   const bool window = ks.mode == KS_WINDOW;
   const double tlo = ks.tlo, thi = ks.thi;
@@ -486,8 +505,8 @@ __device__ __forceinline__ int pair_start(const SetTree &tr, uint64_t A, uint64_
 // above every breakpoint) down to tlo; emit(v1, v2) takes a breakpoint in the
 // range.  *above: a window's consumption just above thi.  Returns false when
 // the walk runs past its event limit.
-template <class ZV, class BV, class EM>
-__device__ __forceinline__ bool pair_walk(int M, const SetTree &tr, uint64_t A, uint64_t S, bool at, ZV zv, BV bv, double lk, const KWalk &ks, EM emit,
+template <class TR, class ZV, class BV, class EM>
+__device__ __forceinline__ bool pair_walk(int M, const TR &tr, uint64_t A, uint64_t S, bool at, ZV zv, BV bv, double lk, const KWalk &ks, EM emit,
                                           double *above_out) {
   const bool window = ks.mode == KS_WINDOW;
   const double tlo = ks.tlo, thi = ks.thi;

@@ -114,11 +114,11 @@ struct EllGeom {
 // correction.  A: the items moving with k; bkc(j, c): the cost in k of item
 // j of lane c's user (j in A); ptl: the lanes' p~ columns [M][64]; Sc, posc:
 // the user's greedy set and positive items, rk(r) its item of rank r.
-template <class RK, class BKC>
+template <class TR, class RK, class BKC>
 __device__ __forceinline__ void lane_walk_pair(const SweepArgs &a, int M, int col, int k, uint64_t A,
                                                uint64_t Sc, uint64_t posc, RK rk, BKC bkc,
                                                const double *ptl, const double *lam, const KWalk *kst,
-                                               const int *kmode, const SetTree &tr,
+                                               const int *kmode, const TR &tr,
                                                XSum *kcorr, XSum *hs, uint32_t *hc, unsigned long long *hmin,
                                                unsigned long long *hmax, uint32_t *kcnt, uint32_t *kovf,
                                                uint32_t *nstage) {
@@ -190,12 +190,12 @@ __device__ __forceinline__ void lane_deal_pairs(int lane, uint64_t pending, uint
 // moving with each knapsack (mskl).  pend: the knapsacks that may have a
 // breakpoint of this user in the pass's range.  S is the greedy set at lambda^t, pos the
 // items with p~ > 0, perm the items ranked by (p~ desc, index asc).
-template <int D, bool BIG, class MSK>
+template <int D, bool BIG, class MSK, class TR>
 __device__ __forceinline__ void scd_user(const SweepArgs &a, int M, int K, int lane, bool act,
                                          int alg5q, int64_t uidx, uint64_t pend,
                                          uint64_t S, uint64_t pos, uint64_t perm, double bmax,
                                          const double *ptl, const float *btl, const uint8_t *ktl,
-                                         const MSK *mskl, const uint8_t *prml, const double *lam, const SetTree &tr,
+                                         const MSK *mskl, const uint8_t *prml, const double *lam, const TR &tr,
                                          const KWalk *kst, const int *kmode,
                                          const double *hwin, XSum *kcorr, XSum *hs, uint32_t *hc,
                                          unsigned long long *hmin, unsigned long long *hmax,
@@ -363,8 +363,9 @@ k_ell(const SweepArgs a, const EllGeom g) {
   size_t off = 0;
   auto carve = [&](size_t bytes) { unsigned char *p = smem + off; off += (bytes + 15) & ~(size_t)15; return p; };
   double *lam = (double *)carve((size_t)(K + 1) * 8);   // [K] = 0 for the clamped reads
-  SetTree tr;
-  if (BREAK) tr = set_tree_load(carve(set_tree_bytes(a.tree.L, M)), a.tree, M, tid, ENT);
+  constexpr int FEW = EM <= 16 ? 3 : 1;
+  SetTreeN<FEW> tr;
+  if (BREAK) tr = set_tree_load<FEW>(carve(set_tree_bytes(a.tree.L, M)), a.tree, M, tid, ENT);
   double *wacc = (double *)carve((size_t)EWM * (K + 2) * 8);
   KWalk *kst = BREAK ? (KWalk *)carve((size_t)K * sizeof(KWalk)) : nullptr;
   XSum *hs = nullptr;
