@@ -1466,3 +1466,75 @@ def test_uniform_row_kernel_above_16_items(M, K, D, Q):
     print("window searches", ctxs[0].window_stats(), "listed", ctxs[0].window_listed(), flush=True)
     fixed = kp.kp_primal_fixup(prob, _lamd(torch, lam * 0.5), want_x=True)
     assert np.array_equal(fixed["x"].cpu().numpy(), oracle.fixup(inst, lam * 0.5)["x"])
+
+
+def _many_users(kind, N):
+    """Many users with few items: spread breakpoints, all users alike (every
+    key held by N events), or uniform rows (two entries per item)."""
+    from util import make
+    rng = np.random.default_rng(N)
+    if kind in ("rows", "general-rows"):
+        return kpgen.make_instance(N, 5, 4, seed=N, Q=2, csr_d=2, budget_frac=0.05)
+    p = 0.5 + rng.integers(0, 1 << 20, (N, 4)) / float(1 << 20)
+    b = rng.integers(1 << 16, 1 << 20, (N, 4, 2)) / float(1 << 20)
+    if kind == "alike":
+        p[:], b[:] = p[0], b[0]
+    return make(p, b, 0.1 * b.sum(axis=(0, 1)) * 2 / 4, kpgen.tree_topq(4, 2), name=kind)
+
+
+@gpu
+@pytest.mark.parametrize("kind,N", [("spread", 32768), ("alike", 32768), ("rows", 32768),
+                                    ("spread", 32769), ("alike", 40007), ("rows", 32831), ("general-rows", 40007)])
+def test_scd_many_events(kind, N):
+    """Searches around the size where a sample replaces the pass that emits
+    every breakpoint (32768 users), with more than 32768 breakpoints per
+    knapsack to select among -- also when one key holds more of them than the
+    selection's list: every update equals the oracle's bit for bit, from
+    lambda = 0, along the trajectory and after a jump back."""
+    kp, torch = _kp()
+    print("case", kind, N, flush=True)
+    inst = _many_users(kind, N)
+    prob = kp.Problem.from_host(inst)
+    ctx = kp.Context()
+    if kind == "general-rows":
+        ctx.set_kernel_choice(False)
+    lam = np.zeros(inst.K)
+    for t in range(5):
+        want = oracle.scd_sweep(inst, lam)
+        got = kp.kp_scd_sweep(prob, _lamd(torch, lam), ctx=ctx)["lam"].cpu().numpy()
+        assert np.array_equal(got, want), (t, got, want)
+        lam = want if t != 3 else np.zeros(inst.K)
+
+
+@gpu
+@pytest.mark.parametrize("kind", ["spread", "rows", "batched"])
+def test_scd_capped_workspace(kind):
+    """Contexts with less and less workspace: every call either gives the
+    oracle's multipliers (events that no longer fit cost passes, no more) or
+    reports KP_ERR_NOMEM, down to the first size that is refused."""
+    kp, torch = _kp()
+    print("case", kind, flush=True)
+    insts = [_many_users("spread" if kind == "batched" else kind, 30000)]
+    if kind == "batched":
+        insts.append(_many_users("rows", 9001))
+    probs = [kp.Problem.from_host(i) for i in insts]
+    lams = [np.zeros(i.K) for i in insts]
+    wants = [oracle.scd_sweep(i, l) for i, l in zip(insts, lams)]
+    size, done = 1 << 29, 0
+    while True:
+        ctx = kp.Context(max_workspace_bytes=size)
+        try:
+            if kind == "batched":
+                outs = kp.kp_scd_sweep_batched(probs, [_lamd(torch, l) for l in lams], ctx=ctx)[0]
+            else:
+                outs = [kp.kp_scd_sweep(probs[0], _lamd(torch, lams[0]), ctx=ctx)["lam"]]
+        except kp.KPError as e:
+            assert kp.STATUS[e.status] == "KP_ERR_NOMEM"
+            break
+        for out, want in zip(outs, wants):
+            assert np.array_equal(out.cpu().numpy(), want), size
+        done += 1
+        ctx.close()
+        size = int(size * 0.96)
+    print("sizes accepted", done, "refused at", size, flush=True)
+    assert done > 0
