@@ -663,7 +663,7 @@ def main():
     avg_ms = ms_k / max(launches, 1)
     achieved = per_launch_bytes / (avg_ms * 1e-3) / 1e9
     traffic = traffic_for(args.workload, per_launch_bytes)
-    lean = bool(meta["csr_d"]) and meta["M"] <= 16
+    lean = bool(meta["csr_d"]) and meta["M"] <= (24 if meta["csr_d"] == 1 else 20)
     # the ceiling streams the arrays the pass reads (the lean kernel never
     # reads rowptr)
     ceiling = stream_ceiling([t for t in (prob.p, prob.b, None if lean else prob.rowptr, prob.col, prob.val)

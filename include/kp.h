@@ -278,9 +278,9 @@ kp_status kp_set_tuning(void *ctx, int32_t M, int32_t K, int32_t b_format, int32
 kp_status kp_get_launch_shape(void *ctx, int32_t *kernel, int32_t *users_per_tile, int32_t *grid);
 /* Tuning of batched plans created later on this context: LDS bytes per block
    of the batched launch (instances with long rows take fewer users per tile
-   to fit it; 0 = 40 KB) and blocks per block that can be resident (the
+   to fit it; 0 = 48 KB) and blocks per block that can be resident (the
    finer the split, the better the dispatcher balances ragged instances;
-   0 = 64).  Results do not depend on these values (g and P up to the
+   0 = 16).  Results do not depend on these values (g and P up to the
    grouping of their FP64 sums). */
 kp_status kp_set_batched_tuning(void *ctx, int32_t lds_bytes, int32_t block_mult);
 

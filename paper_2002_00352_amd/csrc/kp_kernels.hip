@@ -8,16 +8,19 @@
 //   phase B1 one thread per user ranks its items by (p~ desc, index asc) and
 //            runs the hierarchical greedy (Alg.1, as the equivalent laminar
 //            matroid greedy on bitmasks),
-//   phase B2 one thread per (user, knapsack) reduces consumption and, for SCD,
-//            walks the user's consumption step function in lambda_k (the
-//            breakpoints of Alg.3/4) and bins / emits them.
+//   phase B2 reduces consumption and, for SCD, looks at every (user, knapsack)
+//            pair: those that a filter does not settle are queued, dealt over
+//            the block and walked along the user's consumption step function
+//            in lambda_k over the pass's range (the breakpoints of Alg.3/4),
+//            which are binned or emitted.
 // R, g and P are summed in a fixed order: per (user,k) values go to LDS and
 // are added in user order, per block into a private slot, and slots are
 // added in block order by a second kernel.  The threshold search's sums
 // (histogram bins, window corrections) are exact two-limb integers added
 // with integer atomics, so their order does not matter.  This file also
-// holds the threshold search's state machine, the post-processing, the
-// batched plan's helpers and the input checks.
+// holds the batched sweep, the statistics' reductions and the input checks
+// (the threshold search's state machine: kp_search.hip; the post-processing:
+// kp_fixup.hip).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <string.h>
