@@ -32,7 +32,7 @@ hipError_t kp_launch_scd_init(KState *st, int K, const double *lam_in, const uin
 hipError_t kp_launch_scd_locate_select(KState *st, int K, const double *B, const double *R,
                                        const int *rinst, XSum *hist_sum, uint32_t *hist_cnt,
                                        const double *ev1, const double *ev2, uint32_t emit_cap,
-                                       const SelWs &w, int blocks, int nohist, int *pending,
+                                       const SelWs &w, int blocks, const SumCheck &sc, int nohist, int *pending,
                                        unsigned int *win, hipStream_t stream);
 hipError_t kp_launch_scd_select_many(KState *st, int K, const double *B, const double *ev1, const double *ev2,
                                      uint32_t emit_cap, const SelWs &w, int blocks, int *pending,
@@ -81,7 +81,7 @@ size_t kp_resplit_lds(int n);
 hipError_t kp_launch_plan_resplit(const ResplitArgs &r, hipStream_t stream);
 hipError_t kp_launch_batched_aux(int which, const void *tab, int n, KState *st, const void *lam_ptrs,
                                  const int *kinst, const int *klocal, double *hint, const uint64_t *eoff,
-                                 const uint32_t *ecap, const double *frac, hipStream_t stream);
+                                 const uint32_t *ecap, const double *frac, unsigned int *off, hipStream_t stream);
 TileGeom kp_tile_geom(const SweepArgs &a, int U);
 size_t kp_coldesc_size();
 void kp_coldesc_fill(void *dst, const double *partials, const double *lam, const double *B,
@@ -282,6 +282,7 @@ struct Prepared {
   double frac = -1.0;
   int64_t samp_tiles = 0, samp_stride = 1, samp_off = 0;
   int64_t samp_users = 0;
+  int gexp = 0;           // the unit of the grid on which FP64 sums up to 8 times the budgets are exact: 2^gexp
   int stage_grid() const {
     return std::max(std::max(std::max(grid, grid_nh), std::max(ell_grid, dense_grid)), dwin_grid);
   }
@@ -394,6 +395,11 @@ kp_status prepare(const kp_problem *p, bool scd, Prepared &out, const Ctx *ctx =
   pr.rowptr = p->b_rowptr;
   pr.col = p->b_col;
   pr.val = p->b_val;
+  {
+    double top = 0.0;
+    for (int k = 0; k < p->K; ++k) top = std::max(top, p->B[k]);
+    out.gexp = std::min(100, std::max(-56, std::ilogb(top) + 4 - 53));   // (-56: the exact sums' unit)
+  }
   // tile: as many users as fit the staged-cost budget, at most 64
   const size_t per_user = (size_t)M * p->K * 4;
   int U = (int)std::max<size_t>(1, std::min<size_t>(64, kTileBudget / per_user));
@@ -584,6 +590,19 @@ double pair_events(const Prepared &P) {
   return P.row_nnz ? 2.0 + 2.0 * P.pr.M * P.row_nnz / P.pr.K : 8.0;
 }
 
+// What a window's search needs to know about the FP64 consumption of a pass
+// of `blocks` blocks: its bound when every cost is on the grid, and its error
+// otherwise.  The terms are non-negative, so a sum loses at most 2^-53 of
+// itself per addition that a term goes through: those of its block's users,
+// the blocks' tree, and the few of a user's own sums.  abs: the rounding of
+// the exact sums' terms to units of 2^-56.
+void sum_check(const Prepared &P, int64_t blocks, double *lim, double *rel, double *abs) {
+  const double depth = (double)(P.pr.N / std::max<int64_t>(1, blocks) + 512 + blocks + 8 * P.pr.M);
+  *lim = std::ldexp(1.0, P.gexp + 53);
+  *rel = depth * 0x1p-52;
+  *abs = (double)P.pr.N * (P.pr.M + 8) * 0x1p-56;
+}
+
 struct SweepWs {
   double *partials, *B, *ev1, *ev2, *Rtmp, *gtmp, *Ptmp, *sv1, *sv2;
   XSum *hist_sum;
@@ -597,6 +616,7 @@ struct SweepWs {
   unsigned int *win;    // window searches: [0] tried, [1] threshold above, [2] below
   uint32_t emit_cap;
   unsigned int *flist, *fcount;   // users listed by the window pass
+  unsigned int *off;    // some cost is off the grid (SumCheck)
   uint32_t fcap;
   int *modes;           // [0] knapsacks with a window, [1] with another search mode, [2] alternation
                         // windows, [3] dense probe: sampled users with a line above -H
@@ -616,7 +636,7 @@ kp_status carve_ws(Ctx *c, const Prepared &P, bool scd, SweepWs &w) {
   size_t o_P = cv.take(8);
   // status block (cleared with the histograms in one memset): [0] pending
   // knapsacks, [8] walk-limit counter, [16] window counters, [32] list
-  // counters, [48] search-mode counts
+  // counters, [40] off-grid flag, [48] search-mode counts
   size_t o_st = 0, o_hs = 0, o_hc = 0, o_km = 0, o_e1 = 0, o_e2 = 0, o_stat = 0, o_sel = 0;
   uint32_t cap = 0;
   if (scd) o_st = cv.take((size_t)K * sizeof(KState));
@@ -702,6 +722,7 @@ kp_status carve_ws(Ctx *c, const Prepared &P, bool scd, SweepWs &w) {
   w.fcap = fcap;
   w.flist = fcap ? (unsigned int *)(b + o_fl) : nullptr;
   w.fcount = (unsigned int *)(b + o_stat + 32);
+  w.off = (unsigned int *)(b + o_stat + 40);
   w.modes = scd ? (int *)(b + o_stat + 48) : nullptr;
   return KP_OK;
 }
@@ -837,6 +858,9 @@ SweepArgs make_args(const Prepared &P, const double *lam, const SweepWs &w, uint
   a.stage_k = w.sk;
   a.stage_cap = w.stage_cap;
   a.err = w.err;
+  a.gmag = std::ldexp(1.5, P.gexp + 52);
+  a.ginv = std::ldexp(1.0f, -P.gexp);
+  a.off = w.off;
   a.flist = w.flist;
   a.fcount = w.fcount;
   a.fcap = w.fcap;
@@ -1071,6 +1095,7 @@ kp_status kp_scd_sweep_masked(void *ctx, const kp_problem *prob, const double *l
   double *Rd = R ? R : w.Rtmp;
   double *gd = g ? g : w.gtmp;
   double *Pd = primal ? primal : w.Ptmp;
+  SumCheck check = {w.off, 0.0, 0.0, 0.0, nullptr};
   int pass = 0;
   for (;; ++pass) {
     if (pass >= kMaxPasses) return fail(KP_ERR_INTERNAL, "SCD threshold search exceeded %d passes", kMaxPasses);
@@ -1093,8 +1118,10 @@ kp_status kp_scd_sweep_masked(void *ctx, const kp_problem *prob, const double *l
         HIP_TRY(kp_launch_reduce_stats(w.partials, 1, K, lambda_in, w.B, Rd, gd, Pd, c->stream));
       }
     }
+    if (pass == 0) sum_check(P, c->stats_grid, &check.lim, &check.rel, &check.abs);
     HIP_TRY(kp_launch_scd_locate_select(w.st, K, w.B, Rd, nullptr, w.hist_sum, w.hist_cnt, w.ev1, w.ev2,
-                                        w.emit_cap, w.sel, 0, nohist && pass == 0 ? 1 : 0, w.pending, w.win, c->stream));
+                                        w.emit_cap, w.sel, 0, check, nohist && pass == 0 ? 1 : 0, w.pending, w.win,
+                                        c->stream));
     // one copy of the status block: pending, walk-limit counter, window and
     // list counters
     int *st = c->pinned + 32;
@@ -1572,6 +1599,8 @@ struct BatchPlan {
   XSum *hs = nullptr;
   uint32_t *hc = nullptr;
   SelWs sel;
+  SumCheck check;
+  unsigned int *off = nullptr;   // [n] an instance has costs off its grid (cleared by an iteration's init)
   unsigned long long *err = nullptr;
   int *pinned = nullptr;     // [0] pending knapsacks, [2..3] error word, [16..] per-instance flags
   hipGraph_t graph[2] = {nullptr, nullptr};
@@ -1692,10 +1721,10 @@ kp_status plan_later_passes_dev(BatchPlan *p, int dir, hipStream_t s) {
     r.reset = j == 0 ? 1 : 0;
     HIP_TRY(kp_launch_plan_resplit(r, s));
     if (p->T > 0) HIP_TRY(kp_launch_sweep_batched(p->rd, p->rg, p->rboff, p->n, p->gfix, p->lds, s, p->ctl));
-    HIP_TRY(kp_launch_scd_locate_select(p->kst, p->Kf, p->Bf, p->stats, p->kin, p->hs, p->hc, p->e1, p->e2, p->cap, p->sel, kSelBlocksBatched, p->nohist, p->pend,
+    HIP_TRY(kp_launch_scd_locate_select(p->kst, p->Kf, p->Bf, p->stats, p->kin, p->hs, p->hc, p->e1, p->e2, p->cap, p->sel, kSelBlocksBatched, p->check, p->nohist, p->pend,
                                       nullptr, s));
     HIP_TRY(kp_launch_batched_aux(2, nullptr, p->Kf, p->kst, p->lam_tab[1 - dir], p->kin, p->klo, p->hint, nullptr,
-                                  nullptr, nullptr, s));
+                                  nullptr, nullptr, nullptr, s));
     HIP_TRY(kp_launch_inst_active(p->kst, p->koff, p->n, p->active, s));
   }
   HIP_TRY(hipMemcpyAsync(p->pinned, p->pend, sizeof(int), hipMemcpyDeviceToHost, s));
@@ -1707,16 +1736,16 @@ kp_status plan_later_passes_dev(BatchPlan *p, int dir, hipStream_t s) {
 
 kp_status plan_first_pass(BatchPlan *p, int dir, hipStream_t s) {
   HIP_TRY(kp_launch_batched_aux(p->window ? 3 : 1, nullptr, p->Kf, p->kst, p->lam_tab[dir], p->kin, p->klo, p->hint,
-                                p->eoff, p->ecap, p->frac, s));
+                                p->eoff, p->ecap, p->frac, p->off, s));
   kp_status st0 = plan_sample_phase(p, dir, s);
   if (st0 != KP_OK) return st0;
   if (p->T > 0) HIP_TRY(kp_launch_sweep_batched(p->d[dir][1], p->geom, p->boff, p->n, p->GB, p->lds, s));
   HIP_TRY(kp_launch_batched_aux(0, p->coltab[dir], p->ncol, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
-                                nullptr, nullptr, s));
-  HIP_TRY(kp_launch_scd_locate_select(p->kst, p->Kf, p->Bf, p->stats, p->kin, p->hs, p->hc, p->e1, p->e2, p->cap, p->sel, kSelBlocksBatched, p->nohist, p->pend,
+                                nullptr, nullptr, nullptr, s));
+  HIP_TRY(kp_launch_scd_locate_select(p->kst, p->Kf, p->Bf, p->stats, p->kin, p->hs, p->hc, p->e1, p->e2, p->cap, p->sel, kSelBlocksBatched, p->check, p->nohist, p->pend,
                                       nullptr, s));
   HIP_TRY(kp_launch_batched_aux(2, nullptr, p->Kf, p->kst, p->lam_tab[1 - dir], p->kin, p->klo, p->hint, nullptr,
-                                nullptr, nullptr, s));
+                                nullptr, nullptr, nullptr, s));
   HIP_TRY(kp_launch_inst_active(p->kst, p->koff, p->n, p->active, s));
   HIP_TRY(hipMemcpyAsync(p->pinned, p->pend, sizeof(int), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipMemcpyAsync(p->pinned + 2, p->err, 8, hipMemcpyDeviceToHost, s));
@@ -1781,10 +1810,10 @@ kp_status plan_step(BatchPlan *p, int dir, double *stats_out, bool graph) {
       }
     }
     ++passes;
-    HIP_TRY(kp_launch_scd_locate_select(p->kst, p->Kf, p->Bf, p->stats, p->kin, p->hs, p->hc, p->e1, p->e2, p->cap, p->sel, kSelBlocksBatched, 0, p->pend,
+    HIP_TRY(kp_launch_scd_locate_select(p->kst, p->Kf, p->Bf, p->stats, p->kin, p->hs, p->hc, p->e1, p->e2, p->cap, p->sel, kSelBlocksBatched, p->check, 0, p->pend,
                                       nullptr, s));
     HIP_TRY(kp_launch_batched_aux(2, nullptr, p->Kf, p->kst, p->lam_tab[1 - dir], p->kin, p->klo, p->hint, nullptr,
-                                nullptr, nullptr, s));
+                                nullptr, nullptr, nullptr, s));
     HIP_TRY(kp_launch_inst_active(p->kst, p->koff, p->n, p->active, s));
     HIP_TRY(hipMemcpyAsync(p->pinned, p->pend, sizeof(int), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipMemcpyAsync(p->pinned + 2, p->err, 8, hipMemcpyDeviceToHost, s));
@@ -1975,6 +2004,8 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
   const size_t o_sbo = cv.take((size_t)(n + 1) * 4);
   const size_t o_err = cv.take(8);
   const size_t o_pend = cv.take(8);
+  const size_t o_off = cv.take((size_t)n * 4);
+  const size_t o_chk = cv.take((size_t)n * 24);
   const size_t o_kin = cv.take((size_t)Kf * 4);
   const size_t o_klo = cv.take((size_t)Kf * 4);
   const size_t o_lt0 = cv.take((size_t)n * 8);
@@ -2043,6 +2074,8 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
   p->sd[1] = (SweepArgs *)(w + o_sd1);
   p->sboff = (int *)(w + o_sbo);
   p->err = (unsigned long long *)(w + o_err);
+  p->off = (unsigned int *)(w + o_off);
+  p->check = SumCheck{p->off, 0.0, 0.0, 0.0, (const double *)(w + o_chk)};
   p->pend = (int *)(w + o_pend);
   p->kin = (int *)(w + o_kin);
   p->klo = (int *)(w + o_klo);
@@ -2084,7 +2117,7 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
   size_t sso = 0;
   for (int d = 0; d < 2; ++d) for (int f = 0; f < 2; ++f) hd[d][f].resize(n);
   std::vector<TileGeom> hg(n);
-  std::vector<double> hB(Kf);
+  std::vector<double> hB(Kf), hchk(3 * (size_t)n);
   std::vector<int> kin(Kf), klo(Kf);
   std::vector<uint64_t> heo(Kf);
   std::vector<uint32_t> hec(Kf);
@@ -2113,6 +2146,9 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
     a.stage_k = (uint16_t *)(w + o_sk) + soff[s];
     a.stage_cap = scap[s];
     a.err = p->err;
+    a.gmag = std::ldexp(1.5, P[s].gexp + 52);
+    a.ginv = std::ldexp(1.0f, -P[s].gexp);
+    a.off = p->off + s;
     for (int d = 0; d < 2; ++d) {
       a.lam = d == 0 ? lam_a[s] : lam_b[s];
       a.want_stats = 1;
@@ -2131,6 +2167,7 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
       hsd[d][s] = q;
     }
     sso += (size_t)hsd[0][s].ntiles * hsd[0][s].stage_cap;
+    sum_check(P[s], boff[s + 1] - boff[s], &hchk[3 * s], &hchk[3 * s + 1], &hchk[3 * s + 2]);
     hg[s] = kp_tile_geom(hd[0][1][s], P[s].U);
     for (int k = 0; k < K; ++k) {
       hB[koff[s] + k] = P[s].B[k];
@@ -2186,6 +2223,7 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
   for (int d = 0; d < 2 && e == hipSuccess; ++d) e = up(p->sd[d], psd[d].data(), (size_t)n * sizeof(SweepArgs));
   if (e == hipSuccess) e = up(p->sboff, sboff.data(), (size_t)(n + 1) * 4);
   if (e == hipSuccess) e = up(p->frac, hfrac.data(), (size_t)Kf * 8);
+  if (e == hipSuccess) e = up(w + o_chk, hchk.data(), (size_t)n * 24);
   if (e == hipSuccess) e = up(p->geom, pg.data(), (size_t)n * sizeof(TileGeom));
   if (e == hipSuccess) e = up(p->boff, bpos.data(), (size_t)(n + 1) * 4);
   if (e == hipSuccess) e = up(p->koff, koff.data(), (size_t)(n + 1) * 4);

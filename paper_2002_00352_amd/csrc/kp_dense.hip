@@ -127,6 +127,10 @@ __global__ void __launch_bounds__(64) k_dense(const SweepArgs a, int x4) {
   for (int q = 0; q < EK; ++q) accR[q] = 0.0;
   double accG = 0.0, accP = 0.0;
   uint32_t nwalk = 0;   // window pass: users of this wave with a pair to walk
+  double gmag = WIN ? a.gmag : 0.0;
+  float ginv = WIN ? a.ginv : 0.0f;
+  if (WIN) __asm__ volatile("" : "+v"(gmag), "+v"(ginv));
+  uint32_t offg = 0;    // window pass: some consumption is off the grid on which FP64 sums are exact
   for (int64_t tile = blockIdx.x; tile < a.ntiles; tile += gridDim.x) {
     const int64_t u0 = tile * TU;
     const int nu = (int)((N - u0) < TU ? (N - u0) : TU);
@@ -225,6 +229,7 @@ __global__ void __launch_bounds__(64) k_dense(const SweepArgs a, int x4) {
         if (q < K) {
           double v = 0.0;
           for (uint32_t m = S; m; m &= m - 1u) v = v + (double)bl[(__ffs((int)m) - 1) * K + q];
+          if (WIN) offg |= off_grid(v, gmag);
           accR[q] = accR[q] + v;
         }
       }
@@ -308,8 +313,10 @@ __global__ void __launch_bounds__(64) k_dense(const SweepArgs a, int x4) {
         auto rk = [&](int r) -> int { return (int)((permo >> (4 * r)) & 15); };
         const float *bc = sb + (size_t)col * M * K + k;   // lane col's costs in k, stride K
         uint64_t A = 0;
-        for (int j = 0; j < M; ++j)
+        for (int j = 0; j < M; ++j) {
           if (bc[j * K] > 0.0f) A |= 1ull << j;
+          offg |= off_grid(bc[j * K], ginv);
+        }
         lane_walk_pair(a, M, col, k, A, So, poso, rk,
                        [&](int j, int cc) { return (double)sb[((size_t)cc * M + j) * K + k]; }, ptl, lam, kst,
                        kmode, tr, kcorr, nullptr, nullptr, hmin, hmax, kcnt, kovf, nstage);
@@ -333,6 +340,7 @@ __global__ void __launch_bounds__(64) k_dense(const SweepArgs a, int x4) {
   }
   if (WIN) {
     if (lane == 0 && nwalk && a.fcount) atomicAdd(a.fcount + 1, nwalk);
+    report_off_grid(a, offg);
     __syncthreads();
     publish_block(a, K, nullptr, nullptr, hmin, hmax, kcnt, kpos, kovf, nstage, lane, 64, blockIdx.x, kcorr);
   }

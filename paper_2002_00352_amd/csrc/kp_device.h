@@ -108,6 +108,20 @@ __device__ __forceinline__ bool xs_gt(const XSum &a, double B) {
   return H > HB || (H == HB && (double)L > rB);
 }
 
+// Non-zero when v >= 0 is off the grid of SweepArgs::gmag / ginv (a sum of
+// multiples of the unit g below g 2^53 is exact in FP64); the sweeps OR the
+// answers of all they sum and report them at the end.
+__device__ __forceinline__ uint32_t off_grid(double v, double gmag) {
+  const double up = v + gmag;
+  return up - gmag != v ? 1u : 0u;
+}
+__device__ __forceinline__ uint32_t off_grid(float v, float ginv) {
+  return __float_as_uint(__builtin_amdgcn_fractf(v * ginv));
+}
+__device__ __forceinline__ void report_off_grid(const SweepArgs &a, uint32_t off) {
+  if (__ballot(off != 0) && (threadIdx.x & 63) == 0) atomicOr(a.off, 1u);
+}
+
 // Bin of a post-processing key: the number of the nb - 1 ascending
 // splitters below it.
 __device__ __forceinline__ int fx_bin_of(const uint64_t *split, int nb, uint64_t key) {

@@ -477,6 +477,14 @@ k_ell(const SweepArgs a, const EllGeom g) {
 
   uint32_t ch_pos = 0, ch_end = 0;   // the wave's reserved list chunk (window main pass)
   uint32_t nlist = 0;                 // users the wave listed
+  // some cost of this lane's users is off the grid on which FP64 sums are
+  // exact: the breakpoint phases test every cost (with the statistics, or of
+  // the listed users), the window main pass the selected ones
+  // (the unit in a vector register: read from the kernel's arguments it costs
+  // a scalar load and a wait at every use)
+  uint32_t offg = 0;
+  float ginv = !EV && (MODE != KM_SCD || a.want_stats) ? a.ginv : 0.0f;
+  if (!EV) __asm__ volatile("" : "+v"(ginv));
   // tile indices fit 32 bits (the launcher rejects more than 2^31 - 1 tiles)
   for (int tile = (int)blockIdx.x * EWM + wv; tile < (int)ntiles; tile += (int)W) {
     const int64_t u0 = (MODE == KM_SCD ? (int64_t)tile * a.tstride + a.toff : (int64_t)tile) * 64;
@@ -856,6 +864,7 @@ k_ell(const SweepArgs a, const EllGeom g) {
             for (int e = 0; e < KP_SEL_MAX * D; ++e) {
               const int q = sk[e] - c0;
               const bool ok = (unsigned)q < (unsigned)nq && q < K - c0;
+              if (MODE == KM_WMAIN) offg |= off_grid(sv_[e], ginv);
               __hip_atomic_fetch_add(&rows[(ok ? q : 0) * 65 + lane], ok ? (double)sv_[e] : 0.0,
                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
             }
@@ -872,6 +881,7 @@ k_ell(const SweepArgs a, const EllGeom g) {
                 // unselected or foreign entries add +0 to row 0 (a consumption
                 // row, never -0): no branch
                 const bool ok = (S >> j & 1) && (unsigned)q < (unsigned)nq && q < K - c0;
+                if (MODE == KM_WMAIN) offg |= ok ? off_grid(v, ginv) : 0u;
                 __hip_atomic_fetch_add(&rows[(ok ? q : 0) * 65 + lane], ok ? (double)v : 0.0,
                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
               }
@@ -943,6 +953,7 @@ k_ell(const SweepArgs a, const EllGeom g) {
       uint8_t *prml = (uint8_t *)(wreg + sl.prm);
       for (int k = 0; k < K; ++k) mskl[k * 64 + lane] = 0;
       uint64_t pend = 0;
+      uint32_t offt = 0;
       #pragma unroll
       for (int j = 0; j < EM; ++j) {
         if (j < M) {
@@ -954,6 +965,7 @@ k_ell(const SweepArgs a, const EllGeom g) {
             const bool ok = (unsigned)k < (unsigned)K;
             const float v = vl[j * D + t];
             btl[(j * D + t) * 64 + lane] = v;
+            offt |= off_grid(v, ginv);
             ktl[(j * D + t) * 64 + lane] = (uint8_t)(ok ? k : 255);
             // a knapsack may have a breakpoint in the pass's range when one of
             // its moving items is selected, or passes its threshold element
@@ -967,6 +979,7 @@ k_ell(const SweepArgs a, const EllGeom g) {
           }
         }
       }
+      offg |= act ? offt : 0u;
       // Alg.5's setting for this user: item j's only entry is knapsack j
       bool diag = D == 1 && a.alg5_q > 0;
       #pragma unroll
@@ -986,6 +999,7 @@ k_ell(const SweepArgs a, const EllGeom g) {
       if (e < a.fcap) a.flist[e] = KP_LIST_HOLE;
     if (lane == 0 && nlist) atomicAdd(a.fcount + 1, nlist);
   }
+  if (!EV) report_off_grid(a, offg);
   __syncthreads();
   if (MODE == KM_FIX) {
     for (int t = tid; t < a.fx.nb * a.fx.nv; t += ENT)

@@ -100,10 +100,23 @@ struct KState : KWalk {
                        // breakpoint; < 0: exponential buckets
   uint64_t hull_lo, hull_hi;  // atomics: key hull of the bucket's events
   XSum corr;           // KS_WINDOW: sum over users of C_ik(whi+) - v_ik(x(lambda^t))
+  double err;          // what the FP64 consumption may add to the error of fab (0: fab is exact)
   uint64_t sel_lo, sel_hi;    // selection: keys of the bin that holds the threshold
   XSum sel_fab;        // selection: sum of increments above it
   int sel_bin;         // selection: the bin (-1: the sum never exceeds the budget)
   uint32_t ncomp;      // selection: events of that bin compacted (atomic)
+};
+
+// A window's sum above it is the FP64 consumption R at lambda^t plus exact
+// corrections.  R is exact when every cost it sums is a multiple of the grid
+// unit g (the sweeps set *off otherwise) and it is below lim = g 2^53; else it
+// is within rel R + abs of the exact sum, and a search that this decides
+// nothing for goes on with exact buckets.  per: [instance][3] lim, rel, abs of
+// a batch, with *off per instance.
+struct SumCheck {
+  const unsigned int *off;
+  double lim, rel, abs;
+  const double *per;
 };
 
 // Workspace of the selection among emitted breakpoints, per knapsack.
@@ -153,6 +166,11 @@ struct SweepArgs {
   uint32_t stage_cap;
   int pass;
   unsigned long long *err; // walk-limit counter
+  // SCD: 1.5 2^52 grid units (adding and subtracting it rounds to the grid),
+  // 1 / grid unit, and where costs off the grid are reported (SumCheck)
+  double gmag;
+  float ginv;
+  unsigned int *off;
   // post-processing bins (uniform-row kernel, evaluation only; fx.bin null otherwise)
   FixBins fx;
   // window pass split in two kernels: users listed by the first

@@ -314,6 +314,16 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a, const TileGeom &g
   }
 
   // ---- software pipeline: prefetch tile bid ----
+  // some cost is off the grid on which FP64 sums are exact (CSR: every entry of
+  // the pass with the statistics; dense: the consumptions and the costs of
+  // the pairs looked at, M times fewer than all)
+  // (the units in vector registers: read from the kernel's arguments they cost
+  // a scalar load and a wait at every use)
+  uint32_t offg = 0;
+  double gmag = SCD && a.want_stats ? a.gmag : 0.0;
+  float ginv = SCD && (FMT == 0 || a.want_stats) ? a.ginv : 0.0f;
+  if (SCD) __asm__ volatile("" : "+v"(ginv));
+  if (SCD && FMT == 0) __asm__ volatile("" : "+v"(gmag));
   Prefetch f;
   int64_t tile = bid;
   if (tile < a.ntiles) {
@@ -433,6 +443,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a, const TileGeom &g
           else { k = a.pr.col[e_first + e]; v = a.pr.val[e_first + e]; }   // tile beyond the staging
           if ((unsigned)k >= (unsigned)K) continue;   // malformed column: ignored (kp_validate_inputs reports it)
           bt[(size_t)r * K + k] = v;
+          if (SCD) offg |= off_grid(v, ginv);
           if (SCD && v > 0.0f) {
             const int u = r / M;
             atomicOr((unsigned long long *)&Am[u * K + k], 1ull << (r - u * M));
@@ -621,6 +632,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a, const TileGeom &g
       }
       vk[q] = v;
       if (SCD) {
+        if (FMT == 0) offg |= off_grid(v, gmag);
         const int mode = kmode[k];
         if (walk_mode(mode)) {
           const double lk = lam[k];
@@ -674,8 +686,11 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a, const TileGeom &g
           A = Am[q];
         } else {
           #pragma unroll 4
-          for (int j = 0; j < M; ++j)
-            if (bu[j * K + k] > 0.0f) A |= 1ull << j;
+          for (int j = 0; j < M; ++j) {
+            const float bj = bu[j * K + k];
+            if (bj > 0.0f) A |= 1ull << j;
+            offg |= off_grid(bj, ginv);
+          }
         }
         double above = 0.0;   // window: the consumption just above it
         if (fastau && (A & (A - 1)) == 0) {
@@ -766,6 +781,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a, const TileGeom &g
   if (a.want_stats) {
     for (int t = tid; t < K + 2; t += NT) a.partials[(size_t)bid * (K + 2) + t] = acc[t];
   }
+  if (SCD) report_off_grid(a, offg);
   if (SCD) publish_block(a, K, hs, hc, hmin, hmax, kcnt, kpos, kovf, nstage, tid, NT, bid, kxs);
 }
 

@@ -66,6 +66,7 @@ __device__ __forceinline__ void search_start(KState &s) {
   s.n_emit = 0;
   s.overflow = 0;
   s.fab = xs_zero();
+  s.err = 0.0;
   s.hull_lo = ~0ull;
   s.hull_hi = 0;
   s.corr = xs_zero();
@@ -134,6 +135,7 @@ __global__ void k_scd_init(KState *st, int K, const double *lam_in, const uint8_
   s.whi = 0.0;
   s.hw = 0.0;
   s.corr = xs_zero();
+  s.err = 0.0;
   s.eoff = 0;
   s.ecap = 0;
   s.ncomp = 0;
@@ -152,6 +154,13 @@ __global__ void k_scd_init(KState *st, int K, const double *lam_in, const uint8_
     if (s.mode == KS_EXP) search_start(s);
   }
   st[k] = s;
+}
+
+// err rounded up to the units of the exact sums
+__device__ __forceinline__ XSum err_units(double err) {
+  XSum e = xs_of(err);
+  if (err > 0.0) e.lo += 1;
+  return e;
 }
 
 __device__ __forceinline__ int bits_needed(uint64_t x) { return x ? 64 - __clzll((long long)x) : 0; }
@@ -187,7 +196,8 @@ __device__ __forceinline__ XSum shfl_xs(const XSum &v, int src) {
 // bins through global memory took 5-16 us a pass, this 3-4.
 __global__ void __launch_bounds__(64) k_scd_locate(KState *st, int K, const double *B, const double *R,
                                                    const int *rinst, XSum *hist_sum, uint32_t *hist_cnt,
-                                                   uint32_t emit_cap, int nohist, int *pending, unsigned int *win) {
+                                                   uint32_t emit_cap, SumCheck sc, int nohist, int *pending,
+                                                   unsigned int *win) {
   const int k = blockIdx.x, lane = threadIdx.x;
   if (k == 0 && lane == 0) { pending[0] = 0; pending[1] = 0; }   // counted again by the selection
   if (st[k].mode == KS_DONE) return;
@@ -196,6 +206,8 @@ __global__ void __launch_bounds__(64) k_scd_locate(KState *st, int K, const doub
   KState s = st[k];
   if (s.ecap) emit_cap = s.ecap;   // batched: this knapsack's own buffer
   const double Bk = B[k];
+  const int in = rinst ? rinst[k] : 0;
+  const unsigned int off = sc.off[in];
   XSum h = xs_zero();
   uint32_t cnt = 0;
   if (s.mode == KS_EXP || s.mode == KS_REFINE) {
@@ -293,12 +305,18 @@ __global__ void __launch_bounds__(64) k_scd_locate(KState *st, int K, const doub
     // consumption just above the window, summed over users
     // consumption of knapsack k (batched: R of instance rinst[k] sits after
     // the R, g, P columns of the instances before it)
-    const double Rk = rinst ? R[k + 2 * rinst[k]] : R[k];
+    const double Rk = R[k + 2 * in];
     const XSum above = xs_plus(xs_of(Rk), s.corr);
+    const double lim = sc.per ? sc.per[3 * in] : sc.lim, rel = sc.per ? sc.per[3 * in + 1] : sc.rel,
+                 ab = sc.per ? sc.per[3 * in + 2] : sc.abs;
+    s.err = off == 0 && Rk < lim ? 0.0 : rel * fmax(fmax(Rk, Bk), xs_to_double(above)) + ab;
+    const XSum e = err_units(s.err);
     if (win && lane == 0) { atomicAdd(&win[0], 1u); atomicAdd(&win[3], s.n_emit); }
-    if (s.overflow || xs_gt(above, Bk)) {
+    if (s.overflow || xs_gt(xs_plus(above, e), Bk)) {
       if (win && lane == 0) atomicAdd(&win[1], 1u);
-      search_start(s);                  // the threshold lies above the window
+      // the threshold lies above the window, or on its edge as far as R tells
+      if (!s.overflow && !xs_gt(xs_minus(above, e), Bk)) s.flags |= KS_FLAG_TRIED;
+      search_start(s);
     } else {
       s.mode = KS_SELECT_RANGE;         // [klo, khi] is the window
       s.fab = above;
@@ -480,6 +498,17 @@ __global__ void __launch_bounds__(SH_NT) k_sel_compact(KState *st, const double 
   }
 }
 
+// The total over the block (part: LDS [SEL_NT / 64]), to every thread.
+__device__ __forceinline__ XSum block_total(XSum v, XSum *part) {
+  v = wave_suffix(v, threadIdx.x & 63);
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
+  __syncthreads();
+  XSum t = xs_zero();
+  for (int q = 0; q < SEL_NT / 64; ++q) t = xs_plus(t, part[q]);
+  return t;
+}
+
 __global__ void __launch_bounds__(SEL_NT) k_sel_final(KState *st, const double *B, const double *V1,
                                                       const double *V2, uint32_t emit_cap, SelWs w, int binned,
                                                       int *pending, unsigned int *win) {
@@ -546,8 +575,21 @@ __global__ void __launch_bounds__(SEL_NT) k_sel_final(KState *st, const double *
     }
   }
   if ((s.flags & KS_FLAG_WINDOW) && below) {
+    bool sure = true;
+    if (s.err > 0.0 && s.wlo == 0.0) {   // do the increments fit the budget, whatever R lost to rounding?
+      XSum v = xs_zero();
+      for (uint32_t e = tid; e < s.n_emit; e += SEL_NT) xs_add(v, (V2 + eo)[e]);
+      const XSum tot = xs_plus(s.fab, block_total(v, part));
+      sure = !xs_gt(xs_plus(tot, err_units(s.err)), Bk);
+    }
     if (tid == 0) {
-      if (s.wlo == 0.0) {               // every breakpoint is in the window
+      if (s.wlo == 0.0 && !sure) {
+        KState r = s;
+        r.flags |= KS_FLAG_TRIED;
+        search_start(r);
+        st[k] = r;
+        atomicAdd(pending, 1);
+      } else if (s.wlo == 0.0) {               // every breakpoint is in the window
         st[k].result = 0.0;
         st[k].mode = KS_DONE;
       } else {
@@ -648,6 +690,35 @@ __global__ void __launch_bounds__(SEL_NT) k_sel_final(KState *st, const double *
       if (xs_gt(at, Bk)) atomicMax(&kres, (unsigned long long)key);
     }
     __syncthreads();
+  }
+  if (s.err > 0.0) {
+    // the sum from the top must exceed the budget at this breakpoint and not
+    // above it, whatever R lost to rounding; else exact buckets decide
+    const uint64_t res = kres;
+    const XSum ex = err_units(s.err);
+    bool unsure = false;
+    #pragma unroll 1
+    for (int above = 0; above < 2; ++above) {
+      XSum v = xs_zero();
+      for (uint32_t e = tid; e < n; e += SEL_NT) {
+        uint64_t key = 0;
+        if (inlds) key = lkey[e];
+        if (inlds ? key < lo || key > hi : !sel_takes(s, bucket, lo, hi, E1[e], key)) continue;
+        if (key >= res + above) xs_add(v, inlds ? lval[e] : E2[e]);
+      }
+      const XSum at = xs_plus(Fab, block_total(v, part));
+      unsure = unsure || (above ? xs_gt(xs_plus(at, ex), Bk) : !xs_gt(xs_minus(at, ex), Bk));
+    }
+    if (unsure) {
+      if (tid == 0) {
+        KState r = s;
+        r.flags |= KS_FLAG_TRIED;
+        search_start(r);
+        st[k] = r;
+        atomicAdd(pending, 1);
+      }
+      return;
+    }
   }
   if (tid == 0) {
     st[k].result = kdbl(kres);
@@ -783,9 +854,10 @@ __global__ void k_count_modes(const KState *st, int K, int *out) {
 
 __global__ void k_scd_init_flat(KState *st, int Kf, const double *const *lam_in, const int *kinst,
                                 const int *klocal, double *hint, int window, const uint64_t *eoff,
-                                const uint32_t *ecap, const double *frac) {
+                                const uint32_t *ecap, const double *frac, unsigned int *off) {
   const int f = blockIdx.x * blockDim.x + threadIdx.x;
   if (f >= Kf) return;
+  if (klocal[f] == 0) off[kinst[f]] = 0u;
   const double l = lam_in[kinst[f]][klocal[f]];
   KState s;
   s.mode = KS_EXP;
@@ -807,6 +879,7 @@ __global__ void k_scd_init_flat(KState *st, int Kf, const double *const *lam_in,
   s.whi = 0.0;
   s.hw = 0.0;
   s.corr = xs_zero();
+  s.err = 0.0;
   s.eoff = eoff ? eoff[f] : 0;
   s.ecap = ecap ? ecap[f] : 0;
   s.ncomp = 0;
@@ -863,13 +936,13 @@ __global__ void k_scd_finish_flat(const KState *st, int Kf, double *const *lam_o
 
 hipError_t kp_launch_batched_aux(int which, const void *tab, int n, KState *st, const void *lam_ptrs,
                                  const int *kinst, const int *klocal, double *hint, const uint64_t *eoff,
-                                 const uint32_t *ecap, const double *frac, hipStream_t stream) {
+                                 const uint32_t *ecap, const double *frac, unsigned int *off, hipStream_t stream) {
   if (n <= 0) return hipSuccess;
   if (which == 0) return kp_launch_reduce_tab(tab, n, stream);
   if (which == 1 || which == 3) {   // 3: with a window where the last step allows
     hipLaunchKernelGGL(k_scd_init_flat, dim3((n + 63) / 64), dim3(64), 0, stream, st, n,
                        (const double *const *)lam_ptrs, kinst, klocal, hint,
-                       which == 3 ? 1 : 0, eoff, ecap, frac);
+                       which == 3 ? 1 : 0, eoff, ecap, frac, off);
   } else {
     hipLaunchKernelGGL(k_scd_finish_flat, dim3((n + 63) / 64), dim3(64), 0, stream, (const KState *)st,
                        n, (double *const *)lam_ptrs, kinst, klocal, hint);
@@ -921,10 +994,10 @@ SelWs kp_sel_ws(void *mem, int K) {
 hipError_t kp_launch_scd_locate_select(KState *st, int K, const double *B, const double *R,
                                        const int *rinst, XSum *hist_sum, uint32_t *hist_cnt,
                                        const double *ev1, const double *ev2, uint32_t emit_cap,
-                                       const SelWs &w, int blocks, int nohist, int *pending,
+                                       const SelWs &w, int blocks, const SumCheck &sc, int nohist, int *pending,
                                        unsigned int *win, hipStream_t stream) {
   hipLaunchKernelGGL(k_scd_locate, dim3(K), dim3(64), 0, stream, st, K, B, R, rinst, hist_sum,
-                     hist_cnt, emit_cap, nohist, pending, win);
+                     hist_cnt, emit_cap, sc, nohist, pending, win);
   if (blocks > 0) {
     hipLaunchKernelGGL(k_sel_hist, dim3(K, blocks), dim3(SH_NT), 0, stream, st, ev1, ev2, emit_cap, w, 0);
     hipLaunchKernelGGL(k_sel_compact, dim3(K, blocks), dim3(SH_NT), 0, stream, st, B, ev1, ev2, emit_cap, w);

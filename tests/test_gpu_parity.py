@@ -1562,3 +1562,104 @@ def test_uniform_row_copies_trajectory(m, K, D, Q):
         assert np.array_equal(got, want), (t, np.flatnonzero(got != want))
         lam = want
     print("window searches", ctx.window_stats(), "listed", ctx.window_listed(), flush=True)
+
+
+def _wide_costs(inst, seed):
+    """The instance with costs spread over 28 binades (24-bit values of
+    magnitudes in [2^-28, 1), multiples of 2^-51): exact in a user's FP64 sums
+    and in the 2^-56 units of the threshold search, but an FP64 sum over many
+    users rounds."""
+    rng = np.random.default_rng(seed)
+    n = (inst.b if inst.b is not None else inst.val).size
+    v = np.ldexp(rng.integers(1 << 23, 1 << 24, n).astype(np.float64), -51 + rng.integers(0, 28, n)).astype(np.float32)
+    return dataclasses.replace(inst, b=v) if inst.b is not None else dataclasses.replace(inst, val=v)
+
+
+def _tie_budgets(inst, lam, near=None):
+    """Budgets at which the threshold search from lam ends on a tie: B_k is
+    the largest double not above the exact running sum at a breakpoint (the
+    one nearest to near_k, else the one 3 % down the total), so that the sum
+    exceeds it by less than a rounding of its own, or not at all."""
+    import fractions
+    kk, _, v1, v2 = oracle.scd_map(inst, lam)
+    B = np.zeros(inst.K)
+    for k in range(inst.K):
+        a, inc = v1[kk == k], v2[kk == k]
+        o = np.argsort(-a, kind="stable")
+        a, inc = a[o], inc[o]
+        units = [int(x) for x in np.ldexp(inc, 56)]
+        run = np.cumsum(np.array(units, dtype=object))
+        e = int(np.argmin(np.abs(a - near[k]))) if near is not None else int(np.searchsorted(np.cumsum(inc), 0.03 * inc.sum()))
+        while e + 1 < len(a) and a[e + 1] == a[e]:
+            e += 1
+        f = float(fractions.Fraction(int(run[e]), 1 << 56))
+        if fractions.Fraction(f) > fractions.Fraction(int(run[e]), 1 << 56):
+            f = float(np.nextafter(f, 0.0))
+        B[k] = f
+    return B
+
+
+def _tie_instance(kind):
+    if kind in ("rows", "general-rows"):
+        inst = kpgen.make_instance(41_003, 8, 8, seed=91, Q=1, csr_d=2, budget_frac=0.02)
+    else:
+        inst = kpgen.make_instance(41_003, 6, 8, seed=92, Q=1, budget_frac=0.02)
+    return _wide_costs(inst, 93)
+
+
+@gpu
+@pytest.mark.parametrize("kind", ["rows", "general-rows", "dense", "dense-general"])
+def test_window_search_exact_at_ties(kind):
+    """Threshold searches that start with a window compare exact sums: with
+    budgets on a tie of the running sum -- closer to it than the rounding of
+    an FP64 sum over the users -- a cold search (a sample's window), alone,
+    with other tile sizes and in a batch, and a search around the last
+    multiplier return the oracle's multipliers bit for bit."""
+    kp, torch = _kp()
+    print("case ties", kind, flush=True)
+    inst = _tie_instance(kind)
+
+    def context(tile=0):
+        ctx = kp.Context()
+        if "general" in kind:
+            ctx.set_kernel_choice(False)
+        if tile:
+            ctx.set_tuning(inst.M, inst.K, 0 if inst.b is not None else 1, tile, 0)
+        return ctx
+
+    # from zero: a sample opens the window
+    zero = np.zeros(inst.K)
+    cold = dataclasses.replace(inst, B=_tie_budgets(inst, zero))
+    want = oracle.scd_sweep(cold, zero)
+    prob = kp.Problem.from_host(cold)
+    for tile in (0, 3, 7):
+        got = kp.kp_scd_sweep(prob, _lamd(torch, zero), ctx=context(tile))["lam"].cpu().numpy()
+        assert np.array_equal(got, want), (tile, np.flatnonzero(got != want))
+    ctx = context()
+    for use_graph in (False, True):
+        plan = kp.BatchedSCD([prob, prob], use_graph=use_graph, ctx=ctx)
+        outs, _ = plan.step()
+        torch.cuda.synchronize()
+        for out in outs:
+            assert np.array_equal(out.cpu().numpy(), want), (use_graph, np.flatnonzero(out.cpu().numpy() != want))
+        plan.close()
+    # near the solution: a window around the multiplier that the context's
+    # last call returned
+    base = dataclasses.replace(inst, B=np.maximum(cold.B, 1e-3))
+    lam = want
+    for _ in range(8):
+        lam = oracle.scd_sweep(base, lam)
+    lam0 = lam * (1.0 + 1e-3)
+    lam1 = oracle.scd_sweep(base, lam0)
+    step = np.abs(lam1 - lam0)
+    warm = dataclasses.replace(base, B=_tie_budgets(base, lam1, near=lam1 + 0.3 * step))
+    want = oracle.scd_sweep(warm, lam1)
+    for tile in (0, 5):
+        ctx = context(tile)
+        first = kp.kp_scd_sweep(kp.Problem.from_host(base), _lamd(torch, lam0), ctx=ctx)["lam"]
+        assert np.array_equal(first.cpu().numpy(), lam1)
+        before = ctx.window_stats()[0]
+        got = kp.kp_scd_sweep(kp.Problem.from_host(warm), first, ctx=ctx)["lam"].cpu().numpy()
+        assert np.array_equal(got, want), (tile, np.flatnonzero(got != want))
+        print("windows", ctx.window_stats()[0] - before, "kernel", ctx.launch_shape()[0], flush=True)
+        assert ctx.window_stats()[0] > before
