@@ -1663,3 +1663,94 @@ def test_window_search_exact_at_ties(kind):
         assert np.array_equal(got, want), (tile, np.flatnonzero(got != want))
         print("windows", ctx.window_stats()[0] - before, "kernel", ctx.launch_shape()[0], flush=True)
         assert ctx.window_stats()[0] > before
+
+
+def _general_rows(kp, inst):
+    """The CSR instance on the GPU without a declaration of its rows."""
+    host = kp.Problem.from_host(inst)
+    return kp.Problem(host.p, inst.B, inst.tree.parent, inst.tree.cap, inst.tree.leaf_of_item, rowptr=host.rowptr,
+                      col=host.col, val=host.val, N=inst.N, M=inst.M, K=inst.K, row_nnz=0)
+
+
+@gpu
+@pytest.mark.parametrize("use_graph", [False, True])
+def test_batched_sampled_start_trajectory(use_graph):
+    """Batched searches that start from samples (kp_set_sampled_start, here from
+    1000 users on): dense, uniform-row, general CSR and laminar instances with
+    and without a sample in one plan, every update equal to the oracle's bit
+    for bit from lambda = 0 on."""
+    kp, torch = _kp()
+    print("case", use_graph, flush=True)
+    rng = np.random.default_rng(17)
+    insts = [random_instance(rng, 5003, 10, 5, Q=3, frac=0.1), kpgen.config_instance(3, N=4001),
+             random_instance(rng, 3007, 12, 6, tree=random_laminar(12, rng), zero_frac=0.6, frac=0.1).to_csr(),
+             random_instance(rng, 700, 7, 3, Q=2), kpgen.make_instance(40_007, 6, 4, seed=18, Q=2, budget_frac=0.1),
+             kpgen.make_instance(36_001, 8, 5, seed=19, Q=2, csr_d=2, budget_frac=0.1),
+             random_instance(rng, 1000, 30, 16, Q=5, frac=0.1)]
+    probs = [kp.Problem.from_host(i) for i in insts]
+    probs[2], probs[5] = _general_rows(kp, insts[2]), _general_rows(kp, insts[5])
+    ctx = kp.Context()
+    ctx.set_sampled_start(1000)
+    plan = kp.BatchedSCD(probs, use_graph=use_graph, ctx=ctx)
+    lams = [np.zeros(i.K) for i in insts]
+    for t in range(7):
+        outs, _ = plan.step()
+        torch.cuda.synchronize()
+        for s, inst in enumerate(insts):
+            want = oracle.scd_sweep(inst, lams[s])
+            got = outs[s].cpu().numpy()
+            assert np.array_equal(got, want), (t, s, np.flatnonzero(got != want))
+            lams[s] = want
+    plan.close()
+
+
+@gpu
+@pytest.mark.parametrize("use_graph", [False, True])
+@pytest.mark.parametrize("fmt", ["dense", "csr"])
+def test_batched_misled_sample(fmt, use_graph):
+    """A batch whose samples mislead (the sampled tiles hold users with a
+    sixteenth of the other tiles' costs): the windows miss, and the searches
+    go on with histograms in passes from the host, which a plan without
+    histograms on the device lays out anew.  Every update equals the oracle's."""
+    kp, torch = _kp()
+    print("case", fmt, use_graph, flush=True)
+
+    def instances(per_tile):
+        out = []
+        for seed, (N, M, K) in enumerate([(9001, 8, 6), (4003, 8, 6)]):
+            inst = random_instance(np.random.default_rng(seed), N, M, K, Q=2, frac=0.1, zero_frac=0.5 if fmt == "csr" else 0.0)
+            b = inst.b.reshape(N, M, K).copy()
+            b[np.arange(N) // per_tile % 2 == 0] /= 16.0    # (up to 24576 users every other tile is sampled)
+            B = 0.1 * b.astype(np.float64).sum(axis=(0, 1))
+            out.append(make(inst.p.reshape(N, M), b, B, inst.tree))
+        return [i.to_csr() for i in out] if fmt == "csr" else out
+
+    def plan_of(insts, ctx):
+        ctx.set_sampled_start(1000)
+        probs = [_general_rows(kp, i) if fmt == "csr" else kp.Problem.from_host(i) for i in insts]
+        return kp.BatchedSCD(probs, use_graph=use_graph, ctx=ctx)
+
+    probe = plan_of(instances(1), kp.Context())
+    lo, hi = probe.shape()[2:]
+    probe.close()
+    assert lo == hi
+    insts = instances(lo)
+    ctx = kp.Context()
+    ctx.set_timing(True)
+    plan = plan_of(insts, ctx)
+    assert plan.shape()[2:] == (lo, hi)
+    lams = [np.zeros(i.K) for i in insts]
+    passes = []
+    for t in range(5):
+        outs, _ = plan.step()
+        torch.cuda.synchronize()
+        passes.append(ctx.batched_passes() - sum(passes))
+        for s, inst in enumerate(insts):
+            want = oracle.scd_sweep(inst, lams[s])
+            got = outs[s].cpu().numpy()
+            assert np.array_equal(got, want), (t, s, np.flatnonzero(got != want))
+            lams[s] = want
+    plan.close()
+    print("passes per iteration", passes, flush=True)
+    # the first, one or more with histograms; the graph's two device passes lie between
+    assert max(passes) >= (4 if use_graph else 3)
