@@ -136,6 +136,7 @@ constexpr uint32_t kEmitCapMin = 1u << 16, kEmitCapMax = 1u << 23;   // emitted 
 constexpr int kGraphLaterPasses = 2;     // later passes captured with the first in a batched iteration's graph
 constexpr uint32_t kEmitCapBatched = 1u << 16;   // emitted events per (instance, knapsack) per pass (at least)
 constexpr double kEmitBytesBatched = 8.0e9;        // bound on a batch's emission buffers
+constexpr size_t kStageBytesBatched = (size_t)2 << 30;   // staged events of one launch of a batch's sampled pass
 constexpr size_t kBatchedLds = 48 * 1024;          // LDS per block of the batched launch (three per CU; 40 KB 14.1, 24 KB 19.2, 48 KB 13.6 ms for 32 instances)
 constexpr int kSelBlocks = 32;                     // blocks per knapsack that bin and compact more of them
 constexpr int kSelBlocksBatched = 4;
@@ -168,6 +169,7 @@ struct Ctx {
   // searches without a window of problems with at least this many users
   // start from a sample of them (0: never)
   int64_t sample_min = kSampleMin;
+  size_t ws_refused = 0;  // the smallest search workspace that could not be allocated (0: none yet)
   int stats_grid = 0;     // blocks of the last sweep launch (slots of the per-block partials)
   // shape of the last sweep launch: kernel (0 general, 1 uniform-row), users
   // per tile, blocks
@@ -245,6 +247,7 @@ kp_status ensure_ws(Ctx *c, size_t bytes) {
   if (c->max_ws) want = std::min(want, c->max_ws);
   if (hipMalloc(&c->ws, want) != hipSuccess) {
     c->ws = nullptr;
+    (void)hipGetLastError();   // (the next launch must not report it)
     return fail(KP_ERR_NOMEM, "hipMalloc of %zu workspace bytes failed", want);
   }
   c->ws_cap = want;
@@ -563,15 +566,16 @@ kp_status check_rows(Ctx *c, const int64_t *rowptr, int64_t nrows, unsigned int 
 }
 
 // How a search without a window starts (window: windows are on), over tiles of
-// U users: every (ntiles / samp_tiles)-th full tile is a sample.
-void choose_start(Prepared &P, int64_t sample_min, bool window, int U) {
+// U users: every (ntiles / samp_tiles)-th full tile is a sample, of at most
+// max_tiles tiles.
+void choose_start(Prepared &P, int64_t sample_min, bool window, int U, int64_t max_tiles = INT64_MAX) {
   const int64_t N = P.pr.N;
   P.frac = -1.0;
   const int64_t full = N / U;
   if (sample_min > 0 && N >= sample_min) {
     if (!window) return;
     const int64_t want = std::min(std::max(N / 16, kSampleUsersMin), std::min(N / 2, kSampleUsersMax));
-    P.samp_tiles = std::min(full / 2, std::max<int64_t>(1, want / U));
+    P.samp_tiles = std::min(std::min(full / 2, max_tiles), std::max<int64_t>(1, want / U));
     if (P.samp_tiles >= 1) {
       P.samp_stride = full / P.samp_tiles;
       P.samp_off = (P.samp_stride - 1) / 2;
@@ -626,7 +630,9 @@ struct SweepWs {
   size_t sel_clear;     // bytes of its histograms
 };
 
-kp_status carve_ws(Ctx *c, const Prepared &P, bool scd, SweepWs &w) {
+// small: the smallest emission and staging buffers (events that do not fit
+// cost further passes, no more), taken when the full ones cannot be allocated
+kp_status carve_ws(Ctx *c, const Prepared &P, bool scd, SweepWs &w, bool small = false) {
   const int K = P.pr.K;
   Carve cv;
   size_t o_part = cv.take((size_t)P.stage_grid() * (K + 2) * 8);
@@ -677,6 +683,10 @@ kp_status carve_ws(Ctx *c, const Prepared &P, bool scd, SweepWs &w) {
         cap = (uint32_t)std::min<size_t>(cap, std::max<size_t>(4096, left));
       }
     }
+    if (small) {
+      scap = kStageCap;
+      cap = std::min(cap, kEmitCapMin);
+    }
     o_e1 = cv.take((size_t)K * cap * 8);
     o_e2 = cv.take((size_t)K * cap * 8);
   }
@@ -693,7 +703,12 @@ kp_status carve_ws(Ctx *c, const Prepared &P, bool scd, SweepWs &w) {
     fcap = (uint32_t)(P.pr.N + (int64_t)KP_LIST_CHUNK * P.ell_grid * 4);
     o_fl = cv.take((size_t)fcap * 4);
   }
-  kp_status s = ensure_ws(c, cv.off);
+  const bool retry = scd && !small && !c->max_ws;
+  kp_status s = retry && c->ws_refused && cv.off >= c->ws_refused ? KP_ERR_NOMEM : ensure_ws(c, cv.off);
+  if (s == KP_ERR_NOMEM && retry) {
+    c->ws_refused = c->ws_refused ? std::min(c->ws_refused, cv.off) : cv.off;
+    return carve_ws(c, P, scd, w, true);
+  }
   if (s != KP_OK) return s;
   char *b = (char *)c->ws;
   w.partials = (double *)(b + o_part);
@@ -1589,8 +1604,9 @@ struct BatchPlan {
   double *hint = nullptr;   // [2 Kf] bucket widths and last steps carried between iterations
   double *frac = nullptr;   // [Kf] how a search without a window starts
   SweepArgs *sd[2] = {nullptr, nullptr};   // [dir] descriptors of the sampled pass
-  int *sboff = nullptr;     // [n+1] its blocks
-  int SB = 0;               // blocks of the sampled pass (0: no instance samples)
+  int *sboff = nullptr;     // its blocks, chunk by chunk
+  struct SampChunk { int first, n, blocks, tab; };   // instances, and where their block offsets start in sboff
+  std::vector<SampChunk> samp;   // launches of the sampled pass, over the same staging area
   int nohist = 0;           // the passes on the device run without histograms
   uint64_t *eoff = nullptr; // [Kf] start of each knapsack's emission buffer
   uint32_t *ecap = nullptr; // [Kf] its capacity
@@ -1685,8 +1701,9 @@ int plan_resplit(BatchPlan *p, int dir, int *blocks, size_t *lds) {
 // The sampled searches of a batch: a pass over the sampled tiles of the
 // instances with one, and their windows (nothing to do: the blocks exit).
 kp_status plan_sample_phase(BatchPlan *p, int dir, hipStream_t s) {
-  if (p->SB == 0) return KP_OK;
-  HIP_TRY(kp_launch_sweep_batched(p->sd[dir], p->geom, p->sboff, p->n, p->SB, p->lds, s));
+  if (p->samp.empty()) return KP_OK;
+  for (const BatchPlan::SampChunk &q : p->samp)
+    HIP_TRY(kp_launch_sweep_batched(p->sd[dir] + q.first, p->dhg + q.first, p->sboff + q.tab, q.n, q.blocks, p->lds, s));
   HIP_TRY(kp_launch_sample_window(p->kst, p->Kf, p->Bf, p->e1, p->e2, p->cap, p->sel, kSelBlocksBatched, s));
   return KP_OK;
 }
@@ -1854,12 +1871,17 @@ double stage_pairs(const Prepared &P) {
   return (double)P.pr.N * P.pr.K * (P.frac == 0.0 ? 64.0 * pair_events(P) : 1.0);
 }
 
-uint32_t samp_stage(const Prepared &P) {
-  return (uint32_t)std::min(65536.0, (double)P.U * P.pr.K * pair_events(P));
+uint32_t samp_stage(const Prepared &P, int U) {
+  return (uint32_t)std::min(65536.0, (double)U * P.pr.K * pair_events(P));
+}
+// Sampled tiles of an instance whose staged events (18 bytes each) fit one launch.
+int64_t samp_max_tiles(const Prepared &P, int U) {
+  return std::max<int64_t>(1, (int64_t)(kStageBytesBatched / 18 / samp_stage(P, U)));
 }
 
-// lean: the smaller buffers of a plan whose context's workspace is capped (no
-// sampled starts, fewer emitted events: those that do not fit cost passes)
+// lean: the smaller buffers of a plan that a capped workspace or the device's
+// free memory has no room for otherwise (no sampled starts, fewer emitted
+// events: those that do not fit cost passes)
 kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *const *lam_a,
                       double *const *lam_b, BatchPlan **out, bool lean = false) {
   if (n < 1 || !probs || !lam_a || !lam_b) return fail(KP_ERR_INVALID, "bad batch arguments");
@@ -1892,7 +1914,8 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
   // for a pass from the host, on the tiles that leave room for them.
   bool nohist = !lean;
   for (auto &q : P) {
-    if (!lean) choose_start(q, c->sample_min, c->window_enabled, tile_users(q, q.U_nh, false));
+    const int U = tile_users(q, q.U_nh, false);
+    if (!lean) choose_start(q, c->sample_min, c->window_enabled, U, samp_max_tiles(q, U));
     nohist = nohist && q.frac >= 0.0;
   }
   std::vector<int> Uh(n);
@@ -1900,7 +1923,7 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
     Prepared &q = P[s];
     Uh[s] = tile_users(q, q.U, true);
     q.U = nohist ? tile_users(q, q.U_nh, false) : Uh[s];
-    if (!lean && !nohist) choose_start(q, c->sample_min, c->window_enabled, q.U);
+    if (!lean && !nohist) choose_start(q, c->sample_min, c->window_enabled, q.U, samp_max_tiles(q, q.U));
     q.ntiles = (q.pr.N + q.U - 1) / q.U;
   }
   auto hist_lds = [&](int s) { return kp_sweep_lds_bytes(Uh[s], P[s].pr.M, P[s].pr.K, P[s].tree.L, true, P[s].pr.fmt); };
@@ -1990,18 +2013,42 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
     soff[s + 1] = soff[s] + (size_t)nb * scap[s];
   }
   // the sampled pass: a block per sampled tile, its staging every event
-  // of the tile, over the same area
-  std::vector<int> sboff(n + 1, 0);
-  size_t sstage = 0;
-  for (int s = 0; s < n; ++s) sstage += P[s].frac > 0.0 ? (size_t)P[s].samp_tiles * samp_stage(P[s]) : 0;
-  const size_t stage_all = std::max(soff[n], sstage);
+  // of the tile, over the same area; instances whose samples together would
+  // outgrow kStageBytesBatched run in several launches, one after another
+  // (staged at once, 256 instances of 33000 users, M = 32, K = 16, took 33 GB)
+  std::vector<int> sboff;
+  std::vector<size_t> sso(n, 0);
+  size_t stage_all = soff[n];
+  {
+    size_t used = 0;
+    BatchPlan::SampChunk q = {0, 0, 0, 0};
+    sboff.push_back(0);
+    auto close = [&](int next) {
+      if (q.blocks) p->samp.push_back(q);
+      stage_all = std::max(stage_all, used);
+      used = 0;
+      q = {next, 0, 0, (int)sboff.size()};
+      sboff.push_back(0);
+    };
+    for (int s = 0; s < n; ++s) {
+      const size_t tiles = P[s].frac > 0.0 ? (size_t)P[s].samp_tiles : 0;
+      const size_t need = tiles * samp_stage(P[s], P[s].U);
+      if (used && (used + need) * 18 > kStageBytesBatched) close(s);
+      sso[s] = used;
+      used += need;
+      q.n += 1;
+      q.blocks += (int)tiles;
+      sboff.push_back(q.blocks);
+    }
+    close(n);
+  }
   const size_t o_s1 = cv.take(stage_all * 8);
   const size_t o_s2 = cv.take(stage_all * 8);
   const size_t o_sk = cv.take(stage_all * 2);
   const size_t o_frac = cv.take((size_t)Kf * 8);
   const size_t o_sd0 = cv.take((size_t)n * sizeof(SweepArgs));
   const size_t o_sd1 = cv.take((size_t)n * sizeof(SweepArgs));
-  const size_t o_sbo = cv.take((size_t)(n + 1) * 4);
+  const size_t o_sbo = cv.take(sboff.size() * 4);
   const size_t o_err = cv.take(8);
   const size_t o_pend = cv.take(8);
   const size_t o_off = cv.take((size_t)n * 4);
@@ -2034,7 +2081,9 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
   }
   if (hipMalloc(&p->ws, cv.off) != hipSuccess) {
     p->ws = nullptr;
+    (void)hipGetLastError();   // (the next launch must not report it)
     plan_free(p);
+    if (!lean) return plan_create(c, probs, n, lam_a, lam_b, out, true);
     return fail(KP_ERR_NOMEM, "hipMalloc of %zu plan bytes failed", cv.off);
   }
   if (hipHostMalloc((void **)&p->pinned, 64 + (size_t)n * 4, hipHostMallocDefault) != hipSuccess) {
@@ -2114,7 +2163,6 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
   std::vector<SweepArgs> hd[2][2], hsd[2];
   for (int d = 0; d < 2; ++d) hsd[d].resize(n);
   std::vector<double> hfrac(Kf);
-  size_t sso = 0;
   for (int d = 0; d < 2; ++d) for (int f = 0; f < 2; ++f) hd[d][f].resize(n);
   std::vector<TileGeom> hg(n);
   std::vector<double> hB(Kf), hchk(3 * (size_t)n);
@@ -2160,13 +2208,12 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
       q.ntiles = P[s].frac > 0.0 ? P[s].samp_tiles : 0;
       q.tstride = P[s].samp_stride;
       q.toff = P[s].samp_off;
-      q.stage_cap = samp_stage(P[s]);
-      q.stage_v1 = p->s1 + sso;
-      q.stage_v2 = p->s2 + sso;
-      q.stage_k = p->sk + sso;
+      q.stage_cap = samp_stage(P[s], P[s].U);
+      q.stage_v1 = p->s1 + sso[s];
+      q.stage_v2 = p->s2 + sso[s];
+      q.stage_k = p->sk + sso[s];
       hsd[d][s] = q;
     }
-    sso += (size_t)hsd[0][s].ntiles * hsd[0][s].stage_cap;
     sum_check(P[s], boff[s + 1] - boff[s], &hchk[3 * s], &hchk[3 * s + 1], &hchk[3 * s + 2]);
     hg[s] = kp_tile_geom(hd[0][1][s], P[s].U);
     for (int k = 0; k < K; ++k) {
@@ -2206,22 +2253,17 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
   std::vector<int> bpos(n + 1, 0);
   std::vector<SweepArgs> pd[2][2];
   std::vector<TileGeom> pg(n);
-  std::vector<SweepArgs> psd[2];
-  for (int d = 0; d < 2; ++d) psd[d].resize(n);
   for (int d = 0; d < 2; ++d) for (int f = 0; f < 2; ++f) pd[d][f].resize(n);
   for (int i = 0; i < n; ++i) {
     const int si = ord[i];
     bpos[i + 1] = bpos[i] + (boff[si + 1] - boff[si]);
     for (int d = 0; d < 2; ++d) for (int f = 0; f < 2; ++f) pd[d][f][i] = hd[d][f][si];
     pg[i] = hg[si];
-    for (int d = 0; d < 2; ++d) psd[d][i] = hsd[d][si];
-    sboff[i + 1] = sboff[i] + (int)hsd[0][si].ntiles;
   }
-  p->SB = sboff[n];
   for (int d = 0; d < 2 && e == hipSuccess; ++d)
     for (int f = 0; f < 2 && e == hipSuccess; ++f) e = up(p->d[d][f], pd[d][f].data(), (size_t)n * sizeof(SweepArgs));
-  for (int d = 0; d < 2 && e == hipSuccess; ++d) e = up(p->sd[d], psd[d].data(), (size_t)n * sizeof(SweepArgs));
-  if (e == hipSuccess) e = up(p->sboff, sboff.data(), (size_t)(n + 1) * 4);
+  for (int d = 0; d < 2 && e == hipSuccess; ++d) e = up(p->sd[d], hsd[d].data(), (size_t)n * sizeof(SweepArgs));
+  if (e == hipSuccess) e = up(p->sboff, sboff.data(), sboff.size() * 4);
   if (e == hipSuccess) e = up(p->frac, hfrac.data(), (size_t)Kf * 8);
   if (e == hipSuccess) e = up(w + o_chk, hchk.data(), (size_t)n * 24);
   if (e == hipSuccess) e = up(p->geom, pg.data(), (size_t)n * sizeof(TileGeom));

@@ -1754,3 +1754,78 @@ def test_batched_misled_sample(fmt, use_graph):
     print("passes per iteration", passes, flush=True)
     # the first, one or more with histograms; the graph's two device passes lie between
     assert max(passes) >= (4 if use_graph else 3)
+
+
+def _fill_memory(torch, keep):
+    """A tensor that leaves about keep bytes of the GPU's memory free."""
+    torch.cuda.empty_cache()
+    free, _ = torch.cuda.mem_get_info()
+    return torch.empty(free - keep, dtype=torch.uint8, device="cuda")
+
+
+@gpu
+def test_scd_with_little_memory_left():
+    """A sweep whose full workspace does not fit the memory left (2 GB of
+    emission buffers for 3.2e7 users, 1 GB free) runs with smaller buffers: the
+    same multipliers as with room, and the context stays usable."""
+    kp, torch = _kp()
+    N, K = 32_000_000, 64
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    p = torch.rand(N, generator=gen, device="cuda")
+    val = torch.rand(N, generator=gen, device="cuda")
+    col = torch.randint(0, K, (N,), generator=gen, device="cuda", dtype=torch.int32)
+    rowptr = torch.arange(N + 1, device="cuda", dtype=torch.int64)
+    B = 0.05 * torch.zeros(K, dtype=torch.float64, device="cuda").index_add_(0, col.long(), val.double()).cpu().numpy()
+    prob = kp.Problem(p, B, [-1], [1], [0], rowptr=rowptr, col=col, val=val, N=N, M=1, K=K, row_nnz=1)
+    lam = _lamd(torch, np.zeros(K))
+    ctx = kp.Context()
+    want = [kp.kp_scd_sweep(prob, lam, ctx=ctx)["lam"]]
+    want.append(kp.kp_scd_sweep(prob, want[0], ctx=ctx)["lam"])
+    ctx.close()
+    hog = _fill_memory(torch, 1 << 30)
+    ctx = kp.Context()
+    print("case little memory", torch.cuda.mem_get_info(), flush=True)
+    for x, w in ((lam, want[0]), (want[0], want[1])):
+        assert torch.equal(kp.kp_scd_sweep(prob, x, ctx=ctx)["lam"], w)
+    del hog
+    torch.cuda.empty_cache()
+    ev = kp.kp_eval_dual(prob, want[1], ctx=ctx)
+    assert torch.equal(ev["R"], kp.kp_eval_dual(prob, want[1])["R"])
+    assert torch.equal(kp.kp_scd_sweep(prob, lam, ctx=ctx)["lam"], want[0])
+    ctx.close()
+
+
+@gpu
+def test_batched_plan_memory():
+    """A plan over 100 instances of 33000 users (M = 32, K = 16): its workspace
+    stays below the bound of its emission buffers (8e9 bytes) and its staging
+    (2 GiB) plus 1e9 for the rest, and a plan that the memory left has no room
+    for takes smaller buffers; every instance gets the multipliers of a sweep
+    alone."""
+    kp, torch = _kp()
+    from util import make
+    N, M, K, n = 33_000, 32, 16, 100
+    rng = np.random.default_rng(33)
+    b = rng.integers(0, 1 << 20, (N, M, K)).astype(np.float32) / np.float32(1 << 20)
+    inst = make(rng.random((N, M)), b, 0.05 * b.sum(axis=(0, 1), dtype=np.float64), kpgen.tree_topq(M, 4))
+    prob = kp.Problem.from_host(inst)
+    want = kp.kp_scd_sweep(prob, _lamd(torch, np.zeros(K)))["lam"]
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    hog = None
+    for keep in (0, 4 << 30):
+        if keep:
+            hog = _fill_memory(torch, keep)
+        before = torch.cuda.mem_get_info()[0]
+        plan = kp.BatchedSCD([prob] * n)
+        used = before - torch.cuda.mem_get_info()[0]
+        print("plan bytes", used, "kept free", keep, flush=True)
+        assert used < 8.0e9 + (2 << 30) + 1.0e9
+        outs, _ = plan.step()
+        torch.cuda.synchronize()
+        for out in outs:
+            assert torch.equal(out, want)
+        plan.close()
+    del hog
+    torch.cuda.empty_cache()
