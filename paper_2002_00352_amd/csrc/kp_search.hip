@@ -751,13 +751,16 @@ __global__ void k_scd_finish(const KState *st, int K, const double *lam_in, doub
 // short of it by as much.  The sum of n increments from a sample deviates by
 // about 1.3 / sqrt(n) of itself (increments of a spread like the uniform's);
 // at 3.5 deviations a window misses once in thousands.  A sample with too
-// few breakpoints above the threshold, or one that overflowed its buffer,
-// opens the window over everything.  Exactness does not depend on any of it:
-// the window's search compares exact sums over all users, and a miss falls
-// back to the buckets.
+// few breakpoints above the threshold opens the window over everything, when
+// the emission buffer can be expected to hold all users' breakpoints; a sample
+// that overflowed it tells that it cannot, and the search goes on with
+// buckets at once (a window over everything emitted and dropped every
+// breakpoint first: 21 ms of 91 for 2e5 users with M = 32, K = 16, Q = 20).
+// Exactness does not depend on any of it: a window's search is decided
+// exactly over all users, and a miss falls back to the buckets.
 #define KP_SAMPLE_DEV 4.5
 #define SW_NT 256
-__global__ void __launch_bounds__(SW_NT) k_sample_window(KState *st, const double *B, SelWs w) {
+__global__ void __launch_bounds__(SW_NT) k_sample_window(KState *st, const double *B, uint32_t emit_cap, SelWs w) {
   const int k = blockIdx.x, tid = threadIdx.x;
   if (!(st[k].flags & KS_FLAG_SAMPLE) || st[k].mode != KS_EMIT_RANGE) return;
   __shared__ KState s;
@@ -778,7 +781,8 @@ __global__ void __launch_bounds__(SW_NT) k_sample_window(KState *st, const doubl
   }
   __syncthreads();
   double wlo = 0.0, whi = INFINITY;
-  if (any && !s.overflow) {
+  bool buckets = s.overflow != 0;
+  if (any && !buckets) {
     const double Bs = B[k] * s.frac;
     const int shift = sel_shift(s.hull_lo, s.hull_hi, SEL_BITS);
     sel_pick<SEL_BINS, SW_NT>(hs, hc, xs_zero(), Bs, part, &bin, &cum);
@@ -808,7 +812,17 @@ __global__ void __launch_bounds__(SW_NT) k_sample_window(KState *st, const doubl
         const uint64_t key = s.hull_lo + ((uint64_t)bl << shift);
         wlo = kdbl(key - one);
       }
+    } else {
+      buckets = (double)s.n_emit > s.frac * (double)(s.ecap ? s.ecap : emit_cap);
     }
+  }
+  if (buckets) {
+    if (tid == 0) {
+      s.flags |= KS_FLAG_TRIED;
+      search_start(s);
+      st[k] = s;
+    }
+    return;
   }
   if (tid == 0) {
     const double l = s.center;   // lambda_k^t
@@ -1035,6 +1049,6 @@ hipError_t kp_launch_scd_finish(const KState *st, int K, const double *lam_in, d
 hipError_t kp_launch_sample_window(KState *st, int K, const double *B, const double *ev1, const double *ev2,
                                    uint32_t emit_cap, const SelWs &w, int blocks, hipStream_t stream) {
   hipLaunchKernelGGL(k_sel_hist, dim3(K, blocks), dim3(SH_NT), 0, stream, st, ev1, ev2, emit_cap, w, 1);
-  hipLaunchKernelGGL(k_sample_window, dim3(K), dim3(SW_NT), 0, stream, st, B, w);
+  hipLaunchKernelGGL(k_sample_window, dim3(K), dim3(SW_NT), 0, stream, st, B, emit_cap, w);
   return hipGetLastError();
 }

@@ -1829,3 +1829,31 @@ def test_batched_plan_memory():
         plan.close()
     del hog
     torch.cuda.empty_cache()
+
+
+@gpu
+def test_overflowed_sample_goes_to_buckets():
+    """A sample with more breakpoints than the (capped) workspace holds: the
+    searches go on with buckets, without a window over all users that could
+    only overflow too; the multipliers are the oracle's."""
+    kp, torch = _kp()
+    from util import make
+    rng = np.random.default_rng(44)
+    N, M, K = 40_001, 6, 8
+    b = rng.integers(1, 1 << 20, (N, M, K)) / float(1 << 20)
+    inst = make(rng.random((N, M)), b, 0.05 * b.sum(axis=(0, 1)), kpgen.tree_topq(M, 4))
+    prob = kp.Problem.from_host(inst)
+    want = oracle.scd_sweep(inst, np.zeros(K))
+    size, ctx = 1 << 20, None
+    while ctx is None:   # the smallest accepted workspace: 4096 events per knapsack
+        c = kp.Context(max_workspace_bytes=size)
+        try:
+            got = kp.kp_scd_sweep(prob, _lamd(torch, np.zeros(K)), ctx=c)["lam"].cpu().numpy()
+            ctx = c
+        except kp.KPError as e:
+            assert kp.STATUS[e.status] == "KP_ERR_NOMEM"
+            c.close()
+            size = int(size * 1.02)
+    print("case workspace", size, "windows", ctx.window_stats(), flush=True)
+    assert np.array_equal(got, want)
+    assert ctx.window_stats()[0] == 0
