@@ -587,11 +587,13 @@ void choose_start(Prepared &P, int64_t sample_min, bool window, int U, int64_t m
   if (N <= kSampleMin) P.frac = 0.0;
 }
 
-// Breakpoints of a (user, knapsack) pair, roughly: every item that moves with
-// the knapsack enters, and a few leave and enter again.
+// Breakpoints of a (user, knapsack) pair, at most on average: every item that
+// moves with the knapsack enters, and a few leave and enter again (dense
+// M = 32, K = 8: 8.8 with Q = 4, 24 with Q = 20, 32 without a cap).  The rows of
+// general CSR costs are not known here: as if every item moved (8 instead
+// overflowed the buffers of long rows and cost passes).
 double pair_events(const Prepared &P) {
-  if (P.pr.fmt == KP_B_DENSE) return P.pr.M + 4.0;
-  return P.row_nnz ? 2.0 + 2.0 * P.pr.M * P.row_nnz / P.pr.K : 8.0;
+  return P.row_nnz ? 2.0 + 2.0 * P.pr.M * P.row_nnz / P.pr.K : P.pr.M + 4.0;
 }
 
 // What a window's search needs to know about the FP64 consumption of a pass

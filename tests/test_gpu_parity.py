@@ -1832,6 +1832,26 @@ def test_batched_plan_memory():
 
 
 @gpu
+@pytest.mark.parametrize("N", [3001, 34_003])
+def test_long_rows_emit_at_once(N):
+    """General CSR rows with an entry in every knapsack and a loose cap (15
+    breakpoints per user and knapsack): a search from zero emits every
+    breakpoint of the users, or of a sample, without running out of room: one
+    sweep pass, or the sample's and one more."""
+    kp, torch = _kp()
+    print("case", N, flush=True)
+    rng = np.random.default_rng(N)
+    inst = random_instance(rng, N, 18, 4, Q=12, frac=0.2).to_csr()
+    prob = _general_rows(kp, inst)
+    ctx = kp.Context()
+    ctx.set_timing(True)
+    got = kp.kp_scd_sweep(prob, _lamd(torch, np.zeros(inst.K)), ctx=ctx)["lam"].cpu().numpy()
+    print("sweep passes", ctx.timing()[1], flush=True)
+    assert np.array_equal(got, oracle.scd_sweep(inst, np.zeros(inst.K)))
+    assert ctx.timing()[1] == (1 if N < 32768 else 2)
+
+
+@gpu
 def test_overflowed_sample_goes_to_buckets():
     """A sample with more breakpoints than the (capped) workspace holds: the
     searches go on with buckets, without a window over all users that could
