@@ -240,7 +240,8 @@ kp_status kp_tree_from_sets(int32_t M, int32_t L, const int32_t *set_offsets,
    intervals and their algorithmic input bytes: every byte of p and b in the
    layout above once per interval (dense 4*N*M*(1+K); CSR
    4*N*M + 8*(N*M+1) + 8*nnz, rowptr included even where the lean kernel does
-   not read it; a batched iteration: the sum over its instances).
+   not read it; a sampled pass its share of the users' bytes; a batched
+   iteration: the sum over its instances).
    kp_get_batched_passes: the sweep passes inside the timed batched
    iterations.  kp_set_timing resets the totals. */
 kp_status kp_set_timing(void *ctx, int32_t on);

@@ -828,7 +828,7 @@ hipError_t timed_sweep(Ctx *c, const SweepArgs &a, const Prepared &P, bool scd, 
     (void)hipEventRecord(e1, c->stream);
     c->ev_pending.push_back({e0, e1});
     c->sweep_launches += 1;
-    c->sweep_bytes += bytes;
+    c->sweep_bytes += a.sampled ? bytes * P.frac : bytes;   // a sampled pass reads its share of the users
     if (c->ev_pending.size() > 256) drain_events(c, true);
   }
   if (err == hipSuccess) {
@@ -897,7 +897,7 @@ kp_status sample_phase(Ctx *c, const Prepared &P, const SweepWs &w, const double
   a.tstride = P.samp_stride;
   a.toff = P.samp_off;
   HIP_TRY(hipMemsetAsync(w.sel.hsum, 0, w.sel_clear, c->stream));
-  HIP_TRY(timed_sweep(c, a, P, true, P.bytes * P.frac));
+  HIP_TRY(timed_sweep(c, a, P, true, P.bytes));
   HIP_TRY(kp_launch_sample_window(w.st, P.pr.K, w.B, w.ev1, w.ev2, w.emit_cap, w.sel, kSelBlocks, c->stream));
   return KP_OK;
 }

@@ -1877,3 +1877,24 @@ def test_overflowed_sample_goes_to_buckets():
     print("case workspace", size, "windows", ctx.window_stats(), flush=True)
     assert np.array_equal(got, want)
     assert ctx.window_stats()[0] == 0
+
+
+@gpu
+@pytest.mark.parametrize("kind", ["dense", "rows", "general-rows"])
+def test_timing_counts_a_sample_as_its_share(kind):
+    """kp_get_timing credits the sampled pass of a first sweep with its share of
+    the input bytes (12288 of 40960 users in whole tiles, so at most 0.3 of
+    them), the window pass with all of them."""
+    kp, torch = _kp()
+    print("case", kind, flush=True)
+    N = 40_960
+    inst = kpgen.make_instance(N, 8, 5, seed=3, Q=2, budget_frac=0.05, **({} if kind == "dense" else {"csr_d": 2}))
+    prob = _general_rows(kp, inst) if kind == "general-rows" else kp.Problem.from_host(inst)
+    ctx = kp.Context()
+    ctx.set_timing(True)
+    kp.kp_scd_sweep(prob, _lamd(torch, np.zeros(inst.K)), ctx=ctx)
+    _, launches, got = ctx.timing()
+    full = 4 * N * 8 * 6 if kind == "dense" else 4 * N * 8 + 8 * (N * 8 + 1) + 8 * N * 8 * 2
+    print("launches", launches, "bytes", got, "of", full, flush=True)
+    assert launches == 2
+    assert 1.25 * full < got <= 1.3 * full + 1
