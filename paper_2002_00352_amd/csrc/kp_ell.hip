@@ -43,7 +43,7 @@ int kp_ell_max_items(int D) { return D == 1 ? 24 : 20; }
 // class of item counts would spill); above 16 items see launch_ell_big.
 int kp_ell_waves(int M, int K, int D, int L, int mode) {
   if (M > 16) return mode == KM_SCD && ell_lds(M, K, D, L, mode, EW, nullptr) <= (size_t)160 * 1024 ? EW : 2;
-  const bool exact = M == 8 || M == 10 || M == 12 || M == 16;
+  const bool exact = M == 8 || M == 10 || M == 12 || (M == 16 && D == 1);
   if (mode == KM_SCD && exact && ell_lds(M, K, D, L, mode, 8, nullptr) <= (size_t)160 * 1024) return 8;
   return EW;
 }

@@ -639,9 +639,8 @@ k_ell(const SweepArgs a, const EllGeom g) {
     // from the kernel arguments into scalar registers.
     uint64_t S = 0;
     uint32_t rbit[EM];   // 1 << rank (the rank itself is its lowest set bit)
-    double thr[BREAK ? EM : 1];
+    uint32_t alive = 0;
     {
-      uint32_t alive = 0;
       #pragma unroll
       for (int j = 0; j < EM; ++j) {
         rbit[j] = j < M ? 1u << rk[j] : 0u;
@@ -664,31 +663,6 @@ k_ell(const SweepArgs a, const EllGeom g) {
       for (int j = 0; j < EM; ++j)
         if (alive & rbit[j]) S32 |= 1u << j;
       S = S32;
-      if (BREAK) {
-        // per item outside S: the value it has to pass to come in while the
-        // selected items stay (the lowest member of the innermost full set
-        // that holds it, or zero)
-        uint32_t set = 0;
-        #pragma unroll
-        for (int j = 0; j < EM; ++j) thr[j] = 0.0;
-        for (int l = 0; l < L; ++l) {
-          const uint32_t m = (uint32_t)a.tree.mask[l];
-          uint32_t mr = 0;
-          #pragma unroll
-          for (int j = 0; j < EM; ++j)
-            if (m >> j & 1u) mr |= rbit[j];
-          const uint32_t x = alive & mr;
-          if (__popc(x) < a.tree.cap[l]) continue;
-          const uint32_t low = 1u << (31 - __clz((int)x));
-          double zl = 0.0;
-          #pragma unroll
-          for (int j = 0; j < EM; ++j) zl = rbit[j] == low ? pt[j] : zl;
-          #pragma unroll
-          for (int j = 0; j < EM; ++j)
-            if ((m & ~set) >> j & 1u) thr[j] = zl;
-          set |= m;
-        }
-      }
     }
     double bmax = 0.0;
     if (!EV) {
@@ -942,6 +916,32 @@ k_ell(const SweepArgs a, const EllGeom g) {
       }
     }
     if (BREAK) {
+      // per item outside S: the value it has to pass to come in while the
+      // selected items stay (the lowest member of the innermost full set
+      // that holds it, or zero); made here, where the profits and the
+      // statistics' values are dead: next to the ranks it held registers
+      // through the statistics and M = 16 spilled
+      double thr[EM];
+      uint32_t set = 0;
+      #pragma unroll
+      for (int j = 0; j < EM; ++j) thr[j] = 0.0;
+      for (int l = 0; l < L; ++l) {
+        const uint32_t m = (uint32_t)a.tree.mask[l];
+        uint32_t mr = 0;
+        #pragma unroll
+        for (int j = 0; j < EM; ++j)
+          if (m >> j & 1u) mr |= rbit[j];
+        const uint32_t x = alive & mr;
+        if (__popc(x) < a.tree.cap[l]) continue;
+        const uint32_t low = 1u << (31 - __clz((int)x));
+        double zl = 0.0;
+        #pragma unroll
+        for (int j = 0; j < EM; ++j) zl = rbit[j] == low ? pt[j] : zl;
+        #pragma unroll
+        for (int j = 0; j < EM; ++j)
+          if ((m & ~set) >> j & 1u) thr[j] = zl;
+        set |= m;
+      }
       // per-lane scratch over the dead staging area: p~ [M][64], the stored
       // costs and their knapsacks [M*D][64], moving-item masks [K][64]
       const EllScratch sl = ell_scratch(M, D, K);
@@ -1079,7 +1079,9 @@ static hipError_t launch_ell_mw(const SweepArgs &a, const EllGeom &g, size_t lds
     case 8: return launch_ell_x<D, MODE, 8, WPB>(a, g, lds, grid, stream, used);
     case 10: return launch_ell_x<D, MODE, 10, WPB>(a, g, lds, grid, stream, used);
     case 12: return launch_ell_x<D, MODE, 12, WPB>(a, g, lds, grid, stream, used);
-    case 16: return launch_ell_x<D, MODE, 16, WPB>(a, g, lds, grid, stream, used);
+    case 16:   // (two entries per item in 8 waves: more LDS than there is, and registers spill)
+      if constexpr (WPB == EW || D == 1) return launch_ell_x<D, MODE, 16, WPB>(a, g, lds, grid, stream, used);
+      break;
     default: break;
   }
   if constexpr (WPB != EW) {
@@ -1176,7 +1178,9 @@ static int resident_blocks_mw(int M, size_t lds) {
     case 8: return resident_blocks_x<D, MODE, 8, WPB>(lds);
     case 10: return resident_blocks_x<D, MODE, 10, WPB>(lds);
     case 12: return resident_blocks_x<D, MODE, 12, WPB>(lds);
-    case 16: return resident_blocks_x<D, MODE, 16, WPB>(lds);
+    case 16:
+      if constexpr (WPB == EW || D == 1) return resident_blocks_x<D, MODE, 16, WPB>(lds);
+      break;
     default: break;
   }
   if constexpr (WPB != EW) {
