@@ -69,7 +69,7 @@ int kp_ell_resident_grid(int D, int mode, int M, int K, int L);
 hipError_t kp_launch_dense(const SweepArgs &a, int grid, hipStream_t stream, int *used, bool win);
 int kp_dense_tile_users();
 int kp_dense_resident_grid(int M, int K, int L, bool win);
-hipError_t kp_launch_count_modes(const KState *st, int K, int *out, hipStream_t stream);
+hipError_t kp_launch_count_modes(const KState *st, int K, double reach, int *out, hipStream_t stream);
 hipError_t kp_launch_dense_probe(const SweepArgs &a, int *out, hipStream_t stream);
 hipError_t kp_launch_ell_check(const int64_t *rowptr, int64_t nrows, int D, unsigned int *bad,
                                hipStream_t stream);
@@ -129,6 +129,16 @@ constexpr int kMaxGrid = 2048;
 // iteration, SAMPLED_MS ms); smaller instances emit every breakpoint at once.
 constexpr int64_t kSampleMin = 32768;
 constexpr int64_t kSampleUsersMin = 12288, kSampleUsersMax = 1 << 18;
+// Windows from a sample go to the uniform-row kernel's split pass from this
+// many users on, and when none reaches farther than this share of lambda_k^t
+// from it: its gap filter lists few users then (two costs per item, M = 10,
+// K = 20, a first sweep from 1.15 times the solution, step 0.2 of
+// lambda: 2e7 users 4.5 -> 4.2 ms, 5e6 1.43 either way; from 0.85 or 1.3 times,
+// step 0.27-0.34, the full-search kernel 5.8 and 4.4, the split pass 6.0 and
+// 4.8; 1e8 users, second to fourth sweep from zero, 22.3, 22.8, 21.2 -> 15.0,
+// 13.0, 10.7 ms).
+constexpr int64_t kSplitSampledMin = (int64_t)1 << 22;
+constexpr double kSplitReach = 0.1875;
 constexpr int kMaxPasses = 96;
 constexpr uint32_t kStageCap = 4096;    // staged events per block per pass (at least)
 constexpr uint32_t kStageCapMax = 65536;
@@ -1089,7 +1099,7 @@ kp_status kp_scd_sweep_masked(void *ctx, const kp_problem *prob, const double *l
   const bool counts = window && c->delta_valid && (w.fcap || P.dwin_grid || P.frac != 0.0);
   bool searching = sample && !counts;   // some knapsack starts from the sample
   if (counts) {
-    HIP_TRY(kp_launch_count_modes(w.st, K, w.modes, c->stream));
+    HIP_TRY(kp_launch_count_modes(w.st, K, 0.0, w.modes, c->stream));
     const bool probe = P.dwin_grid != 0;
     if (probe) HIP_TRY(kp_launch_dense_probe(make_args(P, lambda_in, w, nullptr, true), w.modes + 3, c->stream));
     HIP_TRY(hipMemcpyAsync(c->pinned + 20, w.modes, 16, hipMemcpyDeviceToHost, c->stream));
@@ -1108,7 +1118,17 @@ kp_status kp_scd_sweep_masked(void *ctx, const kp_problem *prob, const double *l
   }
   const bool nohist = !P.ell_D && !c->interp && P.pr.N > 0 && (P.frac >= 0.0 || (counts && c->pinned[21] == 0));
   HIP_TRY(hipMemsetAsync(w.stat, 0, w.stat_bytes, c->stream));   // status, histograms
-  if (searching && (s = sample_phase(c, P, w, lambda_in)) != KP_OK) return s;
+  if (searching) {
+    if ((s = sample_phase(c, P, w, lambda_in)) != KP_OK) return s;
+    // many users: the split pass also takes the sample's windows when they all
+    // lie near lambda^t (the counts are read back: about 20 us)
+    if (w.fcap && window && P.pr.N >= kSplitSampledMin) {
+      HIP_TRY(kp_launch_count_modes(w.st, K, kSplitReach, w.modes, c->stream));
+      HIP_TRY(hipMemcpyAsync(c->pinned + 20, w.modes, 16, hipMemcpyDeviceToHost, c->stream));
+      HIP_TRY(hipStreamSynchronize(c->stream));
+      split = c->pinned[20] > 0 && c->pinned[21] == 0 && c->pinned[22] == 0;
+    }
+  }
   double *Rd = R ? R : w.Rtmp;
   double *gd = g ? g : w.gtmp;
   double *Pd = primal ? primal : w.Ptmp;

@@ -846,9 +846,10 @@ __global__ void __launch_bounds__(SW_NT) k_sample_window(KState *st, const doubl
 
 // Knapsacks starting with a window and those needing another search mode.
 // out[0]: knapsacks searching with a window, out[1]: with another search
-// mode, out[2]: windows that do not contain lambda_k^t (alternation windows);
+// mode, out[2]: windows that do not contain lambda_k^t (alternation windows),
+// or with reach > 0 windows that extend farther than reach lambda_k^t from it;
 // out[3] is cleared (the dense window pass's probe counts into it)
-__global__ void k_count_modes(const KState *st, int K, int *out) {
+__global__ void k_count_modes(const KState *st, int K, double reach, int *out) {
   __shared__ int c[3];
   if (threadIdx.x < 3) c[threadIdx.x] = 0;
   __syncthreads();
@@ -856,7 +857,8 @@ __global__ void k_count_modes(const KState *st, int K, int *out) {
     const KState &s = st[k];
     if (s.mode == KS_WINDOW) {
       atomicAdd(&c[0], 1);
-      if (s.far) atomicAdd(&c[2], 1);
+      // (result: lambda_k^t until the search ends)
+      if (reach > 0.0 ? !(s.hw <= reach * s.result) : s.far != 0) atomicAdd(&c[2], 1);
     } else if (s.mode != KS_DONE) {
       atomicAdd(&c[1], 1);
     }
@@ -1032,8 +1034,8 @@ hipError_t kp_launch_scd_select_many(KState *st, int K, const double *B, const d
   return hipGetLastError();
 }
 
-hipError_t kp_launch_count_modes(const KState *st, int K, int *out, hipStream_t stream) {
-  hipLaunchKernelGGL(k_count_modes, dim3(1), dim3(256), 0, stream, st, K, out);
+hipError_t kp_launch_count_modes(const KState *st, int K, double reach, int *out, hipStream_t stream) {
+  hipLaunchKernelGGL(k_count_modes, dim3(1), dim3(256), 0, stream, st, K, reach, out);
   return hipGetLastError();
 }
 

@@ -1898,3 +1898,33 @@ def test_timing_counts_a_sample_as_its_share(kind):
     print("launches", launches, "bytes", got, "of", full, flush=True)
     assert launches == 2
     assert 1.25 * full < got <= 1.3 * full + 1
+
+
+@gpu
+def test_sampled_windows_take_the_split_pass():
+    """A first sweep over 4.2e6 users from near the solution: the sample's
+    windows reach lambda^t's neighbourhood only, so the uniform-row kernel's
+    split pass runs them (it counts the users it lists); from zero and from
+    far away the full-search kernel does.  All give the multipliers of the
+    exact buckets."""
+    kp, torch = _kp()
+    N, M, K = (1 << 22) + 77, 5, 3
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(8)
+    p = torch.rand(N * M, generator=gen, device="cuda")
+    val = torch.rand(N * M, generator=gen, device="cuda")
+    col = torch.randint(0, K, (N * M,), generator=gen, device="cuda", dtype=torch.int32)
+    rowptr = torch.arange(N * M + 1, device="cuda", dtype=torch.int64)
+    B = 0.05 * torch.zeros(K, dtype=torch.float64, device="cuda").index_add_(0, col.long(), val.double()).cpu().numpy()
+    prob = kp.Problem(p, B, [-1], [2], [0] * M, rowptr=rowptr, col=col, val=val, N=N, M=M, K=K, row_nnz=1)
+    buckets = kp.Context()
+    buckets.set_window(False)
+    lam = _lamd(torch, np.zeros(K))
+    for _ in range(8):
+        lam = kp.kp_scd_sweep(prob, lam, ctx=buckets)["lam"]
+    for name, start, near in (("zero", lam * 0.0, False), ("near", lam * 1.05, True), ("far", lam * 3.0, False)):
+        ctx = kp.Context()
+        got = kp.kp_scd_sweep(prob, start, ctx=ctx)["lam"]
+        print("case", name, "listed", ctx.window_listed(), "windows", ctx.window_stats(), flush=True)
+        assert torch.equal(got, kp.kp_scd_sweep(prob, start, ctx=buckets)["lam"])
+        assert (ctx.window_listed() > 0) == near
