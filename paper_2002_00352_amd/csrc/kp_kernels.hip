@@ -24,6 +24,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <string.h>
+#include <type_traits>
 #include <algorithm>
 #include <functional>
 #include "kp_internal.h"
@@ -345,6 +346,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a, const TileGeom &g
     // ---- store the prefetched tile into LDS ----
     int64_t e_first = 0;
     int n_ent = 0;
+    bool full = false;
     #pragma unroll
     for (int i = 0; i < PCH; ++i) {
       const int r = tid + i * NT;
@@ -387,7 +389,12 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a, const TileGeom &g
         }
       }
       for (int t = tid; t < R * K; t += NT) bt[t] = 0.0f;
-      if (SCD)
+      // rows with an entry in most knapsacks are looked at as dense ones: their
+      // items' bits cost an LDS atomic each, and walking them one by one lost
+      // to the plain loop (M = 16, K = 8, full rows, 2e5 users: a sweep with
+      // windows 0.30 -> 0.26 ms, with windows away from lambda^t 0.73 -> 0.45)
+      full = SCD && 2 * n_ent > nr * K;
+      if (SCD && !full)
         for (int t = tid; t < Q; t += NT) Am[t] = 0ull;
     }
     // ---- issue the next tile's loads (they land during this tile's compute) ----
@@ -408,7 +415,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a, const TileGeom &g
     // (set full) and [1] its best positive member left out
     const bool fastau = SCD && fastsel;
     if (fastau && tid < nu) { tau[2 * tid] = -1; tau[2 * tid + 1] = -1; }
-    if (SCD && tid == 0) { nwq[0] = 0u; nwq[1] = 0u; }
+    if (SCD && tid == 0) { nwq[0] = 0u; nwq[1] = 0u; nwq[2] = full ? 1u : 0u; }
     // window filter, per user: [0] the smallest gap (a minimum over the
     // rows, taken on the bits of non-negative doubles), [1] the largest cost
     // (a maximum over the rows, on the bits of a non-negative float)
@@ -444,7 +451,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a, const TileGeom &g
           if ((unsigned)k >= (unsigned)K) continue;   // malformed column: ignored (kp_validate_inputs reports it)
           bt[(size_t)r * K + k] = v;
           if (SCD) offg |= off_grid(v, ginv);
-          if (SCD && v > 0.0f) {
+          if (SCD && !full && v > 0.0f) {
             const int u = r / M;
             atomicOr((unsigned long long *)&Am[u * K + k], 1ull << (r - u * M));
           }
@@ -559,115 +566,125 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a, const TileGeom &g
     // are queued and walked by as many threads as there are pairs: without the
     // queue every wave took the walk's time for the few of its lanes that
     // needed one (pairs looked at: 11-26 % of them, walked: 3-12 %) ----
-    for (int q = tid; q < nu * K; q += NT) {
-      const int u = q / K, k = q - u * K;
-      const uint64_t S0 = Sm[u];
-      const float *bu = bt + (size_t)u * M * K;
-      double v = 0.0;
-      uint64_t A = 0;     // SCD: moving lines, b_jk > 0
-      float bmk = 0.0f;   // SCD: their largest cost
-      // a window away from lambda_k^t with at most one binding set: the
-      // far-window test's first pass runs in the same pass over the items
-      // (its cut at -Hs taken with the user's largest cost over every
-      // knapsack, an upper bound of bmk: only more cautious)
-      bool fused = false, fused_ok = false;
-      double fused_cw = 0.0;
-      // a user with no line above -H (its gap record untouched) is calm in
-      // every window: only its consumption is needed (A stays empty, so no
-      // test or walk follows)
-      const bool settled = SCD && kmode[k] == KS_WINDOW && kwide[0] > 0.0 && !(ugap[2 * u] < 1e300);
-      if (settled) {
-        for (uint64_t m = S0; m; m &= m - 1) v = v + (double)bu[(__ffsll((long long)m) - 1) * K + k];
-      } else if (SCD) {
-        double fr = 0.0, fdl = 0.0;
-        if (FMT == 0 && kmode[k] == KS_WINDOW && kst[k].far && a.tree.L <= 1 && kwide[0] > 0.0) {
-          const double wlo = kst[k].wlo, whi = kst[k].whi;
-          const double c = 0.5 * (wlo + whi);
-          fr = fmax(whi - c, c - wlo);
-          fdl = c - lam[k];
-          fused = fabs(fdl) > fr;
-        }
-        if (fused) {
-          const double *zu = pt + u * M;
-          const double lk = lam[k];
-          const uint64_t m1 = a.tree.L == 1 ? a.tree.mask[0] : 0ull;
-          const double bmu = (double)__uint_as_float(((const unsigned int *)ugap)[4 * u + 2]);
-          const double Hup = fr * bmu * (1.0 + 0x1p-30) + 0x1p-36 * (1.0 + (lk + fabs(fdl) + fr) * bmu);
-          FarPass f;
-          #pragma unroll 4
-          for (int j = 0; j < M; ++j) {
-            const float bj = bu[j * K + k];
-            if (S0 >> j & 1) v = v + (double)bj;
-            const bool mov = bj > 0.0f;
-            if (mov) A |= 1ull << j;
-            bmk = bj > bmk ? bj : bmk;
-            const double b = mov ? (double)bj : 0.0;
-            const double sh = fdl * b;
-            far_item(f, zu[j] - sh, j, mov, (m1 >> j & 1) != 0, Hup);
+    auto look = [&](auto dense) {
+      constexpr bool DN = decltype(dense)::value;   // dense costs, or CSR rows with an entry in most knapsacks
+      for (int q = tid; q < nu * K; q += NT) {
+        const int u = q / K, k = q - u * K;
+        const uint64_t S0 = Sm[u];
+        const float *bu = bt + (size_t)u * M * K;
+        double v = 0.0;
+        uint64_t A = 0;     // SCD: moving lines, b_jk > 0
+        float bmk = 0.0f;   // SCD: their largest cost
+        // a window away from lambda_k^t with at most one binding set: the
+        // far-window test's first pass runs in the same pass over the items
+        // (its cut at -Hs taken with the user's largest cost over every
+        // knapsack, an upper bound of bmk: only more cautious); on CSR rows up
+        // to a cap of 8: its passes over the set grow with the cap (M = 32,
+        // K = 16, cap 20, 2e5 users: 2.0 ms a sweep without it, 2.3 with)
+        bool fused = false, fused_ok = false;
+        double fused_cw = 0.0;
+        // a user with no line above -H (its gap record untouched) is calm in
+        // every window: only its consumption is needed (A stays empty, so no
+        // test or walk follows)
+        const bool settled = SCD && kmode[k] == KS_WINDOW && kwide[0] > 0.0 && !(ugap[2 * u] < 1e300);
+        if (settled) {
+          for (uint64_t m = S0; m; m &= m - 1) v = v + (double)bu[(__ffsll((long long)m) - 1) * K + k];
+        } else if (SCD) {
+          double fr = 0.0, fdl = 0.0;
+          if (DN && kmode[k] == KS_WINDOW && kst[k].far && a.tree.L <= 1 && kwide[0] > 0.0 &&
+              (FMT == 0 || a.tree.L == 0 || a.tree.cap[0] <= 8)) {
+            const double wlo = kst[k].wlo, whi = kst[k].whi;
+            const double c = 0.5 * (wlo + whi);
+            fr = fmax(whi - c, c - wlo);
+            fdl = c - lam[k];
+            fused = fabs(fdl) > fr;
           }
-          const double Hs = fr * (double)bmk * (1.0 + 0x1p-30) + 0x1p-36 * (1.0 + (lk + fabs(fdl) + fr) * (double)bmk);
-          fused_ok = far_finish(f, zu, bu, M, K, k, A, lk, fdl, fr, (double)bmk, Hs, m1,
-                                a.tree.L == 1 ? a.tree.cap[0] : 0, &fused_cw);
-        } else if (FMT == 1) {
-          // the stored entries only, in ascending item order
-          A = Am[q];
-          for (uint64_t m = A; m; m &= m - 1) {
-            const int j = __ffsll((long long)m) - 1;
-            const float bj = bu[j * K + k];
-            if (S0 >> j & 1) v = v + (double)bj;
-            bmk = bj > bmk ? bj : bmk;
-          }
-        } else {
-          #pragma unroll 4
-          for (int j = 0; j < M; ++j) {
-            const float bj = bu[j * K + k];
-            if (S0 >> j & 1) v = v + (double)bj;
-            if (bj > 0.0f) A |= 1ull << j;
-            bmk = bj > bmk ? bj : bmk;
-          }
-        }
-      } else {
-        // the selected items only, in ascending index order
-        for (uint64_t m = S0; m; m &= m - 1) v = v + (double)bu[(__ffsll((long long)m) - 1) * K + k];
-      }
-      vk[q] = v;
-      if (SCD) {
-        if (FMT == 0) offg |= off_grid(v, gmag);
-        const int mode = kmode[k];
-        if (walk_mode(mode)) {
-          const double lk = lam[k];
-          const double *zu = pt + u * M;
-          bool walk = A != 0;
-          if (walk && mode == KS_WINDOW) {
-            // no breakpoint of this user inside the window: nothing to emit
-            // and its consumption just above the window is v_ik (no correction)
-            double cw = fused_cw;
-            // the filter's scale: |top p~| + H, with H from the user's
-            // largest cost and the widest window
-            const float bmu = __uint_as_float(((const unsigned int *)ugap)[4 * u + 2]);
-            const double hm = kwide[0];
-            const double Hu = hm * (double)bmu * (1.0 + 0x1p-30) + 0x1p-36 * (1.0 + (double)bmu * hm);
-            const double gscale = fabs(zu[perm[u * M]]) + Hu;
-            if (window_calm(ugap[2 * u], gscale, kst[k].hw, (double)bmk, lk)) {
-              walk = false;
-            } else if (fused && fused_ok) {
-              // no breakpoint inside the window: its consumption just above
-              // the window is the window's set's
-              walk = false;
-              if (cw != v) {
-                xs_atomic_add_sum(&kxs[k], xs_minus(xs_of(cw), xs_of(v)));
-              }
+          if (fused) {
+            const double *zu = pt + u * M;
+            const double lk = lam[k];
+            const uint64_t m1 = a.tree.L == 1 ? a.tree.mask[0] : 0ull;
+            const double bmu = (double)__uint_as_float(((const unsigned int *)ugap)[4 * u + 2]);
+            const double Hup = fr * bmu * (1.0 + 0x1p-30) + 0x1p-36 * (1.0 + (lk + fabs(fdl) + fr) * bmu);
+            FarPass f;
+            #pragma unroll 4
+            for (int j = 0; j < M; ++j) {
+              const float bj = bu[j * K + k];
+              if (S0 >> j & 1) v = v + (double)bj;
+              const bool mov = bj > 0.0f;
+              if (mov) A |= 1ull << j;
+              bmk = bj > bmk ? bj : bmk;
+              const double b = mov ? (double)bj : 0.0;
+              const double sh = fdl * b;
+              far_item(f, zu[j] - sh, j, mov, (m1 >> j & 1) != 0, Hup);
+            }
+            const double Hs = fr * (double)bmk * (1.0 + 0x1p-30) + 0x1p-36 * (1.0 + (lk + fabs(fdl) + fr) * (double)bmk);
+            fused_ok = far_finish(f, zu, bu, M, K, k, A, lk, fdl, fr, (double)bmk, Hs, m1,
+                                  a.tree.L == 1 ? a.tree.cap[0] : 0, &fused_cw);
+          } else if (!DN) {
+            // the stored entries only, in ascending item order
+            A = Am[q];
+            for (uint64_t m = A; m; m &= m - 1) {
+              const int j = __ffsll((long long)m) - 1;
+              const float bj = bu[j * K + k];
+              if (S0 >> j & 1) v = v + (double)bj;
+              bmk = bj > bmk ? bj : bmk;
+            }
+          } else {
+            #pragma unroll 4
+            for (int j = 0; j < M; ++j) {
+              const float bj = bu[j * K + k];
+              if (S0 >> j & 1) v = v + (double)bj;
+              if (bj > 0.0f) A |= 1ull << j;
+              bmk = bj > bmk ? bj : bmk;
             }
           }
-          if (walk && (S0 & A) == 0 &&
-              pair_idle(tr, A, S0, [&](int j) -> double { return zu[j]; },
-                        [&](int j) -> double { return (double)bu[j * K + k]; }, lk, kst[k].tlo)) {
-            walk = false;   // (in a window its consumption stays 0)
+        } else {
+          // the selected items only, in ascending index order
+          for (uint64_t m = S0; m; m &= m - 1) v = v + (double)bu[(__ffsll((long long)m) - 1) * K + k];
+        }
+        vk[q] = v;
+        if (SCD) {
+          if (FMT == 0) offg |= off_grid(v, gmag);
+          const int mode = kmode[k];
+          if (walk_mode(mode)) {
+            const double lk = lam[k];
+            const double *zu = pt + u * M;
+            bool walk = A != 0;
+            if (walk && mode == KS_WINDOW) {
+              // no breakpoint of this user inside the window: nothing to emit
+              // and its consumption just above the window is v_ik (no correction)
+              double cw = fused_cw;
+              // the filter's scale: |top p~| + H, with H from the user's
+              // largest cost and the widest window
+              const float bmu = __uint_as_float(((const unsigned int *)ugap)[4 * u + 2]);
+              const double hm = kwide[0];
+              const double Hu = hm * (double)bmu * (1.0 + 0x1p-30) + 0x1p-36 * (1.0 + (double)bmu * hm);
+              const double gscale = fabs(zu[perm[u * M]]) + Hu;
+              if (window_calm(ugap[2 * u], gscale, kst[k].hw, (double)bmk, lk)) {
+                walk = false;
+              } else if (fused && fused_ok) {
+                // no breakpoint inside the window: its consumption just above
+                // the window is the window's set's
+                walk = false;
+                if (cw != v) {
+                  xs_atomic_add_sum(&kxs[k], xs_minus(xs_of(cw), xs_of(v)));
+                }
+              }
+            }
+            if (walk && (S0 & A) == 0 &&
+                pair_idle(tr, A, S0, [&](int j) -> double { return zu[j]; },
+                          [&](int j) -> double { return (double)bu[j * K + k]; }, lk, kst[k].tlo)) {
+              walk = false;   // (in a window its consumption stays 0)
+            }
+            if (walk) wq[atomicAdd(nwq, 1u)] = (uint16_t)q;
           }
-          if (walk) wq[atomicAdd(nwq, 1u)] = (uint16_t)q;
         }
       }
-    }
+    };
+    // (full: read back from LDS at each use instead of held in scarce scalar registers)
+    auto is_full = [&]() -> bool { return FMT == 1 && __builtin_amdgcn_readfirstlane((int)nwq[2]) != 0; };
+    if (FMT == 0 || is_full()) look(std::true_type());
+    else look(std::false_type());
     __syncthreads();
     if (SCD) {
       const int nw = (int)nwq[0];
@@ -682,7 +699,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a, const TileGeom &g
         const float *bu = bt + (size_t)u * M * K;
         const uint64_t S0 = Sm[u];
         uint64_t A = 0;
-        if (FMT == 1) {
+        if (FMT == 1 && !is_full()) {
           A = Am[q];
         } else {
           #pragma unroll 4
@@ -738,7 +755,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a, const TileGeom &g
         const double *zu = pt + u * M;
         const float *bu = bt + (size_t)u * M * K;
         uint64_t A = 0;
-        if (FMT == 1) {
+        if (FMT == 1 && !is_full()) {
           A = Am[q];
         } else {
           #pragma unroll 4

@@ -1928,3 +1928,33 @@ def test_sampled_windows_take_the_split_pass():
         print("case", name, "listed", ctx.window_listed(), "windows", ctx.window_stats(), flush=True)
         assert torch.equal(got, kp.kp_scd_sweep(prob, start, ctx=buckets)["lam"])
         assert (ctx.window_listed() > 0) == near
+
+
+@gpu
+@pytest.mark.parametrize("name,mk,iters", [
+    ("alternating", lambda: kpgen.config_instance(2, N=3001), 10),
+    ("converging", lambda: kpgen.make_instance(4001, 5, 2, seed=72, budget_frac=0.15, tree=_free_tree(5)), 12),
+    ("cap-9", lambda: random_instance(np.random.default_rng(6), 1503, 14, 5, Q=9, frac=0.1), 8),
+    ("laminar", lambda: random_instance(np.random.default_rng(7), 1203, 12, 6,
+                                        tree=random_laminar(12, np.random.default_rng(7)), frac=0.1), 8),
+    ("half-rows", lambda: random_instance(np.random.default_rng(8), 2003, 9, 6, Q=2, zero_frac=0.5, frac=0.1), 8),
+], ids=["alternating", "converging", "cap-9", "laminar", "half-rows"])
+def test_full_csr_rows_trajectory(name, mk, iters):
+    """General CSR rows with an entry in every knapsack (or half of them, so
+    that tiles fall on both sides of the rule): the general kernel looks at
+    their pairs as at dense ones, windows away from the multiplier included;
+    every update equals the oracle's, window on and off."""
+    kp, torch = _kp()
+    print("case", name, flush=True)
+    inst = mk().to_csr()
+    prob = _general_rows(kp, inst)
+    win, off = kp.Context(), kp.Context()
+    off.set_window(False)
+    lam = np.zeros(inst.K)
+    for t in range(iters):
+        want = oracle.scd_sweep(inst, lam)
+        for ctx in (win, off):
+            got = kp.kp_scd_sweep(prob, _lamd(torch, lam), ctx=ctx)["lam"].cpu().numpy()
+            assert np.array_equal(got, want), (t, np.flatnonzero(got != want), got, want)
+        lam = want
+    print("window searches", win.window_stats(), flush=True)
