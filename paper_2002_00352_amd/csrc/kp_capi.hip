@@ -606,6 +606,17 @@ double pair_events(const Prepared &P) {
   return P.row_nnz ? 2.0 + 2.0 * P.pr.M * P.row_nnz / P.pr.K : P.pr.M + 4.0;
 }
 
+// Breakpoints that one knapsack of an instance can have at most: each lets an
+// item in, alone or for one of smaller cost, so the members' positions in the
+// order of the costs add up to more after it, and at most to the number of
+// items that can be selected times M.
+double max_events(const Prepared &P) {
+  int rank = P.pr.M;
+  for (int l = 0; l < P.tree.L; ++l)
+    if (__builtin_popcountll(P.tree.mask[l]) == P.pr.M) rank = std::min(rank, P.tree.cap[l]);
+  return (double)P.pr.N * P.pr.M * rank;
+}
+
 // What a window's search needs to know about the FP64 consumption of a pass
 // of `blocks` blocks: its bound when every cost is on the grid, and its error
 // otherwise.  The terms are non-negative, so a sum loses at most 2^-53 of
@@ -1637,6 +1648,7 @@ struct BatchPlan {
   XSum *hs = nullptr;
   uint32_t *hc = nullptr;
   SelWs sel;
+  int sel_blocks = 0;        // blocks per knapsack that bin many emitted events (0: no knapsack can have many)
   SumCheck check;
   unsigned int *off = nullptr;   // [n] an instance has costs off its grid (cleared by an iteration's init)
   unsigned long long *err = nullptr;
@@ -1726,7 +1738,7 @@ kp_status plan_sample_phase(BatchPlan *p, int dir, hipStream_t s) {
   if (p->samp.empty()) return KP_OK;
   for (const BatchPlan::SampChunk &q : p->samp)
     HIP_TRY(kp_launch_sweep_batched(p->sd[dir] + q.first, p->dhg + q.first, p->sboff + q.tab, q.n, q.blocks, p->lds, s));
-  HIP_TRY(kp_launch_sample_window(p->kst, p->Kf, p->Bf, p->e1, p->e2, p->cap, p->sel, kSelBlocksBatched, s));
+  HIP_TRY(kp_launch_sample_window(p->kst, p->Kf, p->Bf, p->e1, p->e2, p->cap, p->sel, std::max(1, p->sel_blocks), s));
   return KP_OK;
 }
 
@@ -1760,7 +1772,7 @@ kp_status plan_later_passes_dev(BatchPlan *p, int dir, hipStream_t s) {
     r.reset = j == 0 ? 1 : 0;
     HIP_TRY(kp_launch_plan_resplit(r, s));
     if (p->T > 0) HIP_TRY(kp_launch_sweep_batched(p->rd, p->rg, p->rboff, p->n, p->gfix, p->lds, s, p->ctl));
-    HIP_TRY(kp_launch_scd_locate_select(p->kst, p->Kf, p->Bf, p->stats, p->kin, p->hs, p->hc, p->e1, p->e2, p->cap, p->sel, kSelBlocksBatched, p->check, p->nohist, p->pend,
+    HIP_TRY(kp_launch_scd_locate_select(p->kst, p->Kf, p->Bf, p->stats, p->kin, p->hs, p->hc, p->e1, p->e2, p->cap, p->sel, p->sel_blocks, p->check, p->nohist, p->pend,
                                       nullptr, s));
     HIP_TRY(kp_launch_batched_aux(2, nullptr, p->Kf, p->kst, p->lam_tab[1 - dir], p->kin, p->klo, p->hint, nullptr,
                                   nullptr, nullptr, nullptr, s));
@@ -1781,7 +1793,7 @@ kp_status plan_first_pass(BatchPlan *p, int dir, hipStream_t s) {
   if (p->T > 0) HIP_TRY(kp_launch_sweep_batched(p->d[dir][1], p->geom, p->boff, p->n, p->GB, p->lds, s));
   HIP_TRY(kp_launch_batched_aux(0, p->coltab[dir], p->ncol, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
                                 nullptr, nullptr, nullptr, s));
-  HIP_TRY(kp_launch_scd_locate_select(p->kst, p->Kf, p->Bf, p->stats, p->kin, p->hs, p->hc, p->e1, p->e2, p->cap, p->sel, kSelBlocksBatched, p->check, p->nohist, p->pend,
+  HIP_TRY(kp_launch_scd_locate_select(p->kst, p->Kf, p->Bf, p->stats, p->kin, p->hs, p->hc, p->e1, p->e2, p->cap, p->sel, p->sel_blocks, p->check, p->nohist, p->pend,
                                       nullptr, s));
   HIP_TRY(kp_launch_batched_aux(2, nullptr, p->Kf, p->kst, p->lam_tab[1 - dir], p->kin, p->klo, p->hint, nullptr,
                                 nullptr, nullptr, nullptr, s));
@@ -1849,7 +1861,7 @@ kp_status plan_step(BatchPlan *p, int dir, double *stats_out, bool graph) {
       }
     }
     ++passes;
-    HIP_TRY(kp_launch_scd_locate_select(p->kst, p->Kf, p->Bf, p->stats, p->kin, p->hs, p->hc, p->e1, p->e2, p->cap, p->sel, kSelBlocksBatched, p->check, 0, p->pend,
+    HIP_TRY(kp_launch_scd_locate_select(p->kst, p->Kf, p->Bf, p->stats, p->kin, p->hs, p->hc, p->e1, p->e2, p->cap, p->sel, p->sel_blocks, p->check, 0, p->pend,
                                       nullptr, s));
     HIP_TRY(kp_launch_batched_aux(2, nullptr, p->Kf, p->kst, p->lam_tab[1 - dir], p->kin, p->klo, p->hint, nullptr,
                                 nullptr, nullptr, nullptr, s));
@@ -2020,7 +2032,13 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
   const size_t o_hc = cv.take((size_t)Kf * KP_NB * 4);
   const size_t o_e1 = cv.take((size_t)ioff[n] * 8);
   const size_t o_e2 = cv.take((size_t)ioff[n] * 8);
-  const size_t o_sel = cv.take(kp_sel_bytes(Kf));
+  // (a batch of small instances, none of which can emit more events than one
+  // block selects from, needs no binning: 2000 instances of 200 users took 3 GB
+  // and two launches of 4e4 idle blocks a pass for it)
+  for (int s = 0; s < n; ++s)
+    if (P[s].frac > 0.0 || max_events(P[s]) > (double)SEL_SMALL) p->sel_blocks = kSelBlocksBatched;
+  const int Ksel = p->sel_blocks ? Kf : 0;
+  const size_t o_sel = cv.take(kp_sel_bytes(Ksel));
   const size_t o_eo = cv.take((size_t)Kf * 8);
   const size_t o_ec = cv.take((size_t)Kf * 4);
   // staged events per block, per instance: scaled with the block's share of
@@ -2139,7 +2157,7 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
   p->hc = (uint32_t *)(w + o_hc);
   p->e1 = (double *)(w + o_e1);
   p->e2 = (double *)(w + o_e2);
-  p->sel = kp_sel_ws(w + o_sel, Kf);
+  p->sel = kp_sel_ws(w + o_sel, Ksel);
   p->frac = (double *)(w + o_frac);
   p->sd[0] = (SweepArgs *)(w + o_sd0);
   p->sd[1] = (SweepArgs *)(w + o_sd1);
@@ -2309,7 +2327,7 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
   if (e == hipSuccess) e = hipMemsetAsync(p->ctl, 0, 16, st);
   if (e == hipSuccess) e = hipMemsetAsync(p->hs, 0, (size_t)Kf * KP_NB * sizeof(XSum), st);
   if (e == hipSuccess) e = hipMemsetAsync(p->hc, 0, (size_t)Kf * KP_NB * 4, st);
-  if (e == hipSuccess) e = hipMemsetAsync(w + o_sel, 0, kp_sel_clear_bytes(Kf), st);
+  if (e == hipSuccess) e = hipMemsetAsync(w + o_sel, 0, kp_sel_clear_bytes(Ksel), st);
   if (e == hipSuccess) e = hipMemsetAsync(p->err, 0, 8, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);   // host tables go out of scope
   if (e != hipSuccess) {

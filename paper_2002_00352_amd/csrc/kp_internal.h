@@ -10,6 +10,7 @@
 #define SEL_BITS 11            // key bins of the selection's first step over many blocks
 #define SEL_BINS (1 << SEL_BITS)
 #define SEL_COMP 16384         // events of the threshold's bin it compacts
+#define SEL_SMALL 32768u       // events that one block selects from by itself
 #define KP_PROBE_USERS 4096   // users sampled by the dense window pass's probe
 #define KP_WIN_MULT 1.25       // window half-width around lambda_k^t, in units of the last step
 #define KP_WIN_MAX_REL 0.03125 // windows wider than this fraction of lambda_k^t are not tried

@@ -342,7 +342,6 @@ __global__ void __launch_bounds__(64) k_scd_locate(KState *st, int K, const doub
 // cost up to 2.8 ms of a sweep (1e6 events); a single block that sorted 4096
 // events and scanned them with one thread 0.1-0.9 ms even on small problems.
 #define SEL_NT 1024
-#define SEL_SMALL 32768u
 #define SEL_FEW 256        // candidates compared all with all
 
 __device__ __forceinline__ bool sel_mode(int m) { return m == KS_SELECT_BUCKET || m == KS_SELECT_RANGE; }

@@ -1958,3 +1958,28 @@ def test_full_csr_rows_trajectory(name, mk, iters):
             assert np.array_equal(got, want), (t, np.flatnonzero(got != want), got, want)
         lam = want
     print("window searches", win.window_stats(), flush=True)
+
+
+@gpu
+@pytest.mark.parametrize("use_graph", [False, True])
+def test_batched_small_instances(use_graph):
+    """A batch of instances so small that one block selects among all the
+    breakpoints a knapsack can have (N M times the items that can be taken at
+    most 32768; the last instance just there), so that the plan has no binning
+    steps: every update equals the oracle's."""
+    kp, torch = _kp()
+    print("case", use_graph, flush=True)
+    rng = np.random.default_rng(4)
+    insts = [random_instance(rng, 100 + 13 * s, 4 + s % 5, 1 + s % 4, Q=1 + s % 3, frac=0.1) for s in range(24)]
+    insts.append(random_instance(rng, 327, 10, 3, tree=_free_tree(10), frac=0.2))
+    probs = [kp.Problem.from_host(i) for i in insts]
+    plan = kp.BatchedSCD(probs, use_graph=use_graph)
+    lams = [np.zeros(i.K) for i in insts]
+    for t in range(5):
+        outs, _ = plan.step()
+        torch.cuda.synchronize()
+        for s, inst in enumerate(insts):
+            want = oracle.scd_sweep(inst, lams[s])
+            assert np.array_equal(outs[s].cpu().numpy(), want), (t, s)
+            lams[s] = want
+    plan.close()
