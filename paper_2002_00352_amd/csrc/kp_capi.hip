@@ -123,10 +123,11 @@ constexpr int kTileRowsMin = 160;        // item rows per tile at least, when th
 constexpr size_t kMaxLds = 160 * 1024;   // LDS per workgroup on gfx950
 constexpr int kMaxGrid = 2048;
 // A search without a window on an instance of at least kSampleMin users starts
-// from a sample of the users, 1/16 of them between these bounds (c3's recipe,
-// 5e6 users from lambda = 0: 11 full passes of exponential buckets and
-// refinements in four iterations, 45.7 ms; one sampled and one window pass an
-// iteration, SAMPLED_MS ms); smaller instances emit every breakpoint at once.
+// from a sample of the users, 1/16 of them between these bounds (5e6 users with
+// two costs per item, M = 10, K = 20, from lambda = 0: 11 full passes of
+// exponential buckets and refinements in four iterations, 52 ms; one sampled
+// and one window pass an iteration, 7.5 ms); smaller instances emit every
+// breakpoint at once.
 constexpr int64_t kSampleMin = 32768;
 constexpr int64_t kSampleUsersMin = 12288, kSampleUsersMax = 1 << 18;
 // Windows from a sample go to the uniform-row kernel's split pass from this
@@ -1634,7 +1635,7 @@ struct BatchPlan {
   void *lam_tab[2] = {nullptr, nullptr};   // [dir]: lambda_in pointer table; the other dir's is lambda_out
   void *coltab[2] = {nullptr, nullptr};    // [dir]: statistics column table (reads lambda_in)
   KState *kst = nullptr;
-  double *hint = nullptr;   // [2 Kf] bucket widths and last steps carried between iterations
+  double *hint = nullptr;   // [5 Kf] carried between iterations: bucket widths, last steps, two past multipliers, results
   double *frac = nullptr;   // [Kf] how a search without a window starts
   SweepArgs *sd[2] = {nullptr, nullptr};   // [dir] descriptors of the sampled pass
   int *sboff = nullptr;     // its blocks, chunk by chunk

@@ -7,11 +7,11 @@
 // the staging area is reused as per-lane scratch for the rest of the tile.
 // Per lane: cost-adjusted profits (FP64, stored columns ascending, no FMA),
 // ranks by (p~ desc, index asc), the laminar greedy (Alg.1 as the matroid
-// greedy), its consumption / profit / dual sums, and for SCD every knapsack's
-// breakpoints: a knapsack moving one item of the user has at most one, at the
-// item's threshold element; knapsacks moving several items of the user are
-// queued, and once the one-item cases are done the wave's (user, knapsack)
-// pairs are walked exactly, dealt over all 64 lanes.  R, g and P are summed
+// greedy), its consumption / profit / dual sums, and for SCD the knapsacks that
+// may have a breakpoint of the user in the pass's range: one whose moving
+// items stay below what they would have to pass at the range's lower end has
+// none.  The wave's (user, knapsack) pairs that are left are dealt over all 64
+// lanes and walked exactly (pair_start, pair_walk).  R, g and P are summed
 // in a fixed order (per-lane LDS columns, fixed-order row sums, waves added
 // in order per block, blocks added in order by a second kernel); the
 // threshold search's sums are exact two-limb integers (order-free atomics).
