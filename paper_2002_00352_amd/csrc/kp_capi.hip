@@ -2087,8 +2087,9 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
   const size_t o_s2 = cv.take(stage_all * 8);
   const size_t o_sk = cv.take(stage_all * 2);
   const size_t o_frac = cv.take((size_t)Kf * 8);
-  const size_t o_sd0 = cv.take((size_t)n * sizeof(SweepArgs));
-  const size_t o_sd1 = cv.take((size_t)n * sizeof(SweepArgs));
+  const int nsd = p->samp.empty() ? 0 : n;   // descriptors of the sampled pass
+  const size_t o_sd0 = cv.take((size_t)nsd * sizeof(SweepArgs));
+  const size_t o_sd1 = cv.take((size_t)nsd * sizeof(SweepArgs));
   const size_t o_sbo = cv.take(sboff.size() * 4);
   const size_t o_err = cv.take(8);
   const size_t o_pend = cv.take(8);
@@ -2202,7 +2203,7 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
     p->ilds[s] = hist_lds(s);
   }
   std::vector<SweepArgs> hd[2][2], hsd[2];
-  for (int d = 0; d < 2; ++d) hsd[d].resize(n);
+  for (int d = 0; d < 2; ++d) hsd[d].resize(nsd);
   std::vector<double> hfrac(Kf);
   for (int d = 0; d < 2; ++d) for (int f = 0; f < 2; ++f) hd[d][f].resize(n);
   std::vector<TileGeom> hg(n);
@@ -2244,6 +2245,7 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
       hd[d][1][s] = a;
       a.want_stats = 0;
       hd[d][0][s] = a;
+      if (!nsd) continue;
       SweepArgs q = a;
       q.sampled = 1;
       q.ntiles = P[s].frac > 0.0 ? P[s].samp_tiles : 0;
@@ -2303,7 +2305,7 @@ kp_status plan_create(Ctx *c, const kp_problem *probs, int n, const double *cons
   }
   for (int d = 0; d < 2 && e == hipSuccess; ++d)
     for (int f = 0; f < 2 && e == hipSuccess; ++f) e = up(p->d[d][f], pd[d][f].data(), (size_t)n * sizeof(SweepArgs));
-  for (int d = 0; d < 2 && e == hipSuccess; ++d) e = up(p->sd[d], hsd[d].data(), (size_t)n * sizeof(SweepArgs));
+  for (int d = 0; nsd && d < 2 && e == hipSuccess; ++d) e = up(p->sd[d], hsd[d].data(), (size_t)nsd * sizeof(SweepArgs));
   if (e == hipSuccess) e = up(p->sboff, sboff.data(), sboff.size() * 4);
   if (e == hipSuccess) e = up(p->frac, hfrac.data(), (size_t)Kf * 8);
   if (e == hipSuccess) e = up(w + o_chk, hchk.data(), (size_t)n * 24);
