@@ -296,7 +296,7 @@ struct Prepared {
   double frac = -1.0;
   int64_t samp_tiles = 0, samp_stride = 1, samp_off = 0;
   int64_t samp_users = 0;
-  int gexp = 0;           // the unit of the grid on which FP64 sums up to 8 times the budgets are exact: 2^gexp
+  int gexp = 0;           // 2^gexp: the unit of the grid on which FP64 sums up to many times the budgets are exact
   int stage_grid() const {
     return std::max(std::max(std::max(grid, grid_nh), std::max(ell_grid, dense_grid)), dwin_grid);
   }
@@ -412,7 +412,11 @@ kp_status prepare(const kp_problem *p, bool scd, Prepared &out, const Ctx *ctx =
   {
     double top = 0.0;
     for (int k = 0; k < p->K; ++k) top = std::max(top, p->B[k]);
-    out.gexp = std::min(100, std::max(-56, std::ilogb(top) + 4 - 53));   // (-56: the exact sums' unit)
+    // sums up to 128 times the largest budget where that leaves a unit of 2^-28
+    // (costs like 0.1 in fp32 are multiples of 2^-27), else fewer, at least 8
+    // times; -56: the exact sums' unit
+    const int e = std::ilogb(top) - 53;
+    out.gexp = std::min(100, std::max(-56, std::max(e + 4, std::min(e + 8, -28))));
   }
   // tile: as many users as fit the staged-cost budget, at most 64
   const size_t per_user = (size_t)M * p->K * 4;

@@ -316,15 +316,21 @@ __global__ void __launch_bounds__(64) k_scd_locate(KState *st, int K, const doub
     // the R, g, P columns of the instances before it)
     const double Rk = R[k + 2 * in];
     const XSum above = xs_plus(xs_of(Rk), s.corr);
-    const double lim = sc.per ? sc.per[3 * in] : sc.lim, rel = sc.per ? sc.per[3 * in + 1] : sc.rel,
-                 ab = sc.per ? sc.per[3 * in + 2] : sc.abs;
-    s.err = off == 0 && Rk < lim ? 0.0 : rel * fmax(fmax(Rk, Bk), xs_to_double(above)) + ab;
-    const XSum e = err_units(s.err);
+    const double lim = sc.per ? sc.per[3 * in] : sc.lim;
     if (win && lane == 0) { atomicAdd(&win[0], 1u); atomicAdd(&win[3], s.n_emit); }
-    if (s.overflow || xs_gt(xs_plus(above, e), Bk)) {
+    bool over = s.overflow || xs_gt(above, Bk);   // the threshold lies above the window
+    s.err = 0.0;
+    if (off != 0 || !(Rk < lim)) {
+      const double rel = sc.per ? sc.per[3 * in + 1] : sc.rel, ab = sc.per ? sc.per[3 * in + 2] : sc.abs;
+      s.err = rel * fmax(fmax(Rk, Bk), xs_to_double(above)) + ab;
+      const XSum e = err_units(s.err);
+      if (!s.overflow && xs_gt(xs_plus(above, e), Bk) && !xs_gt(xs_minus(above, e), Bk)) {
+        over = true;                    // on its edge, as far as R tells: buckets
+        s.flags |= KS_FLAG_TRIED;
+      }
+    }
+    if (over) {
       if (win && lane == 0) atomicAdd(&win[1], 1u);
-      // the threshold lies above the window, or on its edge as far as R tells
-      if (!s.overflow && !xs_gt(xs_minus(above, e), Bk)) s.flags |= KS_FLAG_TRIED;
       search_start(s);
     } else {
       s.mode = KS_SELECT_RANGE;         // [klo, khi] is the window
@@ -513,6 +519,7 @@ __device__ __forceinline__ XSum block_total(XSum v, XSum *part) {
   if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
   __syncthreads();
   XSum t = xs_zero();
+  #pragma unroll 1
   for (int q = 0; q < SEL_NT / 64; ++q) t = xs_plus(t, part[q]);
   return t;
 }
@@ -535,7 +542,7 @@ __global__ void __launch_bounds__(SEL_NT) k_sel_final(KState *st, const double *
   __shared__ double lval[KEEP];
   __shared__ int bin;
   __shared__ XSum cum;
-  __shared__ uint32_t cnt, fill;
+  __shared__ uint32_t cnt, fill, kunsure;
   __shared__ unsigned long long kmin, kmax, kres;
   if (tid == 0) s = st[k];
   __syncthreads();
@@ -553,6 +560,11 @@ __global__ void __launch_bounds__(SEL_NT) k_sel_final(KState *st, const double *
   uint64_t lo, hi;
   XSum Fab = s.fab;
   bool below = false;                  // a window's increments do not take the sum past B_k
+  // err > 0: whether a result holds whatever R lost to rounding (else exact
+  // buckets decide); sure: that the increments fit the budget
+  const bool chk = s.err > 0.0;
+  const XSum ex = err_units(s.err);
+  bool sure = !chk;
   if (big) {
     for (int t = tid; t < SEL_BINS; t += SEL_NT) {
       w.hsum[(size_t)k * SEL_BINS + t] = xs_zero();
@@ -579,32 +591,28 @@ __global__ void __launch_bounds__(SEL_NT) k_sel_final(KState *st, const double *
       XSum tot = Fab;
       for (int q = 0; q < SEL_NT / 64; ++q) tot = xs_plus(tot, part[q]);
       below = !xs_gt(tot, Bk);
+      if (chk) sure = !xs_gt(xs_plus(tot, ex), Bk);
       __syncthreads();
     }
   }
   if ((s.flags & KS_FLAG_WINDOW) && below) {
-    bool sure = true;
-    if (s.err > 0.0 && s.wlo == 0.0) {   // do the increments fit the budget, whatever R lost to rounding?
+    if (chk && big && s.wlo == 0.0) {
       XSum v = xs_zero();
+      #pragma unroll 1
       for (uint32_t e = tid; e < s.n_emit; e += SEL_NT) xs_add(v, (V2 + eo)[e]);
       const XSum tot = xs_plus(s.fab, block_total(v, part));
-      sure = !xs_gt(xs_plus(tot, err_units(s.err)), Bk);
+      sure = !xs_gt(xs_plus(tot, ex), Bk);
     }
     if (tid == 0) {
-      if (s.wlo == 0.0 && !sure) {
-        KState r = s;
-        r.flags |= KS_FLAG_TRIED;
-        search_start(r);
-        st[k] = r;
-        atomicAdd(pending, 1);
-      } else if (s.wlo == 0.0) {               // every breakpoint is in the window
+      if (s.wlo == 0.0 && sure) {       // every breakpoint is in the window
         st[k].result = 0.0;
         st[k].mode = KS_DONE;
       } else {
         KState r = s;                   // below the window: search again
+        if (s.wlo == 0.0) r.flags |= KS_FLAG_TRIED;
+        else if (win) atomicAdd(&win[2], 1u);
         search_start(r);
         st[k] = r;
-        if (win) atomicAdd(&win[2], 1u);
         atomicAdd(pending, 1);
       }
     }
@@ -677,9 +685,10 @@ __global__ void __launch_bounds__(SEL_NT) k_sel_final(KState *st, const double *
     __syncthreads();
   }
   // the candidates, compared all with all (or all equal: kmin)
-  if (tid == 0) { kres = kmin; fill = 0; }
+  if (tid == 0) { kres = kmin; fill = 0; kunsure = 0; }
   __syncthreads();
-  if (cnt <= SEL_FEW && kmin < kmax) {
+  const bool few = cnt <= SEL_FEW && kmin < kmax;
+  if (few) {
     XSum *fv = hs;   // [256]
     __shared__ uint64_t fk[SEL_FEW];
     for (uint32_t e = tid; e < n; e += SEL_NT) {
@@ -696,28 +705,31 @@ __global__ void __launch_bounds__(SEL_NT) k_sel_final(KState *st, const double *
       for (uint32_t q = 0; q < fill; ++q)
         if (fk[q] >= key) at = xs_plus(at, fv[q]);
       if (xs_gt(at, Bk)) atomicMax(&kres, (unsigned long long)key);
+      // no running sum, nor the one above them all, may lie that close to the budget
+      if (chk && (xs_gt(xs_plus(at, ex), Bk) != xs_gt(xs_minus(at, ex), Bk) || xs_gt(xs_plus(Fab, ex), Bk))) kunsure = 1;
     }
     __syncthreads();
   }
-  if (s.err > 0.0) {
-    // the sum from the top must exceed the budget at this breakpoint and not
-    // above it, whatever R lost to rounding; else exact buckets decide
-    const uint64_t res = kres;
-    const XSum ex = err_units(s.err);
-    bool unsure = false;
-    #pragma unroll 1
-    for (int above = 0; above < 2; ++above) {
+  if (chk) {
+    if (!few) {
+      // every candidate has the same key: the sum with them must exceed the
+      // budget, and the one above them not (one event is the rule near
+      // convergence: a wave adds up to 64)
+      const bool small = inlds && n <= 64;
       XSum v = xs_zero();
-      for (uint32_t e = tid; e < n; e += SEL_NT) {
-        uint64_t key = 0;
-        if (inlds) key = lkey[e];
-        if (inlds ? key < lo || key > hi : !sel_takes(s, bucket, lo, hi, E1[e], key)) continue;
-        if (key >= res + above) xs_add(v, inlds ? lval[e] : E2[e]);
+      if (!small || tid < 64) {
+        for (uint32_t e = tid; e < n; e += SEL_NT) {
+          uint64_t key = 0;
+          if (inlds) key = lkey[e];
+          if (inlds ? key >= lo && key <= hi : sel_takes(s, bucket, lo, hi, E1[e], key)) xs_add(v, inlds ? lval[e] : E2[e]);
+        }
+        v = small ? wave_suffix(v, lane) : v;
       }
-      const XSum at = xs_plus(Fab, block_total(v, part));
-      unsure = unsure || (above ? xs_gt(xs_plus(at, ex), Bk) : !xs_gt(xs_minus(at, ex), Bk));
+      if (!small) v = block_total(v, part);
+      if (tid == 0 && (!xs_gt(xs_minus(xs_plus(Fab, v), ex), Bk) || xs_gt(xs_plus(Fab, ex), Bk))) kunsure = 1;
+      __syncthreads();
     }
-    if (unsure) {
+    if (kunsure) {
       if (tid == 0) {
         KState r = s;
         r.flags |= KS_FLAG_TRIED;
